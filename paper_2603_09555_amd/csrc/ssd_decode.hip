@@ -180,7 +180,7 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_any_kernel(
 }
 
 // Several steps in one launch (inputs of all steps known up front, e.g. a short continuation of a
-// cached prompt): the state of a (layer, batch row, head) stays in registers across the steps, so
+// cached prompt), for fp32 io, few steps and the shapes ssd_decode_steps_mfma.hip does not take: the state of a (layer, batch row, head) stays in registers across the steps, so
 // it is read and written once instead of once per step, and the per-step traffic shrinks to the
 // step's inputs and its output row.  What then bounds the kernel is the vector ALU, so the layout
 // minimises instructions per state element: LPR (<= 16) lanes share a row, each lane owns NV groups
@@ -382,6 +382,8 @@ hipError_t launch_decode(int nlayers, const Dims &d, float *state, const void *x
 hipError_t launch_decode_steps(int nsteps, int nlayers, const Dims &d, float *state, const void *x,
                                const float *dt, const float *A, const void *B, const void *C, const float *D,
                                void *y, hipStream_t stream) {
+  if (decode_steps_mfma_supported(nsteps, nlayers, d))
+    return launch_decode_steps_mfma(nsteps, nlayers, d, state, x, dt, A, B, C, D, y, stream);
   const bool resident =
       d.bf16 ? launch_steps_resident<IoBf16>(nsteps, nlayers, d, state, x, dt, A, B, C, D, y, stream)
              : launch_steps_resident<IoF32>(nsteps, nlayers, d, state, x, dt, A, B, C, D, y, stream);
