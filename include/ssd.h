@@ -251,7 +251,7 @@ SSD_API ssd_status ssd_decode_step_layers(int32_t nlayers, const ssd_shape *shap
  *     B, C (nsteps, nlayers, batch, ngroups, dstate);  A, D (nlayers, nheads);
  *     state (nlayers, batch, nheads, headdim, dstate) in/out: the state after the last step.
  * The result equals nsteps calls of ssd_decode_step_layers up to the order of
- * the fp32 summations (over dstate; from 8 steps on, bf16 io, also over steps).
+ * the fp32 summations (over dstate; from 9 steps on, bf16 io, also over steps).
  * For the common head shapes the state stays on chip between the steps and moves
  * through memory once per call instead of once per step.
  * Errors: as ssd_decode_step_layers (only the base pointers need 16-byte alignment).

@@ -366,9 +366,10 @@ __global__ __launch_bounds__(kThr, 2) void decode_steps_mfma_kernel(const StepsP
 
 }  // namespace
 
-// Fewer steps than this are left to decode_steps_kernel, which there is as fast (64 layers, batch 1, 4 steps: 73 us
-// against 74; 8 steps: 93 against 75) and whose state is bit for bit that of single steps.
-constexpr int kMinSteps = 8;
+// Fewer steps than this are left to decode_steps_kernel, whose state is bit for bit that of single steps, which callers
+// that check a few drafted tokens may count on; there is little to gain there (64 layers, batch 1: 4 steps 73 us against
+// 74; 8 steps 93 against 75).
+constexpr int kMinSteps = 9;
 
 bool decode_steps_mfma_supported(int nsteps, int nlayers, const Dims &d) {
   const unsigned long long lim = 0xFFFF0000ull;  // 32 rows of a tensor must be addressable with 32-bit byte offsets
