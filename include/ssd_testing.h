@@ -22,9 +22,11 @@ extern "C" {
 typedef enum {
   SSD_KNOB_FORCE_GENERIC = 0, /* 1: every prefill runs on the generic fp32 kernels; 0: default */
   SSD_KNOB_SEG_CHUNKS = 1,    /* k > 0: k chunks per segment in the MFMA prefill; 0: library's choice */
-  SSD_KNOB_SEG_BLOCKS = 2,    /* k > 0: k 64-token blocks per segment (when SEG_CHUNKS is 0); 0: default */
+  SSD_KNOB_SEG_BLOCKS = 2,    /* k > 0: k 64-token blocks per segment (when SEG_CHUNKS is 0); 0: default.  fp32 io
+                                 (unless knob 0, 6 or 7 is set): split operands, segments of about k 32-token blocks */
   SSD_KNOB_SEG_PARTS = 3,     /* k > 0: pieces per segment in the states-only pass, if k divides the
-                                 segment length and the state slots suffice; 0: default */
+                                 segment length and the state slots suffice; 0: default.  fp32 io with
+                                 SEG_BLOCKS: workgroups that share a sequence of one segment */
   SSD_KNOB_Y_STREAM = 4,      /* 0 / 1: ordinary / non-temporal stores of y in the full scan; -1: default */
   SSD_KNOB_DECODE_STREAM = 5, /* 0 / 1: ordinary / non-temporal accesses to the decode state; -1: default */
   SSD_KNOB_FORCE_MFMA_F32 = 6, /* 1: fp32 io runs on the fp32 MFMA kernel whenever the shape is eligible (headdim
@@ -50,7 +52,8 @@ SSD_API void ssd_testing_reset_knobs(void);
  * per sequence, plan[3] pieces per segment in the states-only pass, plan[4] 1 if the full scan sums the
  * chain over segment states itself and no separate pass runs (h0_aliases_final_state != 0: as for a call
  * whose h0 and final_state share memory, which rules that out).  For the fp32 MFMA family: plan[5] time
- * segments per sequence.  The other entries are zero.
+ * segments per sequence on fp32 MFMA, or 0 on split operands, and then plan[1] 32-token blocks in the longest
+ * segment, plan[2] segments, plan[3] workgroups that share one.  The other entries are zero.
  * Errors: SSD_ERR_NULL; the shape errors of ssd_prefill. */
 SSD_API ssd_status ssd_testing_prefill_plan(const ssd_shape *shape, int32_t h0_aliases_final_state,
                                             int32_t plan[8]);

@@ -51,6 +51,10 @@ bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 bool force_generic() { return ssd::knobs().force_generic != 0; }
 
 bool use_mfma(const Dims &d) { return !force_generic() && ssd::mfma_supported(d); }
+bool use_split_f32(const Dims &d) {
+  const ssd::Knobs &k = ssd::knobs();  // (knobs of the other fp32 families keep this one out)
+  return !force_generic() && k.force_mfma_f32 == 0 && k.f32_segments == 0 && ssd::split_f32_chosen(d);
+}
 bool use_mfma_f32(const Dims &d) { return !force_generic() && ssd::mfma_f32_supported(d, ssd::knobs().force_mfma_f32 != 0); }
 
 // Enough for either kernel family that may run the shape, so that which one does (a test may force the
@@ -94,6 +98,8 @@ ssd_status prefill_impl(const ssd_shape *shape, const void *x, const float *dt, 
   const hipError_t e =
       use_mfma(d)
           ? ssd::launch_prefill_mfma(d, x, dt, A, B, C, D, h0, y, final_state, workspace, stream, trace)
+      : use_split_f32(d)
+          ? ssd::launch_prefill_split_f32(d, x, dt, A, B, C, D, h0, y, final_state, workspace, stream, trace)
       : use_mfma_f32(d)
           ? ssd::launch_prefill_mfma_f32(d, x, dt, A, B, C, D, h0, y, final_state, stream, trace)
           : ssd::launch_prefill_generic(d, x, dt, A, B, C, D, h0, y, final_state, workspace, stream,
@@ -123,7 +129,7 @@ size_t ssd_prefill_workspace_bytes(const ssd_shape *shape) {
 const char *ssd_prefill_path(const ssd_shape *shape) {
   Dims d;
   if (make_dims(shape, false, &d) != SSD_OK) return "invalid";
-  return use_mfma(d) ? "mfma_bf16" : use_mfma_f32(d) ? "mfma_f32" : "generic_f32";
+  return use_mfma(d) ? "mfma_bf16" : use_split_f32(d) || use_mfma_f32(d) ? "mfma_f32" : "generic_f32";
 }
 
 ssd_status ssd_testing_prefill_plan(const ssd_shape *shape, int32_t h0_aliases_final_state, int32_t plan[8]) {
@@ -138,6 +144,9 @@ ssd_status ssd_testing_prefill_plan(const ssd_shape *shape, int32_t h0_aliases_f
     plan[2] = pl.segments;
     plan[3] = pl.parts;
     plan[4] = pl.fold;
+  } else if (use_split_f32(d)) {
+    plan[0] = 2;
+    ssd::split_f32_plan(d, &plan[1], &plan[2], &plan[3]);
   } else if (use_mfma_f32(d)) {
     plan[0] = 2;
     plan[5] = ssd::mfma_f32_time_segments(d);

@@ -100,8 +100,8 @@ inline void trace_mark(KernelTrace *t, hipStream_t s, const char *name) {
 struct Knobs {
   int force_generic = 0;   // 1: every prefill takes the generic fp32 kernels
   int seg_chunks = 0;      // > 0: chunks per segment of the MFMA prefill
-  int seg_blocks = 0;      // > 0: 64-token blocks per segment (if seg_chunks is not set)
-  int seg_parts = 0;       // > 0: pieces per segment in the states-only pass
+  int seg_blocks = 0;      // > 0: 64-token blocks per segment (if seg_chunks is not set); split fp32: 32-token blocks
+  int seg_parts = 0;       // > 0: pieces per segment in the states-only pass; split fp32: workgroups per segment
   int y_stream = -1;       // 0 / 1: ordinary / non-temporal stores of y in the full scan
   int decode_stream = -1;  // 0 / 1: ordinary / non-temporal accesses to the decode state
   int force_mfma_f32 = 0;  // 1: fp32 io takes the fp32 MFMA kernel whenever the shape is eligible
@@ -149,6 +149,16 @@ bool mfma_f32_supported(const Dims &d, bool whenever_eligible);  // false: only 
 hipError_t launch_prefill_mfma_f32(const Dims &d, const void *x, const float *dt, const float *A, const void *B,
                                    const void *C, const float *D, const float *h0, void *y, float *final_state,
                                    hipStream_t stream, KernelTrace *trace = nullptr);
+
+// fp32 io on bf16 MFMA with split operands; see ssd_prefill_split_f32.hip.  split_f32_chosen: whether it is expected
+// to be the fastest of the three families for the shape.
+bool split_f32_supported(const Dims &d);
+double f32_other_us(const Dims &d);  // modelled time of the faster of the two other families
+bool split_f32_chosen(const Dims &d);
+void split_f32_plan(const Dims &d, int *seg_blocks, int *segments, int *parts);
+hipError_t launch_prefill_split_f32(const Dims &d, const void *x, const float *dt, const float *A, const void *B,
+                                    const void *C, const float *D, const float *h0, void *y, float *final_state,
+                                    void *workspace, hipStream_t stream, KernelTrace *trace = nullptr);
 
 // Device-side tables of a packed variable-length batch (all int32; see ssd_prefill_mfma.hip, "tables of a
 // variable-length call").  tok0 == nullptr: plain batch.

@@ -471,6 +471,14 @@ int f32_time_segments(const Dims &d, double *walk_us) {
 // over the whole chip, cost four launches and then time proportional to the work.  A long sequence with few
 // heads is theirs.  Both estimates are fits to a handful of timings on MI355X (microseconds); where they are
 // within a tenth of each other the MFMA kernel is taken.
+static double f32_mfma_us(const Dims &d) {
+  double walk_us;
+  f32_time_segments(d, &walk_us);
+  return 8.0 + walk_us;
+}
+static double f32_generic_us(const Dims &d) {
+  return 33.0 + static_cast<double>(d.Bt) * d.T * d.H * (0.9 + 0.0005 * d.P * d.N) * 1e-3;
+}
 bool mfma_f32_supported(const Dims &d, bool whenever_eligible) {
   const unsigned long long wgs = static_cast<unsigned long long>(d.Bt) * d.H * (d.P / kCols);
   // one batch row of x and of B / C must be addressable with 32-bit byte offsets
@@ -478,13 +486,14 @@ bool mfma_f32_supported(const Dims &d, bool whenever_eligible) {
   if (d.bf16 || d.P % kCols != 0 || d.N % 8 != 0 || d.N > 128 || wgs > 0x7fffffffull / 64 || t * d.H * d.P * 4 > lim ||
       t * d.G * d.N * 4 > lim)
     return false;
-  if (whenever_eligible) return true;
-  double walk_us;
-  f32_time_segments(d, &walk_us);
-  const double mfma_us = 8.0 + walk_us;
-  const double token_heads = static_cast<double>(d.Bt) * d.T * d.H;
-  const double generic_us = 33.0 + token_heads * (0.9 + 0.0005 * d.P * d.N) * 1e-3;
-  return mfma_us <= 1.1 * generic_us;
+  return whenever_eligible || f32_mfma_us(d) <= 1.1 * f32_generic_us(d);
+}
+
+double f32_other_us(const Dims &d) {
+  const double generic_us = f32_generic_us(d);
+  if (!mfma_f32_supported(d, true)) return generic_us;
+  const double mfma_us = f32_mfma_us(d);
+  return mfma_us < generic_us ? mfma_us : generic_us;
 }
 
 int mfma_f32_time_segments(const Dims &d) { return f32_time_segments(d, nullptr); }

@@ -1,0 +1,556 @@
+// Prefill for fp32 io (x, B, C, y in fp32) on the bf16 matrix pipe: every fp32 operand is split into three bf16
+// parts (ssd_split_bf16.hpp) and a product of two of them is six matrix instructions, accumulated in fp32 -- fp32
+// accuracy at 16 / 6 times the rate of the fp32 matrix instruction, and the prompt cut up over the whole chip.
+// Shapes: headdim a multiple of 32, dstate a multiple of 8 up to 128.
+//
+// The chunked algorithm (Alg. 1; Eq. 3) on blocks of 32 tokens, with cs_l the block-relative inclusive prefix sum of
+// dt*A and S the state entering the block:
+//     G[l][s] = C_l . B_s                                                     (s <= l; once per workgroup)
+//     y[l][p] = exp(cs_l) sum_n C[l][n] S[p][n] + sum_s (G[l][s] dt_s exp(cs_l - cs_s)) x[s][p] + D x[l][p]
+//     S'      = exp(cs_31) S + sum_s (dt_s exp(cs_31 - cs_s) x[s][p]) B[s][n]
+// The mask is applied un-factorised, on the scores in registers, so any step size is exact.
+//
+// One wave per slice of 32 headdim columns x dstate, its state in MFMA accumulators; four slices of one B/C group
+// per workgroup, which stages the split B and C once for them.  Layouts as in ssd_decode_steps_mfma.hip.
+// The sequence is cut into S segments: a states-only launch computes every segment's end state from zero, a pass
+// chains them (Alg. 1, "InterChunkRecurrence"), and the full launch walks every segment from its entering state.  The
+// states between the launches lie in the caller's workspace where it holds that many -- it is sized for one per chunk,
+// 8 for 2048 tokens at a chunk length of 256 where 16 are wanted --, and otherwise in y, each in the rows of the segment
+// it enters: a wave reads the state of its slice and later writes its outputs there, and no other wave touches those
+// columns.  A segment then has at least as many tokens as a state slice has 128-byte pieces.
+// With one segment only the full launch runs; `sub` workgroups may then share the sequence, each first carrying the
+// state over the blocks of the ones before it (a third of a block's work, no output).
+// Bound: issue.  A block of four slices takes 4.7 us alone on a CU, 6.4 with a second workgroup, of which the matrix
+// instructions are 1.6 (3840 cycles a wave); 1100 vector instructions a wave (the splits: 700) come between them.
+// Two waves per slice (half of dstate each, outputs summed through LDS) took 4.4 us alone but 9 for two; matrix and
+// vector instructions interleaved by hand or by scheduling groups 5.4 and more (spills).
+// Measured against the fp32 matrix instruction kernel (ssd_prefill_mfma_f32.hip), us: 2048 tokens x 24 heads x 64 x 128
+// 113 / 53 (13 us of it the chain and the gaps), 8 such prompts 502 / 195, 3 x 2428 x 20 196 / 93, 2 x 3593 x 11 x 64 x
+// 16 70 / 35, 4096 x 4 x 32 x 16 56 / 24; final state against 64 bits 1.7e-7 / 9.7e-8, y 2.6e-8 both.
+#include <type_traits>
+
+#include "ssd_split_bf16.hpp"
+
+namespace ssd {
+namespace {
+using namespace split;
+
+constexpr int kTok = 32;             // tokens per block
+constexpr int kCols = 32;            // headdim columns per wave
+constexpr int kWaves = 4;
+constexpr int kThr = 64 * kWaves;
+constexpr int kXStride = kCols + 8;  // floats per row of an x tile (four rows apart: 32 of the 64 banks)
+constexpr int kGStride = kTok + 4;   // floats per row of the score tile
+constexpr int kTurnStride = 32 + 4;  // floats per row of a state tile on its way through LDS
+constexpr float kLog2e = 1.4426950408889634f;
+constexpr uint32_t kNowhere = 0xFFFFFF00u;  // an offset beyond any descriptor
+
+struct SplitParams {
+  const float *x, *dt, *A, *B, *C, *D, *h0;
+  float *y, *final_state;
+  float *slots;                    // states entering the segments, [batch row][head][segment]; nullptr: they lie in y
+  float *decay;                    // decay: log2 of every segment's total decay, [batch row][head][segment]
+  int T, H, P, N, G, Bt, hpg;
+  int nslice, cpg;               // slices per group; workgroups per group
+  int S;                         // segments per sequence; segment s begins at block segment_begin(s)
+  int sub, sub_blocks;           // S = 1: workgroups that share the sequence, output blocks of each
+  int slot0;                     // the first segment starts from its slot in y, not from h0 (which final_state aliases)
+  DtXform dtx;
+};
+
+__host__ __device__ __forceinline__ int segment_begin(int s, int S, int nblocks) {
+  return static_cast<int>(static_cast<long long>(s) * nblocks / S);
+}
+// The state slice of (batch row b, head h, columns p0 ..) that enters segment s: 32 rows (headdim) of NT pieces of 32
+// floats.  In the workspace they lie as in any state; in y, piece (c, nt) is the 32 columns of y's row number c NT + nt
+// of the segment.
+__device__ __forceinline__ float *state_slot(const SplitParams &p, int b, int h, int p0, int s, int nblocks) {
+  if (p.slots != nullptr) return p.slots + (((static_cast<size_t>(b) * p.H + h) * p.S + s) * p.P + p0) * p.N;
+  const size_t tok = static_cast<size_t>(b) * p.T + static_cast<size_t>(segment_begin(s, p.S, nblocks)) * kTok;
+  return p.y + (tok * p.H + h) * p.P + p0;
+}
+
+template <int NT, bool kStatesOnly>
+struct SplitLds {
+  static constexpr int kN = 32 * NT;
+  static constexpr int kRow = kN + 8;                       // bf16 elements per row of a part of B or C
+  static constexpr int kPart = kTok * kRow;
+  static constexpr int kBC = (kStatesOnly ? 3 : 6) * kPart * 2;  // bytes
+  static constexpr int kX = kWaves * kTok * kXStride * 4;
+  static constexpr int kG = kStatesOnly ? 0 : kTok * kGStride * 4;
+  static constexpr int kTurn = kWaves * kCols * kTurnStride * 4;
+  static constexpr int kTiles = kBC + kX + kG;
+  static constexpr int kBytes = kTiles > kTurn ? kTiles : kTurn;
+};
+
+template <int NT, bool kStatesOnly>
+__global__ __launch_bounds__(kThr, 2) void split_f32_kernel(const SplitParams p) {
+  using L = SplitLds<NT, kStatesOnly>;
+  constexpr int N = L::kN;                       // dstate padded to whole tiles
+  constexpr int kPieces = kTok * (N / 4) / kThr;  // 16-byte pieces of a B or C tile per thread
+  __shared__ __align__(16) uint8_t smem[L::kBytes];
+  __shared__ __align__(16) float s_cs[kWaves][kTok], s_dt[kWaves][kTok], s_w[kWaves][kTok];
+  uint16_t *const sB = reinterpret_cast<uint16_t *>(smem);  // three parts of B, then of C: [token][n]
+  uint16_t *const sC = sB + 3 * L::kPart;
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = lane & 31, kg = lane >> 5;
+  float *const sX = reinterpret_cast<float *>(smem + L::kBC) + wave * (kTok * kXStride);  // x [token][column], this wave's
+  float *const sG = reinterpret_cast<float *>(smem + L::kBC + L::kX);                     // scores [l][s]
+
+  // ---- which slice, segment and blocks ----
+  const int col = blockIdx.x % p.cpg;
+  const int bg = (blockIdx.x / p.cpg) % (p.Bt * p.G), piece = blockIdx.x / p.cpg / (p.Bt * p.G);
+  const int g = bg % p.G, b = bg / p.G;
+  const int seg = kStatesOnly ? piece : piece / p.sub, part = kStatesOnly ? 0 : piece % p.sub;
+  const int nblocks = (p.T + kTok - 1) / kTok;
+  const int j0 = segment_begin(seg, p.S, nblocks), jend = segment_begin(seg + 1, p.S, nblocks);
+  // the state alone over [j0, j1), everything over [j1, j2)
+  const int j1 = kStatesOnly ? jend : min(jend, j0 + part * p.sub_blocks);
+  const int j2 = kStatesOnly ? jend : min(jend, j1 + p.sub_blocks);
+  if (!kStatesOnly && j1 >= j2) return;  // uniform over the workgroup
+
+  const int slice_raw = kWaves * col + wave;
+  const bool live = slice_raw < p.nslice;  // (a wave without a slice repeats the last one and stores nothing)
+  const int slice = live ? slice_raw : p.nslice - 1;
+  const int per_head = p.P / kCols;
+  const int h = g * p.hpg + slice / per_head, p0 = kCols * (slice % per_head);
+  const size_t bh = static_cast<size_t>(b) * p.H + h;
+  const float alog = p.A[h] * kLog2e;
+  const float Dh = p.D[h];
+  const float dbias = p.dtx.bias != nullptr ? p.dtx.bias[h] : 0.f;
+
+  // ---- addressing: rows (tokens) of x / y, of B / C and of dt ----
+  const uint32_t xrow = static_cast<uint32_t>(p.H) * p.P * 4, brow = static_cast<uint32_t>(p.G) * p.N * 4,
+                 drow = static_cast<uint32_t>(p.H) * 4;
+  const size_t tok0 = static_cast<size_t>(b) * p.T;
+  const uint8_t *const xb = reinterpret_cast<const uint8_t *>(p.x) + tok0 * xrow + (static_cast<size_t>(h) * p.P + p0) * 4;
+  uint8_t *const yb = reinterpret_cast<uint8_t *>(p.y) + tok0 * xrow + (static_cast<size_t>(h) * p.P + p0) * 4;
+  const uint8_t *const Bb = reinterpret_cast<const uint8_t *>(p.B) + tok0 * brow + static_cast<size_t>(g) * p.N * 4;
+  const uint8_t *const Cb = reinterpret_cast<const uint8_t *>(p.C) + tok0 * brow + static_cast<size_t>(g) * p.N * 4;
+  const uint8_t *const db = reinterpret_cast<const uint8_t *>(p.dt) + tok0 * drow + static_cast<size_t>(h) * 4;
+  // descriptor of the rows of block j that exist, `width` bytes of each
+  auto rows_of = [&](const uint8_t *base, uint32_t row, uint32_t width, int j) {
+    const int n = min(kTok, p.T - j * kTok);
+    return make_rsrc(base + static_cast<size_t>(j) * kTok * row, n > 0 ? (n - 1) * row + width : 0u);
+  };
+
+  // ---- data of a block in flight ----
+  u32x4 r_b[kPieces], r_c[kStatesOnly ? 1 : kPieces], r_x[4];
+  float r_dt;
+  uint32_t v_bc[kPieces];
+#pragma unroll
+  for (int k = 0; k < kPieces; ++k) {
+    const int item = tid + kThr * k, n0 = 4 * (item % (N / 4));
+    v_bc[k] = n0 < p.N ? static_cast<uint32_t>(item / (N / 4)) * brow + 4 * n0 : kNowhere;
+  }
+  // (with_c, uniform: a block of which only the state is wanted needs no C; its loads are pointed beyond the
+  // descriptor, where they cost nothing, rather than put behind a branch)
+  auto load_block = [&](int j, bool with_c) __attribute__((always_inline)) {
+    const Rsrc rB = rows_of(Bb, brow, p.N * 4, j);
+#pragma unroll
+    for (int k = 0; k < kPieces; ++k) r_b[k] = buf_load16(rB, v_bc[k]);
+    const Rsrc rx = rows_of(xb, xrow, 4 * kCols, j);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) r_x[k] = buf_load16(rx, static_cast<uint32_t>(8 * k + (lane >> 3)) * xrow + 16 * (lane & 7));
+    r_dt = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rows_of(db, drow, 4, j), r * drow, 0, 0));
+    if constexpr (!kStatesOnly) {
+      const Rsrc rC = rows_of(Cb, brow, p.N * 4, j);
+#pragma unroll
+      for (int k = 0; k < kPieces; ++k) r_c[k] = buf_load16(rC, with_c ? v_bc[k] : kNowhere);
+    }
+  };
+
+  // ---- the state slice, through LDS into the accumulators: 32 rows of NT pieces of 32 floats, in memory order (row
+  //      stride dstate) or in a slot (row stride NT rows of y) ----
+  float *const turn = reinterpret_cast<float *>(smem) + wave * (kCols * kTurnStride);
+  auto st_off = [&](int nt, int k, bool in_y) {  // byte offset of this lane's 16 bytes of rows 8 k .., tile nt
+    const uint32_t row = 8 * k + (lane >> 3);
+    const uint32_t at = in_y ? (row * NT + nt) * xrow : row * (p.N * 4u) + 128 * nt;
+    return 32 * nt + 4 * (lane & 7) < p.N ? at + 16 * (lane & 7) : kNowhere;
+  };
+  const uint32_t st_size = kCols * p.N * 4u, slot_size = p.slots != nullptr ? st_size : (kCols * NT - 1) * xrow + 4 * kCols;
+  const size_t st_base = (bh * p.P + p0) * p.N;
+  f32x16 H[NT];
+  if constexpr (kStatesOnly) {
+    load_block(j0, false);
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) H[nt] = f32x16{};
+  } else {
+    const bool slot = seg > 0 || p.slot0;
+    const float *src = slot ? state_slot(p, b, h, p0, seg, nblocks) : p.h0 != nullptr ? p.h0 + st_base : nullptr;
+    const Rsrc rs = make_rsrc(src != nullptr ? src : p.x, src == nullptr ? 0u : slot ? slot_size : st_size);
+    u32x4 raw[NT][4];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) raw[nt][k] = buf_load16(rs, st_off(nt, k, slot && p.slots == nullptr));
+    load_block(j0, j0 == j1);
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        *reinterpret_cast<u32x4 *>(turn + (8 * k + (lane >> 3)) * kTurnStride + 4 * (lane & 7)) = raw[nt][k];
+#pragma unroll
+      for (int i4 = 0; i4 < 4; ++i4) {
+        const f32x4 v = *reinterpret_cast<const f32x4 *>(turn + pi_of_row(r) * kTurnStride + 8 * i4 + 4 * kg);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) H[nt][4 * i4 + i] = v[i];
+      }
+    }
+  }
+
+  // LDS addresses of this lane (elements)
+  const uint32_t a_c = r * L::kRow + 8 * kg;                                 // C as a 32-row operand, + 16 kk
+  const int tj = lane & 15, t_half = (lane >> 4) & 1;                        // transposed reads: quad tj of the group
+  const uint32_t a_bt = (4 * kg + (tj >> 2)) * L::kRow + 16 * t_half + 8 * (tj & 1) + 4 * ((tj >> 1) & 1);
+  const int sq = wave >> 1, lq = wave > 0 ? 1 : 0;                           // waves 0-2: quarters (0,0), (0,1), (1,1) of the scores
+  const uint32_t a_sb = (16 * sq + tj) * L::kRow + 8 * (lane >> 4);          // B, C as 16-row operands, + 32 kk
+  const uint32_t a_sc = (16 * lq + tj) * L::kRow + 8 * (lane >> 4);
+  float log2_total = 0.f;
+
+  auto block = [&](int j, auto full_tag) __attribute__((always_inline)) {
+    constexpr bool kFull = decltype(full_tag)::value;
+    __syncthreads();  // the previous block's readers (at first: the turning of the state) are done with LDS
+    // ---- registers -> LDS ----
+#pragma unroll
+    for (int k = 0; k < kPieces; ++k) {
+      const int item = tid + kThr * k, c4 = item % (N / 4);
+      // the columns of a group of 16 in the order 0-3, 8-11, 4-7, 12-15
+      const int dst = (item / (N / 4)) * L::kRow + 16 * (c4 >> 2) + 8 * (c4 & 1) + 4 * ((c4 >> 1) & 1);
+      uint32_t t[3][2];
+      const f32x4 vb = __builtin_bit_cast(f32x4, r_b[k]);
+      const float b4[4] = {vb.x, vb.y, vb.z, vb.w};
+      split3_even<4>(b4, t);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x2 *>(sB + q * L::kPart + dst) = u32x2{t[q][0], t[q][1]};
+      if constexpr (kFull) {
+        const f32x4 vc = __builtin_bit_cast(f32x4, r_c[k]);
+        const float c4v[4] = {vc.x, vc.y, vc.z, vc.w};
+        split3_even<4>(c4v, t);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x2 *>(sC + q * L::kPart + dst) = u32x2{t[q][0], t[q][1]};
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) *reinterpret_cast<u32x4 *>(sX + (8 * k + (lane >> 3)) * kXStride + 4 * (lane & 7)) = r_x[k];
+    // ---- decays: lane r (both halves) = token; tokens beyond the sequence have step size zero.  The decay from a
+    //      token to the end of the block is summed from the end: the newest tokens weigh most ----
+    const float dtv = j * kTok + r < p.T ? dt_apply_branchless(r_dt, dbias, p.dtx) : 0.f;
+    const float d = dtv * alog;
+    const float cs = prefix32(d), after = suffix32(d), total = read_lane(cs, kTok - 1);
+    if (kg == 0) {
+      if constexpr (kFull) {
+        s_cs[wave][r] = cs;
+        s_dt[wave][r] = dtv;
+      }
+      s_w[wave][r] = dtv * exp2_fast(after);
+    }
+    const float el = exp2_fast(cs), e_all = exp2_fast(total);
+    if constexpr (kStatesOnly) log2_total += total;
+    load_block(min(j + 1, j2 - 1), j + 1 >= j1);  // (after the last block: a harmless repeat, no branch)
+    __syncthreads();
+
+    f32x16 Y = {};
+    if constexpr (kFull) {
+      // ---- scores: a quarter of the 32 x 32 tile per wave (the fourth wave's, above the diagonal, repeats the third's) ----
+      if (wave < 3) {
+        f32x4 acc = {};
+#pragma unroll
+        for (int kk = 0; kk < N / 32; ++kk) {
+          Op bq[3], cq[3];
+#pragma unroll
+          for (int q = 0; q < 3; ++q) {
+            bq[q].q = *reinterpret_cast<const u32x4 *>(sB + q * L::kPart + a_sb + 32 * kk);
+            cq[q].q = *reinterpret_cast<const u32x4 *>(sC + q * L::kPart + a_sc + 32 * kk);
+          }
+#pragma unroll
+          for (int t = 0; t < 6; ++t) acc = mfma16(bq[kPairA[t]], cq[kPairB[t]], acc);
+        }
+        *reinterpret_cast<f32x4 *>(sG + (16 * lq + tj) * kGStride + 16 * sq + 4 * (lane >> 4)) = acc;
+      }
+      // ---- Y^T[p][l]: the state's part, then scaled by the decay up to token l = r ----
+#pragma unroll
+      for (int kk = 0; kk < N / 16; ++kk) {
+        Op c[3], hp[3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) c[q].q = *reinterpret_cast<const u32x4 *>(sC + q * L::kPart + a_c + 16 * kk);
+        float v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = H[kk >> 1][8 * (kk & 1) + i];
+        split3_even(v, hp);
+        Y = mfma6(hp, c, Y);
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i) Y[i] *= el;
+      __syncthreads();  // the scores are in LDS
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      // x^T: headdim column pi(r), tokens 16 q + {4kg.., 8 + 4kg..}
+      float xv[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) xv[i] = sX[(16 * q + 8 * (i >> 2) + 4 * kg + (i & 3)) * kXStride + pi_of_row(r)];
+      if constexpr (kFull) {
+        // masked scores, transposed: element i is token s of the same order, the column l = r
+        Op gm[3], xo[3];
+        float v[8];
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+          const int sb = 16 * q + 8 * hf + 4 * kg;
+          const f32x4 gv = *reinterpret_cast<const f32x4 *>(sG + r * kGStride + sb);
+          const f32x4 cs_s = *reinterpret_cast<const f32x4 *>(&s_cs[wave][sb]);
+          const f32x4 dt_s = *reinterpret_cast<const f32x4 *>(&s_dt[wave][sb]);
+#pragma unroll
+          for (int i = 0; i < 4; ++i)  // (above the diagonal the tile holds whatever was there: selected, not multiplied)
+            v[4 * hf + i] = sb + i <= r ? gv[i] * (dt_s[i] * exp2_fast(cs - cs_s[i])) : 0.f;
+        }
+        split3_even(v, gm);
+        split3_even(xv, xo);
+        Y = mfma6(xo, gm, Y);
+      }
+      // ---- the state to the end of the block ----
+      Op xm[3];
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf) {
+        const f32x4 w = *reinterpret_cast<const f32x4 *>(&s_w[wave][16 * q + 8 * hf + 4 * kg]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) xv[4 * hf + i] *= w[i];
+      }
+      split3_even(xv, xm);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        if (q == 0) {
+#pragma unroll
+          for (int i = 0; i < 16; ++i) H[nt][i] *= e_all;
+        }
+        Op bt[3];
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+          bt[t].h[0] = lds_read_tr(sB + t * L::kPart + a_bt + 32 * nt + 16 * q * L::kRow);
+          bt[t].h[1] = lds_read_tr(sB + t * L::kPart + a_bt + 32 * nt + (16 * q + 8) * L::kRow);
+        }
+        H[nt] = mfma6(bt, xm, H[nt]);
+      }
+    }
+    if constexpr (kFull) {
+      // ---- y: lane (r, kg) holds columns 16 kg .. 16 kg + 15 of token r ----
+      const int n = min(kTok, p.T - j * kTok);
+      const Rsrc ry = make_rsrc(yb + static_cast<size_t>(j) * kTok * xrow, live ? (n - 1) * xrow + 4 * kCols : 0u);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const f32x4 xr = *reinterpret_cast<const f32x4 *>(sX + r * kXStride + 16 * kg + 4 * c);
+        f32x4 o;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[i] = fmaf(Dh, xr[i], Y[4 * c + i]);
+        buf_store16(ry, static_cast<uint32_t>(r) * xrow + 64 * kg + 16 * c, __builtin_bit_cast(u32x4, o));
+      }
+    }
+  };
+  for (int j = j0; j < j1; ++j) block(j, std::false_type{});
+  if constexpr (!kStatesOnly) {
+    for (int j = j1; j < j2; ++j) block(j, std::true_type{});
+  }
+
+  // ---- the state back to memory: the segment's local end state, or the final state (Alg. 1, "Store") ----
+  if (!kStatesOnly && j2 < nblocks) return;
+  __syncthreads();
+  float *const dst = kStatesOnly ? state_slot(p, b, h, p0, seg + 1, nblocks) : p.final_state + st_base;
+  const Rsrc rs = make_rsrc(dst, !live ? 0u : kStatesOnly ? slot_size : st_size);
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+#pragma unroll
+    for (int i4 = 0; i4 < 4; ++i4)
+      *reinterpret_cast<f32x4 *>(turn + pi_of_row(r) * kTurnStride + 8 * i4 + 4 * kg) =
+          f32x4{H[nt][4 * i4], H[nt][4 * i4 + 1], H[nt][4 * i4 + 2], H[nt][4 * i4 + 3]};
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      buf_store16(rs, st_off(nt, k, kStatesOnly && p.slots == nullptr),
+                  *reinterpret_cast<const u32x4 *>(turn + (8 * k + (lane >> 3)) * kTurnStride + 4 * (lane & 7)));
+  }
+  if (kStatesOnly && live && p0 == 0 && lane == 0) p.decay[bh * p.S + seg] = log2_total;
+}
+
+// slot[0] = h0 (only where the full launch reads it there); slot[s] = exp2(decay[s-1]) * slot[s-1] + local[s-1].
+// grid (ceil(P*N/1024), Bt*H), four consecutive state elements per thread; the loads, which do not depend on the
+// chain, are issued eight segments at a time.
+constexpr int kPassThr = 256;
+__global__ __launch_bounds__(kPassThr) void split_pass_kernel(const SplitParams p) {
+  constexpr int kAhead = 8;
+  const int e = (blockIdx.x * kPassThr + threadIdx.x) * 4;
+  if (e >= p.P * p.N) return;
+  const int nblocks = (p.T + kTok - 1) / kTok, NT = (p.N + 31) / 32;
+  const int b = blockIdx.y / p.H, h = blockIdx.y % p.H;
+  const int row = e / p.N, n = e % p.N;
+  const size_t piece = p.slots != nullptr ? static_cast<size_t>(row % kCols) * p.N + n
+                                          : static_cast<size_t>((row % kCols) * NT + n / 32) * p.H * p.P + n % 32;
+  auto at = [&](int s) { return reinterpret_cast<f32x4 *>(state_slot(p, b, h, row / kCols * kCols, s, nblocks) + piece); };
+  f32x4 run = {};
+  if (p.h0 != nullptr) run = *reinterpret_cast<const f32x4 *>(p.h0 + static_cast<size_t>(blockIdx.y) * p.P * p.N + e);
+  const float *const dp = p.decay + static_cast<size_t>(blockIdx.y) * p.S;
+  if (p.slot0) *at(0) = run;
+  for (int s0 = 1; s0 < p.S; s0 += kAhead) {
+    f32x4 v[kAhead];
+    float d[kAhead];
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) {
+      const int s = min(s0 + k, p.S - 1);  // (clamped: the surplus loads of the last group are not used)
+      v[k] = *at(s);
+      d[k] = dp[s - 1];
+    }
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) {
+      if (s0 + k < p.S) {
+        const float f = exp2_fast(d[k]);
+        run = f32x4{fmaf(f, run.x, v[k].x), fmaf(f, run.y, v[k].y), fmaf(f, run.z, v[k].z), fmaf(f, run.w, v[k].w)};
+        *at(s0 + k) = run;
+      }
+    }
+  }
+}
+
+}  // namespace
+
+// How a sequence is cut up.
+struct SplitPlan {
+  int segments, sub, sub_blocks;
+  double us;  // modelled time
+};
+
+// Segments whose states fit: the workspace holds (S + 1 values per head and segment fit it), or every segment's rows of
+// y do (see state_slot).
+static bool slots_in_workspace(const Dims &d, int S) {
+  return static_cast<size_t>(d.Bt) * d.H * S * (static_cast<size_t>(d.P) * d.N + 1) * sizeof(float) <= generic_workspace_bytes(d);
+}
+static bool segments_fit(const Dims &d, int S) {
+  const int nblocks = (d.T + kTok - 1) / kTok, rows = kCols * ((d.N + 31) / 32);
+  return slots_in_workspace(d, S) ||
+         (nblocks / S * kTok >= rows && d.T - segment_begin(S - 1, S, nblocks) * kTok >= rows);
+}
+
+// Microseconds on MI355X, fits to timings of 10 shapes: a full block; a block of which only the state is updated, in
+// the states-only launch and in the full one; by state tiles.  A CU holds two workgroups, which slow each other by a
+// third; a launch of more runs in rounds.
+constexpr double kFullUs[4] = {2.2, 3.2, 4.1, 4.9}, kStateUs[4] = {1.0, 1.2, 1.4, 1.55}, kCarryUs[4] = {0.75, 1.3, 1.7, 2.1};
+static double rounds_us(long wgs, double us) {
+  double t = 0.0;
+  for (; wgs > 0; wgs -= 512) t += us * (wgs <= 256 ? 1.0 : 1.0 + 0.33 * ((wgs < 512 ? wgs : 512) - 256) / 256.0);
+  return t;
+}
+
+static SplitPlan split_plan(const Dims &d) {
+  const int nblocks = (d.T + kTok - 1) / kTok, NT = (d.N + 31) / 32;
+  const long wgs = static_cast<long>(d.Bt) * d.G * ((d.hpg * (d.P / kCols) + kWaves - 1) / kWaves);
+  const int ks = knobs().seg_blocks, kp = knobs().seg_parts;
+  SplitPlan pl = {1, 1, nblocks, 8.0 + 0.5 * NT + rounds_us(wgs, nblocks * kFullUs[NT - 1])};
+  if (ks > 0) {
+    pl.segments = (nblocks + ks - 1) / ks;
+    while (pl.segments > 1 && !segments_fit(d, pl.segments)) --pl.segments;
+    pl.sub = kp > 0 && pl.segments == 1 ? kp : 1;
+    pl.sub_blocks = (nblocks + pl.sub - 1) / pl.sub;
+    return pl;
+  }
+  for (int sub = 2; sub <= nblocks && sub <= 16 && wgs * sub <= 512; ++sub) {
+    const int len = (nblocks + sub - 1) / sub;
+    const double us = 8.0 + 0.5 * NT + rounds_us(wgs * sub, len * kFullUs[NT - 1] + (nblocks - len) * kCarryUs[NT - 1]);
+    if (us < pl.us) pl = {1, sub, len, us};
+  }
+  const double state_mb = static_cast<double>(d.Bt) * d.H * d.P * d.N * 4e-6;
+  for (int S = 2; S <= nblocks && S <= 64; ++S) {
+    if (!segments_fit(d, S)) continue;
+    const int len = (nblocks + S - 1) / S;
+    const double us = 16.0 + 2.4 * NT + S * state_mb / 4.5 + rounds_us(wgs * (S - 1), len * kStateUs[NT - 1]) +
+                      rounds_us(wgs * S, len * kFullUs[NT - 1]);
+    if (us < pl.us) pl = {S, 1, nblocks, us};
+  }
+  return pl;
+}
+
+bool split_f32_supported(const Dims &d) {
+  const unsigned long long lim = 0xFFFF0000ull, t = static_cast<unsigned long long>(d.T);
+  return !d.bf16 && d.P % kCols == 0 && d.N % 8 == 0 && d.N <= 128 && t * d.H * d.P * 4 <= lim && t * d.G * d.N * 4 <= lim &&
+         static_cast<unsigned long long>(d.Bt) * d.H <= 65535 &&
+         static_cast<unsigned long long>(d.Bt) * d.H * (d.P / kCols) * 64 <= 0x7fffffffull;
+}
+
+bool split_f32_chosen(const Dims &d) {
+  if (!split_f32_supported(d)) return false;
+  if (knobs().seg_blocks > 0) return true;
+  return split_plan(d).us < f32_other_us(d);
+}
+
+void split_f32_plan(const Dims &d, int *seg_blocks, int *segments, int *parts) {
+  const SplitPlan pl = split_plan(d);
+  const int nblocks = (d.T + kTok - 1) / kTok;
+  *seg_blocks = (nblocks + pl.segments - 1) / pl.segments;
+  *segments = pl.segments;
+  *parts = pl.sub;
+}
+
+template <int NT>
+static void launch_nt(const SplitParams &p, unsigned wgs, hipStream_t stream, KernelTrace *trace) {
+  if (p.S > 1) {
+    hipLaunchKernelGGL((split_f32_kernel<NT, true>), dim3(wgs * (p.S - 1)), dim3(kThr), 0, stream, p);
+    trace_mark(trace, stream, "segment_states");
+    hipLaunchKernelGGL(split_pass_kernel, dim3((p.P * p.N + 4 * kPassThr - 1) / (4 * kPassThr), p.Bt * p.H), dim3(kPassThr), 0,
+                       stream, p);
+    trace_mark(trace, stream, "segment_pass");
+  }
+  hipLaunchKernelGGL((split_f32_kernel<NT, false>), dim3(wgs * p.S * p.sub), dim3(kThr), 0, stream, p);
+  trace_mark(trace, stream, "prefill_f32");
+}
+
+hipError_t launch_prefill_split_f32(const Dims &d, const void *x, const float *dt, const float *A, const void *B,
+                                    const void *C, const float *D, const float *h0, void *y, float *final_state,
+                                    void *workspace, hipStream_t stream, KernelTrace *trace) {
+  const SplitPlan pl = split_plan(d);
+  SplitParams p;
+  p.x = static_cast<const float *>(x);
+  p.dt = dt;
+  p.A = A;
+  p.B = static_cast<const float *>(B);
+  p.C = static_cast<const float *>(C);
+  p.D = D;
+  p.h0 = h0;
+  p.y = static_cast<float *>(y);
+  p.final_state = final_state;
+  // (decays: S values per head, of which the workspace holds at least one per token and head)
+  p.decay = static_cast<float *>(workspace);
+  p.slots = nullptr;
+  if (pl.segments > 1 && slots_in_workspace(d, pl.segments)) {
+    p.slots = static_cast<float *>(workspace);
+    p.decay = p.slots + static_cast<size_t>(d.Bt) * d.H * pl.segments * d.P * d.N;
+  }
+  p.T = d.T;
+  p.H = d.H;
+  p.P = d.P;
+  p.N = d.N;
+  p.G = d.G;
+  p.Bt = d.Bt;
+  p.hpg = d.hpg;
+  p.nslice = d.hpg * (d.P / kCols);
+  p.cpg = (p.nslice + kWaves - 1) / kWaves;
+  p.S = pl.segments;
+  p.sub = pl.sub;
+  p.sub_blocks = pl.sub_blocks;
+  p.dtx = d.dtx;
+  const size_t state_bytes = static_cast<size_t>(d.Bt) * d.H * d.P * d.N * sizeof(float);
+  const char *const h = reinterpret_cast<const char *>(h0), *const f = reinterpret_cast<const char *>(final_state);
+  const bool aliases = h0 != nullptr && h < f + state_bytes && f < h + state_bytes;
+  p.slot0 = aliases && p.S > 1;
+  if (aliases && p.S == 1) {  // the workgroup that stores the final state must be the one that reads h0
+    p.sub = 1;
+    p.sub_blocks = (d.T + kTok - 1) / kTok;
+  }
+  const unsigned wgs = static_cast<unsigned>(d.Bt) * d.G * p.cpg;
+  switch ((d.N + 31) / 32) {
+    case 1: launch_nt<1>(p, wgs, stream, trace); break;
+    case 2: launch_nt<2>(p, wgs, stream, trace); break;
+    case 3: launch_nt<3>(p, wgs, stream, trace); break;
+    default: launch_nt<4>(p, wgs, stream, trace); break;
+  }
+  return hipGetLastError();
+}
+
+}  // namespace ssd

@@ -48,6 +48,12 @@ __device__ __forceinline__ void split3(const float v[8], Op o[3]) {
   }
 }
 
+// D(16x16) += A(16x32) * B(32x16).  Lane (r = lane%16, kg = lane/16) supplies A[r][8kg..8kg+7] and B[8kg..8kg+7][r];
+// it receives D[4kg + i][r] in element i.
+__device__ __forceinline__ f32x4 mfma16(const Op &a, const Op &b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, c, 0, 0, 0);
+}
+
 __device__ __forceinline__ float bf_lo(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ __forceinline__ float bf_hi(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
 __device__ __forceinline__ uint32_t pack2(float lo, float hi) {  // two fp32 -> packed bf16, RNE
@@ -56,6 +62,37 @@ __device__ __forceinline__ uint32_t pack2(float lo, float hi) {  // two fp32 -> 
   const f32x2 v = {lo, hi};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
+// The parts for a product in which BOTH factors are split: six products stand for the nine (mid lo, lo mid and
+// lo lo are left out), so the two lower parts are rounded to nearest -- what is left out then has no preferred sign
+// and is about 2^-26 of the product.  W = values, a multiple of 2; part p of values 2k, 2k+1 goes to out[p][k].
+template <int W>
+__device__ __forceinline__ void split3_even(const float *v, uint32_t (*out)[W / 2]) {
+#pragma unroll
+  for (int k = 0; k < W / 2; ++k) {
+    const uint32_t a = __float_as_uint(v[2 * k]), b = __float_as_uint(v[2 * k + 1]);
+    out[0][k] = __builtin_amdgcn_perm(b, a, 0x07060302u);
+    const float ra = v[2 * k] - __uint_as_float(a & 0xffff0000u), rb = v[2 * k + 1] - __uint_as_float(b & 0xffff0000u);
+    const uint32_t m = pack2(ra, rb);
+    out[1][k] = m;
+    out[2][k] = pack2(ra - bf_lo(m), rb - bf_hi(m));
+  }
+}
+__device__ __forceinline__ void split3_even(const float v[8], Op o[3]) {
+  uint32_t t[3][4];
+  split3_even<8>(v, t);
+#pragma unroll
+  for (int p = 0; p < 3; ++p)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) o[p].u[k] = t[p][k];
+}
+// The six products, smallest first.
+constexpr int kPairA[6] = {1, 2, 0, 1, 0, 0}, kPairB[6] = {1, 0, 2, 0, 1, 0};
+__device__ __forceinline__ f32x16 mfma6(const Op a[3], const Op b[3], f32x16 c) {
+#pragma unroll
+  for (int t = 0; t < 6; ++t) c = mfma(a[kPairA[t]], b[kPairB[t]], c);
+  return c;
+}
+
 __device__ __forceinline__ float exp2_fast(float v) { return __builtin_amdgcn_exp2f(v); }
 
 // Transposed LDS read (ds_read_b64_tr_b16).  Inside each group of 16 lanes, lane j names four consecutive
@@ -66,6 +103,34 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ u32x2 lds_read_tr(const uint16_t *p) {
   typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
   return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)p));
+}
+
+// Sums over 32 lanes (both halves of the wave hold the same values), by lane moves of the vector ALU inside rows of
+// 16 lanes and one row's total for the other.  (Every lane must be active where a move is evaluated.)
+template <int kCtrl>
+__device__ __forceinline__ float dpp_or_zero(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kCtrl, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float read_lane(float v, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+__device__ __forceinline__ float prefix32(float v) {  // the lanes up to and including this one
+  v += dpp_or_zero<0x111>(v);  // row_shr:1
+  v += dpp_or_zero<0x112>(v);
+  v += dpp_or_zero<0x114>(v);
+  v += dpp_or_zero<0x118>(v);
+  const float first = read_lane(v, 15);
+  return v + ((threadIdx.x & 16) ? first : 0.f);
+}
+__device__ __forceinline__ float suffix32(float v) {  // the lanes behind this one
+  const float over = read_lane(v, 16), next = dpp_or_zero<0x101>(v);  // row_shl:1
+  v = (threadIdx.x & 31) == 15 ? over : next;
+  v += dpp_or_zero<0x101>(v);
+  v += dpp_or_zero<0x102>(v);
+  v += dpp_or_zero<0x104>(v);
+  v += dpp_or_zero<0x108>(v);
+  const float second = read_lane(v, 16);
+  return v + ((threadIdx.x & 16) ? 0.f : second);
 }
 
 // Buffer addressing: loads beyond the descriptor's size return zero, stores beyond it are dropped.

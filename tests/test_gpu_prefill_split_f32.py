@@ -1,0 +1,112 @@
+"""fp32 prefill on split bf16 operands: segments, their states in the workspace or in y, shared single segments."""
+import pytest
+import torch
+
+from oracle import ssd_oracle
+from paper_2603_09555_amd import inputs
+from parity import TOL, assert_close
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ssd():
+    from paper_2603_09555_amd import ssd
+    return ssd
+
+
+@pytest.fixture(autouse=True)
+def _reset(ssd):
+    ssd.reset_knobs()
+    yield
+    ssd.reset_knobs()
+
+
+def run(ssd, cfg, inp, h0=None, alias=False, **kw):
+    dev = {k: v.cuda() for k, v in inp.items()}
+    h = None if h0 is None else h0.cuda()
+    y, st = ssd.ssd_prefill(dev["x"], dev["dt"], dev["A"], dev["B"], dev["C"], dev["D"], cfg.chunk, h0=h,
+                            final_state=h if alias else None, **kw)
+    torch.cuda.synchronize()
+    return y, st
+
+
+def check(ssd, cfg, inp, h0, y, st, what):
+    y_ref, st_ref = ssd_oracle.prefill(inp["x"], inp["dt"], inp["A"], inp["B"], inp["C"], inp["D"], h0=h0)
+    assert_close(y, y_ref, TOL["f32"], what + " y")
+    assert_close(st, st_ref, TOL["f32"], what + " final state")
+
+
+CASES = [
+    # Bt, T, H, P, N, G, L, h0, blocks per segment, workgroups per segment
+    (1, 31, 2, 32, 8, 1, 64, False, 1, 1),       # less than a block; dstate padded
+    (2, 33, 4, 64, 16, 2, 64, True, 2, 2),       # a block and a token; one segment shared by two
+    (1, 300, 5, 64, 128, 1, 64, True, 2, 1),     # ten slices over three workgroups; states in the workspace
+    (1, 640, 3, 64, 128, 1, 512, True, 4, 1),    # ... in y (chunks too long for the workspace); segments of 4 blocks
+    (2, 500, 6, 96, 72, 3, 1000, False, 5, 1),   # ... in y, dstate 72, slices of one head over two workgroups
+    (3, 1000, 4, 32, 40, 2, 100, True, 7, 1),    # uneven segments
+    (1, 700, 8, 64, 64, 4, 64, False, 22, 4),    # one segment, four workgroups each
+    (1, 256, 2, 32, 96, 1, 64, True, 1, 1),      # as many segments as blocks
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c)))
+def test_split_prefill_matches_oracle(ssd, case):
+    *dims, with_h0, seg, sub = case
+    cfg = inputs.SSDConfig("t", *dims, "f32")
+    ssd.set_knob("seg_blocks", seg)
+    ssd.set_knob("seg_parts", sub)
+    plan = ssd.prefill_plan(ssd.make_shape(*dims, torch.float32))
+    print("split fp32", case, plan, flush=True)
+    assert plan["path"] == "mfma_f32" and plan["f32_segments"] == 0
+    inp = inputs.make_prefill_inputs(cfg, seed=3)
+    h0 = inputs.make_state(cfg, seed=3, scale=0.3) if with_h0 else None
+    y, st = run(ssd, cfg, inp, h0)
+    check(ssd, cfg, inp, h0, y, st, "split")
+    y2, st2 = run(ssd, cfg, inp, h0)
+    assert torch.equal(y, y2) and torch.equal(st, st2)
+    if h0 is not None:   # h0 and final_state in one buffer: the same results
+        y3, st3 = run(ssd, cfg, inp, h0, alias=True)
+        if plan["segments"] > 1 or plan["parts"] == 1:
+            assert torch.equal(y, y3) and torch.equal(st, st3)
+        check(ssd, cfg, inp, h0, y3, st3, "aliased")
+
+
+@pytest.mark.parametrize("seg", [4, 64])
+def test_split_prefill_steep_decay_and_step_size_map(ssd, seg):
+    cfg = inputs.SSDConfig("t", 2, 600, 4, 64, 128, 1, 256, "f32")
+    ssd.set_knob("seg_blocks", seg)
+    inp = inputs.make_prefill_inputs(cfg, seed=5)
+    inp["dt"] = torch.full_like(inp["dt"], 0.5)
+    inp["A"] = torch.tensor([-1.0, -6.0, -12.0, -24.0])
+    y, st = run(ssd, cfg, inp)
+    check(ssd, cfg, inp, None, y, st, "steep")
+    g = torch.Generator().manual_seed(6)
+    raw, bias = torch.randn(inp["dt"].shape, generator=g) * 1.5 - 3.0, torch.randn((4,), generator=g) * 0.5
+    inp2 = dict(inp, dt=raw)
+    y, st = run(ssd, cfg, inp2, dt_bias=bias.cuda(), dt_softplus=True, dt_limit=(1e-3, 0.5))
+    inp2["dt"] = torch.from_numpy(ssd_oracle.dt_transform(raw, bias, True, (1e-3, 0.5))).float()
+    check(ssd, cfg, inp2, None, y, st, "map")
+
+
+def test_split_prefill_replayed_from_a_hip_graph(ssd):
+    """States between the launches lie in y: replays, with eager work between them, leave what an eager call leaves."""
+    cfg = inputs.SSDConfig("t", 1, 1024, 6, 64, 128, 1, 1024, "f32")
+    ssd.set_knob("seg_blocks", 8)
+    dev = {k: v.cuda() for k, v in inputs.make_prefill_inputs(cfg, seed=9).items()}
+    args = [dev[k] for k in ("x", "dt", "A", "B", "C", "D")]
+    y_ref, st_ref = ssd.ssd_prefill(*args, cfg.chunk)
+    y, st = torch.empty_like(y_ref), torch.empty_like(st_ref)
+    ws = torch.empty((ssd.prefill_workspace_bytes(ssd.make_shape(1, 1024, 6, 64, 128, 1, 1024, torch.float32)),),
+                     dtype=torch.uint8, device="cuda")
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            ssd.ssd_prefill(*args, cfg.chunk, y=y, final_state=st, workspace=ws)
+    torch.cuda.current_stream().wait_stream(side)
+    for _ in range(3):
+        y.fill_(7.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, y_ref) and torch.equal(st, st_ref)

@@ -99,3 +99,28 @@ def test_f32_time_segments_over_a_grid_of_shapes():
         assert s == 1 or wgs * s <= 256          # the library cuts only as far as the workgroups run side by side
         if wgs * 2 <= 256 and nblocks >= 2:
             assert s >= 2                        # and does cut when half the chip would idle
+
+
+def test_split_f32_plans():
+    """fp32 prompts large enough to be worth several launches: cut into segments whose states fit either the
+    workspace or their own rows of y; small ones keep the single launch."""
+    base = inputs.CONFIGS["c0_tiny_f32"]
+    split = 0
+    for Bt, T, H, P, N, L in itertools.product([1, 2, 8], [64, 65, 512, 2000, 4096], [2, 11, 24], [32, 64], [16, 72, 128], [64, 256]):
+        c = base.with_(batch=Bt, seqlen=T, nheads=H, headdim=P, dstate=N, chunk=L)
+        sh = shape_of(c)
+        p = ssd.prefill_plan(sh)
+        assert p["path"] in ("mfma_f32", "generic_f32")
+        if p["path"] == "generic_f32" or p["f32_segments"]:
+            continue
+        split += 1
+        S, nblocks = p["segments"], (T + 31) // 32
+        assert 1 <= S <= nblocks and p["seg_blocks"] == (nblocks + S - 1) // S and p["parts"] >= 1
+        assert S == 1 or p["parts"] == 1
+        if S > 1 and ssd.prefill_workspace_bytes(sh) < Bt * H * S * (P * N + 1) * 4:
+            rows = 32 * ((N + 31) // 32)
+            begin = [s * nblocks // S * 32 for s in range(S)] + [T]
+            assert all(b - a >= rows for a, b in zip(begin, begin[1:]))
+    assert split > 100
+    p = ssd.prefill_plan(shape_of(base.with_(seqlen=2048, nheads=24, headdim=64, dstate=128, chunk=256)))
+    assert p["path"] == "mfma_f32" and (p["segments"], p["seg_blocks"], p["f32_segments"]) == (16, 4, 0)
