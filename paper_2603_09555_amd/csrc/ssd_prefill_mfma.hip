@@ -114,11 +114,15 @@ struct NSlice {
 //   blk0[q], item0[q]    number of blocks / segments of the sequences before q (entry nseq: totals)
 //   slot0[q]             number of state slots before q: a sequence of several segments has one slot
 //                        per segment, a sequence of one segment needs none
-//   blk_seq[i], item_seq[i]   sequence that block i / entry i of the segment list belongs to
+//   blk_seq[i]           sequence that block i belongs to
+//   item_seq[i]          sequence that entry i of the segment list belongs to, plus kLastSegment if the entry is its
+//                        last segment; -1 beyond the list, up to the capacity that grids are sized for
 // Blocks and segments are numbered over the whole batch; workspace arrays are indexed by those
 // numbers (capacities nb_cap, slot_cap are upper bounds that the host can compute from the token
 // count and the number of sequences alone).  Boundaries that are not non-decreasing within
 // [0, total] give empty tables: every later kernel then finds nothing to do.
+
+constexpr int kLastSegment = 1 << 30;
 
 __global__ __launch_bounds__(256) void varlen_scan_kernel(const int32_t *__restrict__ cu, int nseq, int total,
                                                           int blk_len, int seg_blocks, int32_t *__restrict__ tok0,
@@ -198,7 +202,7 @@ constexpr int kSortMax = 2048;
 __global__ __launch_bounds__(256) void varlen_fill_kernel(const int32_t *__restrict__ blk0,
                                                           const int32_t *__restrict__ item0, int nseq,
                                                           int seg_blocks, int32_t *__restrict__ blk_seq,
-                                                          int32_t *__restrict__ item_seq) {
+                                                          int32_t *__restrict__ item_seq, int item_cap) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i < blk0[nseq]) blk_seq[i] = owner_of(blk0, nseq, i);
   const int n_items = item0[nseq], n_full = n_items - nseq;
@@ -209,6 +213,8 @@ __global__ __launch_bounds__(256) void varlen_fill_kernel(const int32_t *__restr
       if (item0[mid] - mid <= i) lo = mid; else hi = mid;
     }
     item_seq[i] = lo;
+  } else if (i >= n_items && i < item_cap) {
+    item_seq[i] = -1;
   }
   // (no early return above: the barrier below is reached by every thread)
   __shared__ int16_t last_blocks[kSortMax];  // blocks in the last segment of every sequence (<= seg_blocks)
@@ -229,7 +235,96 @@ __global__ __launch_bounds__(256) void varlen_fill_kernel(const int32_t *__restr
         rank += (other > mine || (other == mine && k < q)) ? 1 : 0;
       }
     }
-    item_seq[n_full + rank] = q;
+    item_seq[n_full + rank] = q | kLastSegment;
+  }
+}
+
+// Both steps in one workgroup, for batches small enough for it (one thread per sequence; the lists filled in a few
+// trips): the scans run across the threads and the searches in LDS.  64 sequences, 16384 tokens: the two kernels above
+// take 7.4 + 4.7 us and a launch between them, most of it one thread's serial sum; this one
+// 5.6 us (the whole call 185 -> 174; 11 sequences, 763 tokens, 9 heads: 36 -> 30).
+constexpr int kTableThreads = 1024;
+constexpr int kTableBlocks = 16 * kTableThreads;  // most blocks (and list entries) it fills
+__global__ __launch_bounds__(kTableThreads) void varlen_tables_kernel(
+    const int32_t *__restrict__ cu, int nseq, int total, int blk_len, int seg_blocks, int32_t *__restrict__ tok0,
+    int32_t *__restrict__ len, int32_t *__restrict__ blk0, int32_t *__restrict__ item0, int32_t *__restrict__ slot0,
+    int32_t *__restrict__ blk_seq, int32_t *__restrict__ item_seq, int item_cap) {
+  constexpr int kWaves = kTableThreads / 64;
+  __shared__ int s_blk[kTableThreads + 1], s_item[kTableThreads + 1], s_sum[3][kWaves];
+  __shared__ int s_last[kTableThreads];
+  __shared__ int s_bad;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (tid == 0) s_bad = 0;
+  __syncthreads();
+  int a = 0, l = 0, n = 0, segs = 0;
+  if (tid < nseq) {
+    a = cu[tid];
+    const int b = cu[tid + 1];
+    if (a < 0 || b < a || b > total) {
+      s_bad = 1;
+    } else {
+      l = b - a;
+      n = (l + blk_len - 1) / blk_len;
+      segs = max(1, (n + seg_blocks - 1) / seg_blocks);
+    }
+  }
+  // exclusive sums over the sequences: blocks, segments, state slots
+  const int own[3] = {n, segs, segs > 1 ? segs : 0};
+  int sum[3] = {own[0], own[1], own[2]};
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const int up = __shfl_up(sum[k], off, 64);
+      sum[k] += lane >= off ? up : 0;
+    }
+  }
+  if (lane == 63) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) s_sum[k][wave] = sum[k];
+  }
+  __syncthreads();
+  const bool bad = s_bad != 0;
+  for (int w = 0; w < wave; ++w) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) sum[k] += s_sum[k][w];
+  }
+  if (tid < nseq) {
+    tok0[tid] = bad ? 0 : a;
+    len[tid] = bad ? 0 : l;
+    blk0[tid] = s_blk[tid] = bad ? 0 : sum[0] - own[0];
+    item0[tid] = s_item[tid] = bad ? 0 : sum[1] - own[1];
+    slot0[tid] = bad ? 0 : sum[2] - own[2];
+    s_last[tid] = n - (segs - 1) * seg_blocks;  // blocks in the last segment
+    if (tid == nseq - 1) {
+      blk0[nseq] = s_blk[nseq] = bad ? 0 : sum[0];
+      item0[nseq] = s_item[nseq] = bad ? 0 : sum[1];
+      slot0[nseq] = bad ? 0 : sum[2];
+    }
+  }
+  __syncthreads();
+  const int blocks = s_blk[nseq], n_items = s_item[nseq], n_full = bad ? 0 : n_items - nseq;
+  for (int i = tid; i < blocks; i += kTableThreads) blk_seq[i] = owner_of(s_blk, nseq, i);
+  for (int i = tid; i < item_cap; i += kTableThreads) {
+    if (i < n_full) {
+      int lo = 0, hi = nseq;
+      while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (s_item[mid] - mid <= i) lo = mid; else hi = mid;
+      }
+      item_seq[i] = lo;
+    } else if (i >= n_items) {
+      item_seq[i] = -1;
+    }
+  }
+  if (tid < nseq && !bad) {
+    const int mine = s_last[tid];
+    int rank = 0;
+    for (int k = 0; k < nseq; ++k) {
+      const int other = s_last[k];
+      rank += (other > mine || (other == mine && k < tid)) ? 1 : 0;
+    }
+    item_seq[n_full + rank] = tid | kLastSegment;
   }
 }
 
@@ -631,6 +726,8 @@ __device__ __forceinline__ bool wg_coords_varlen(const ScanParams &p, bool last_
   // number of workgroups.  The list is sorted by length; for the full pass (whose entries differ in
   // length) it is first dealt into eight hands, hand k holding entries k, k + 8, ..., and the hands
   // are laid end to end: every XCD then works on the same mix of long and short entries, long first.
+  // (By the list's actual length: split by its capacity, which would save this trip to memory, four sequences of 2202
+  // tokens in 20 segments of a capacity of 24 left some XCDs three rounds of workgroups and others two: 128 -> 153 us.)
   const int total = n_list * p.cols;
   const int per_xcd = (total + kXcds - 1) / kXcds;
   const int id = blockIdx.x;
@@ -646,7 +743,7 @@ __device__ __forceinline__ bool wg_coords_varlen(const ScanParams &p, bool last_
     const int pos = item < big ? item % (base + 1) : (item - big) % base;
     item = pos * kXcds + hand;
   }
-  const int q = p.vp.item_seq[item];
+  const int q = p.vp.item_seq[item] & (kLastSegment - 1);
   const int first = p.vp.item0[q];
   v.b = q;
   v.S = p.vp.item0[q + 1] - first;
@@ -1599,7 +1696,8 @@ void chunk_scan_kernel(const ScanParams p) {
 }
 
 // ---- segment_pass: slot[0] = h0; slot[sg] = exp2(decay[sg-1]) * slot[sg-1] + local[sg-1] --------
-// grid (P*N/1024, rows <= sequences*H), four consecutive state elements per thread.  seg_state slot sg (sg >= 1)
+// grid (P*N/1024, rows), four consecutive state elements per thread; a row is a (sequence, head), of a packed batch a
+// (non-last segment, head).  seg_state slot sg (sg >= 1)
 // holds the local end state of segment sg-1 on entry and the state entering segment sg on exit.
 // The chain over segments is serial, but the loads do not depend on it: they are issued eight
 // segments at a time (sixteen measured slower) before the chain consumes them, so the kernel pays a few memory round trips
@@ -1610,14 +1708,18 @@ __global__ __launch_bounds__(kThreads) void segment_pass_kernel(float *__restric
                                                                 int rows, const VarPlan vp, const NSlice ns) {
   constexpr int kAhead = 8;
   const int e = (blockIdx.x * kThreads + threadIdx.x) * 4;
-  if (vp.tok0 != nullptr && vp.slot0[vp.nseq] == 0) return;  // no sequence has more than one segment
-  for (size_t bh = blockIdx.y; bh < static_cast<size_t>(rows); bh += gridDim.y) {  // (sequence, head)
+  for (size_t row = blockIdx.y; row < static_cast<size_t>(rows); row += gridDim.y) {
   int S = S_plain;
-  size_t slot0 = bh * S_plain;
+  size_t bh = row, slot0 = row * S_plain;  // (sequence, head); its first slot
   if (vp.tok0 != nullptr) {
-    const int q = static_cast<int>(bh / H), h = static_cast<int>(bh % H);
+    // one row per head and non-last segment of the list; the row of a sequence's first segment does its chain
+    const int i = static_cast<int>(row / H), h = static_cast<int>(row % H);
+    const int q = vp.item_seq[i];
+    if (q < 0 || (q & kLastSegment)) continue;
     const int first = vp.item0[q];
+    if (i != first - q) continue;
     S = vp.item0[q + 1] - first;
+    bh = static_cast<size_t>(q) * H + h;
     slot0 = static_cast<size_t>(h) * vp.slot_cap + vp.slot0[q];
   }
   if (S < 2) continue;  // a single segment starts from h0 itself
@@ -1929,9 +2031,11 @@ hipError_t launch_slice(const Dims &d, const NSlice ns, const int32_t *cu, const
   p.slots = (S - 1) * parts + 1;
   p.vp = vp;
   p.fold = pl.fold;
-  if (varlen || S > 1) {
-    // (a packed batch always takes this route: whether any sequence has more than one segment is
-    // known on the device only; workgroups of last segments leave the states-only pass at once)
+  // a non-last segment is seg_blocks whole blocks; no more of them than that allows, and no states pass if that is none
+  const int full_cap = varlen ? (w.NB - d.Bt) / seg_blocks : 0;
+  if (varlen ? full_cap > 0 : S > 1) {
+    // (which sequences of a packed batch have more than one segment is known on the device only: the workgroups of
+    // entries that are last segments, or none, leave at once)
     // heads per workgroup of the states-only kernel.  Two, with two workgroups per CU, measured with the current
     // loop: 40.0 against 35.8 us at 16384 tokens x 80 heads, 31.4 against 28.7 at 8 x 4096 x 48, 14.0 against
     // 15.6 at 2048 x 24 -- slower where it matters.
@@ -1939,14 +2043,14 @@ hipError_t launch_slice(const Dims &d, const NSlice ns, const int32_t *cu, const
     p.cols = d.G * p.cpg;
     p.segs = (S - 1) * parts;
     p.total = p.cols * p.segs * d.Bt;
-    if (varlen) p.total = p.cols * items;
+    if (varlen) p.total = p.cols * full_cap;
     p.per_xcd = (p.total + kXcds - 1) / kXcds;
     hipLaunchKernelGGL((chunk_scan_kernel<true, kStatesHeads>), dim3(kXcds * p.per_xcd), dim3(128 * kStatesHeads), 0,
                        stream, p);
     trace_mark(trace, stream, "segment_states");
-    const int rows_bh = d.Bt * Hs;  // a packed batch may have many one-segment sequences: rows are looped over
+    const int rows_bh = (varlen ? full_cap : d.Bt) * Hs;
     if (!p.fold)
-      hipLaunchKernelGGL(segment_pass_kernel, dim3(kP * kN / (4 * kThreads), rows_bh > (varlen ? 2048 : 65535) ? (varlen ? 2048 : 65535) : rows_bh),
+      hipLaunchKernelGGL(segment_pass_kernel, dim3(kP * kN / (4 * kThreads), rows_bh > 65535 ? 65535 : rows_bh),
                          dim3(kThreads), 0, stream, seg_state, seg_decay, h0, p.slots, Hs, rows_bh, vp, ns);
     if (!p.fold) trace_mark(trace, stream, "segment_pass");
   }
@@ -1990,12 +2094,19 @@ hipError_t launch(const Dims &d, const int32_t *cu, const void *x, const float *
 // blk0, item0, slot0 of nseq + 1 entries each, blk_seq of nb_cap, item_seq of item_cap entries).
 void launch_varlen_tables(const int32_t *cu, int total, int blk_len, int seg_blocks, int item_cap, const VarPlan &vp,
                           hipStream_t stream) {
+  const int cap = vp.nb_cap > item_cap ? vp.nb_cap : item_cap;
+  if (vp.nseq <= kTableThreads && cap <= kTableBlocks) {
+    hipLaunchKernelGGL(varlen_tables_kernel, dim3(1), dim3(kTableThreads), 0, stream, cu, vp.nseq, total, blk_len, seg_blocks,
+                       const_cast<int32_t *>(vp.tok0), const_cast<int32_t *>(vp.len), const_cast<int32_t *>(vp.blk0),
+                       const_cast<int32_t *>(vp.item0), const_cast<int32_t *>(vp.slot0),
+                       const_cast<int32_t *>(vp.blk_seq), const_cast<int32_t *>(vp.item_seq), item_cap);
+    return;
+  }
   hipLaunchKernelGGL(varlen_scan_kernel, dim3(1), dim3(256), 0, stream, cu, vp.nseq, total, blk_len, seg_blocks,
                      const_cast<int32_t *>(vp.tok0), const_cast<int32_t *>(vp.len), const_cast<int32_t *>(vp.blk0),
                      const_cast<int32_t *>(vp.item0), const_cast<int32_t *>(vp.slot0));
-  const int cap = vp.nb_cap > item_cap ? vp.nb_cap : item_cap;
   hipLaunchKernelGGL(varlen_fill_kernel, dim3((cap + 255) / 256), dim3(256), 0, stream, vp.blk0, vp.item0, vp.nseq,
-                     seg_blocks, const_cast<int32_t *>(vp.blk_seq), const_cast<int32_t *>(vp.item_seq));
+                     seg_blocks, const_cast<int32_t *>(vp.blk_seq), const_cast<int32_t *>(vp.item_seq), item_cap);
 }
 
 // The kernels work on 64-token blocks whatever the chunk length is (results do not depend on it); the chunk

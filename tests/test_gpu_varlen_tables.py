@@ -1,0 +1,64 @@
+"""The tables of a packed batch at the edges of the one-workgroup kernel: around a wave and a workgroup of sequences,
+beyond it (two kernels), and lists longer than one trip of its threads."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ssd_oracle
+from paper_2603_09555_amd import inputs
+from parity import TOL, assert_close
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ssd():
+    from paper_2603_09555_amd import ssd
+    return ssd
+
+
+def lengths(nseq, kind):
+    r = np.random.default_rng(nseq)
+    if kind == "short":          # empty ones among them
+        return r.integers(0, 7, nseq)
+    if kind == "mixed":          # some of several segments
+        ln = r.integers(0, 40, nseq)
+        ln[:: max(1, nseq // 4)] += 700
+        return ln
+    return np.full(nseq, 64 * 1200 // nseq)   # "blocks": more 64-token blocks than threads
+
+
+@pytest.mark.parametrize("io", ["bf16", "f32"])   # f32: the generic kernels, whose blocks are chunks
+@pytest.mark.parametrize("case", [(1, "mixed"), (63, "mixed"), (64, "mixed"), (65, "mixed"), (1024, "short"), (1025, "short"),
+                                  (2, "blocks")], ids=str)
+def test_packed_batch_tables(ssd, case, io):
+    nseq, kind = case
+    lens = lengths(nseq, kind)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    T, H, P, N, L = int(cu[-1]), 2, 64, 128 if io == "bf16" else 16, 64
+    cfg = inputs.SSDConfig("t", 1, T, H, P, N, 1, L, io)
+    inp = inputs.make_prefill_inputs(cfg, seed=13)
+    pk = {k: (v[0] if k in ("x", "dt", "B", "C") else v) for k, v in inp.items()}
+    h0 = inputs.make_state(inputs.SSDConfig("h", nseq, 1, H, P, N, 1, L, io), seed=13, scale=0.1)
+    print("packed tables", case, io, "tokens", T, flush=True)
+    dev = {k: v.cuda() for k, v in pk.items()}
+    y, st = ssd.ssd_prefill_varlen(dev["x"], dev["dt"], dev["A"], dev["B"], dev["C"], dev["D"], torch.from_numpy(cu).cuda(), L,
+                                   h0=h0.cuda())
+    torch.cuda.synchronize()
+    y_ref, st_ref = ssd_oracle.prefill_varlen(pk["x"], pk["dt"], pk["A"], pk["B"], pk["C"], pk["D"], cu, h0=h0)
+    assert_close(y, y_ref, TOL[io], "y")
+    assert_close(st, st_ref, TOL[io], "final state")
+
+
+@pytest.mark.parametrize("nseq", [3, 1024, 1025])
+def test_rejected_boundaries_write_nothing(ssd, nseq):
+    T, H = 2000, 2
+    cfg = inputs.SSDConfig("t", 1, T, H, 64, 128, 1, 64, "bf16")
+    dev = {k: (v[0] if k in ("x", "dt", "B", "C") else v).cuda() for k, v in inputs.make_prefill_inputs(cfg, seed=1).items()}
+    cu = np.linspace(0, T, nseq + 1).astype(np.int32)
+    cu[nseq // 2 + 1] = cu[nseq // 2] - 1   # decreasing once
+    y, st = torch.full_like(dev["x"], 3.0), torch.full((nseq, H, 64, 128), 5.0, device="cuda")
+    ssd.ssd_prefill_varlen(dev["x"], dev["dt"], dev["A"], dev["B"], dev["C"], dev["D"], torch.from_numpy(cu).cuda(), 64, y=y,
+                           final_state=st)
+    torch.cuda.synchronize()
+    assert (y == 3.0).all() and (st == 5.0).all()
