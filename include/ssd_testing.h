@@ -34,10 +34,12 @@ typedef enum {
                                  expects the generic kernels to be faster; 0: default */
   SSD_KNOB_F32_SEGMENTS = 7,   /* k > 0: the fp32 MFMA kernel cuts every sequence into k time segments (at most
                                  one per 64-token block); 0: library's choice */
-  SSD_KNOB_FOLD_MAX_SLOTS = 8  /* k >= 0: a plain batch whose chain over segment-state slots, (segments - 1) x
+  SSD_KNOB_FOLD_MAX_SLOTS = 8, /* k >= 0: a plain batch whose chain over segment-state slots, (segments - 1) x
                                  pieces, is at most k long runs no separate pass over those states -- every
                                  segment of the full scan sums the slots before it as it loads them; 0: never.
                                  Default 3.  Reset with ssd_testing_reset_knobs */
+  SSD_KNOB_SCAN_HEADS = 9      /* 2 / 4: head slices per workgroup in both passes of the bf16 MFMA prefill; any other
+                                 value: library's choice */
 } ssd_knob;
 
 /* Sets one knob.  Errors: SSD_ERR_SHAPE for an unknown knob. */
@@ -51,7 +53,8 @@ SSD_API void ssd_testing_reset_knobs(void);
  * MFMA family (per state slice of 128 columns): plan[1] 64-token blocks per segment, plan[2] segments
  * per sequence, plan[3] pieces per segment in the states-only pass, plan[4] 1 if the full scan sums the
  * chain over segment states itself and no separate pass runs (h0_aliases_final_state != 0: as for a call
- * whose h0 and final_state share memory, which rules that out).  For the fp32 MFMA family: plan[5] time
+ * whose h0 and final_state share memory, which rules that out), plan[6] and plan[7] head slices per
+ * workgroup of the full scan and of the states-only pass.  For the fp32 MFMA family: plan[5] time
  * segments per sequence on fp32 MFMA, or 0 on split operands, and then plan[1] 32-token blocks in the longest
  * segment, plan[2] segments, plan[3] workgroups that share one.  The other entries are zero.
  * Errors: SSD_ERR_NULL; the shape errors of ssd_prefill. */

@@ -144,6 +144,8 @@ ssd_status ssd_testing_prefill_plan(const ssd_shape *shape, int32_t h0_aliases_f
     plan[2] = pl.segments;
     plan[3] = pl.parts;
     plan[4] = pl.fold;
+    plan[6] = pl.heads;
+    plan[7] = pl.state_heads;
   } else if (use_split_f32(d)) {
     plan[0] = 2;
     ssd::split_f32_plan(d, &plan[1], &plan[2], &plan[3]);
@@ -401,6 +403,7 @@ ssd_status ssd_testing_set_knob(int32_t knob, int32_t value) {
     case SSD_KNOB_FORCE_MFMA_F32: k.force_mfma_f32 = value > 0 ? 1 : 0; return SSD_OK;
     case SSD_KNOB_F32_SEGMENTS: k.f32_segments = value > 0 ? value : 0; return SSD_OK;
     case SSD_KNOB_FOLD_MAX_SLOTS: k.fold_max_slots = value > 0 ? value : 0; return SSD_OK;
+    case SSD_KNOB_SCAN_HEADS: k.scan_heads = value == 2 || value == 4 ? value : 0; return SSD_OK;
     default: return SSD_ERR_SHAPE;
   }
 }

@@ -106,6 +106,7 @@ struct Knobs {
   int decode_stream = -1;  // 0 / 1: ordinary / non-temporal accesses to the decode state
   int force_mfma_f32 = 0;  // 1: fp32 io takes the fp32 MFMA kernel whenever the shape is eligible
   int f32_segments = 0;    // > 0: time segments per sequence in the fp32 MFMA kernel
+  int scan_heads = 0;      // 2 / 4: head slices per workgroup in the bf16 scan; 0: library's choice
   int fold_max_slots = 3;  // most state slots a segment sums by itself instead of a pass over segment states (0: never)
 };
 Knobs &knobs();
@@ -134,6 +135,7 @@ hipError_t launch_prefill_generic(const Dims &d, const void *x, const float *dt,
 // How the bf16 MFMA prefill cuts a call up (for the launcher and for the test-only plan query).
 struct SlicePlan {
   int seg_blocks, segments, parts, fold;
+  int heads, state_heads;  // head slices per workgroup: full scan, states-only pass
 };
 SlicePlan mfma_plan(const Dims &d, bool h0_aliases_final_state);
 int mfma_f32_time_segments(const Dims &d);

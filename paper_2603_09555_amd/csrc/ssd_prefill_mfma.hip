@@ -40,10 +40,10 @@
 //                  (diagonal blocks only, bf16) and a transposed copy of B, both shared by all heads of
 //                  the group; per (batch, head, block) the prefix sums of dt*A turned into per-token
 //                  input factors, per-row output factors and per-block state factors.
-//   chunk_scan<true>  ("segment_states") per (batch, 4 heads, segment): the segment's end state from a
+//   chunk_scan<true>  ("segment_states") per (batch, 4 or 2 heads, segment): the segment's end state from a
 //                  zero start (only the chunk-state accumulation), so that segments can run in parallel.
 //   segment_pass   sequential pass over segment end states -> state entering each segment.
-//   chunk_scan<false> per (batch, 4 heads, segment): everything above, from the entering state.
+//   chunk_scan<false> per (batch, 4 or 2 heads, segment): everything above, from the entering state.
 // A segment is a whole number of 64-token blocks; with one segment only the first and the last kernel
 // run, and with few segments segment_pass does not: the last kernel sums the few states itself.
 #include <cmath>
@@ -663,7 +663,7 @@ struct ScanParams {
   float *seg_state;        // states-only: local end state of a segment -> the slot of the NEXT segment
   float *seg_decay;        // states-only: log2 of the segment's total decay, one per slot
   int T, H, G, hpg, NB, seg_blocks, S;  // H, hpg count 64-column slices
-  int cpg;                 // workgroups ("head groups of four") per B/C group: ceil(hpg / 4); the slots of the
+  int cpg;                 // workgroups ("head groups of four", or of two) per B/C group: ceil(hpg / 4); the slots of the
                            // last one beyond hpg repeat the group's last slice with every store suppressed
   // The states-only pass may cut every segment into `parts` pieces of `part_blocks` blocks (more,
   // shorter workgroups when the segments alone would leave most of the chip idle); the pass over
@@ -794,9 +794,8 @@ constexpr bool kRowStores = SSD_ROW_STORES != 0;
 constexpr int kRawStride = 40;                       // raw x rows: 32 columns + 16 bytes, in bf16 elements
 constexpr int kGLowStride = 32 + 8;                  // G rows 0..31 keep only columns 0..31 (the rest is masked)
 constexpr int kGTile = 32 * kGLowStride + 32 * kGStride;  // elements of a compacted G tile
-// HPW = heads per workgroup (two waves each).  Both kernels take four heads: the full kernel's LDS tiles
-// fill the CU; the states-only kernel could run two smaller workgroups per CU, but its grid then no
-// longer divides evenly over the CUs and the measured time was worse.
+// HPW = heads per workgroup (two waves each): four, where the full kernel's LDS tiles fill the CU and two waves share a
+// SIMD, or two, one wave per SIMD, for launches that would otherwise leave half of the chip idle (see small_grid).
 // kYMode, how y leaves: kYPlain -- ordinary stores; kYStream -- non-temporal stores, so that writing y does not
 // evict x, which the states-only pass has just pulled into the memory-side cache, before this kernel reads it
 // again (chosen per launch, see stream_y()); kYAdd -- added to what y already holds (the later state slices
@@ -822,9 +821,11 @@ template <bool kStatesOnly, int HPW, int kYMode, bool kMixed>
 __device__ __forceinline__ void scan_walk(const ScanParams &p, const SeqView &sv, const LdsTiles lds) {
   static_assert(!(kStatesOnly && kYMode != kYPlain), "the states-only pass writes no y");
   static_assert(!(kStatesOnly && kMixed), "the states-only pass needs no second form");
-  static_assert(kStatesOnly || HPW == kHeadsPerWg, "the full kernel is written for four heads per workgroup");
   constexpr int kThr = 128 * HPW;
-  constexpr int kBtPieces = kN * kBlk * 2 / 16 / kThr;  // 16-byte pieces of the B^T tile per thread
+  constexpr int kBtPieces = kN * kBlk * 2 / 16 / kThr;  // 16-byte pieces per thread of the B^T tile,
+  constexpr int kCPieces = kBlk * kN * 2 / 16 / kThr;   // of the C tile
+  constexpr int kGPieces = kBlk * kBlk * 2 / 16 / kThr; // and of the G tile
+  constexpr int kPieces = kBtPieces + kCPieces + kGPieces;
   using L = ScanLds<kStatesOnly, HPW>;
   // (generic pointers derived from the address-space pointers: the compiler keeps them LDS accesses)
   uint16_t (*const sC)[L::kCElems] = reinterpret_cast<uint16_t (*)[L::kCElems]>((uint16_t *)lds.sC);
@@ -884,23 +885,27 @@ __device__ __forceinline__ void scan_walk(const ScanParams &p, const SeqView &sv
   auto c_rsrc = [&](int jb) { return make_rsrc(cb + static_cast<size_t>(jb) * kBlk * crow, cbytes - static_cast<uint32_t>(jb) * kBlk * crow); };
   const uint32_t vt = static_cast<uint32_t>(tid) * 16;  // shared tiles: 16 bytes per thread, tid-major
   const uint32_t xcol = static_cast<uint32_t>(h) * (kP * 2) + 64 * ph;
-  uint32_t vx[4], vc[2], ve[2];
+  uint32_t vx[4], vc[kCPieces];
 #pragma unroll
   for (int i = 0; i < 4; ++i) vx[i] = static_cast<uint32_t>(4 * tg + i) * xrow + xcol + 16 * cg;
 #pragma unroll
-  for (int k = 0; k < 2; ++k) {
+  for (int k = 0; k < kCPieces; ++k) {
     const int c = tid + kThr * k;
     vc[k] = static_cast<uint32_t>(c >> 4) * crow + 16 * (c & 15);
-    ve[k] = static_cast<uint32_t>(r + 32 * k) * xrow + xcol + 32 * kg;  // output layout: token r + 32k, 32 bytes
   }
   const uint32_t vf = static_cast<uint32_t>(kBlk + 4 * tg) * 4;  // input factors of this thread's four tokens
   // G: thread -> (row, 16-byte piece); in rows 0..31 only pieces 0..3 are kept (s <= l < 32), the
   // threads of the other pieces duplicate a kept one (same data to the same place)
-  const int g_row = tid >> 3, g_pc = (g_row < 32) ? (tid & 3) : (tid & 7);
-  const uint32_t vg = static_cast<uint32_t>(g_row * kBlk + 8 * g_pc) * 2;
+  uint32_t vg[kGPieces], lds_g[kGPieces];
+#pragma unroll
+  for (int k = 0; k < kGPieces; ++k) {
+    const int g_row = (tid + kThr * k) >> 3, g_pc = (g_row < 32) ? (tid & 3) : (tid & 7);
+    vg[k] = static_cast<uint32_t>(g_row * kBlk + 8 * g_pc) * 2;
+    lds_g[k] = (g_row < 32 ? g_row * kGLowStride : 32 * kGLowStride + (g_row - 32) * kGStride) + 8 * g_pc;
+  }
 
   // ---- data of a block in flight (registers) ----
-  u32x4 r_c[2], r_bt[kBtPieces], r_g;  // shared tiles: this thread's 16-byte pieces
+  u32x4 r_c[kCPieces], r_bt[kBtPieces], r_g[kGPieces];  // shared tiles: this thread's 16-byte pieces
   // own slice: 4 tokens x 8 columns, and the input factors of the 4 tokens (fp32 bits); two blocks
   // of them are in flight (x comes from HBM and is the stream that must never run dry)
   constexpr int kSets = 2;
@@ -920,26 +925,26 @@ __device__ __forceinline__ void scan_walk(const ScanParams &p, const SeqView &sv
     } else if (!kStatesOnly) {
       const Rsrc rc = c_rsrc(jb);
 #pragma unroll
-      for (int k = 0; k < 2; ++k) r_c[k] = buf_load16(rc, vc[k], 0);
-      r_g = buf_load16(rs_g, vg, jb * (kBlk * kBlk * 2));
+      for (int k = 0; k < kCPieces; ++k) r_c[k] = buf_load16(rc, vc[k], 0);
+#pragma unroll
+      for (int k = 0; k < kGPieces; ++k) r_g[k] = buf_load16(rs_g, vg[k], jb * (kBlk * kBlk * 2));
     }
   };
 
   // LDS destinations of this thread's pieces (fixed)
-  uint32_t lds_bt[kBtPieces], lds_c[2];
+  uint32_t lds_bt[kBtPieces], lds_c[kCPieces];
 #pragma unroll
   for (int k = 0; k < kBtPieces; ++k) {
     const int c = tid + kThr * k;
     lds_bt[k] = (c >> 3) * kBtStride + 8 * (c & 7);
   }
 #pragma unroll
-  for (int k = 0; k < 2; ++k) {
+  for (int k = 0; k < kCPieces; ++k) {
     const int c = tid + kThr * k;
     // C columns are permuted inside each group of 16 so that one 16-byte read yields
     // n-offsets {4kg..4kg+3, 8+4kg..8+4kg+3}
     lds_c[k] = (c >> 4) * kCStride + 16 * ((c & 15) >> 1) + 4 * (c & 1);
   }
-  const uint32_t lds_g = (g_row < 32 ? g_row * kGLowStride : 32 * kGLowStride + (g_row - 32) * kGStride) + 8 * g_pc;
   // Xm^T: column 8cg + c of the half goes to row pi^-1(8cg + c) = 16 (cg & 1) + 4 (cg >> 1) + 8 (c >> 2) + (c & 3)
   uint16_t *const xm_dst = myX + (16 * (cg & 1) + 4 * (cg >> 1)) * kXStride + 4 * tg;
   uint16_t *const raw_dst = myRaw + (4 * tg) * kRawStride + 8 * cg;
@@ -960,16 +965,17 @@ __device__ __forceinline__ void scan_walk(const ScanParams &p, const SeqView &sv
       *reinterpret_cast<u32x2 *>(dst) =
           mk2(pack2(f0 * bf_lo(a0), f1 * bf_lo(a1)), pack2(f2 * bf_lo(a2), f3 * bf_lo(a3)));
   };
-  auto stage_tile = [&](int piece, int buf) {  // pieces 0,1: B^T; 2,3: C; 4: G
-    if (piece < 2) {
+  auto stage_tile = [&](int piece, int buf) __attribute__((always_inline)) {  // B^T's pieces first, then C's, then G's
+    if (piece < kBtPieces) {
       *reinterpret_cast<u32x4 *>(&sBt[buf][lds_bt[piece]]) = r_bt[piece];
     } else if constexpr (!kStatesOnly) {
-      if (piece < 4) {
-        uint16_t *d2 = &sC[buf][lds_c[piece - 2]];
-        *reinterpret_cast<u32x2 *>(d2) = mk2(r_c[piece - 2].x, r_c[piece - 2].y);
-        *reinterpret_cast<u32x2 *>(d2 + 8) = mk2(r_c[piece - 2].z, r_c[piece - 2].w);
+      const int c = piece - kBtPieces, k = c - kCPieces;
+      if (k < 0) {
+        uint16_t *d2 = &sC[buf][lds_c[c]];
+        *reinterpret_cast<u32x2 *>(d2) = mk2(r_c[c].x, r_c[c].y);
+        *reinterpret_cast<u32x2 *>(d2 + 8) = mk2(r_c[c].z, r_c[c].w);
       } else {
-        *reinterpret_cast<u32x4 *>(&sG[buf][lds_g]) = r_g;
+        *reinterpret_cast<u32x4 *>(&sG[buf][lds_g[k]]) = r_g[k];
       }
     }
   };
@@ -1282,7 +1288,7 @@ __device__ __forceinline__ void scan_walk(const ScanParams &p, const SeqView &sv
 #pragma unroll
       for (int c = 0; c < 8; ++c) stage_column(c, 0);
 #pragma unroll
-      for (int piece = 0; piece < 5; ++piece) stage_tile(piece, 0);
+      for (int piece = 0; piece < kPieces; ++piece) stage_tile(piece, 0);
       if constexpr (!kRowStores) stage_raw(0);
       // the following blocks are requested in the order the loop requests blocks (shared tiles, own
       // slices, row factors): the compiler derives its waits from the order of outstanding loads,
@@ -1381,7 +1387,11 @@ __device__ __forceinline__ void scan_walk(const ScanParams &p, const SeqView &sv
         }
         Y[0] = mfma(ho, co[kk & 1][0], Y[0]);
         Y[1] = mfma(ho, co[kk & 1][1], Y[1]);
-        if (kk < 5) stage_tile(kk, buf ^ 1);
+        constexpr int kPerGroup = kPieces / 5;
+        if (kk < 5) {
+#pragma unroll
+          for (int k = 0; k < kPerGroup; ++k) stage_tile(kPerGroup * kk + k, buf ^ 1);
+        }
         if (kk == 4) {
           load_rowf(at(jb + 1));
           if constexpr (kMixed) {
@@ -1673,7 +1683,8 @@ __device__ __forceinline__ bool walk_meets_steep_block(const ScanParams &p, cons
 }
 
 template <bool kStatesOnly, int HPW, int kYMode = kYPlain>
-__global__ __launch_bounds__(128 * HPW) __attribute__((amdgpu_waves_per_eu(2, 2)))
+__global__ __launch_bounds__(128 * HPW)
+__attribute__((amdgpu_waves_per_eu(kStatesOnly || HPW == kHeadsPerWg ? 2 : 1, kStatesOnly || HPW == kHeadsPerWg ? 2 : 1)))
 void chunk_scan_kernel(const ScanParams p) {
   using L = ScanLds<kStatesOnly, HPW>;
   __shared__ __align__(16) uint16_t sC[L::kCBufs][L::kCElems];
@@ -1779,7 +1790,7 @@ double rounds_time(long wgs, double blocks, double t_idle, double t_busy) {
 // (at least 64), which keeps the workspace of a very long prompt small: the choice below would not
 // take more anyway.
 // Workgroups of four head slots per batch row and segment: every B/C group has ceil(slices per group / 4).
-int head_groups(const Dims &d) { return d.G * ((d.hpg * (d.P / kP) + kHeadsPerWg - 1) / kHeadsPerWg); }
+int head_groups(const Dims &d, int heads = kHeadsPerWg) { return d.G * ((d.hpg * (d.P / kP) + heads - 1) / heads); }
 int max_segments(const Dims &d) {
   const int nblocks = (d.T + kBlk - 1) / kBlk;
   const long groups = static_cast<long>(d.Bt) * head_groups(d);
@@ -1850,6 +1861,48 @@ int choose_seg_blocks(const Dims &d, int min_blocks, int max_slots, int max_part
     }
   }
   return best_blocks;
+}
+
+// A launch whose workgroups number at most one per CU when they take two heads each takes two: a wave has its SIMD to
+// itself instead of sharing it, which is worth more than the shared tiles that are then staged twice as often.  On 45
+// drawn shapes (64 to 11600 tokens, 4 to 166 slices) at up to 13 segment lengths each: both passes with two heads against
+// four, grids of up to 64 (counted with two heads) 0.87 of the time, up to 128 0.88, up to 256 0.91 (0.82 to 1.01); up
+// to 400, where the second round begins, 1.15.  (2048 tokens x 24 heads 36.1 -> 32.5 us, 376 x 22 in batches of 4 29.9
+// -> 25.6.  The states-only pass alone gains up to 700 workgroups, 0.98, but loses at 16384 tokens x 80 heads, 35.8 ->
+// 40.0 us.)  y must not need the streaming stores (x of more than 64 MiB).
+bool small_grid(long wgs_of_two) { return wgs_of_two <= kNumCUs; }
+
+// Blocks per segment with two heads per workgroup, or 0 where four are expected to be faster than that (blocks4 a
+// segment).  Microseconds of a whole call, fitted to the same 45 shapes (6 and 7 % rms); against the fastest of all the
+// timed plans the choice loses 1 %.  The fit for four heads only serves this comparison, where the grid of four would
+// need more than half of the CUs; 12 % must be gained there: 3 x 3001 tokens x 20 heads 50.3 -> 47.5 (6 blocks instead
+// of 4), while 6 x 1403 x 34 would lose 7 %.
+int two_head_blocks(const Dims &d, int min_blocks, int blocks4, int parts4) {
+  const int nblocks = (d.T + kBlk - 1) / kBlk;
+  const long groups2 = static_cast<long>(d.Bt) * head_groups(d, 2), groups4 = static_cast<long>(d.Bt) * head_groups(d);
+  const double seqs = static_cast<double>(d.Bt) * d.H * (d.P / kP);
+  int best = 0;
+  double best_us = 0.0;
+  for (int cand = min_blocks > 2 ? min_blocks : nblocks < 2 ? 1 : 2; cand <= nblocks; ++cand) {
+    const int S = (nblocks + cand - 1) / cand;
+    if (!small_grid(groups2 * S)) continue;
+    const double load = static_cast<double>(groups2 * S) / kNumCUs;
+    double us = 12.3 + (1.94 + 0.39 * load) * cand + 2.0 * load;
+    if (S > 1) us += 4.5 + 0.74 * cand;
+    if (S > 2) us += 0.0109 * S * seqs + 0.18 * (S - 1);
+    if (best == 0 || us < best_us) {
+      best = cand;
+      best_us = us;
+    }
+  }
+  const int S4 = (nblocks + blocks4 - 1) / blocks4, slots = (S4 - 1) * parts4;
+  if (best == 0 || small_grid(groups2 * S4)) return best;
+  auto rounds = [](long wgs) { return static_cast<double>((wgs + kNumCUs - 1) / kNumCUs); };
+  const double r = rounds(groups4 * S4), load = groups4 * S4 / (kNumCUs * r);
+  double us4 = 12.9 + r * ((2.29 + 0.54 * load) * blocks4 + 9.8 * load);
+  if (S4 > 1) us4 += 2.7 + 0.87 * rounds(groups4 * slots) * (blocks4 / parts4);
+  if (slots > 1) us4 += 0.0147 * (slots + 1) * seqs + 0.2 * slots;
+  return best_us < 0.88 * us4 ? best : 0;
 }
 
 // Blocks per segment of a packed batch of several sequences.  Their lengths are known on the device only, and the one
@@ -1961,6 +2014,14 @@ bool stream_y(const Dims &d, int rows) {
   return 4 * x_bytes > kMemCacheBytes;
 }
 
+// Entries of a packed batch's list of segments, at most: all of them; those that are not the last of their sequence (a
+// non-last segment is seg_blocks whole blocks with a token behind them).
+int list_items(const Dims &d, const Layout &w, int seg_blocks) {
+  const int items = w.NB / seg_blocks + d.Bt + 1;
+  return items < w.items_max ? items : w.items_max;
+}
+int full_items(const Dims &d, const Layout &w, int seg_blocks) { return (w.NB - d.Bt - 1) / seg_blocks; }
+
 // d: plain batch (cu == nullptr), or Bt = number of sequences and T = total tokens of a packed batch.
 // One state slice ns (see NSlice): y and final_state columns of that slice are written.
 // How a call is cut up: blocks per segment, segments per sequence (0 for a packed batch, where the
@@ -1986,12 +2047,40 @@ SlicePlan plan_slice(const Dims &d, bool varlen, bool h0_aliases_final_state) {
     (void)states_cost(groups, seqs, pl.segments, pl.seg_blocks, w.S_max, 8, &pl.parts);
     if (const int k = knobs().seg_parts; k >= 1 && pl.seg_blocks % k == 0 && (pl.segments - 1) * k + 1 <= w.S_max) pl.parts = k;
   }
+  // two heads per workgroup (see small_grid): possibly other segments, which are then not cut into pieces
+  const Knobs &kn = knobs();
+  const bool may_choose = kn.scan_heads == 0 && kn.seg_chunks == 0 && kn.seg_blocks == 0 && kn.seg_parts == 0;
+  const bool may_two = kn.scan_heads == 0 && !stream_y(d, varlen ? 1 : d.Bt);
+  const int seqs = varlen ? 1 : d.Bt;
+  pl.heads = pl.state_heads = kn.scan_heads == 2 ? 2 : kHeadsPerWg;
+  if (!varlen && may_choose && may_two) {
+    if (const int b = two_head_blocks(d, (w.NB + w.S_max - 1) / w.S_max, pl.seg_blocks, pl.parts); b > 0) {
+      if (b != pl.seg_blocks) pl.parts = 1;
+      pl.seg_blocks = b;
+      pl.segments = (w.NB + b - 1) / b;
+    }
+  }
+  if (may_two) {  // (packed batch: by the most entries that the lists can have)
+    const long full = varlen ? full_items(d, w, pl.seg_blocks) : static_cast<long>(pl.segments - 1) * pl.parts;
+    const long all = varlen ? list_items(d, w, pl.seg_blocks) : pl.segments;
+    if (small_grid(all * seqs * head_groups(d, 2))) pl.heads = 2;
+    if (small_grid(full * seqs * head_groups(d, 2))) pl.state_heads = 2;
+  }
   // A short chain over state slots is a sum of few terms (and h0), which the later segments' workgroups form
   // as they load their state -- one launch and one round trip of every state through memory less (8 x 4096
   // tokens x 48 heads: 162 -> 152 us).  Not when h0 and final_state share memory: the last segment might
   // store the final state before the first has read h0.
   pl.fold = !varlen && pl.segments >= 2 && (pl.segments - 1) * pl.parts <= knobs().fold_max_slots && !h0_aliases_final_state ? 1 : 0;
   return pl;
+}
+
+// The workgroups of a pass: `heads` head slices each, `segs` segments per sequence, `items` in all.
+void map_to(ScanParams &p, int heads, int segs, int items) {
+  p.cpg = (p.hpg + heads - 1) / heads;
+  p.cols = p.G * p.cpg;
+  p.segs = segs;
+  p.total = p.cols * items;
+  p.per_xcd = (p.total + kXcds - 1) / kXcds;
 }
 
 hipError_t launch_slice(const Dims &d, const NSlice ns, const int32_t *cu, const void *x, const float *dt,
@@ -2022,8 +2111,7 @@ hipError_t launch_slice(const Dims &d, const NSlice ns, const int32_t *cu, const
     const int n1 = d.Bt + 1;
     int32_t *tok0 = t, *len = t + n1, *blk0 = t + 2 * n1, *item0 = t + 3 * n1, *slot0 = t + 4 * n1,
             *blk_seq = t + 5 * n1, *item_seq = blk_seq + w.NB;
-    items = w.NB / seg_blocks + d.Bt + 1;
-    if (items > w.items_max) items = w.items_max;
+    items = list_items(d, w, seg_blocks);
     S = 0;  // per sequence, from the tables
     vp = VarPlan{tok0, len, blk0, item0, slot0, blk_seq, item_seq, d.Bt, w.NB, w.S_max};
     if (!add_to_y) {  // (a later state slice finds the tables of the first)
@@ -2061,7 +2149,6 @@ hipError_t launch_slice(const Dims &d, const NSlice ns, const int32_t *cu, const
   p.Hrec = d.H;
   p.G = d.G;
   p.hpg = d.hpg * pdiv;
-  p.cpg = (p.hpg + kHeadsPerWg - 1) / kHeadsPerWg;
   p.NB = w.NB;
   p.seg_blocks = seg_blocks;
   p.S = S;
@@ -2071,23 +2158,17 @@ hipError_t launch_slice(const Dims &d, const NSlice ns, const int32_t *cu, const
   p.slots = (S - 1) * parts + 1;
   p.vp = vp;
   p.fold = pl.fold;
-  // a non-last segment is seg_blocks whole blocks with a token behind them; no more of them than that allows, and no
-  // states pass if that is none
-  const int full_cap = varlen ? (w.NB - d.Bt - 1) / seg_blocks : 0;
+  // no states pass if no sequence can have more than one segment
+  const int full_cap = varlen ? full_items(d, w, seg_blocks) : 0;
   if (varlen ? full_cap > 0 : S > 1) {
     // (which sequences of a packed batch have more than one segment is known on the device only: the workgroups of
     // entries that are last segments, or none, leave at once)
-    // heads per workgroup of the states-only kernel.  Two, with two workgroups per CU, measured with the current
-    // loop: 40.0 against 35.8 us at 16384 tokens x 80 heads, 31.4 against 28.7 at 8 x 4096 x 48, 14.0 against
-    // 15.6 at 2048 x 24 -- slower where it matters.
-    constexpr int kStatesHeads = kHeadsPerWg;
-    p.cols = d.G * p.cpg;
-    p.segs = (S - 1) * parts;
-    p.total = p.cols * p.segs * d.Bt;
-    if (varlen) p.total = p.cols * full_cap;
-    p.per_xcd = (p.total + kXcds - 1) / kXcds;
-    hipLaunchKernelGGL((chunk_scan_kernel<true, kStatesHeads>), dim3(kXcds * p.per_xcd), dim3(128 * kStatesHeads), 0,
-                       stream, p);
+    map_to(p, pl.state_heads, (S - 1) * parts, varlen ? full_cap : (S - 1) * parts * d.Bt);
+    const dim3 grid(kXcds * p.per_xcd), block(128 * pl.state_heads);
+    if (pl.state_heads == 2)
+      hipLaunchKernelGGL((chunk_scan_kernel<true, 2>), grid, block, 0, stream, p);
+    else
+      hipLaunchKernelGGL((chunk_scan_kernel<true, kHeadsPerWg>), grid, block, 0, stream, p);
     trace_mark(trace, stream, "segment_states");
     const int rows_bh = (varlen ? full_cap : d.Bt) * Hs;
     if (!p.fold)
@@ -2095,20 +2176,20 @@ hipError_t launch_slice(const Dims &d, const NSlice ns, const int32_t *cu, const
                          dim3(kThreads), 0, stream, seg_state, seg_decay, h0, p.slots, Hs, rows_bh, vp, ns);
     if (!p.fold) trace_mark(trace, stream, "segment_pass");
   }
-  p.cols = d.G * p.cpg;
-  p.segs = S;
-  p.total = p.cols * p.segs * d.Bt;
-  if (varlen) p.total = p.cols * items;
-  p.per_xcd = (p.total + kXcds - 1) / kXcds;
-  if (add_to_y)
-    hipLaunchKernelGGL((chunk_scan_kernel<false, kHeadsPerWg, kYAdd>), dim3(kXcds * p.per_xcd), dim3(kScanThreads), 0,
-                       stream, p);
-  else if (stream_y(d, rows))
-    hipLaunchKernelGGL((chunk_scan_kernel<false, kHeadsPerWg, kYStream>), dim3(kXcds * p.per_xcd), dim3(kScanThreads), 0,
-                       stream, p);
-  else
-    hipLaunchKernelGGL((chunk_scan_kernel<false, kHeadsPerWg>), dim3(kXcds * p.per_xcd), dim3(kScanThreads), 0, stream,
-                       p);
+  map_to(p, pl.heads, S, varlen ? items : S * d.Bt);
+  const dim3 grid(kXcds * p.per_xcd), block(128 * pl.heads);
+  if (pl.heads == 2) {
+    if (add_to_y)
+      hipLaunchKernelGGL((chunk_scan_kernel<false, 2, kYAdd>), grid, block, 0, stream, p);
+    else
+      hipLaunchKernelGGL((chunk_scan_kernel<false, 2>), grid, block, 0, stream, p);
+  } else if (add_to_y) {
+    hipLaunchKernelGGL((chunk_scan_kernel<false, kHeadsPerWg, kYAdd>), grid, block, 0, stream, p);
+  } else if (stream_y(d, rows)) {
+    hipLaunchKernelGGL((chunk_scan_kernel<false, kHeadsPerWg, kYStream>), grid, block, 0, stream, p);
+  } else {
+    hipLaunchKernelGGL((chunk_scan_kernel<false, kHeadsPerWg>), grid, block, 0, stream, p);
+  }
   trace_mark(trace, stream, "chunk_scan");
   return hipGetLastError();
 }
