@@ -678,6 +678,15 @@ def main():
             io_b = 2 if c.io_dtype == "bf16" else 4
             fused_bytes = (2 * 4 * state.numel() / nb + Ly * c.batch * (2 * c.nheads * c.headdim * io_b +
                                                                        4 * c.nheads + 2 * c.ngroups * c.dstate * io_b))
+            # from nine steps on (bf16 io, dstate 64 or 128) the steps run as blocks on the matrix pipe, bound by the
+            # state's one trip through memory; shorter calls and other shapes step by step on the vector ALU
+            if c.io_dtype == "bf16" and nb >= 9 and c.dstate in (64, 128) and c.headdim % 32 == 0:
+                fused_bound = dict(bound="hbm", frac_of_hbm_peak=round(fused_bytes / us_fused / 1e3 / PEAK_HBM_GBS, 4))
+            else:
+                frac = decode_flops(c, Ly) / us_fused / 1e6
+                fused_bound = dict(bound="alu", peak_tflops=PEAK_VALU_F32_TFLOPS,
+                                   frac_of_fp32_valu_peak=round(frac / PEAK_VALU_F32_TFLOPS, 4),
+                                   frac_of_non_packed_fp32_peak=round(frac / PEAK_VALU_F32_NON_PACKED, 4))
             decode[name].update(
                 graph_us_per_step=None if us_graph is None else round(us_graph, 3),
                 graph_hbm_gbs=None if us_graph is None else round(bytes_step / us_graph / 1e3, 1), steps_per_graph=nb,
@@ -685,9 +694,7 @@ def main():
                                 speedup_vs_stacked=round(us / us_fused, 2),
                                 bytes_per_step=int(fused_bytes), hbm_gbs=round(fused_bytes / us_fused / 1e3, 1),
                                 gflops=round(decode_flops(c, Ly) / us_fused / 1e3, 1),
-                                bound="alu", peak_tflops=PEAK_VALU_F32_TFLOPS,
-                                frac_of_fp32_valu_peak=round(decode_flops(c, Ly) / us_fused / 1e6 / PEAK_VALU_F32_TFLOPS, 4),
-                                frac_of_non_packed_fp32_peak=round(decode_flops(c, Ly) / us_fused / 1e6 / PEAK_VALU_F32_NON_PACKED, 4)))
+                                **fused_bound))
             log("[bench] decode %s: graph replay %s us/step; %d steps per launch %.2f us/step (%.1fx)" %
                 (name, "-" if us_graph is None else "%.2f" % us_graph, nb, us_fused, us / us_fused))
             del ys_blk
