@@ -1873,23 +1873,23 @@ int choose_seg_blocks(const Dims &d, int min_blocks, int max_slots, int max_part
 bool small_grid(long wgs_of_two) { return wgs_of_two <= kNumCUs; }
 
 // Blocks per segment with two heads per workgroup, or 0 where four are expected to be faster than that (blocks4 a
-// segment).  Microseconds of a whole call, fitted to the same 45 shapes (6 and 7 % rms); against the fastest of all the
-// timed plans the choice loses 1 %.  The fit for four heads only serves this comparison, where the grid of four would
-// need more than half of the CUs; 12 % must be gained there: 3 x 3001 tokens x 20 heads 50.3 -> 47.5 (6 blocks instead
-// of 4), while 6 x 1403 x 34 would lose 7 %.
+// segment).  Microseconds of a whole call, fitted to 105 drawn shapes (64 to 14000 tokens, 4 to 200 slices) at every
+// segment length (575 and 378 timings, 3.4 and 5.3 % rms).  The fit for four heads only serves this comparison, where
+// the grid of four would need more than half of the CUs: on 40 other such shapes the choice is 0.9 % behind the fastest
+// of the timed plans.  3 x 3001 tokens x 20 heads 50.3 -> 46.5 (6 blocks instead of 4), 2048 x 80 49.8 -> 46.5.
 int two_head_blocks(const Dims &d, int min_blocks, int blocks4, int parts4) {
   const int nblocks = (d.T + kBlk - 1) / kBlk;
   const long groups2 = static_cast<long>(d.Bt) * head_groups(d, 2), groups4 = static_cast<long>(d.Bt) * head_groups(d);
   const double seqs = static_cast<double>(d.Bt) * d.H * (d.P / kP);
+  const int fold_max = knobs().fold_max_slots;
   int best = 0;
   double best_us = 0.0;
   for (int cand = min_blocks > 2 ? min_blocks : nblocks < 2 ? 1 : 2; cand <= nblocks; ++cand) {
-    const int S = (nblocks + cand - 1) / cand;
+    const int S = (nblocks + cand - 1) / cand, slots = S - 1;
     if (!small_grid(groups2 * S)) continue;
     const double load = static_cast<double>(groups2 * S) / kNumCUs;
-    double us = 12.3 + (1.94 + 0.39 * load) * cand + 2.0 * load;
-    if (S > 1) us += 4.5 + 0.74 * cand;
-    if (S > 2) us += 0.0109 * S * seqs + 0.18 * (S - 1);
+    double us = 12.1 + (1.95 + 0.32 * load) * cand + 3.45 * load;
+    if (slots > 0) us += 3.56 + 0.71 * cand + (slots <= fold_max ? (0.98 + 0.0022 * seqs) * slots : 4.74 + 0.0138 * slots * seqs);
     if (best == 0 || us < best_us) {
       best = cand;
       best_us = us;
@@ -1899,10 +1899,12 @@ int two_head_blocks(const Dims &d, int min_blocks, int blocks4, int parts4) {
   if (best == 0 || small_grid(groups2 * S4)) return best;
   auto rounds = [](long wgs) { return static_cast<double>((wgs + kNumCUs - 1) / kNumCUs); };
   const double r = rounds(groups4 * S4), load = groups4 * S4 / (kNumCUs * r);
-  double us4 = 12.9 + r * ((2.29 + 0.54 * load) * blocks4 + 9.8 * load);
-  if (S4 > 1) us4 += 2.7 + 0.87 * rounds(groups4 * slots) * (blocks4 / parts4);
-  if (slots > 1) us4 += 0.0147 * (slots + 1) * seqs + 0.2 * slots;
-  return best_us < 0.88 * us4 ? best : 0;
+  double us4 = 5.2 + r * (2.62 * blocks4 + 20.5 * load);
+  if (slots > 0) {
+    us4 += 1.28 * rounds(groups4 * slots) * (blocks4 / parts4);
+    us4 += slots <= fold_max ? 0.0109 * slots * seqs : 6.25 + 0.012 * slots * seqs;
+  }
+  return best_us < us4 ? best : 0;
 }
 
 // Blocks per segment of a packed batch of several sequences.  Their lengths are known on the device only, and the one
