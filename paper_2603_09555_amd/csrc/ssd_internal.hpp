@@ -29,12 +29,18 @@ __device__ __forceinline__ float dt_apply_biased(float v, float bias, const DtXf
 __device__ __forceinline__ float dt_apply(float v, int h, const DtXform &t) {
   return dt_apply_biased(v, t.bias != nullptr ? t.bias[h] : 0.f, t);
 }
-// The same map without a branch (hardware exp2 / log2, relative error about 2e-7), for code whose loads
-// must not wait at a join: softplus(v) = max(v, 0) + log(1 + exp(-|v|)).
+// The same map without a branch (hardware exp2, log2 and reciprocal), for code whose loads must not wait at a join:
+// softplus(v) = max(v, 0) + log(1 + e), e = exp(-|v|).  Small step sizes keep their relative accuracy -- 2e-7 from
+// v = -80 to 20, where log1pf(expf(v)) has 1.2e-7 --: what the product with log2(e) rounds away comes back as a factor of
+// e, and what 1 + e rounds away, which is most of a small e, as the first term of the logarithm's series.
 __device__ __forceinline__ float dt_apply_branchless(float v, float bias, const DtXform &t) {
   v += bias;
-  const float e = __builtin_amdgcn_exp2f(-fabsf(v) * 1.4426950408889634f);
-  const float sp = fmaxf(v, 0.f) + 0.6931471805599453f * __builtin_amdgcn_logf(1.f + e);
+  const float a = -fabsf(v), p = a * 1.44269502f;
+  const float low = fmaf(a, 1.92596303e-8f, fmaf(a, 1.44269502f, -p));  // 1.44269502 + 1.926e-8 = log2(e)
+  const float e2 = __builtin_amdgcn_exp2f(p);
+  const float e = fmaf(e2, a > -128.f ? low * 0.693147182f : 0.f, e2);
+  const float u = 1.f + e;
+  const float sp = fmaxf(v, 0.f) + fmaf(0.693147182f, __builtin_amdgcn_logf(u), (e - (u - 1.f)) * __builtin_amdgcn_rcpf(u));
   v = t.softplus ? sp : v;
   const float cl = fminf(fmaxf(v, t.lo), t.hi);
   return t.hi > 0.f ? cl : v;
