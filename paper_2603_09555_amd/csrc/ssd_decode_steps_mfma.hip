@@ -10,7 +10,9 @@
 // scores, the weighted input -- is split into three bf16 parts without loss (ssd_split_bf16.hpp), so every product
 // is exact and every sum is fp32: the result differs from single steps by the order of fp32 sums.  The decay
 // between a step and the end of the block is summed from the end, so the newest inputs, which weigh most, carry the
-// smallest exponent error.
+// smallest exponent error.  The mask takes cs apart into ch + cl (cut_decay, coarse_part), ch exact: its weights are
+//     exp(cl_l) (exp(ch_l - ch_s) (dt_s exp(-cl_s))),
+// the factor of the row l applied to y as a whole.
 //
 // The step-by-step kernel (decode_steps_kernel) is bound by the vector ALU, three instructions per state element
 // and step.  Here a state element costs one split (11 instructions per two values) and its share of 3 + 3 matrix
@@ -78,7 +80,7 @@ __global__ __launch_bounds__(kThr, 2) void decode_steps_mfma_kernel(const StepsP
   constexpr int kPer = 2 * kItems / kThr;       // per thread, B and C together
   static_assert(kPer * kThr == 2 * kItems, "the threads share the tiles evenly");
   __shared__ __align__(16) uint8_t smem[L::kBytes];
-  __shared__ __align__(16) float s_cs[kWaves][kTok], s_dt[kWaves][kTok], s_w[kWaves][kTok];
+  __shared__ __align__(16) float s_ch[kWaves][kTok], s_in[kWaves][kTok], s_w[kWaves][kTok];
   __shared__ int s_odd;
   uint16_t *const sB = reinterpret_cast<uint16_t *>(smem);
   uint16_t *const sC = sB + L::kTile;
@@ -204,24 +206,25 @@ __global__ __launch_bounds__(kThr, 2) void decode_steps_mfma_kernel(const StepsP
     }
     // ---- decays: lane r (both halves) = step s0 + r; steps beyond the last have step size zero ----
     const float dtv = s0 + r < p.nsteps ? dt_apply_biased(r_dt, dbias, p.dtx) : 0.f;
-    const float d = dtv * alog;
-    float cs = d, sfx = d;  // inclusive sums from the start and from the end of the block
+    const float d = cut_decay(dtv * alog);
+    float ch = coarse_part(d), cl = d - ch, sfx = d;  // inclusive sums from the start (two parts) and from the end
 #pragma unroll
     for (int off = 1; off < kTok; off <<= 1) {
-      const float up = __shfl_up(cs, off, kTok), dn = __shfl_down(sfx, off, kTok);
-      cs += r >= off ? up : 0.f;
+      const float up = __shfl_up(ch, off, kTok), ul = __shfl_up(cl, off, kTok), dn = __shfl_down(sfx, off, kTok);
+      ch += r >= off ? up : 0.f;
+      cl += r >= off ? ul : 0.f;
       sfx += r + off < kTok ? dn : 0.f;
     }
-    const float total = __shfl(cs, kTok - 1, kTok);
+    const float total = __shfl(sfx, 0, kTok);
     float after = __shfl_down(sfx, 1, kTok);  // sum of the steps behind this one
     after = r == kTok - 1 ? 0.f : after;
-    any_odd |= !(fabsf(total) < 1e30f) || !(fabsf(dtv) < 1e30f) || (seen & 0xffffu) >= 0x7f80u || seen >= 0x7f800000u;
+    any_odd |= !(fabsf(dtv) < 1e30f) || (seen & 0xffffu) >= 0x7f80u || seen >= 0x7f800000u;
     if (kg == 0) {
-      s_cs[wave][r] = cs;
-      s_dt[wave][r] = dtv;
+      s_ch[wave][r] = ch;
+      s_in[wave][r] = dtv * exp2_fast(-cl);
       s_w[wave][r] = dtv * exp2_fast(after);
     }
-    const float el = exp2_fast(cs), e_all = exp2_fast(total);
+    const float el = exp2_fast(ch), el_low = exp2_fast(cl), e_all = exp2_fast(total);
     if (__builtin_amdgcn_ballot_w64(any_odd) != 0 && lane == 0) s_odd = 1;
     load_block(s0 + kTok);
     __syncthreads();
@@ -244,11 +247,11 @@ __global__ __launch_bounds__(kThr, 2) void decode_steps_mfma_kernel(const StepsP
 #pragma unroll
         for (int hf = 0; hf < 2; ++hf) {
           const int sb = 16 * q + 8 * hf + 4 * kg;
-          const f32x4 cs_s = *reinterpret_cast<const f32x4 *>(&s_cs[wave][sb]);
-          const f32x4 dt_s = *reinterpret_cast<const f32x4 *>(&s_dt[wave][sb]);
+          const f32x4 ch_s = *reinterpret_cast<const f32x4 *>(&s_ch[wave][sb]);
+          const f32x4 in_s = *reinterpret_cast<const f32x4 *>(&s_in[wave][sb]);
 #pragma unroll
           for (int j = 0; j < 4; ++j)
-            v[4 * hf + j] = sb + j <= r ? gt[8 * q + 4 * hf + j] * (dt_s[j] * exp2_fast(cs - cs_s[j])) : 0.f;
+            v[4 * hf + j] = sb + j <= r ? gt[8 * q + 4 * hf + j] * (in_s[j] * exp2_fast(ch - ch_s[j])) : 0.f;
         }
         split3(v, gm[q]);
       }
@@ -288,7 +291,7 @@ __global__ __launch_bounds__(kThr, 2) void decode_steps_mfma_kernel(const StepsP
         u32x4 o;
 #pragma unroll
         for (int w = 0; w < 4; ++w)
-          o[w] = pack2(fmaf(Dh, bf_lo(xv[w]), Y[8 * c + 2 * w]), fmaf(Dh, bf_hi(xv[w]), Y[8 * c + 2 * w + 1]));
+          o[w] = pack2(fmaf(el_low, Y[8 * c + 2 * w], Dh * bf_lo(xv[w])), fmaf(el_low, Y[8 * c + 2 * w + 1], Dh * bf_hi(xv[w])));
         buf_store16(ry, static_cast<uint32_t>(r) * xr32 + 32 * kg + 16 * c, o);
       }
     }

@@ -95,6 +95,13 @@ __device__ __forceinline__ f32x16 mfma6(const Op a[3], const Op b[3], f32x16 c) 
 
 __device__ __forceinline__ float exp2_fast(float v) { return __builtin_amdgcn_exp2f(v); }
 
+// The log2 decays of a block's steps, so that differences of their prefix sums -- the decay between two steps -- come
+// out right also behind a step that decays everything away.  A step is cut off at 2^-160, which is zero either way, and
+// taken apart into a multiple of 2^-8, whose sums over 32 steps are exact (at most 5120, 21 bits), and the rest, whose
+// sums stay below 2^-4 (error 2^-27).
+__device__ __forceinline__ float cut_decay(float d) { return d < -160.f ? -160.f : d; }  // (a NaN stays)
+__device__ __forceinline__ float coarse_part(float d) { return __builtin_rintf(d * 256.f) * 0.00390625f; }
+
 // Transposed LDS read (ds_read_b64_tr_b16).  Inside each group of 16 lanes, lane j names four consecutive
 // 16-bit elements -- a quad --; lane i receives element i % 4 of the quads of lanes i/4, 4 + i/4, 8 + i/4 and
 // 12 + i/4.  With quad j of a group at row j/4, four columns per j%4, lane i gets four rows of one column: the

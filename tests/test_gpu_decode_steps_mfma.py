@@ -97,3 +97,27 @@ def test_blocked_steps_keep_infinities_where_the_recurrence_has_them(ssd, where)
         assert torch.equal(torch.isnan(got), torch.isnan(ref)) and torch.equal(torch.isinf(got), torch.isinf(ref))
         ok = torch.isfinite(ref)
         assert_close(torch.where(ok, got, 0.0), np.asarray(torch.where(ok, ref, 0.0).cpu(), dtype=np.float64), tol, where)
+
+
+@pytest.mark.parametrize("size", [1e3, 1e5, 1e12])
+def test_blocked_steps_are_exact_behind_steps_of_any_size(ssd, size):
+    """Steps that decay everything away (dt |A| = size), at the start, in the middle and twice in a block: the decay between
+    the gentle steps behind them is not to be had from prefix sums that hold the large ones to 24 bits.  Every product and
+    sum is fp32 with a largest exponent of a few units, some 1e-6; then y is rounded to bf16, at most 2^-8 of the value."""
+    S, Ly, Bt, H, P, N, G = 40, 1, 1, 4, 64, 128, 1
+    state, x, dt, A, B, C, D = make(S, Ly, Bt, H, P, N, G, dt_scale=1e-3)
+    D.zero_()
+    for s, h in ((3, 0), (16, 1), (2, 2), (7, 2), (33, 2)):
+        dt[s, 0, 0, h] = size / -A[0, h]
+        x[s, 0, 0, h] = (x[s, 0, 0, h].float() / size).bfloat16()   # (its own input would drown what follows)
+    sd = state.cuda()
+    print("blocked decode steps behind a step of", size, flush=True)
+    y = ssd.ssd_decode_steps_layers(sd, *[t.cuda() for t in (x, dt, A, B, C, D)])
+    torch.cuda.synchronize()
+    y_ref, st_ref = ssd_oracle.decode_steps_layers(state, x, dt, A, B, C, D)
+    got = y.float().cpu().double().numpy()
+    for s in range(S):
+        for h in range(H):
+            err = np.linalg.norm(got[s, 0, 0, h] - y_ref[s, 0, 0, h]) / np.linalg.norm(y_ref[s, 0, 0, h])
+            assert err <= 2.0 ** -8, (s, h, err)
+    assert_close(sd, st_ref, 1e-5, "state")
