@@ -8,7 +8,9 @@
 //     G[l][s] = C_l . B_s                                                     (s <= l; once per workgroup)
 //     y[l][p] = exp(cs_l) sum_n C[l][n] S[p][n] + sum_s (G[l][s] dt_s exp(cs_l - cs_s)) x[s][p] + D x[l][p]
 //     S'      = exp(cs_31) S + sum_s (dt_s exp(cs_31 - cs_s) x[s][p]) B[s][n]
-// The mask is applied un-factorised, on the scores in registers, so any step size is exact.
+// The mask is applied on the scores in registers.  Its exponents are differences of prefix sums in two parts, cs = ch +
+// cl (cut_decay, coarse_part): the weights are exp(cl_l) (exp(ch_l - ch_s) (dt_s exp(-cl_s))), right to some 2^-23 for
+// any step sizes, the factor of the row l applied to y as a whole.
 //
 // One wave per slice of 32 headdim columns x dstate, its state in MFMA accumulators; four slices of one B/C group
 // per workgroup, which stages the split B and C once for them.  Layouts as in ssd_decode_steps_mfma.hip.
@@ -89,7 +91,7 @@ __global__ __launch_bounds__(kThr, 2) void split_f32_kernel(const SplitParams p)
   constexpr int N = L::kN;                       // dstate padded to whole tiles
   constexpr int kPieces = kTok * (N / 4) / kThr;  // 16-byte pieces of a B or C tile per thread
   __shared__ __align__(16) uint8_t smem[L::kBytes];
-  __shared__ __align__(16) float s_cs[kWaves][kTok], s_dt[kWaves][kTok], s_w[kWaves][kTok];
+  __shared__ __align__(16) float s_ch[kWaves][kTok], s_in[kWaves][kTok], s_w[kWaves][kTok];
   uint16_t *const sB = reinterpret_cast<uint16_t *>(smem);  // three parts of B, then of C: [token][n]
   uint16_t *const sC = sB + 3 * L::kPart;
 
@@ -238,16 +240,21 @@ __global__ __launch_bounds__(kThr, 2) void split_f32_kernel(const SplitParams p)
     // ---- decays: lane r (both halves) = token; tokens beyond the sequence have step size zero.  The decay from a
     //      token to the end of the block is summed from the end: the newest tokens weigh most ----
     const float dtv = j * kTok + r < p.T ? dt_apply_branchless(r_dt, dbias, p.dtx) : 0.f;
-    const float d = dtv * alog;
-    const float cs = prefix32(d), after = suffix32(d), total = read_lane(cs, kTok - 1);
+    const float d = cut_decay(dtv * alog), after = suffix32(d), total = read_lane(after + d, 0);
+    float ch = 0.f, cl = 0.f;
+    if constexpr (kFull) {
+      const float dh = coarse_part(d);
+      ch = prefix32(dh);
+      cl = prefix32(d - dh);
+    }
     if (kg == 0) {
       if constexpr (kFull) {
-        s_cs[wave][r] = cs;
-        s_dt[wave][r] = dtv;
+        s_ch[wave][r] = ch;
+        s_in[wave][r] = dtv * exp2_fast(-cl);
       }
       s_w[wave][r] = dtv * exp2_fast(after);
     }
-    const float el = exp2_fast(cs), e_all = exp2_fast(total);
+    const float el = exp2_fast(ch), el_low = exp2_fast(cl), e_all = exp2_fast(total);
     if constexpr (kStatesOnly) log2_total += total;
     load_block(min(j + 1, j2 - 1), j + 1 >= j1);  // (after the last block: a harmless repeat, no branch)
     __syncthreads();
@@ -300,11 +307,11 @@ __global__ __launch_bounds__(kThr, 2) void split_f32_kernel(const SplitParams p)
         for (int hf = 0; hf < 2; ++hf) {
           const int sb = 16 * q + 8 * hf + 4 * kg;
           const f32x4 gv = *reinterpret_cast<const f32x4 *>(sG + r * kGStride + sb);
-          const f32x4 cs_s = *reinterpret_cast<const f32x4 *>(&s_cs[wave][sb]);
-          const f32x4 dt_s = *reinterpret_cast<const f32x4 *>(&s_dt[wave][sb]);
+          const f32x4 ch_s = *reinterpret_cast<const f32x4 *>(&s_ch[wave][sb]);
+          const f32x4 in_s = *reinterpret_cast<const f32x4 *>(&s_in[wave][sb]);
 #pragma unroll
           for (int i = 0; i < 4; ++i)  // (above the diagonal the tile holds whatever was there: selected, not multiplied)
-            v[4 * hf + i] = sb + i <= r ? gv[i] * (dt_s[i] * exp2_fast(cs - cs_s[i])) : 0.f;
+            v[4 * hf + i] = sb + i <= r ? gv[i] * (in_s[i] * exp2_fast(ch - ch_s[i])) : 0.f;
         }
         split3_even(v, gm);
         split3_even(xv, xo);
@@ -343,7 +350,7 @@ __global__ __launch_bounds__(kThr, 2) void split_f32_kernel(const SplitParams p)
         const f32x4 xr = *reinterpret_cast<const f32x4 *>(sX + r * kXStride + 16 * kg + 4 * c);
         f32x4 o;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) o[i] = fmaf(Dh, xr[i], Y[4 * c + i]);
+        for (int i = 0; i < 4; ++i) o[i] = fmaf(el_low, Y[4 * c + i], Dh * xr[i]);
         buf_store16(ry, static_cast<uint32_t>(r) * xrow + 64 * kg + 16 * c, __builtin_bit_cast(u32x4, o));
       }
     }

@@ -1,4 +1,5 @@
 """fp32 prefill on split bf16 operands: segments, their states in the workspace or in y, shared single segments."""
+import numpy as np
 import pytest
 import torch
 
@@ -110,3 +111,26 @@ def test_split_prefill_replayed_from_a_hip_graph(ssd):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(y, y_ref) and torch.equal(st, st_ref)
+
+
+@pytest.mark.parametrize("size", [1e2, 1e4, 1e6])
+def test_split_prefill_is_exact_behind_steps_of_any_size(ssd, size):
+    """Tokens that decay everything away (dt |A| = size) among gentle ones: the decay between the tokens behind them is a
+    difference of prefix sums that hold the large step too.  Exponents are good to 2^-26 and each term of an output to a
+    handful of roundings of 2^-24: 5e-7 of the terms' magnitudes bounds a head's outputs at a token."""
+    H, T = 4, 200
+    cfg = inputs.SSDConfig("t", 1, T, H, 64, 128, 1, 64, "f32")
+    ssd.set_knob("seg_blocks", 3)
+    inp = inputs.make_prefill_inputs(cfg, seed=8)
+    inp["D"].zero_()
+    for t, h in ((3, 0), (16, 1), (2, 2), (7, 2), (100, 2)):
+        inp["dt"][0, t, h] = size / -inp["A"][h]
+        inp["x"][0, t, h] /= size   # (its own input would drown what follows)
+    print("split fp32 behind a step of", size, flush=True)
+    y, st = run(ssd, cfg, inp)
+    y_ref, st_ref = ssd_oracle.prefill(inp["x"], inp["dt"], inp["A"], inp["B"], inp["C"], inp["D"])
+    mag, _ = ssd_oracle.prefill(inp["x"].abs(), inp["dt"], inp["A"], inp["B"].abs(), inp["C"].abs(), inp["D"])
+    err = float((np.linalg.norm(y.cpu().double().numpy() - y_ref, axis=-1) / np.linalg.norm(mag, axis=-1)).max())
+    print("  y off by at most %.2e of its terms" % err, flush=True)
+    assert err <= 5e-7
+    assert_close(st, st_ref, 1e-6, "final state")
