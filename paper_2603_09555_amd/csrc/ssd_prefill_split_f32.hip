@@ -12,6 +12,10 @@
 // cl (cut_decay, coarse_part): the weights are exp(cl_l) (exp(ch_l - ch_s) (dt_s exp(-cl_s))), right to some 2^-23 for
 // any step sizes, the factor of the row l applied to y as a whole.
 //
+// A block whose x, B, C or entering state holds an infinity, a NaN or a value of 2^30 and more (or a step size of 2^40)
+// would lose what the recurrence keeps -- an infinity has no parts, a masked score of zero times it is a NaN, sums of
+// products overflow --; from there on its workgroup applies the recurrence as it stands, in the same registers.
+//
 // One wave per slice of 32 headdim columns x dstate, its state in MFMA accumulators; four slices of one B/C group
 // per workgroup, which stages the split B and C once for them.  Layouts as in ssd_decode_steps_mfma.hip.
 // The sequence is cut into S segments: a states-only launch computes every segment's end state from zero, a pass
@@ -85,6 +89,13 @@ struct SplitLds {
   static constexpr int kBytes = kTiles > kTurn ? kTiles : kTurn;
 };
 
+// The largest magnitude of four values and one seen before, or NaN if one is (two v_maximum3), and whether it is outside
+// the range of the contractions.
+__device__ __forceinline__ float larger(float seen, f32x4 v) {
+  return max_or_nan(max_or_nan(max_or_nan(max_or_nan(seen, fabsf(v.x)), fabsf(v.y)), fabsf(v.z)), fabsf(v.w));
+}
+__device__ __forceinline__ bool out_of_range(float seen) { return !(seen < 0x1p30f); }
+
 template <int NT, bool kStatesOnly>
 __global__ __launch_bounds__(kThr, 2) void split_f32_kernel(const SplitParams p) {
   using L = SplitLds<NT, kStatesOnly>;
@@ -92,6 +103,7 @@ __global__ __launch_bounds__(kThr, 2) void split_f32_kernel(const SplitParams p)
   constexpr int kPieces = kTok * (N / 4) / kThr;  // 16-byte pieces of a B or C tile per thread
   __shared__ __align__(16) uint8_t smem[L::kBytes];
   __shared__ __align__(16) float s_ch[kWaves][kTok], s_in[kWaves][kTok], s_w[kWaves][kTok];
+  __shared__ int s_odd;                                     // a value outside the range of the contractions was met
   uint16_t *const sB = reinterpret_cast<uint16_t *>(smem);  // three parts of B, then of C: [token][n]
   uint16_t *const sC = sB + 3 * L::kPart;
 
@@ -175,6 +187,8 @@ __global__ __launch_bounds__(kThr, 2) void split_f32_kernel(const SplitParams p)
   const uint32_t st_size = kCols * p.N * 4u, slot_size = p.slots != nullptr ? st_size : (kCols * NT - 1) * xrow + 4 * kCols;
   const size_t st_base = (bh * p.P + p0) * p.N;
   f32x16 H[NT];
+  if (tid == 0) s_odd = 0;
+  bool odd = false;
   if constexpr (kStatesOnly) {
     load_block(j0, false);
 #pragma unroll
@@ -201,6 +215,13 @@ __global__ __launch_bounds__(kThr, 2) void split_f32_kernel(const SplitParams p)
         for (int i = 0; i < 4; ++i) H[nt][4 * i4 + i] = v[i];
       }
     }
+    float seen[4] = {};
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int i4 = 0; i4 < 4; ++i4)
+        seen[i4] = larger(seen[i4], f32x4{H[nt][4 * i4], H[nt][4 * i4 + 1], H[nt][4 * i4 + 2], H[nt][4 * i4 + 3]});
+    odd = out_of_range(max_or_nan(max_or_nan(seen[0], seen[1]), max_or_nan(seen[2], seen[3])));
   }
 
   // LDS addresses of this lane (elements)
@@ -212,10 +233,12 @@ __global__ __launch_bounds__(kThr, 2) void split_f32_kernel(const SplitParams p)
   const uint32_t a_sc = (16 * lq + tj) * L::kRow + 8 * (lane >> 4);
   float log2_total = 0.f;
 
-  auto block = [&](int j, auto full_tag) __attribute__((always_inline)) {
+  // (false, with the state as it was: the block holds a value outside the range of the contractions)
+  auto block = [&](int j, auto full_tag) __attribute__((always_inline)) -> bool {
     constexpr bool kFull = decltype(full_tag)::value;
     __syncthreads();  // the previous block's readers (at first: the turning of the state) are done with LDS
     // ---- registers -> LDS ----
+    float seen[3] = {};
 #pragma unroll
     for (int k = 0; k < kPieces; ++k) {
       const int item = tid + kThr * k, c4 = item % (N / 4);
@@ -225,18 +248,24 @@ __global__ __launch_bounds__(kThr, 2) void split_f32_kernel(const SplitParams p)
       const f32x4 vb = __builtin_bit_cast(f32x4, r_b[k]);
       const float b4[4] = {vb.x, vb.y, vb.z, vb.w};
       split3_even<4>(b4, t);
+      seen[0] = larger(seen[0], vb);
 #pragma unroll
       for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x2 *>(sB + q * L::kPart + dst) = u32x2{t[q][0], t[q][1]};
       if constexpr (kFull) {
         const f32x4 vc = __builtin_bit_cast(f32x4, r_c[k]);
         const float c4v[4] = {vc.x, vc.y, vc.z, vc.w};
         split3_even<4>(c4v, t);
+        seen[1] = larger(seen[1], vc);
 #pragma unroll
         for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x2 *>(sC + q * L::kPart + dst) = u32x2{t[q][0], t[q][1]};
       }
     }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) *reinterpret_cast<u32x4 *>(sX + (8 * k + (lane >> 3)) * kXStride + 4 * (lane & 7)) = r_x[k];
+    for (int k = 0; k < 4; ++k) {
+      const f32x4 v = __builtin_bit_cast(f32x4, r_x[k]);
+      *reinterpret_cast<f32x4 *>(sX + (8 * k + (lane >> 3)) * kXStride + 4 * (lane & 7)) = v;
+      seen[2] = larger(seen[2], v);
+    }
     // ---- decays: lane r (both halves) = token; tokens beyond the sequence have step size zero.  The decay from a
     //      token to the end of the block is summed from the end: the newest tokens weigh most ----
     const float dtv = j * kTok + r < p.T ? dt_apply_branchless(r_dt, dbias, p.dtx) : 0.f;
@@ -255,9 +284,11 @@ __global__ __launch_bounds__(kThr, 2) void split_f32_kernel(const SplitParams p)
       s_w[wave][r] = dtv * exp2_fast(after);
     }
     const float el = exp2_fast(ch), el_low = exp2_fast(cl), e_all = exp2_fast(total);
-    if constexpr (kStatesOnly) log2_total += total;
+    odd |= out_of_range(max_or_nan(max_or_nan(seen[0], seen[1]), seen[2])) || !(fabsf(dtv) < 0x1p40f) || !(fabsf(d) < 1e30f);
+    if (__builtin_amdgcn_ballot_w64(odd) != 0 && lane == 0) s_odd = 1;
     load_block(min(j + 1, j2 - 1), j + 1 >= j1);  // (after the last block: a harmless repeat, no branch)
     __syncthreads();
+    const int met_odd = s_odd;  // uniform over the workgroup; waited for where the state is about to change
 
     f32x16 Y = {};
     if constexpr (kFull) {
@@ -293,6 +324,8 @@ __global__ __launch_bounds__(kThr, 2) void split_f32_kernel(const SplitParams p)
       for (int i = 0; i < 16; ++i) Y[i] *= el;
       __syncthreads();  // the scores are in LDS
     }
+    if (met_odd != 0) return false;
+    if constexpr (kStatesOnly) log2_total += total;
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       // x^T: headdim column pi(r), tokens 16 q + {4kg.., 8 + 4kg..}
@@ -354,10 +387,47 @@ __global__ __launch_bounds__(kThr, 2) void split_f32_kernel(const SplitParams p)
         buf_store16(ry, static_cast<uint32_t>(r) * xrow + 64 * kg + 16 * c, __builtin_bit_cast(u32x4, o));
       }
     }
+    return true;
   };
-  for (int j = j0; j < j1; ++j) block(j, std::false_type{});
+  int j = j0;
+  bool in_range = true;
+  for (; j < j1 && in_range; j += in_range) in_range = block(j, std::false_type{});
   if constexpr (!kStatesOnly) {
-    for (int j = j1; j < j2; ++j) block(j, std::true_type{});
+    for (; j < j2 && in_range; j += in_range) in_range = block(j, std::true_type{});
+  }
+  // ---- what is left of a walk that met such a block: the recurrence, token by token.  A lane holds half of a state row,
+  //      the columns 32 nt + 8 i4 + 4 kg + 0 .. 3 of row pi(r) ----
+  for (; j < j2; ++j) {
+    const int n = min(kTok, p.T - j * kTok);
+    const Rsrc rB = rows_of(Bb, brow, p.N * 4, j), rC = rows_of(Cb, brow, p.N * 4, j), rx = rows_of(xb, xrow, 4 * kCols, j);
+    const Rsrc ry = make_rsrc(yb + static_cast<size_t>(j) * kTok * xrow, live && j >= j1 && !kStatesOnly ? (n - 1) * xrow + 4 * kCols : 0u);
+    const float raw = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rows_of(db, drow, 4, j), r * drow, 0, 0));
+    const float dtv = r < n ? dt_apply_branchless(raw, dbias, p.dtx) : 0.f;
+    if constexpr (kStatesOnly) log2_total += read_lane(prefix32(cut_decay(dtv * alog)), kTok - 1);
+#pragma clang loop unroll(disable)
+    for (int t = 0; t < n; ++t) {
+      const float dt_t = read_lane(dtv, t), dA = exp2_fast(dt_t * alog);
+      const uint32_t at = t * xrow + 4 * pi_of_row(r);
+      const float xv = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rx, at, 0, 0)), ux = dt_t * xv;
+      float part = 0.f;
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) {
+          const int n0 = 32 * nt + 8 * i4 + 4 * kg;
+          const uint32_t off = n0 < p.N ? t * brow + 4 * n0 : kNowhere;
+          const f32x4 bv = __builtin_bit_cast(f32x4, buf_load16(rB, off)), cv = __builtin_bit_cast(f32x4, buf_load16(rC, off));
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {  // (a column of padding stays zero whatever x is)
+            const float v = n0 < p.N ? fmaf(dA, H[nt][4 * i4 + i], ux * bv[i]) : 0.f;
+            H[nt][4 * i4 + i] = v;
+            part = fmaf(cv[i], v, part);
+          }
+        }
+      }
+      part += __shfl_xor(part, 32, 64);
+      if (kg == 0) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(fmaf(Dh, xv, part)), ry, at, 0, 0);
+    }
   }
 
   // ---- the state back to memory: the segment's local end state, or the final state (Alg. 1, "Store") ----

@@ -134,3 +134,45 @@ def test_split_prefill_is_exact_behind_steps_of_any_size(ssd, size):
     print("  y off by at most %.2e of its terms" % err, flush=True)
     assert err <= 5e-7
     assert_close(st, st_ref, 1e-6, "final state")
+
+
+@pytest.mark.parametrize("where", ["x", "B", "C", "dt", "h0", "huge x", "huge B and C"])
+@pytest.mark.parametrize("seg, sub", [(3, 1), (64, 2)])
+def test_split_prefill_keeps_infinities_where_the_recurrence_has_them(ssd, where, seg, sub):
+    """An infinity or a NaN reaches exactly the outputs that the recurrence lets it reach, as what it is there; values next
+    to the end of fp32's range, and products that leave it, do no harm where the recurrence's stay inside."""
+    H, T, P, N = 4, 300, 64, 72
+    cfg = inputs.SSDConfig("t", 2, T, H, P, N, 1, 64, "f32")
+    ssd.set_knob("seg_blocks", seg)
+    ssd.set_knob("seg_parts", sub)
+    inp = inputs.make_prefill_inputs(cfg, seed=15)
+    inp["dt"] = inp["dt"].clamp(max=0.01)
+    h0 = inputs.make_state(cfg, seed=15, scale=0.3)
+    if where == "x":
+        inp["x"][0, 130, 1, 7] = float("inf")
+    elif where == "B":
+        inp["B"][1, 70, 0, 5] = float("-inf")
+        inp["B"][0, 299, 0, 71] = float("nan")
+    elif where == "C":
+        inp["C"][0, 33, 0, 40] = float("inf")
+    elif where == "dt":
+        inp["dt"][1, 36, 2] = float("nan")
+    elif where == "h0":
+        h0[0, 3, 60, 71] = float("-inf")
+    elif where == "huge x":
+        inp["x"][0, 40, 2, 9] = 3.4e38
+    else:
+        inp["B"][0, 100], inp["C"][0, 100] = inp["B"][0, 100] * 1e20, inp["C"][0, 100] * 1e20
+        inp["x"][0, 100] = inp["x"][0, 100] * 1e-20
+    print("split fp32, out of range:", where, seg, sub, flush=True)
+    y, st = run(ssd, cfg, inp, h0)
+    with np.errstate(all="ignore"):
+        y_ref, st_ref = ssd_oracle.prefill(inp["x"], inp["dt"], inp["A"], inp["B"], inp["C"], inp["D"], h0=h0)
+    for got, ref, heads, what in ((y, y_ref, 2, "y"), (st, st_ref, 1, "final state")):
+        got = got.cpu().double().numpy()
+        for kind in (np.isnan, np.isposinf, np.isneginf):
+            assert np.array_equal(kind(got), kind(ref)), (what, kind)
+        got, ref = np.moveaxis(got, heads, 0).reshape(H, -1), np.moveaxis(ref, heads, 0).reshape(H, -1)
+        for h in range(H):   # (a head at a time: one with huge values would hide the others)
+            ok = np.isfinite(ref[h])
+            assert np.linalg.norm(got[h][ok] - ref[h][ok]) <= 1e-5 * np.linalg.norm(ref[h][ok]), (what, h)
