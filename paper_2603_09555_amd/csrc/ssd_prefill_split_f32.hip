@@ -9,8 +9,8 @@
 //     y[l][p] = exp(cs_l) sum_n C[l][n] S[p][n] + sum_s (G[l][s] dt_s exp(cs_l - cs_s)) x[s][p] + D x[l][p]
 //     S'      = exp(cs_31) S + sum_s (dt_s exp(cs_31 - cs_s) x[s][p]) B[s][n]
 // The mask is applied on the scores in registers.  Its exponents are differences of prefix sums in two parts, cs = ch +
-// cl (cut_decay, coarse_part): the weights are exp(cl_l) (exp(ch_l - ch_s) (dt_s exp(-cl_s))), right to some 2^-23 for
-// any step sizes, the factor of the row l applied to y as a whole.
+// cl (cut_decay, coarse_part): the weights are (dt_s exp(-cl_s)) (exp(cl_l) exp(ch_l - ch_s)), right to some 2^-23 for
+// any step sizes.
 //
 // A block whose x, B, C or entering state holds an infinity, a NaN or a value of 2^30 and more (or a step size of 2^40)
 // would lose what the recurrence keeps -- an infinity has no parts, a masked score of zero times it is a NaN, sums of
@@ -283,7 +283,7 @@ __global__ __launch_bounds__(kThr, 2) void split_f32_kernel(const SplitParams p)
       }
       s_w[wave][r] = dtv * exp2_fast(after);
     }
-    const float el = exp2_fast(ch), el_low = exp2_fast(cl), e_all = exp2_fast(total);
+    const float el_low = exp2_fast(cl), el = exp2_fast(ch) * el_low, e_all = exp2_fast(total);
     odd |= out_of_range(max_or_nan(max_or_nan(seen[0], seen[1]), seen[2])) || !(fabsf(dtv) < 0x1p40f) || !(fabsf(d) < 1e30f);
     if (__builtin_amdgcn_ballot_w64(odd) != 0 && lane == 0) s_odd = 1;
     load_block(min(j + 1, j2 - 1), j + 1 >= j1);  // (after the last block: a harmless repeat, no branch)
@@ -344,7 +344,7 @@ __global__ __launch_bounds__(kThr, 2) void split_f32_kernel(const SplitParams p)
           const f32x4 in_s = *reinterpret_cast<const f32x4 *>(&s_in[wave][sb]);
 #pragma unroll
           for (int i = 0; i < 4; ++i)  // (above the diagonal the tile holds whatever was there: selected, not multiplied)
-            v[4 * hf + i] = sb + i <= r ? gv[i] * (in_s[i] * exp2_fast(ch - ch_s[i])) : 0.f;
+            v[4 * hf + i] = sb + i <= r ? gv[i] * (in_s[i] * (el_low * exp2_fast(ch - ch_s[i]))) : 0.f;
         }
         split3_even(v, gm);
         split3_even(xv, xo);
@@ -383,7 +383,7 @@ __global__ __launch_bounds__(kThr, 2) void split_f32_kernel(const SplitParams p)
         const f32x4 xr = *reinterpret_cast<const f32x4 *>(sX + r * kXStride + 16 * kg + 4 * c);
         f32x4 o;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) o[i] = fmaf(el_low, Y[4 * c + i], Dh * xr[i]);
+        for (int i = 0; i < 4; ++i) o[i] = fmaf(Dh, xr[i], Y[4 * c + i]);
         buf_store16(ry, static_cast<uint32_t>(r) * xrow + 64 * kg + 16 * c, __builtin_bit_cast(u32x4, o));
       }
     }

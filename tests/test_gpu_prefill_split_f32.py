@@ -176,3 +176,26 @@ def test_split_prefill_keeps_infinities_where_the_recurrence_has_them(ssd, where
         for h in range(H):   # (a head at a time: one with huge values would hide the others)
             ok = np.isfinite(ref[h])
             assert np.linalg.norm(got[h][ok] - ref[h][ok]) <= 1e-5 * np.linalg.norm(ref[h][ok]), (what, h)
+
+
+def errors_against_64_bits(ssd, cfg, inp, h0, knob):
+    ssd.reset_knobs()
+    ssd.set_knob(*knob)
+    got = run(ssd, cfg, inp, h0)
+    ref = ssd_oracle.prefill(inp["x"], inp["dt"], inp["A"], inp["B"], inp["C"], inp["D"], h0=h0)
+    return [float(np.linalg.norm(g.cpu().double().numpy() - r) / np.linalg.norm(r)) for g, r in zip(got, ref)]
+
+
+@pytest.mark.parametrize("dims", [(1, 2048, 8, 64, 128, 1, 256), (2, 700, 6, 32, 16, 2, 64), (3, 500, 5, 64, 72, 1, 128)], ids=str)
+@pytest.mark.parametrize("with_h0", [False, True])
+def test_split_prefill_is_as_accurate_as_the_fp32_matrix_instruction(ssd, dims, with_h0):
+    """Against 64 bits, relative 2-norms: at most the error of the kernel that forms its products and sums in the fp32 matrix
+    instruction (a tenth more for the luck of single roundings), and 5e-7 -- a part lost anywhere is 1.5e-5."""
+    cfg = inputs.SSDConfig("t", *dims, "f32")
+    inp = inputs.make_prefill_inputs(cfg, seed=17)
+    h0 = inputs.make_state(cfg, seed=17, scale=0.02) if with_h0 else None
+    split = errors_against_64_bits(ssd, cfg, inp, h0, ("seg_blocks", 4))
+    fp32 = errors_against_64_bits(ssd, cfg, inp, h0, ("force_mfma_f32", 1))
+    print("  off by %.2e, state %.2e; fp32 matrix instruction %.2e, %.2e" % (*split, *fp32), flush=True)
+    for s, f in zip(split, fp32):
+        assert s <= 1.1 * f and s <= 5e-7
