@@ -199,3 +199,20 @@ def test_split_prefill_is_as_accurate_as_the_fp32_matrix_instruction(ssd, dims, 
     print("  off by %.2e, state %.2e; fp32 matrix instruction %.2e, %.2e" % (*split, *fp32), flush=True)
     for s, f in zip(split, fp32):
         assert s <= 1.1 * f and s <= 5e-7
+
+
+def test_split_products_are_fp32_products(ssd):
+    """The state of one token is one product per element, of dt x (exact here: dt = 1) and B.  Of it, at most 2^-24 is left
+    out, and the sum of the parts' products is cut off once more at 2^-23: three units of 2^-24."""
+    H, P, N = 8, 64, 128
+    ssd.set_knob("seg_blocks", 1)
+    g = torch.Generator().manual_seed(1)
+    x, B, C = (torch.randn(s, generator=g) for s in ((4, 1, H, P), (4, 1, 1, N), (4, 1, 1, N)))
+    dt, A, D = torch.ones(4, 1, H), -torch.ones(H), torch.zeros(H)
+    print("split fp32, one token", flush=True)
+    _, st = ssd.ssd_prefill(*[t.cuda() for t in (x, dt, A, B, C, D)], 64)
+    torch.cuda.synchronize()
+    ref = x.double()[:, 0, :, :, None] * B.double()[:, 0, :, None, :]
+    err = float(((st.cpu().double() - ref) / ref).abs().max()) * 2 ** 24
+    print("  products off by at most %.2f units of 2^-24" % err, flush=True)
+    assert err <= 3.0
