@@ -545,7 +545,8 @@ static SplitPlan split_plan(const Dims &d) {
 }
 
 bool split_f32_supported(const Dims &d) {
-  const unsigned long long lim = 0xFFFF0000ull, t = static_cast<unsigned long long>(d.T);
+  // (the rows of a whole block are addressed, whether they exist or not: 32-bit byte offsets must not wrap)
+  const unsigned long long lim = 0xFFFF0000ull, t = static_cast<unsigned long long>(d.T < kTok ? kTok : d.T);
   return !d.bf16 && d.P % kCols == 0 && d.N % 8 == 0 && d.N <= 128 && t * d.H * d.P * 4 <= lim && t * d.G * d.N * 4 <= lim &&
          static_cast<unsigned long long>(d.Bt) * d.H <= 65535 &&
          static_cast<unsigned long long>(d.Bt) * d.H * (d.P / kCols) * 64 <= 0x7fffffffull;

@@ -124,3 +124,17 @@ def test_split_f32_plans():
     assert split > 100
     p = ssd.prefill_plan(shape_of(base.with_(seqlen=2048, nheads=24, headdim=64, dstate=128, chunk=256)))
     assert p["path"] == "mfma_f32" and (p["segments"], p["seg_blocks"], p["f32_segments"]) == (16, 4, 0)
+
+
+@pytest.mark.parametrize("T, H, P, N, G, fits", [(1, 4096, 8160, 8, 1, True), (1, 4096, 8224, 8, 1, False), (31, 16384, 2080, 8, 1, False),
+                                                 (33, 16384, 2016, 8, 1, False), (2, 4, 32, 128, 4, True)])
+def test_split_f32_offsets_of_a_whole_block(T, H, P, N, G, fits):
+    """The split kernel addresses the 32 rows of a block whether the prompt has them or not: 32 rows of x take at most the
+    32-bit byte offsets, or the shape is not its own."""
+    ssd.set_knob("seg_blocks", 1)   # (asks for the split kernel wherever it can run)
+    try:
+        p = ssd.prefill_plan(ssd.make_shape(1, T, H, P, N, G, 64, torch.float32))
+    finally:
+        ssd.reset_knobs()
+    taken = p["path"] == "mfma_f32" and p["segments"] > 0
+    assert taken == fits == (max(T, 32) * H * P * 4 <= 0xFFFF0000)
