@@ -64,7 +64,11 @@ struct StepsLds {
   static constexpr int kBytes = kTiles > kTurn ? kTiles : kTurn;
 };
 
-// Largest magnitudes of packed bf16 pairs, as bits (an infinity or a NaN has 0x7f80 or more).
+// Largest magnitudes of packed bf16 pairs, as bits (an infinity or a NaN has 0x7f80 or more).  x, B and C of 2^24 and more,
+// step sizes of 2^40 and a state of 2^60 are left to the recurrence, as are infinities and NaNs: below that no product on
+// the way leaves fp32's range that the recurrence's stay inside (a score C.B may, where x is as small as they are large).
+constexpr uint32_t kIoLimit = 0x4b80u, kStateLimit = 0x5d800000u;
+constexpr float kDtLimit = 0x1p40f;
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t max_bf16(uint32_t seen, uint32_t u) {
   return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, seen), __builtin_bit_cast(u16x2, u & 0x7fff7fffu)));
@@ -171,7 +175,7 @@ __global__ __launch_bounds__(kThr, 2) void decode_steps_mfma_kernel(const StepsP
       }
     }
   }
-  bool any_odd = odd >= 0x7f800000u || !(fabsf(Ah) < __builtin_inff());
+  bool any_odd = odd >= kStateLimit || !(fabsf(Ah) < __builtin_inff());
 
   // LDS addresses of this lane (elements)
   const uint32_t a_row = r * L::kRowStride + 8 * kg;  // row-major operands of the B and C tiles, + 16 kk
@@ -218,7 +222,7 @@ __global__ __launch_bounds__(kThr, 2) void decode_steps_mfma_kernel(const StepsP
     const float total = __shfl(sfx, 0, kTok);
     float after = __shfl_down(sfx, 1, kTok);  // sum of the steps behind this one
     after = r == kTok - 1 ? 0.f : after;
-    any_odd |= !(fabsf(dtv) < 1e30f) || (seen & 0xffffu) >= 0x7f80u || seen >= 0x7f800000u;
+    any_odd |= !(fabsf(dtv) < kDtLimit) || (seen & 0xffffu) >= kIoLimit || seen >= kIoLimit << 16;
     if (kg == 0) {
       s_ch[wave][r] = ch;
       s_in[wave][r] = dtv * exp2_fast(-cl);
@@ -328,8 +332,8 @@ __global__ __launch_bounds__(kThr, 2) void decode_steps_mfma_kernel(const StepsP
   __syncthreads();
 
   if (s_odd != 0) {
-    // An input or the state holds an infinity or a NaN: a zero of the mask times it would reach steps and rows that
-    // the recurrence keeps clear of it.  The workgroup applies the recurrence as it stands, to the state in memory
+    // An input or the state holds an infinity, a NaN or a value beyond the limits above: a zero of the mask times an
+    // infinity would reach steps and rows that the recurrence keeps clear of it.  The workgroup applies the recurrence as it stands, to the state in memory
     // (which nothing has been written to yet): one row at a time, lanes across dstate.
     if (!live) return;
     for (int s = 0; s < p.nsteps; ++s) {

@@ -121,3 +121,33 @@ def test_blocked_steps_are_exact_behind_steps_of_any_size(ssd, size):
             err = np.linalg.norm(got[s, 0, 0, h] - y_ref[s, 0, 0, h]) / np.linalg.norm(y_ref[s, 0, 0, h])
             assert err <= 2.0 ** -8, (s, h, err)
     assert_close(sd, st_ref, 1e-5, "state")
+
+
+@pytest.mark.parametrize("where", ["B and C", "x and B", "state"])
+def test_blocked_steps_with_values_whose_products_leave_fp32(ssd, where):
+    """Large B and C (or x) at one step whose counterpart is as small: the recurrence multiplies a large one by a small one,
+    a score C.B would overflow.  As single steps, head by head."""
+    S, Ly, Bt, H, P, N, G = 40, 1, 1, 4, 64, 128, 1
+    state, x, dt, A, B, C, D = make(S, Ly, Bt, H, P, N, G)
+    D.zero_()
+    def scale(t, s, by):
+        t[s] = (t[s].float() * by).bfloat16()
+    if where == "B and C":
+        scale(B, 34, 1e22), scale(C, 34, 1e22), scale(x, 34, 1e-22)
+        state.mul_(1e-20)
+    elif where == "x and B":
+        scale(x, 5, 1e25), scale(B, 5, 1e-25)
+    else:
+        state[0, 0, 2] *= 1e34
+        scale(C, 7, 1e-30)
+    dev = [t.cuda() for t in (x, dt, A, B, C, D)]
+    sd, s1 = state.cuda(), state.cuda()
+    print("blocked decode steps, large", where, flush=True)
+    y = ssd.ssd_decode_steps_layers(sd, *dev)
+    y1 = torch.stack([ssd.ssd_decode_step_layers(s1, dev[0][i].clone(), dev[1][i].clone(), dev[2], dev[3][i].clone(),
+                                                 dev[4][i].clone(), dev[5]) for i in range(S)])
+    torch.cuda.synchronize()
+    got, ref = y.double()[:, 0, 0], y1.double()[:, 0, 0]
+    assert torch.isfinite(got).all() and torch.isfinite(ref).all()
+    assert ((got - ref).norm(dim=-1) <= 2.0 ** -8 * ref.norm(dim=-1)).all()
+    assert ((sd - s1).double().flatten(3).norm(dim=-1) <= 1e-5 * s1.double().flatten(3).norm(dim=-1)).all()
