@@ -61,6 +61,13 @@ SSD_API void ssd_testing_reset_knobs(void);
 SSD_API ssd_status ssd_testing_prefill_plan(const ssd_shape *shape, int32_t h0_aliases_final_state,
                                             int32_t plan[8]);
 
+/* How ssd_prefill_varlen would cut up a packed batch of these boundaries (a HOST array here) under the current knobs, on
+ * the bf16 MFMA kernels.  plan[1] 64-token blocks per segment, which the device chooses from the boundaries, plan[2]
+ * segments of the whole batch, plan[3] the shortest segment it may choose, plan[4] 1 if there is a choice, plan[6] and
+ * plan[7] as above; plan[0] and all others 0 for a call that runs on the generic kernels.
+ * Errors: SSD_ERR_NULL; the shape errors of ssd_prefill_varlen; SSD_ERR_SHAPE for boundaries it would reject. */
+SSD_API ssd_status ssd_testing_varlen_plan(const ssd_shape *shape, const int32_t *cu_seqlens, int32_t plan[8]);
+
 #ifdef __cplusplus
 }
 #endif

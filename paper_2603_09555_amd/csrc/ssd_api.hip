@@ -229,6 +229,26 @@ size_t ssd_prefill_varlen_workspace_bytes(const ssd_shape *shape) {
   return mfma > generic ? mfma : generic;
 }
 
+ssd_status ssd_testing_varlen_plan(const ssd_shape *shape, const int32_t *cu_seqlens, int32_t plan[8]) {
+  Dims d;
+  if (shape == nullptr || cu_seqlens == nullptr || plan == nullptr) return SSD_ERR_NULL;
+  if (const ssd_status st = make_dims(shape, false, &d, true); st != SSD_OK) return st;
+  for (int q = 0; q < d.Bt; ++q)
+    if (cu_seqlens[q] < 0 || cu_seqlens[q + 1] < cu_seqlens[q] || cu_seqlens[q + 1] > d.T) return SSD_ERR_SHAPE;
+  for (int i = 0; i < 8; ++i) plan[i] = 0;
+  if (!force_generic() && ssd::mfma_varlen_supported(d)) {
+    const ssd::SlicePlan pl = ssd::mfma_varlen_plan(d, cu_seqlens);
+    plan[0] = 1;
+    plan[1] = pl.seg_blocks;
+    plan[2] = pl.segments;
+    plan[3] = pl.shortest;
+    plan[4] = pl.from_lengths;
+    plan[6] = pl.heads;
+    plan[7] = pl.state_heads;
+  }
+  return SSD_OK;
+}
+
 namespace {
 ssd_status varlen_impl(const ssd_shape *shape, const ssd_dt_transform *dtx, const int32_t *cu_seqlens, const void *x,
                        const float *dt, const float *A, const void *B, const void *C, const float *D, const float *h0,

@@ -142,8 +142,13 @@ hipError_t launch_prefill_generic(const Dims &d, const void *x, const float *dt,
 struct SlicePlan {
   int seg_blocks, segments, parts, fold;
   int heads, state_heads;  // head slices per workgroup: full scan, states-only pass
+  // packed batch: the device chooses the segment length from the sequences' lengths (seg_blocks is the shortest it may)
+  bool from_lengths = false;
+  int shortest = 0;  // (of mfma_varlen_plan, where seg_blocks is the choice)
 };
 SlicePlan mfma_plan(const Dims &d, bool h0_aliases_final_state);
+// ... and a packed batch of these boundaries (host array): seg_blocks as the device chooses it, segments of the whole batch.
+SlicePlan mfma_varlen_plan(const Dims &d, const int32_t *cu_host);
 int mfma_f32_time_segments(const Dims &d);
 bool mfma_supported(const Dims &d);
 size_t mfma_workspace_bytes(const Dims &d);
@@ -174,7 +179,15 @@ struct VarPlan {
   const int32_t *tok0, *len, *blk0, *item0, *slot0, *blk_seq, *item_seq;
   int nseq, nb_cap, slot_cap;
 };
-void launch_varlen_tables(const int32_t *cu, int total, int blk_len, int seg_blocks, int item_cap, const VarPlan &vp,
+// Blocks per segment of a packed batch: one of the first `count` candidates (ascending), chosen on the device from the
+// lengths; see packed_cost in ssd_prefill_mfma.hip.
+struct SegChoice {
+  static constexpr int kMost = 32;
+  int cand[kMost];
+  int count, heads, max_items;  // head slices per workgroup of the scan; list entries that still run side by side
+  float fill, slices;           // share of the chip that one entry's workgroups take; 64-column slices of all heads
+};
+void launch_varlen_tables(const int32_t *cu, int total, int blk_len, const SegChoice &choice, int item_cap, const VarPlan &vp,
                           hipStream_t stream);
 size_t generic_varlen_workspace_bytes(const Dims &d);
 hipError_t launch_prefill_generic_varlen(const Dims &d, const int32_t *cu_seqlens, const void *x, const float *dt,

@@ -421,7 +421,9 @@ hipError_t launch_prefill_generic_varlen(const Dims &d_in, const int32_t *cu, co
   // blocks of the tables = chunks; "segments" of one chunk each (only their total is used: zero
   // marks rejected boundaries)
   const VarPlan vp = {t, t + n1, t + 2 * n1, t + 3 * n1, t + 4 * n1, t + 5 * n1, t + 5 * n1 + cap, d.Bt, cap, 0};
-  launch_varlen_tables(cu, d.T, d.L, 1, cap + d.Bt + 1, vp, stream);
+  SegChoice one = {};
+  one.cand[0] = one.count = 1;
+  launch_varlen_tables(cu, d.T, d.L, one, cap + d.Bt + 1, vp, stream);
   return d.bf16 ? launch_typed<IoBf16>(d, vp, x, dt, A, B, C, D, h0, y, final_state, cs, states, stream, nullptr)
                 : launch_typed<IoF32>(d, vp, x, dt, A, B, C, D, h0, y, final_state, cs, states, stream, nullptr);
 }

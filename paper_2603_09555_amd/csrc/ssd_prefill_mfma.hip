@@ -111,19 +111,16 @@ struct NSlice {
 // cumulative lengths) is handled as a batch whose rows differ in length: every sequence gets whole
 // 64-token blocks of its own (the ragged last block of each is masked by the buffer descriptors, as
 // for a plain batch) and one or more segments.  Two tiny kernels turn the boundaries into tables:
-//   tok0[q], len[q]      first token and length of sequence q
+//   tok0[q], len[q]      first token and length of sequence q; len[nseq]: blocks per segment
 //   blk0[q], item0[q]    number of blocks / segments of the sequences before q (entry nseq: totals)
 //   slot0[q]             number of state slots before q: a sequence of several segments has one slot
 //                        per segment, a sequence of one segment needs none
 //   blk_seq[i]           sequence that block i belongs to
-//   item_seq[i]          sequence that entry i of the segment list belongs to, plus kLastSegment if the entry is its
-//                        last segment; -1 beyond the list, up to the capacity that grids are sized for
+//   item_seq[i]          sequence that entry i of the segment list belongs to
 // Blocks and segments are numbered over the whole batch; workspace arrays are indexed by those
 // numbers (capacities nb_cap, slot_cap are upper bounds that the host can compute from the token
 // count and the number of sequences alone).  Boundaries that are not non-decreasing within
 // [0, total] give empty tables: every later kernel then finds nothing to do.
-
-constexpr int kLastSegment = 1 << 30;
 
 __global__ __launch_bounds__(256) void varlen_scan_kernel(const int32_t *__restrict__ cu, int nseq, int total,
                                                           int blk_len, int seg_blocks, int32_t *__restrict__ tok0,
@@ -153,6 +150,7 @@ __global__ __launch_bounds__(256) void varlen_scan_kernel(const int32_t *__restr
   sslot[tid] = ns;
   __syncthreads();
   if (tid == 0) {  // exclusive prefix over the 256 partial sums
+    len[nseq] = seg_blocks;
     int a = 0, b = 0, c = 0;
     for (int i = 0; i < 256; ++i) {
       const int t = sblk[i], u = sitem[i], v = sslot[i];
@@ -203,7 +201,7 @@ constexpr int kSortMax = 2048;
 __global__ __launch_bounds__(256) void varlen_fill_kernel(const int32_t *__restrict__ blk0,
                                                           const int32_t *__restrict__ item0, int nseq,
                                                           int seg_blocks, int32_t *__restrict__ blk_seq,
-                                                          int32_t *__restrict__ item_seq, int item_cap) {
+                                                          int32_t *__restrict__ item_seq) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i < blk0[nseq]) blk_seq[i] = owner_of(blk0, nseq, i);
   const int n_items = item0[nseq], n_full = n_items - nseq;
@@ -214,8 +212,6 @@ __global__ __launch_bounds__(256) void varlen_fill_kernel(const int32_t *__restr
       if (item0[mid] - mid <= i) lo = mid; else hi = mid;
     }
     item_seq[i] = lo;
-  } else if (i >= n_items && i < item_cap) {
-    item_seq[i] = -1;
   }
   // (no early return above: the barrier below is reached by every thread)
   __shared__ int16_t last_blocks[kSortMax];  // blocks in the last segment of every sequence (<= seg_blocks)
@@ -236,28 +232,69 @@ __global__ __launch_bounds__(256) void varlen_fill_kernel(const int32_t *__restr
         rank += (other > mine || (other == mine && k < q)) ? 1 : 0;
       }
     }
-    item_seq[n_full + rank] = q | kLastSegment;
+    item_seq[n_full + rank] = q;
   }
+}
+
+// A reduction over the wave, uniform: rotations inside rows of 16 lanes, then the four rows' results.
+template <typename Op>
+__device__ __forceinline__ int wave_reduce(int v, Op op) {
+  v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, false));  // row_ror:8
+  v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x124, 0xf, 0xf, false));
+  v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x122, 0xf, 0xf, false));
+  v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x121, 0xf, 0xf, false));
+  return op(op(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+            op(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+}
+
+// Modelled time (us) of a packed batch of `nseq` sequences, `blocks` blocks in all and `longest` in the longest, cut into
+// segments of s blocks, `items` of them.  The scan: the busiest CU's load -- a workgroup's start counts as some blocks --
+// and the longest walk; with segments that are not the last of their sequence also the states-only pass, the same way, and
+// the chain.  Fitted to 240 drawn batches (2 to 128 sequences, 380 to 16500 tokens, 4 to 80 heads; ragged, equal, one or a
+// few long among short ones) at every length from the host's shortest on; 8 and 9 % rms, the choice 2.2 % behind the
+// fastest of the timed plans.  Against the length of one sequence of all the tokens: 1.07 in the geometric mean.  A length
+// guessed on the host cannot serve both a ragged batch and one long prompt among short ones: the guess of four times the
+// mean left 8192 + 63 x 1 tokens x 24 heads uncut, 322 us (now 75; 89 with the length of one sequence).
+__host__ __device__ inline float packed_cost(const SegChoice &c, int s, int blocks, int longest, int nseq, int items) {
+  auto both = [](float a, float b) { return sqrtf(a * a + b * b); };
+  const float n = static_cast<float>(items), full = static_cast<float>(items - nseq), len = static_cast<float>(s);
+  const float walk = s < longest ? len : static_cast<float>(longest), grid = n * c.fill < 1.f ? n * c.fill : 1.f;
+  float us;
+  if (c.heads == 2) {
+    us = 8.1f + (1.96f + 0.13f * grid) * both((blocks + 6.7f * n) * c.fill, walk + 6.7f);
+    if (items > nseq) us += 0.021f * full * c.slices + 0.835f * (len + 4.f) * both(1.f, full * c.fill);
+  } else {
+    us = 10.4f + (2.36f + 0.23f * grid) * both((blocks + 5.1f * n) * c.fill, walk + 5.1f);
+    if (items > nseq) us += 0.025f * full * c.slices + 0.76f * (len + 7.2f) * both(1.f, full * c.fill);
+  }
+  return items > c.max_items ? 1.25f * us : us;
 }
 
 // Both steps in one workgroup, for batches small enough for it (one thread per sequence; the lists filled in a few
 // trips): the scans run across the threads and the searches in LDS.  64 sequences, 16384 tokens: the two kernels above
 // take 7.4 + 4.7 us and a launch between them, most of it one thread's serial sum; this one
 // 5.6 us (the whole call 185 -> 174; 11 sequences, 763 tokens, 9 heads: 36 -> 30).
+// It also chooses the segment length: a wave per candidate.
 constexpr int kTableThreads = 1024;
 constexpr int kTableBlocks = 16 * kTableThreads;  // most blocks (and list entries) it fills
 __global__ __launch_bounds__(kTableThreads) void varlen_tables_kernel(
-    const int32_t *__restrict__ cu, int nseq, int total, int blk_len, int seg_blocks, int32_t *__restrict__ tok0,
+    const int32_t *__restrict__ cu, int nseq, int total, int blk_len, const SegChoice choice, int32_t *__restrict__ tok0,
     int32_t *__restrict__ len, int32_t *__restrict__ blk0, int32_t *__restrict__ item0, int32_t *__restrict__ slot0,
-    int32_t *__restrict__ blk_seq, int32_t *__restrict__ item_seq, int item_cap) {
+    int32_t *__restrict__ blk_seq, int32_t *__restrict__ item_seq) {
   constexpr int kWaves = kTableThreads / 64;
+  constexpr int kOwn = SegChoice::kMost / kWaves;  // candidates per wave
+  __shared__ float s_cost[SegChoice::kMost];
+  __shared__ int s_cand[SegChoice::kMost];
   __shared__ int s_blk[kTableThreads + 1], s_item[kTableThreads + 1], s_sum[3][kWaves];
   __shared__ int s_last[kTableThreads];
   __shared__ int s_bad;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (tid == 0) s_bad = 0;
+  int mine_k[kOwn];
+#pragma unroll
+  for (int j = 0; j < kOwn; ++j) mine_k[j] = choice.cand[__builtin_amdgcn_readfirstlane(wave) + kWaves * j];
   __syncthreads();
-  int a = 0, l = 0, n = 0, segs = 0;
+  int a = 0, l = 0, n = 0;
   if (tid < nseq) {
     a = cu[tid];
     const int b = cu[tid + 1];
@@ -266,9 +303,41 @@ __global__ __launch_bounds__(kTableThreads) void varlen_tables_kernel(
     } else {
       l = b - a;
       n = (l + blk_len - 1) / blk_len;
-      segs = max(1, (n + seg_blocks - 1) / seg_blocks);
     }
+    s_last[tid] = n;
   }
+  // blocks per segment
+  int seg_blocks = choice.cand[0];
+  if (choice.count > 1) {
+    __syncthreads();
+    int longest = 0, blocks = 0;
+    for (int q = lane; q < nseq; q += 64) {
+      longest = max(longest, s_last[q]);
+      blocks += s_last[q];
+    }
+    longest = wave_reduce(longest, [](int x, int y) { return max(x, y); });
+    blocks = wave_reduce(blocks, [](int x, int y) { return x + y; });
+#pragma unroll
+    for (int j = 0; j < kOwn; ++j) {
+      const int s = mine_k[j], k = wave + kWaves * j;
+      if (k >= choice.count) break;
+      const float inv = 1.f / static_cast<float>(s);
+      int items = 0;
+      for (int q = lane; q < nseq; q += 64)  // ceil(n / s), at least one (exact: n is at most kTableBlocks)
+        items += max(1, static_cast<int>((static_cast<float>(s_last[q] + s) - 0.5f) * inv));
+      items = wave_reduce(items, [](int x, int y) { return x + y; });
+      if (lane == 0) {
+        s_cost[k] = packed_cost(choice, s, blocks, longest, nseq, items);
+        s_cand[k] = s;
+      }
+    }
+    __syncthreads();
+    // the cheapest, the shortest of equals: a positive float orders like its bits, whose last five give way to the index
+    int best = lane < choice.count ? ((__float_as_int(s_cost[lane]) & ~31) | lane) : 0x7fffffff;
+    best = wave_reduce(best, [](int x, int y) { return min(x, y); });
+    seg_blocks = s_cand[best & 31];
+  }
+  const int segs = tid < nseq ? max(1, (n + seg_blocks - 1) / seg_blocks) : 0;
   // exclusive sums over the sequences: blocks, segments, state slots
   const int own[3] = {n, segs, segs > 1 ? segs : 0};
   int sum[3] = {own[0], own[1], own[2]};
@@ -298,6 +367,7 @@ __global__ __launch_bounds__(kTableThreads) void varlen_tables_kernel(
     slot0[tid] = bad ? 0 : sum[2] - own[2];
     s_last[tid] = n - (segs - 1) * seg_blocks;  // blocks in the last segment
     if (tid == nseq - 1) {
+      len[nseq] = seg_blocks;
       blk0[nseq] = s_blk[nseq] = bad ? 0 : sum[0];
       item0[nseq] = s_item[nseq] = bad ? 0 : sum[1];
       slot0[nseq] = bad ? 0 : sum[2];
@@ -306,17 +376,13 @@ __global__ __launch_bounds__(kTableThreads) void varlen_tables_kernel(
   __syncthreads();
   const int blocks = s_blk[nseq], n_items = s_item[nseq], n_full = bad ? 0 : n_items - nseq;
   for (int i = tid; i < blocks; i += kTableThreads) blk_seq[i] = owner_of(s_blk, nseq, i);
-  for (int i = tid; i < item_cap; i += kTableThreads) {
-    if (i < n_full) {
-      int lo = 0, hi = nseq;
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (s_item[mid] - mid <= i) lo = mid; else hi = mid;
-      }
-      item_seq[i] = lo;
-    } else if (i >= n_items) {
-      item_seq[i] = -1;
+  for (int i = tid; i < n_full; i += kTableThreads) {
+    int lo = 0, hi = nseq;
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (s_item[mid] - mid <= i) lo = mid; else hi = mid;
     }
+    item_seq[i] = lo;
   }
   if (tid < nseq && !bad) {
     const int mine = s_last[tid];
@@ -325,7 +391,7 @@ __global__ __launch_bounds__(kTableThreads) void varlen_tables_kernel(
       const int other = s_last[k];
       rank += (other > mine || (other == mine && k < tid)) ? 1 : 0;
     }
-    item_seq[n_full + rank] = tid | kLastSegment;
+    item_seq[n_full + rank] = tid;
   }
 }
 
@@ -685,7 +751,7 @@ struct ScanParams {
 // `blk0` (per group / per head: stride `blk_stride`), and whose state slots (one per segment, per
 // head: stride `slot_stride`) start at `slot0`.
 struct SeqView {
-  int col, sg, S, b, nb;
+  int col, sg, S, b, nb, seg_blocks;
   size_t tok0, blk0, blk_stride, slot0, slot_stride;
   uint32_t len;
 };
@@ -709,6 +775,7 @@ __device__ __forceinline__ bool wg_coords(const ScanParams &p, bool last_too, Se
   v.b = w / (p.cols * p.segs);
   v.S = p.S;
   v.nb = p.NB;
+  v.seg_blocks = p.seg_blocks;
   v.tok0 = static_cast<size_t>(v.b) * p.T;
   v.len = static_cast<uint32_t>(p.T);
   v.blk0 = static_cast<size_t>(v.b) * p.NB;   // times G (tiles) or H (records) in the caller's stride
@@ -719,8 +786,13 @@ __device__ __forceinline__ bool wg_coords(const ScanParams &p, bool last_too, Se
 }
 // Variable-length batch: the list (see varlen_fill_kernel) and with it the split over the XCDs come
 // from the device-side tables; the grid was sized for the host's upper bound on its length.
+// (The tables don't change while a kernel runs; read as constant memory they come through the scalar cache, where the next
+// workgroup finds them: as ordinary loads they cost every workgroup's start 1.1 us.)
+__device__ __forceinline__ int table_at(const int32_t *t, int i) {
+  return ((const __attribute__((address_space(4))) int32_t *)t)[i];
+}
 __device__ __forceinline__ bool wg_coords_varlen(const ScanParams &p, bool last_too, SeqView &v) {
-  const int n_items = p.vp.item0[p.vp.nseq];
+  const int n_items = table_at(p.vp.item0, p.vp.nseq), seg_blocks = table_at(p.vp.len, p.vp.nseq);
   const int n_full = n_items - p.vp.nseq;
   const int n_list = last_too ? n_items : n_full;
   // The same contiguous split over the XCDs as for a plain batch, so that every XCD gets the same
@@ -744,17 +816,18 @@ __device__ __forceinline__ bool wg_coords_varlen(const ScanParams &p, bool last_
     const int pos = item < big ? item % (base + 1) : (item - big) % base;
     item = pos * kXcds + hand;
   }
-  const int q = p.vp.item_seq[item] & (kLastSegment - 1);
-  const int first = p.vp.item0[q];
+  const int q = table_at(p.vp.item_seq, item);
+  const int first = table_at(p.vp.item0, q);
   v.b = q;
-  v.S = p.vp.item0[q + 1] - first;
+  v.seg_blocks = seg_blocks;
+  v.S = table_at(p.vp.item0, q + 1) - first;
   v.sg = item < n_full ? item - (first - q) : v.S - 1;
-  v.len = static_cast<uint32_t>(p.vp.len[q]);
+  v.len = static_cast<uint32_t>(table_at(p.vp.len, q));
   v.nb = static_cast<int>((v.len + kBlk - 1) / kBlk);
-  v.tok0 = static_cast<size_t>(p.vp.tok0[q]);
-  v.blk0 = static_cast<size_t>(p.vp.blk0[q]);
+  v.tok0 = static_cast<size_t>(table_at(p.vp.tok0, q));
+  v.blk0 = static_cast<size_t>(table_at(p.vp.blk0, q));
   v.blk_stride = static_cast<size_t>(p.vp.nb_cap);
-  v.slot0 = static_cast<size_t>(p.vp.slot0[q]);
+  v.slot0 = static_cast<size_t>(table_at(p.vp.slot0, q));
   v.slot_stride = static_cast<size_t>(p.vp.slot_cap);
   return true;
 }
@@ -860,7 +933,7 @@ __device__ __forceinline__ void scan_walk(const ScanParams &p, const SeqView &sv
   const size_t bh = static_cast<size_t>(sv.b) * p.H + h;  // row of final_state
   const int r = lane & 31, kg = lane >> 5;
   // (the states-only pass walks a piece of a segment, the full scan a whole segment)
-  const int walk = kStatesOnly ? p.part_blocks : p.seg_blocks;
+  const int walk = kStatesOnly && plain ? p.part_blocks : sv.seg_blocks;
   const int jb0 = min(sv.nb, sg * walk);
   const int jb1 = min(sv.nb, jb0 + walk);
   const int cg = lane & 3, tg = lane >> 2;  // x staging: columns 8cg..8cg+7 of the half, tokens 4tg..4tg+3
@@ -1674,7 +1747,7 @@ __device__ __forceinline__ bool walk_meets_steep_block(const ScanParams &p, cons
   const int hrec = h / p.pdiv;
   const bool plain = p.vp.tok0 == nullptr;
   const size_t rec0 = plain ? (sv.blk0 * p.Hrec + static_cast<size_t>(hrec) * sv.blk_stride) : (hrec * sv.blk_stride + sv.blk0);
-  const int jb0 = min(sv.nb, sv.sg * p.seg_blocks), jb1 = min(sv.nb, jb0 + p.seg_blocks);
+  const int jb0 = min(sv.nb, sv.sg * sv.seg_blocks), jb1 = min(sv.nb, jb0 + sv.seg_blocks);
   const float *marks = p.prep + rec0 * kRec + 2 * kBlk + 2;
   float lowest = 1.f;
   for (int j = jb0; j < jb1; j += 64)
@@ -1717,17 +1790,17 @@ void chunk_scan_kernel(const ScanParams p) {
 __global__ __launch_bounds__(kThreads) void segment_pass_kernel(float *__restrict__ seg_state,
                                                                 const float *__restrict__ seg_decay,
                                                                 const float *__restrict__ h0, int S_plain, int H,
-                                                                int rows, const VarPlan vp, const NSlice ns) {
+                                                                size_t rows, const VarPlan vp, const NSlice ns) {
   constexpr int kAhead = 8;
   const int e = (blockIdx.x * kThreads + threadIdx.x) * 4;
-  for (size_t row = blockIdx.y; row < static_cast<size_t>(rows); row += gridDim.y) {
+  if (vp.tok0 != nullptr) rows = static_cast<size_t>(max(0, vp.item0[vp.nseq] - vp.nseq)) * H;  // (none if rejected)
+  for (size_t row = blockIdx.y; row < rows; row += gridDim.y) {
   int S = S_plain;
   size_t bh = row, slot0 = row * S_plain;  // (sequence, head); its first slot
   if (vp.tok0 != nullptr) {
     // one row per head and non-last segment of the list; the row of a sequence's first segment does its chain
     const int i = static_cast<int>(row / H), h = static_cast<int>(row % H);
     const int q = vp.item_seq[i];
-    if (q < 0 || (q & kLastSegment)) continue;
     const int first = vp.item0[q];
     if (i != first - q) continue;
     S = vp.item0[q + 1] - first;
@@ -1907,43 +1980,6 @@ int two_head_blocks(const Dims &d, int min_blocks, int blocks4, int parts4) {
   return best_us < us4 ? best : 0;
 }
 
-// Blocks per segment of a packed batch of several sequences.  Their lengths are known on the device only, and the one
-// sequence of all the tokens that the choice above would have in mind is cut far too finely for them: the sequences
-// fill the chip themselves, every further segment pays for its start, and a length that no sequence can exceed needs
-// neither states pass nor chain (two launches).  The model supposes a longest sequence of four times the mean and four
-// blocks, and weighs in, at 6 %, the case that one sequence has nearly all the tokens.  Microseconds, fitted to 110
-// drawn batches (2 to 128 sequences, 512 to 16384 tokens, 4 to 160 slices) at up to 20 lengths each; on 70 others the
-// choice is 1.2 % behind the best of them, where the one sequence's was 13 %: 64 sequences, 16384 tokens x 80 heads
-// 173 -> 169, 18 of 5166 x 68 97 -> 70, 10 of 659 x 80 34 -> 29.
-int choose_varlen_blocks(const Dims &d, int min_blocks) {
-  const int nblocks = (d.T + kBlk - 1) / kBlk, n = d.Bt;
-  if (n < 2 || knobs().seg_chunks >= 1 || knobs().seg_blocks >= 1 || nblocks <= min_blocks) return 0;
-  const double fill = head_groups(d) / static_cast<double>(kNumCUs), slices = static_cast<double>(d.H) * (d.P / kP);
-  const double start = 1.9;  // a workgroup's start and end, in blocks
-  auto both = [](double a, double b) { return sqrt(a * a + b * b); };  // the busiest CU: the load, or the longest walk
-  auto cost = [&](int s, double longest) {
-    const double split = s < longest ? 1.0 - s / longest : 0.0;
-    const double full = 0.8 * nblocks * split / s;  // non-last segments
-    const double walk = (s < longest ? s : longest) + start;
-    double us = 2.6 * both((nblocks + 0.5 * n + start * (n + full)) * fill, walk);
-    if (s < nblocks) us += 12.0 + 0.04 * full * slices;
-    if (full > 0.0) us += 1.6 * both(walk, (s + start) * full * fill);
-    return us;
-  };
-  const double most = nblocks - 0.5 * (n - 1), guess = 4.0 * nblocks / n + 4.0;
-  const double longest = guess < most ? guess : most < 1.0 ? 1.0 : most;
-  int best = nblocks;
-  double best_us = 0.94 * cost(nblocks, longest) + 0.06 * cost(nblocks, most);
-  for (int s = min_blocks; s < nblocks && s <= longest + 1.0; ++s) {
-    const double us = 0.94 * cost(s, longest) + 0.06 * cost(s, most);
-    if (us < best_us) {
-      best_us = us;
-      best = s;
-    }
-  }
-  return best;
-}
-
 // Workspace.  Plain batch: rows = Bt sequences of NB blocks each.  Variable-length batch: one "row" whose
 // NB is the block capacity ceil(total / 64) + nseq (every sequence may end in a partial block), whose
 // segment list holds at most NB / (blocks per chunk) + nseq + 1 entries (a segment is at least a
@@ -2016,13 +2052,10 @@ bool stream_y(const Dims &d, int rows) {
   return 4 * x_bytes > kMemCacheBytes;
 }
 
-// Entries of a packed batch's list of segments, at most: all of them; those that are not the last of their sequence (a
-// non-last segment is seg_blocks whole blocks with a token behind them).
-int list_items(const Dims &d, const Layout &w, int seg_blocks) {
-  const int items = w.NB / seg_blocks + d.Bt + 1;
-  return items < w.items_max ? items : w.items_max;
-}
+// Entries of a packed batch's list of segments, at most: those that are not the last of their sequence (each is
+// seg_blocks whole blocks with a token behind them); all of them.
 int full_items(const Dims &d, const Layout &w, int seg_blocks) { return (w.NB - d.Bt - 1) / seg_blocks; }
+int list_items(const Dims &d, const Layout &w, int seg_blocks) { return d.Bt + full_items(d, w, seg_blocks); }
 
 // d: plain batch (cu == nullptr), or Bt = number of sequences and T = total tokens of a packed batch.
 // One state slice ns (see NSlice): y and final_state columns of that slice are written.
@@ -2035,9 +2068,7 @@ SlicePlan plan_slice(const Dims &d, bool varlen, bool h0_aliases_final_state) {
   if (varlen) one.Bt = 1;
   SlicePlan pl;
   // shortest segment: a chunk for a packed batch; what the state slots allow for a plain one
-  pl.seg_blocks = varlen ? choose_varlen_blocks(d, d.L / kBlk) : 0;
-  if (pl.seg_blocks == 0)
-    pl.seg_blocks = choose_seg_blocks(one, varlen ? d.L / kBlk : (w.NB + w.S_max - 1) / w.S_max, w.S_max, varlen ? 1 : 8);
+  pl.seg_blocks = choose_seg_blocks(one, varlen ? d.L / kBlk : (w.NB + w.S_max - 1) / w.S_max, w.S_max, varlen ? 1 : 8);
   if (!varlen && (w.NB + pl.seg_blocks - 1) / pl.seg_blocks > w.S_max) pl.seg_blocks = (w.NB + w.S_max - 1) / w.S_max;
   pl.segments = varlen ? 0 : (w.NB + pl.seg_blocks - 1) / pl.seg_blocks;
   // pieces per segment for the states-only pass (see ScanParams): the split with the least modelled
@@ -2054,6 +2085,9 @@ SlicePlan plan_slice(const Dims &d, bool varlen, bool h0_aliases_final_state) {
   const bool may_choose = kn.scan_heads == 0 && kn.seg_chunks == 0 && kn.seg_blocks == 0 && kn.seg_parts == 0;
   const bool may_two = kn.scan_heads == 0 && !stream_y(d, varlen ? 1 : d.Bt);
   const int seqs = varlen ? 1 : d.Bt;
+  // (the lengths of several sequences are known on the device only; see segment_choice)
+  pl.from_lengths = varlen && d.Bt > 1 && d.Bt <= kTableThreads && w.NB <= kTableBlocks && list_items(d, w, pl.seg_blocks) <= kTableBlocks &&
+                    kn.seg_chunks == 0 && kn.seg_blocks == 0 && full_items(d, w, pl.seg_blocks) > 0;
   pl.heads = pl.state_heads = kn.scan_heads == 2 ? 2 : kHeadsPerWg;
   if (!varlen && may_choose && may_two) {
     if (const int b = two_head_blocks(d, (w.NB + w.S_max - 1) / w.S_max, pl.seg_blocks, pl.parts); b > 0) {
@@ -2062,7 +2096,11 @@ SlicePlan plan_slice(const Dims &d, bool varlen, bool h0_aliases_final_state) {
       pl.segments = (w.NB + b - 1) / b;
     }
   }
-  if (may_two) {  // (packed batch: by the most entries that the lists can have)
+  if (varlen && pl.from_lengths) {
+    // (of the same 240 batches: none with two heads 1.9 % slower on average, all of small_grid's 0.7 %)
+    const long groups2 = head_groups(d, 2);
+    if (may_two && small_grid(d.Bt * groups2) && small_grid((w.NB - d.Bt) * groups2 / 4)) pl.heads = pl.state_heads = 2;
+  } else if (may_two) {  // (packed batch of one segment length: by the most entries that the lists can have)
     const long full = varlen ? full_items(d, w, pl.seg_blocks) : static_cast<long>(pl.segments - 1) * pl.parts;
     const long all = varlen ? list_items(d, w, pl.seg_blocks) : pl.segments;
     if (small_grid(all * seqs * head_groups(d, 2))) pl.heads = 2;
@@ -2074,6 +2112,27 @@ SlicePlan plan_slice(const Dims &d, bool varlen, bool h0_aliases_final_state) {
   // store the final state before the first has read h0.
   pl.fold = !varlen && pl.segments >= 2 && (pl.segments - 1) * pl.parts <= knobs().fold_max_slots && !h0_aliases_final_state ? 1 : 0;
   return pl;
+}
+
+// What the device may choose the segment length of a packed batch from: lengths from that of one sequence of all the tokens
+// -- the shortest that pays, and what grids and tables are sized for -- to all the tokens, 13 % apart and more.
+SegChoice segment_choice(const Dims &d, const SlicePlan &pl) {
+  SegChoice c = {};
+  const int nblocks = (d.T + kBlk - 1) / kBlk;
+  c.cand[0] = pl.seg_blocks;
+  c.count = 1;
+  if (!pl.from_lengths) return c;
+  const double ratio = fmax(1.13, pow(static_cast<double>(nblocks) / pl.seg_blocks, 1.0 / 20));
+  while (c.count < SegChoice::kMost && c.cand[c.count - 1] < nblocks) {
+    const int last = c.cand[c.count - 1], next = static_cast<int>(last * ratio + 0.5);
+    c.cand[c.count++] = next > last ? (next < nblocks ? next : nblocks) : last + 1;
+  }
+  c.heads = pl.heads;
+  const int groups = head_groups(d, pl.heads);
+  c.max_items = pl.heads == 2 ? kNumCUs / groups : 0x7fffffff;
+  c.fill = static_cast<float>(groups) / kNumCUs;
+  c.slices = static_cast<float>(d.H) * (d.P / kP);
+  return c;
 }
 
 // The workgroups of a pass: `heads` head slices each, `segs` segments per sequence, `items` in all.
@@ -2117,7 +2176,7 @@ hipError_t launch_slice(const Dims &d, const NSlice ns, const int32_t *cu, const
     S = 0;  // per sequence, from the tables
     vp = VarPlan{tok0, len, blk0, item0, slot0, blk_seq, item_seq, d.Bt, w.NB, w.S_max};
     if (!add_to_y) {  // (a later state slice finds the tables of the first)
-      launch_varlen_tables(cu, d.T, kBlk, seg_blocks, items, vp, stream);
+      launch_varlen_tables(cu, d.T, kBlk, segment_choice(d, pl), items, vp, stream);
       trace_mark(trace, stream, "varlen_tables");
     }
   }
@@ -2172,9 +2231,10 @@ hipError_t launch_slice(const Dims &d, const NSlice ns, const int32_t *cu, const
     else
       hipLaunchKernelGGL((chunk_scan_kernel<true, kHeadsPerWg>), grid, block, 0, stream, p);
     trace_mark(trace, stream, "segment_states");
-    const int rows_bh = (varlen ? full_cap : d.Bt) * Hs;
+    const size_t rows_bh = static_cast<size_t>(varlen ? full_cap : d.Bt) * Hs;
+    const size_t most_rows = varlen ? 512 : 65535;  // (packed: most rows hold no chain, and there may be none at all)
     if (!p.fold)
-      hipLaunchKernelGGL(segment_pass_kernel, dim3(kP * kN / (4 * kThreads), rows_bh > 65535 ? 65535 : rows_bh),
+      hipLaunchKernelGGL(segment_pass_kernel, dim3(kP * kN / (4 * kThreads), rows_bh > most_rows ? most_rows : rows_bh),
                          dim3(kThreads), 0, stream, seg_state, seg_decay, h0, p.slots, Hs, rows_bh, vp, ns);
     if (!p.fold) trace_mark(trace, stream, "segment_pass");
   }
@@ -2214,23 +2274,24 @@ hipError_t launch(const Dims &d, const int32_t *cu, const void *x, const float *
 }  // namespace
 
 // Tables of a packed batch for blocks of blk_len tokens (the MFMA kernels: 64; the generic kernels:
-// one chunk) and segments of seg_blocks blocks.  vp names the table arrays (device, int32: tok0, len,
+// one chunk).  vp names the table arrays (device, int32: tok0, len,
 // blk0, item0, slot0 of nseq + 1 entries each, blk_seq of nb_cap, item_seq of item_cap entries).
-void launch_varlen_tables(const int32_t *cu, int total, int blk_len, int seg_blocks, int item_cap, const VarPlan &vp,
+void launch_varlen_tables(const int32_t *cu, int total, int blk_len, const SegChoice &choice, int item_cap, const VarPlan &vp,
                           hipStream_t stream) {
   const int cap = vp.nb_cap > item_cap ? vp.nb_cap : item_cap;
   if (vp.nseq <= kTableThreads && cap <= kTableBlocks) {
-    hipLaunchKernelGGL(varlen_tables_kernel, dim3(1), dim3(kTableThreads), 0, stream, cu, vp.nseq, total, blk_len, seg_blocks,
+    hipLaunchKernelGGL(varlen_tables_kernel, dim3(1), dim3(kTableThreads), 0, stream, cu, vp.nseq, total, blk_len, choice,
                        const_cast<int32_t *>(vp.tok0), const_cast<int32_t *>(vp.len), const_cast<int32_t *>(vp.blk0),
                        const_cast<int32_t *>(vp.item0), const_cast<int32_t *>(vp.slot0),
-                       const_cast<int32_t *>(vp.blk_seq), const_cast<int32_t *>(vp.item_seq), item_cap);
+                       const_cast<int32_t *>(vp.blk_seq), const_cast<int32_t *>(vp.item_seq));
     return;
   }
+  const int seg_blocks = choice.cand[0];
   hipLaunchKernelGGL(varlen_scan_kernel, dim3(1), dim3(256), 0, stream, cu, vp.nseq, total, blk_len, seg_blocks,
                      const_cast<int32_t *>(vp.tok0), const_cast<int32_t *>(vp.len), const_cast<int32_t *>(vp.blk0),
                      const_cast<int32_t *>(vp.item0), const_cast<int32_t *>(vp.slot0));
   hipLaunchKernelGGL(varlen_fill_kernel, dim3((cap + 255) / 256), dim3(256), 0, stream, vp.blk0, vp.item0, vp.nseq,
-                     seg_blocks, const_cast<int32_t *>(vp.blk_seq), const_cast<int32_t *>(vp.item_seq), item_cap);
+                     seg_blocks, const_cast<int32_t *>(vp.blk_seq), const_cast<int32_t *>(vp.item_seq));
 }
 
 // The kernels work on 64-token blocks whatever the chunk length is (results do not depend on it); the chunk
@@ -2250,6 +2311,30 @@ size_t mfma_workspace_bytes(const Dims &d) { return make_layout(with_block_chunk
 
 SlicePlan mfma_plan(const Dims &d, bool h0_aliases_final_state) {
   return plan_slice(with_block_chunk(d), false, h0_aliases_final_state);
+}
+
+SlicePlan mfma_varlen_plan(const Dims &d_in, const int32_t *cu) {
+  const Dims d = with_block_chunk(d_in);
+  SlicePlan pl = plan_slice(d, true, false);
+  const SegChoice c = segment_choice(d, pl);
+  pl.shortest = pl.seg_blocks;
+  float best = 0.f;
+  for (int k = 0; k < c.count; ++k) {
+    int items = 0, longest = 0, blocks = 0;
+    for (int q = 0; q < d.Bt; ++q) {
+      const int n = (cu[q + 1] - cu[q] + kBlk - 1) / kBlk;
+      items += n > c.cand[k] ? (n + c.cand[k] - 1) / c.cand[k] : 1;
+      longest = n > longest ? n : longest;
+      blocks += n;
+    }
+    const float us = c.count > 1 ? packed_cost(c, c.cand[k], blocks, longest, d.Bt, items) : 0.f;
+    if (k == 0 || us < best) {
+      best = us;
+      pl.seg_blocks = c.cand[k];
+      pl.segments = items;
+    }
+  }
+  return pl;
 }
 
 hipError_t launch_prefill_mfma(const Dims &d, const void *x, const float *dt, const float *A, const void *B,

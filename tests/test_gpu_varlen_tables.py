@@ -62,3 +62,24 @@ def test_rejected_boundaries_write_nothing(ssd, nseq):
                            final_state=st)
     torch.cuda.synchronize()
     assert (y == 3.0).all() and (st == 5.0).all()
+
+
+@pytest.mark.parametrize("lens", [[4000] + 64 * [1], 40 * [1] + [2500, 0, 1300], [7000] + 1023 * [1], [64, 65, 129, 1000]],
+                         ids=lambda v: "%dx" % len(v))
+def test_one_long_prompt_among_short_rows(ssd, lens):
+    """The segment length is chosen on the device from the lengths: several segments for the long ones."""
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    T, H, P, N, L = int(cu[-1]), 6, 64, 128, 64
+    plan = ssd.varlen_plan(lens, H, P, N, 1, L)
+    print("one long prompt among short rows", len(lens), plan, flush=True)
+    assert plan["chosen"] and plan["items"] > len(lens)
+    pk = {k: (v[0] if k in ("x", "dt", "B", "C") else v)
+          for k, v in inputs.make_prefill_inputs(inputs.SSDConfig("t", 1, T, H, P, N, 1, L, "bf16"), seed=14).items()}
+    h0 = inputs.make_state(inputs.SSDConfig("h", len(lens), 1, H, P, N, 1, L, "bf16"), seed=14, scale=0.1)
+    dev = {k: v.cuda() for k, v in pk.items()}
+    y, st = ssd.ssd_prefill_varlen(dev["x"], dev["dt"], dev["A"], dev["B"], dev["C"], dev["D"], torch.from_numpy(cu).cuda(), L,
+                                   h0=h0.cuda())
+    torch.cuda.synchronize()
+    y_ref, st_ref = ssd_oracle.prefill_varlen(pk["x"], pk["dt"], pk["A"], pk["B"], pk["C"], pk["D"], cu, h0=h0)
+    assert_close(y, y_ref, TOL["bf16"], "y")
+    assert_close(st, st_ref, TOL["bf16"], "final state")

@@ -1,0 +1,52 @@
+"""How a packed batch is cut up (``ssd_testing_varlen_plan``: host arithmetic, the device's choice evaluated on the host)."""
+import random
+
+import pytest
+
+from paper_2603_09555_amd import ssd
+
+
+@pytest.fixture(autouse=True)
+def _reset():
+    ssd.reset_knobs()
+    yield
+    ssd.reset_knobs()
+
+
+def plan(lengths, heads, groups=1, chunk=256):
+    return ssd.varlen_plan(lengths, heads, 64, 128, groups, chunk)
+
+
+@pytest.mark.parametrize("lengths, heads, most", [([2016] + 32 * [1], 24, 6), ([4000] + 64 * [1], 24, 8), ([4096] + 31 * [1], 80, 10),
+                                                  ([8192] + 63 * [1], 80, 18), ([1] * 63 + [8192], 24, 12),
+                                                  ([3000, 3000] + 60 * [1], 24, 8)], ids=lambda v: str(v)[:20])
+def test_a_long_prompt_among_short_rows_is_cut(lengths, heads, most):
+    """Uncut, a few workgroups walk the whole prompt while the chip idles (8192 + 63 x 1 tokens: 322 us against 75)."""
+    p = plan(lengths, heads)
+    assert p["chosen"] and p["shortest"] <= p["seg_blocks"] <= most
+
+
+@pytest.mark.parametrize("lengths, heads", [([64] * 64, 80), ([256] * 16, 80), ([300] * 48 + [700] * 6, 80)], ids=lambda v: str(v)[:20])
+def test_sequences_that_fill_the_chip_are_not_cut(lengths, heads):
+    p = plan(lengths, heads)
+    assert p["items"] == len(lengths)
+
+
+def test_plans_stay_within_what_the_host_sized():
+    """Over drawn batches: the choice is between the host's shortest length and all the tokens, the list is that of this
+    length, and one sequence, a forced length and a batch that cannot be cut leave no choice."""
+    r = random.Random(3)
+    for _ in range(300):
+        n, heads, groups, chunk = r.randint(1, 200), r.randint(1, 40), r.choice([1, 2, 4]), r.choice([16, 64, 100, 256])
+        lengths = [r.choice([0, 1, r.randint(0, 300), r.randint(0, 3000)]) for _ in range(n)]
+        lengths[r.randrange(n)] += 1
+        p = plan(lengths, heads * groups, groups, chunk)
+        blocks = [(v + 63) // 64 for v in lengths]
+        total = (sum(lengths) + 63) // 64
+        assert p["mfma"] and (chunk + 63) // 64 <= p["shortest"] <= p["seg_blocks"] <= max(total, p["shortest"])
+        assert p["items"] == sum(max(1, -(-b // p["seg_blocks"])) for b in blocks)
+        assert p["items"] - n <= (total - 1) // p["shortest"]   # what the grid of the states-only pass is sized for
+        assert p["chosen"] == (n > 1 and total > p["shortest"]) and p["heads"] in (2, 4)
+    ssd.set_knob("seg_blocks", 7)
+    p = plan([3000] + 9 * [5], 8)
+    assert not p["chosen"] and p["seg_blocks"] == p["shortest"] == 7
