@@ -180,9 +180,9 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_any_kernel(
 }
 
 // Several steps in one launch (inputs of all steps known up front, e.g. a short continuation of a
-// cached prompt), for fp32 io, few steps and the shapes ssd_decode_steps_mfma.hip does not take: the state of a (layer, batch row, head) stays in registers across the steps, so
-// it is read and written once instead of once per step, and the per-step traffic shrinks to the
-// step's inputs and its output row.  What then bounds the kernel is the vector ALU, so the layout
+// cached prompt), for fp32 io, few steps and the shapes ssd_decode_steps_mfma.hip does not take: the
+// state of a (layer, batch row, head) stays in registers across the steps, so it is read and written
+// once instead of once per step, and the per-step traffic shrinks to the step's inputs and its output row.  What then bounds the kernel is the vector ALU, so the layout
 // minimises instructions per state element: LPR (<= 16) lanes share a row, each lane owns NV groups
 // of four consecutive n (group v covers n = 4 (v LPR + lane) ..), so a row's C.h is reduced inside a
 // 16-lane DPP row by four single add-with-lane-permute instructions, without LDS traffic.
@@ -382,7 +382,7 @@ hipError_t launch_decode(int nlayers, const Dims &d, float *state, const void *x
 hipError_t launch_decode_steps(int nsteps, int nlayers, const Dims &d, float *state, const void *x,
                                const float *dt, const float *A, const void *B, const void *C, const float *D,
                                void *y, hipStream_t stream) {
-  if (decode_steps_mfma_supported(nsteps, nlayers, d))
+  if (decode_steps_mfma_chosen(nsteps, nlayers, d))
     return launch_decode_steps_mfma(nsteps, nlayers, d, state, x, dt, A, B, C, D, y, stream);
   const bool resident =
       d.bf16 ? launch_steps_resident<IoBf16>(nsteps, nlayers, d, state, x, dt, A, B, C, D, y, stream)

@@ -373,19 +373,26 @@ __global__ __launch_bounds__(kThr, 2) void decode_steps_mfma_kernel(const StepsP
 
 }  // namespace
 
-// Fewer steps than this are left to decode_steps_kernel, whose state is bit for bit that of single steps, which callers
-// that check a few drafted tokens may count on; there is little to gain there (64 layers, batch 1: 4 steps 73 us against
-// 74; 8 steps 93 against 75).
+// Fewer steps than this are left to decode_steps_kernel, whose state is bit for bit that of single steps: callers that check
+// a few drafted tokens may count on it, and eight steps were held to it before this kernel was there.  That, not the time,
+// draws the line (64 layers, batch 1: 4 steps 73 us here, 74 there; 8 steps 75 and 93).
 constexpr int kMinSteps = 9;
+// With one or two slices per group (a B/C group of its own for heads of 32 or 64 columns) half of a workgroup's waves and
+// more have none and take up the room of those that do.  A call of more workgroups than run side by side (two per CU) then
+// needs this many steps times slices.  us there / here, 24 layers x batch 8: 24 heads and groups x 64 x 128, 9 steps 88 /
+// 93, 16 steps 130 / 94; x 64 x 64, 9 steps 44 / 50, 16 steps 69 / 51; 8 heads and groups x 32 x 128, 9 steps 18.5 / 30, 16
+// steps 27 / 30, 40 steps 56 / 45.  (headdim 32 with dstate 64 has no such kernel: a launch per step, 142 us for 9.)
+constexpr int kMinWork = 22, kFullGrid = 512;
 
-bool decode_steps_mfma_supported(int nsteps, int nlayers, const Dims &d) {
+bool decode_steps_mfma_chosen(int nsteps, int nlayers, const Dims &d) {
   const unsigned long long lim = 0xFFFF0000ull;  // 32 rows of a tensor must be addressable with 32-bit byte offsets
   const unsigned long long npairs = static_cast<unsigned long long>(nlayers) * d.Bt * d.H;
   const unsigned long long nbc = static_cast<unsigned long long>(nlayers) * d.Bt * d.G;
   const unsigned long long slots = static_cast<unsigned long long>(d.hpg) * (d.P / kCols);
+  const unsigned long long wgs = nbc * ((slots + kWaves - 1) / kWaves);
+  if (slots <= kWaves / 2 && wgs > kFullGrid && nsteps * slots < kMinWork && !(d.P == 32 && d.N == 64)) return false;
   return d.bf16 && nsteps >= kMinSteps && (d.N == 64 || d.N == 128) && d.P % kCols == 0 &&
-         npairs * d.P * 2 * kTok <= lim && nbc * d.N * 2 * kTok <= lim && npairs * 4 * kTok <= lim &&
-         nbc * ((slots + kWaves - 1) / kWaves) <= 0x7fffffffull;
+         npairs * d.P * 2 * kTok <= lim && nbc * d.N * 2 * kTok <= lim && npairs * 4 * kTok <= lim && wgs <= 0x7fffffffull;
 }
 
 hipError_t launch_decode_steps_mfma(int nsteps, int nlayers, const Dims &d, float *state, const void *x, const float *dt,

@@ -127,7 +127,7 @@ hipError_t launch_decode_steps(int nsteps, int nlayers, const Dims &d, float *st
                                void *y, hipStream_t stream);
 
 // Several steps as contractions over blocks of 32 steps (bf16 io); see ssd_decode_steps_mfma.hip.
-bool decode_steps_mfma_supported(int nsteps, int nlayers, const Dims &d);
+bool decode_steps_mfma_chosen(int nsteps, int nlayers, const Dims &d);
 hipError_t launch_decode_steps_mfma(int nsteps, int nlayers, const Dims &d, float *state, const void *x, const float *dt,
                                     const float *A, const void *B, const void *C, const float *D, void *y,
                                     hipStream_t stream);

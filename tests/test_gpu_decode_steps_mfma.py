@@ -151,3 +151,21 @@ def test_blocked_steps_with_values_whose_products_leave_fp32(ssd, where):
     assert torch.isfinite(got).all() and torch.isfinite(ref).all()
     assert ((got - ref).norm(dim=-1) <= 2.0 ** -8 * ref.norm(dim=-1)).all()
     assert ((sd - s1).double().flatten(3).norm(dim=-1) <= 1e-5 * s1.double().flatten(3).norm(dim=-1)).all()
+
+
+@pytest.mark.parametrize("S, H, P, N", [(9, 8, 32, 128), (21, 8, 32, 128), (10, 8, 64, 64)])
+def test_few_slices_per_group_stay_on_the_step_by_step_kernel(ssd, S, H, P, N):
+    """A B/C group per head, more workgroups than run side by side, few steps: half of the blocked kernel's waves would have
+    no slice.  The step-by-step kernel's state is that of single steps bit for bit."""
+    Ly, Bt = 12, 8
+    state, x, dt, A, B, C, D = make(S, Ly, Bt, H, P, N, H)
+    dev = [t.cuda() for t in (x, dt, A, B, C, D)]
+    sd, s1 = state.cuda(), state.cuda()
+    print("few slices per group", S, H, P, N, flush=True)
+    y = ssd.ssd_decode_steps_layers(sd, *dev)
+    for i in range(S):
+        ssd.ssd_decode_step_layers(s1, dev[0][i].clone(), dev[1][i].clone(), dev[2], dev[3][i].clone(), dev[4][i].clone(), dev[5])
+    torch.cuda.synchronize()
+    assert torch.equal(sd, s1)
+    y_ref, _ = ssd_oracle.decode_steps_layers(state, x, dt, A, B, C, D)
+    assert_close(y, y_ref, TOL["bf16"], "y")
