@@ -465,12 +465,14 @@ int f32_time_segments(const Dims &d, double *walk_us) {
   return best;
 }
 
-// Shapes the kernel takes, and among them those it is expected to win on.  It walks a sequence block by block
-// with one workgroup per (batch row, head, 32 columns, time segment), so its time is (rounds of 256
-// workgroups) x (the longest walk, see above); the generic fp32 kernels are chunk-parallel
-// over the whole chip, cost four launches and then time proportional to the work.  A long sequence with few
-// heads is theirs.  Both estimates are fits to a handful of timings on MI355X (microseconds); where they are
-// within a tenth of each other the MFMA kernel is taken.
+// Shapes the kernel takes, and among them those it is expected to win on.  Three families share fp32 io.  Prompts large
+// enough for three launches go to the split operands (split_f32_chosen, which asks before this and compares itself
+// with the faster of the other two); of the rest, this kernel walks a sequence block by block with one workgroup per
+// (batch row, head, 32 columns, time segment), so its time is (rounds of 256 workgroups) x (the longest walk, see
+// above); the generic fp32 kernels are chunk-parallel over the whole chip, cost four launches and then time
+// proportional to the work, and take what is left of long sequences with few heads as well as the shapes the others do not
+// know.  Both estimates are fits to a handful of timings on MI355X (microseconds); where they are within a tenth of
+// each other the MFMA kernel is taken.
 static double f32_mfma_us(const Dims &d) {
   double walk_us;
   f32_time_segments(d, &walk_us);
