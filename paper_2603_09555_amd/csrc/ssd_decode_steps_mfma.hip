@@ -210,18 +210,9 @@ __global__ __launch_bounds__(kThr, 2) void decode_steps_mfma_kernel(const StepsP
     }
     // ---- decays: lane r (both halves) = step s0 + r; steps beyond the last have step size zero ----
     const float dtv = s0 + r < p.nsteps ? dt_apply_biased(r_dt, dbias, p.dtx) : 0.f;
-    const float d = cut_decay(dtv * alog);
-    float ch = coarse_part(d), cl = d - ch, sfx = d;  // inclusive sums from the start (two parts) and from the end
-#pragma unroll
-    for (int off = 1; off < kTok; off <<= 1) {
-      const float up = __shfl_up(ch, off, kTok), ul = __shfl_up(cl, off, kTok), dn = __shfl_down(sfx, off, kTok);
-      ch += r >= off ? up : 0.f;
-      cl += r >= off ? ul : 0.f;
-      sfx += r + off < kTok ? dn : 0.f;
-    }
-    const float total = __shfl(sfx, 0, kTok);
-    float after = __shfl_down(sfx, 1, kTok);  // sum of the steps behind this one
-    after = r == kTok - 1 ? 0.f : after;
+    const float d = cut_decay(dtv * alog), dh = coarse_part(d);
+    const float ch = prefix32(dh), cl = prefix32(d - dh);  // from the start of the block, in two parts
+    const float after = suffix32(d), total = read_lane(after + d, 0);
     any_odd |= !(fabsf(dtv) < kDtLimit) || (seen & 0xffffu) >= kIoLimit || seen >= kIoLimit << 16;
     if (kg == 0) {
       s_ch[wave][r] = ch;
