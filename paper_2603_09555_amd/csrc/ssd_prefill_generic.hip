@@ -64,12 +64,14 @@ __global__ __launch_bounds__(64) void chunk_cumsum_kernel(const float *__restric
   const int lane = threadIdx.x;
   const float Ah = A[h];
   const int len = cv.len;
+  constexpr float kCut = kCutLog2 * 0.69314718f;
   float carry = 0.f;
   float *out = cs + cv.idx * L;
   for (int base = 0; base < len; base += 64) {
     const int l = base + lane;
     float v = 0.f;
     if (l < len) v = dt[(cv.tok + l) * H + h] * Ah;
+    v = v < kCut ? kCut : v;  // (see cut_decay; a NaN stays)
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
       const float up = __shfl_up(v, off, 64);

@@ -95,6 +95,7 @@ struct F32Params {
   int T, H, P, N, G, hpg;
   int tseg;  // time segments per sequence (>= 1), each a workgroup of its own
   DtXform dtx;
+  int dt_plain;  // the step sizes are used as given
 };
 
 // NT: 32-column tiles of the state (dstate <= 32 NT; columns beyond dstate are zero padding).
@@ -215,8 +216,11 @@ __global__ __launch_bounds__(kF32Threads) void prefill_f32_kernel(const F32Param
       for (int j = 0; j < 4; ++j) sXT[(c0 + j) * kRowT + row] = r_x[k][j];
     }
     if (wave == 0) {  // lane = token; tokens beyond the sequence have step size zero (state-neutral)
-      const float dtv = static_cast<uint32_t>(jb_staged * kTok + lane) < T ? dt_apply_branchless(r_dt, dbias, p.dtx) : 0.f;
-      const float cs = wave_prefix_sum(dtv * alog);
+      float dtv = r_dt;
+      if (!p.dt_plain) dtv = dt_apply_branchless(r_dt, dbias, p.dtx);  // (no load is outstanding that a branch would make wait)
+      dtv = static_cast<uint32_t>(jb_staged * kTok + lane) < T ? dtv : 0.f;
+      // (cut_decay, on the step size: the product joins the first sum)
+      const float cs = wave_prefix_sum((dtv * alog < kCutLog2 ? kCutLog2 * __builtin_amdgcn_rcpf(alog) : dtv) * alog);
       const float c63 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, cs), 63));
       sCs[lane] = cs;
       sDt[lane] = dtv;
@@ -520,6 +524,7 @@ hipError_t launch_prefill_mfma_f32(const Dims &d, const void *x, const float *dt
   p.G = d.G;
   p.hpg = d.hpg;
   p.dtx = d.dtx;
+  p.dt_plain = d.dtx.identity();
   p.tseg = f32_time_segments(d, nullptr);
   const dim3 grid(static_cast<unsigned>(d.Bt) * d.H * (d.P / kCols) * p.tseg), block(kF32Threads);
   const int nt = (d.N + 31) / 32;

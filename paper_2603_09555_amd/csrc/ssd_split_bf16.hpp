@@ -105,10 +105,9 @@ __device__ __forceinline__ f32x16 mfma6(const Op a[3], const Op b[3], f32x16 c) 
 __device__ __forceinline__ float exp2_fast(float v) { return __builtin_amdgcn_exp2f(v); }
 
 // The log2 decays of a block's steps, so that differences of their prefix sums -- the decay between two steps -- come
-// out right also behind a step that decays everything away.  A step is cut off at 2^-160, which is zero either way, and
-// taken apart into a multiple of 2^-8, whose sums over 32 steps are exact (at most 5120, 21 bits), and the rest, whose
-// sums stay below 2^-4 (error 2^-27).
-__device__ __forceinline__ float cut_decay(float d) { return d < -160.f ? -160.f : d; }  // (a NaN stays)
+// out right also behind steps that decay everything away.  A step is cut off (cut_decay) and taken apart into a multiple
+// of 2^-8, whose sums over 32 steps are exact (at most 5120, 21 bits), and the rest, whose sums stay below 2^-4 (error
+// 2^-27).
 __device__ __forceinline__ float coarse_part(float d) { return __builtin_rintf(d * 256.f) * 0.00390625f; }
 
 // Transposed LDS read (ds_read_b64_tr_b16).  Inside each group of 16 lanes, lane j names four consecutive
