@@ -62,6 +62,7 @@ struct SplitParams {
   int sub, sub_blocks;           // S = 1: workgroups that share the sequence, output blocks of each
   int slot0;                     // the first segment starts from its slot in y, not from h0 (which final_state aliases)
   DtXform dtx;
+  int dt_plain;                    // the step sizes are used as given
 };
 
 __host__ __device__ __forceinline__ int segment_begin(int s, int S, int nblocks) {
@@ -268,7 +269,9 @@ __global__ __launch_bounds__(kThr, 2) void split_f32_kernel(const SplitParams p)
     }
     // ---- decays: lane r (both halves) = token; tokens beyond the sequence have step size zero.  The decay from a
     //      token to the end of the block is summed from the end: the newest tokens weigh most ----
-    const float dtv = j * kTok + r < p.T ? dt_apply_branchless(r_dt, dbias, p.dtx) : 0.f;
+    float dtv = r_dt;
+    if (!p.dt_plain) dtv = dt_apply_branchless(r_dt, dbias, p.dtx);  // (no load is outstanding that a branch would make wait)
+    dtv = j * kTok + r < p.T ? dtv : 0.f;
     const float d = cut_decay(dtv * alog), after = suffix32(d), total = read_lane(after + d, 0);
     float ch = 0.f, cl = 0.f;
     if constexpr (kFull) {
@@ -619,6 +622,7 @@ hipError_t launch_prefill_split_f32(const Dims &d, const void *x, const float *d
   p.sub = pl.sub;
   p.sub_blocks = pl.sub_blocks;
   p.dtx = d.dtx;
+  p.dt_plain = d.dtx.identity();
   const size_t state_bytes = static_cast<size_t>(d.Bt) * d.H * d.P * d.N * sizeof(float);
   const char *const h = reinterpret_cast<const char *>(h0), *const f = reinterpret_cast<const char *>(final_state);
   const bool aliases = h0 != nullptr && h < f + state_bytes && f < h + state_bytes;
