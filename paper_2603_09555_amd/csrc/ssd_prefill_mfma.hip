@@ -2062,6 +2062,7 @@ int list_items(const Dims &d, const Layout &w, int seg_blocks) { return d.Bt + f
 // How a call is cut up: blocks per segment, segments per sequence (0 for a packed batch, where the
 // device-side tables hold them per sequence), pieces per segment of the states-only pass, and whether the
 // full scan sums the chain over state slots itself (ScanParams::fold).
+bool packed_uncut(const Dims &d, const SlicePlan &pl);
 SlicePlan plan_slice(const Dims &d, bool varlen, bool h0_aliases_final_state) {
   const Layout w = make_layout(d, varlen);
   Dims one = d;  // the segment length of a packed batch is chosen as for one sequence of all its tokens
@@ -2096,12 +2097,17 @@ SlicePlan plan_slice(const Dims &d, bool varlen, bool h0_aliases_final_state) {
       pl.segments = (w.NB + b - 1) / b;
     }
   }
-  if (varlen && pl.from_lengths) {
+  if (pl.from_lengths) {
     // (on the same 240 batches two heads never are 2.0 % slower on average, wherever the sequences alone fit 1.1 %: few
     // long ones would be cut too coarsely)
     const long groups2 = head_groups(d, 2);
     if (may_two && small_grid(d.Bt * groups2) && small_grid((w.NB - d.Bt) * groups2 / 4)) pl.heads = pl.state_heads = 2;
-  } else if (may_two) {  // (packed batch of one segment length: by the most entries that the lists can have)
+    if (packed_uncut(d, pl)) {
+      pl.from_lengths = false;
+      pl.seg_blocks = w.NB - d.Bt;
+    }
+  }
+  if (!pl.from_lengths && may_two) {  // (packed batch of one segment length: by the most entries that the lists can have)
     const long full = varlen ? full_items(d, w, pl.seg_blocks) : static_cast<long>(pl.segments - 1) * pl.parts;
     const long all = varlen ? list_items(d, w, pl.seg_blocks) : pl.segments;
     if (small_grid(all * seqs * head_groups(d, 2))) pl.heads = 2;
@@ -2134,6 +2140,24 @@ SegChoice segment_choice(const Dims &d, const SlicePlan &pl) {
   c.fill = static_cast<float>(groups) / kNumCUs;
   c.slices = static_cast<float>(d.H) * (d.P / kP);
   return c;
+}
+
+// Whether a short packed batch is left uncut, whatever its lengths: cutting it, or the chance of it, costs the launches of
+// the states pass and the chain (8 us), which is a quarter of such a call and more.  So it is where the worst mix -- one
+// sequence and a token for each of the others -- is at most a tenth slower uncut by the model.  Up to 20 blocks, where
+// the model is good to that: of 240 drawn batches 40, 31 to 43 us each, are 3 to 10 us faster for it and none is slower.
+bool packed_uncut(const Dims &d, const SlicePlan &pl) {
+  const int nblocks = (d.T + kBlk - 1) / kBlk;
+  if (nblocks > 20) return false;
+  const SegChoice c = segment_choice(d, pl);
+  const int blocks = nblocks + d.Bt - 1;
+  float best = 0.f, uncut = 0.f;
+  for (int k = 0; k < c.count; ++k) {
+    const int s = c.cand[k];
+    uncut = packed_cost(c, s, blocks, nblocks, d.Bt, d.Bt - 1 + (nblocks + s - 1) / s);  // (the last candidate: no cut)
+    if (k == 0 || uncut < best) best = uncut;
+  }
+  return uncut - 8.f <= 1.1f * best;
 }
 
 // The workgroups of a pass: `heads` head slices each, `segs` segments per sequence, `items` in all.

@@ -64,7 +64,7 @@ def test_rejected_boundaries_write_nothing(ssd, nseq):
     assert (y == 3.0).all() and (st == 5.0).all()
 
 
-@pytest.mark.parametrize("lens", [[4000] + 64 * [1], 40 * [1] + [2500, 0, 1300], [7000] + 1023 * [1], [64, 65, 129, 1000]],
+@pytest.mark.parametrize("lens", [[4000] + 64 * [1], 40 * [1] + [2500, 0, 1300], [7000] + 1023 * [1], [64, 65, 129, 2000]],
                          ids=lambda v: "%dx" % len(v))
 def test_one_long_prompt_among_short_rows(ssd, lens):
     """The segment length is chosen on the device from the lengths: several segments for the long ones."""

@@ -32,6 +32,13 @@ def test_sequences_that_fill_the_chip_are_not_cut(lengths, heads):
     assert p["items"] == len(lengths)
 
 
+@pytest.mark.parametrize("lengths, heads", [([70] * 11, 9), ([60] * 10, 24), ([600] + [5] * 9, 45)], ids=lambda v: str(v)[:20])
+def test_short_batches_are_not_cut_whatever_their_lengths(lengths, heads):
+    """... and launch neither the states pass nor the chain."""
+    p = plan(lengths, heads)
+    assert not p["chosen"] and p["items"] == len(lengths)
+
+
 def test_plans_stay_within_what_the_host_sized():
     """Over drawn batches: the choice is between the host's shortest length and all the tokens, the list is that of this
     length, and one sequence, a forced length and a batch that cannot be cut leave no choice."""
