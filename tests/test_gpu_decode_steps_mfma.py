@@ -169,3 +169,32 @@ def test_few_slices_per_group_stay_on_the_step_by_step_kernel(ssd, S, H, P, N):
     assert torch.equal(sd, s1)
     y_ref, _ = ssd_oracle.decode_steps_layers(state, x, dt, A, B, C, D)
     assert_close(y, y_ref, TOL["bf16"], "y")
+
+
+@pytest.mark.parametrize("raw", [False, True])
+@pytest.mark.parametrize("P, N, G", [(64, 128, 1), (32, 64, 2)])
+def test_blocked_steps_carry_the_state_in_fp32(ssd, raw, P, N, G):
+    """Products with bf16 values are exact and sums are fp32: the state is off by a few roundings of 2^-24, with the raw step
+    size (its bias has an axis of layers) also by the map's 2e-7 and the sum's with the bias.  Two parts instead of three
+    would leave 2^-16."""
+    S, Ly, Bt, H = 64, 3, 2, 4
+    state, x, dt, A, B, C, D = make(S, Ly, Bt, H, P, N, G, seed=93)
+    kw = {}
+    if raw:
+        g = torch.Generator().manual_seed(6)
+        dt, bias = 0.5 * torch.randn((S, Ly, Bt, H), generator=g), 0.1 * torch.randn((Ly, H), generator=g) - 4.6
+        kw = dict(dt_bias=bias.cuda(), dt_softplus=True, dt_limit=(1e-3, 1e-1))
+    sd = state.cuda()
+    ssd.ssd_decode_steps_layers(sd, *[t.cuda() for t in (x, dt, A, B, C, D)], **kw)
+    torch.cuda.synchronize()
+    if raw:
+        v = dt.double() + bias.double()[None, :, None, :]
+        dt = torch.nn.functional.softplus(v, threshold=1e9).clamp(1e-3, 1e-1)
+    h = state.double()
+    for s in range(S):   # the recurrence in 64 bits
+        Bs = B[s].double().repeat_interleave(H // G, dim=2)
+        h = torch.exp(dt[s].double() * A.double()[:, None, :])[..., None, None] * h \
+            + (dt[s].double()[..., None] * x[s].double())[..., None] * Bs[:, :, :, None, :]
+    err = float((sd.cpu().double() - h).norm() / h.norm())
+    print("  state off by %.2e" % err, flush=True)
+    assert err <= 5e-7
