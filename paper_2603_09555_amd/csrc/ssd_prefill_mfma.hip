@@ -833,7 +833,6 @@ __device__ __forceinline__ bool wg_coords_varlen(const ScanParams &p, bool last_
 }
 
 constexpr int kHeadsPerWg = 4;
-constexpr int kScanThreads = 2 * 64 * kHeadsPerWg;  // two waves per head, one per half of headdim
 constexpr int kGStride = kBlk + 8;
 
 // Waits until no vector memory operation of the wave is outstanding.  Used once, at the end of a
@@ -1461,6 +1460,7 @@ __device__ __forceinline__ void scan_walk(const ScanParams &p, const SeqView &sv
         Y[0] = mfma(ho, co[kk & 1][0], Y[0]);
         Y[1] = mfma(ho, co[kk & 1][1], Y[1]);
         constexpr int kPerGroup = kPieces / 5;
+        static_assert(kPerGroup * 5 == kPieces, "five groups stage all pieces");
         if (kk < 5) {
 #pragma unroll
           for (int k = 0; k < kPerGroup; ++k) stage_tile(kPerGroup * kk + k, buf ^ 1);
