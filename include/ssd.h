@@ -106,7 +106,12 @@ SSD_API size_t ssd_prefill_workspace_bytes(const ssd_shape *shape);
  *                      alias an input
  *  final_state         output (device), fp32 (batch, nheads, headdim, dstate)
  *  workspace           device scratch of at least ssd_prefill_workspace_bytes()
- *                      bytes, 256-byte aligned; contents are undefined afterwards
+ *                      bytes, 256-byte aligned; contents are undefined afterwards.
+ *                      Every kernel family may write all of it ("mfma_f32" of
+ *                      ssd_prefill_path too, which once left it alone): calls
+ *                      that may overlap in time -- on other streams, from other
+ *                      threads -- need one each.  y, too, may hold intermediate
+ *                      values until the call has completed
  *  seqlen need not be a multiple of chunk (the last chunk is short).
  *  Errors: SSD_ERR_NULL, _SHAPE, _DTYPE, _ALIGN, _WORKSPACE, _HIP.
  */
@@ -323,8 +328,11 @@ SSD_API ssd_status ssd_conv1d_step(int32_t batch, int32_t ksize, int32_t io_dtyp
  * Name of the kernel family ssd_prefill would use for this shape:
  * "mfma_bf16" (bf16 io: bf16 MFMA contractions over LDS-staged tiles, fp32
  * accumulation), "mfma_f32" (fp32 io, headdim a multiple of 32, dstate a multiple
- * of 8 up to 128: contractions of fp32 accuracy on the matrix pipe, on fp32 MFMA for
- * small prompts and on split bf16 operands for larger ones), "generic_f32" (plain fp32 vector kernels, any shape), or "invalid".
+ * of 8 up to 128: contractions on the matrix pipe with fp32 accumulation; small
+ * prompts on fp32 MFMA, in one launch; larger ones with every operand split into
+ * three bf16 parts, six products of which stand for an fp32 product and leave out
+ * at most 2^-24 of it, in up to three launches that use the workspace),
+ * "generic_f32" (plain fp32 vector kernels, any shape), or "invalid".
  * Host-only.
  */
 SSD_API const char *ssd_prefill_path(const ssd_shape *shape);

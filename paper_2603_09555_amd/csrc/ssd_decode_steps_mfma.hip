@@ -17,10 +17,10 @@
 // The step-by-step kernel (decode_steps_kernel) is bound by the vector ALU, three instructions per state element
 // and step.  Here a state element costs one split (11 instructions per two values) and its share of 3 + 3 matrix
 // instructions per 32 steps, and the call is bound by reading and writing the state once.
-// Measured, 64 layers x 80 heads x 64 x 128, us per call, step-by-step kernel / this one: 8 steps 93 / 75, 16 steps
-// 141 / 78, 64 steps 413 / 107 (423 MB that must move: 3.9 TB/s); batch 16: 8 steps 1230 / 1010, 16 steps 1904 / 1018
-// (5.4 GB and more); one layer: 64 steps 47.6 / 13.  Final state of 64 steps against 64 bits: 1.5e-7 / 8e-8.  Two waves
-// per SIMD: at three (168 registers) the spills cost more than the third wave gives (8 steps 96, 64 steps 133).
+// Measured, 64 layers x 80 heads x 64 x 128, us per call, step-by-step kernel / this one: 9 steps 89 / 68, 16 steps 133 / 72,
+// 64 steps 412 / 101 (423 MB that must move: 4.2 TB/s); batch 16: 16 steps 1895 / 975 (5.4 GB and more); one layer: 64
+// steps 47 / 10.7.  Final state of 64 steps against 64 bits: 1.5e-7 / 8e-8.  Two waves per SIMD: at three (168 registers)
+// the spills cost more than the third wave gives (64 steps 133).
 //
 // One wave per slice of 32 headdim columns x dstate, four slices of one B/C group per workgroup (they share the
 // staged B and C).  The state slice sits in MFMA accumulators: tile nt, element i of lane (r, kg) is state column

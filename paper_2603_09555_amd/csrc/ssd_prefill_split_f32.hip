@@ -26,13 +26,16 @@
 // columns.  A segment then has at least as many tokens as a state slice has 128-byte pieces.
 // With one segment only the full launch runs; `sub` workgroups may then share the sequence, each first carrying the
 // state over the blocks of the ones before it (a third of a block's work, no output).
-// Bound: issue.  A block of four slices takes 4.7 us alone on a CU, 6.4 with a second workgroup, of which the matrix
-// instructions are 1.6 (3840 cycles a wave); 1100 vector instructions a wave (the splits: 700) come between them.
-// Two waves per slice (half of dstate each, outputs summed through LDS) took 4.4 us alone but 9 for two; matrix and
-// vector instructions interleaved by hand or by scheduling groups 5.4 and more (spills).
+// Bound: issue.  A block of four slices takes 5.2 us where one workgroup has the chip, 7.3 with one per CU, 10.3 with two
+// each (dstate 128); the matrix instructions are 1.6 of it (3840 cycles a wave), about 1150 vector instructions a wave
+// (the splits: 700) come between them.  Two waves per slice (half of dstate each, outputs summed through LDS) were 6 %
+// faster alone and half as fast for two; matrix and vector instructions interleaved by hand or by scheduling groups 15 %
+// slower and more (spills).
 // Measured against the fp32 matrix instruction kernel (ssd_prefill_mfma_f32.hip), us: 2048 tokens x 24 heads x 64 x 128
-// 113 / 53 (13 us of it the chain and the gaps), 8 such prompts 502 / 195, 3 x 2428 x 20 196 / 93, 2 x 3593 x 11 x 64 x
-// 16 70 / 35, 4096 x 4 x 32 x 16 56 / 24; final state against 64 bits 1.7e-7 / 9.7e-8, y 2.6e-8 both.
+// 108.7 / 52.3 (13 of it the chain and the gaps), 8 such prompts 504 / 191, 3 x 2428 x 20 190 / 90, 2 x 3593 x 11 x 64 x
+// 16 71 / 42, 4096 x 4 x 32 x 16 (generic kernels before: 116 there) 37; final state against 64 bits 1.4e-7 / 9.5e-8, y
+// 2.6e-8 both.  Of it the checks for values out of range take 1 us of the first, the leading parts rounded instead of cut
+// off 0.7, the mask's sums in two parts 0.3.
 #include <type_traits>
 
 #include "ssd_split_bf16.hpp"
