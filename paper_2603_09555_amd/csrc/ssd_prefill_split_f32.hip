@@ -33,7 +33,7 @@
 // slower and more (spills).
 // Measured against the fp32 matrix instruction kernel (ssd_prefill_mfma_f32.hip), us: 2048 tokens x 24 heads x 64 x 128
 // 108.7 / 52.3 (13 of it the chain and the gaps), 8 such prompts 504 / 191, 3 x 2428 x 20 190 / 90, 2 x 3593 x 11 x 64 x
-// 16 71 / 42, 4096 x 4 x 32 x 16 (generic kernels before: 116 there) 37; final state against 64 bits 1.4e-7 / 9.5e-8, y
+// 16 70 / 43, 4096 x 4 x 32 x 16 55 / 37; final state against 64 bits 1.4e-7 / 9.5e-8, y
 // 2.6e-8 both.  Of it the checks for values out of range take 1 us of the first, the leading parts rounded instead of cut
 // off 0.7, the mask's sums in two parts 0.3.
 #include <type_traits>
