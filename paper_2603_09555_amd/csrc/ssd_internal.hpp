@@ -51,6 +51,10 @@ __device__ __forceinline__ float dt_apply_branchless(float v, float bias, const 
 // behind.  (A NaN stays.)
 constexpr float kCutLog2 = -160.f;
 __device__ __forceinline__ float cut_decay(float d) { return d < kCutLog2 ? kCutLog2 : d; }
+// The same on the step size, whose product with alog = A log2(e) may then join the first sum (one rounding less).
+__device__ __forceinline__ float cut_step(float dt, float alog) {
+  return dt * alog < kCutLog2 ? kCutLog2 * __builtin_amdgcn_rcpf(alog) : dt;
+}
 
 // Validated problem dimensions (host side).
 struct Dims {

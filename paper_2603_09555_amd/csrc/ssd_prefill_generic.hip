@@ -70,8 +70,8 @@ __global__ __launch_bounds__(64) void chunk_cumsum_kernel(const float *__restric
   for (int base = 0; base < len; base += 64) {
     const int l = base + lane;
     float v = 0.f;
-    if (l < len) v = dt[(cv.tok + l) * H + h] * Ah;
-    v = v < kCut ? kCut : v;  // (see cut_decay; a NaN stays)
+    if (l < len) v = dt[(cv.tok + l) * H + h];
+    v = (v * Ah < kCut ? kCut * __builtin_amdgcn_rcpf(Ah) : v) * Ah;  // (see cut_step)
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
       const float up = __shfl_up(v, off, 64);

@@ -617,9 +617,9 @@ __device__ __forceinline__ void block_cumsum_block(float (*tile)[kCumHeads + 1],
     live[k] = h0 + hh < H;
     ah[k] = live[k] ? a_head[k] * kLog2e : 0.f;
     dtv[k] = tile[lane][hh];
-    v[k] = cut_decay(dtv[k] * ah[k]);
+    v[k] = cut_step(dtv[k], ah[k]) * ah[k];
     // prefix sum at token 31 of the next block: the sum of its first 32 terms
-    nx[k] = lane < kBlk / 2 ? cut_decay(tile[kBlk + lane][hh] * ah[k]) : 0.f;
+    nx[k] = lane < kBlk / 2 ? cut_step(tile[kBlk + lane][hh], ah[k]) * ah[k] : 0.f;
   }
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
@@ -1407,7 +1407,7 @@ __device__ __forceinline__ void scan_walk(const ScanParams &p, const SeqView &sv
       if constexpr (kSteep) {
         const float alog = factor_ptr(jb)[3];
         dt_t = kg ? rowf1 : rowf0;
-        cs_t = cut_decay(dt_t * alog);
+        cs_t = cut_step(dt_t, alog) * alog;
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
           const float up = __shfl_up(cs_t, off, 64);

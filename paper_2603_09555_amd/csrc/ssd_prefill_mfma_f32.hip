@@ -219,8 +219,7 @@ __global__ __launch_bounds__(kF32Threads) void prefill_f32_kernel(const F32Param
       float dtv = r_dt;
       if (!p.dt_plain) dtv = dt_apply_branchless(r_dt, dbias, p.dtx);  // (no load is outstanding that a branch would make wait)
       dtv = static_cast<uint32_t>(jb_staged * kTok + lane) < T ? dtv : 0.f;
-      // (cut_decay, on the step size: the product joins the first sum)
-      const float cs = wave_prefix_sum((dtv * alog < kCutLog2 ? kCutLog2 * __builtin_amdgcn_rcpf(alog) : dtv) * alog);
+      const float cs = wave_prefix_sum(cut_step(dtv, alog) * alog);
       const float c63 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, cs), 63));
       sCs[lane] = cs;
       sDt[lane] = dtv;
