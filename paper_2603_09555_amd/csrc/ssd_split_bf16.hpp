@@ -68,8 +68,8 @@ __device__ __forceinline__ uint32_t pack2(float lo, float hi) {  // two fp32 -> 
 // is left out has no preferred sign and is at most 2^-24 of the product, the rounding of an fp32 product itself (with a
 // truncated leading part up to 2^-22).  A state of one token, which is one product per element, is then 2.4 units of
 // 2^-24 off at most (4.3), 0.58 rms (0.69); 1.0 and 0.42 from the fp32 matrix instruction.  Sums of many products are
-// no further off than with that instruction, since they are rounded less often: 0.85 of its error in the final state of
-// 23 drawn prompts, 1.00 in y.  The two products left out cost 2 us more of 52 (2048 tokens x 24 heads) and change none of
+// no further off than with that instruction, since they are rounded less often: 0.84 of its error in the final state of
+// 21 drawn prompts, 1.00 in y.  The two products left out cost 2 us more of 52 (2048 tokens x 24 heads) and change none of
 // these sums.  (Values of 2^30 and more don't come here; see out_of_range.)  W = values, a multiple of 2; part p of
 // values 2k, 2k+1 goes to out[p][k].
 template <int W>
