@@ -83,3 +83,37 @@ def test_one_long_prompt_among_short_rows(ssd, lens):
     y_ref, st_ref = ssd_oracle.prefill_varlen(pk["x"], pk["dt"], pk["A"], pk["B"], pk["C"], pk["D"], cu, h0=h0)
     assert_close(y, y_ref, TOL["bf16"], "y")
     assert_close(st, st_ref, TOL["bf16"], "final state")
+
+
+def test_captured_call_follows_the_lengths(ssd):
+    """The lengths and the segment length they lead to are the device's: a captured call is right for whatever boundaries its
+    tensor holds at a replay, with eager work in between."""
+    T, H, nseq = 3000, 4, 12
+    dev = {k: (v[0] if k in ("x", "dt", "B", "C") else v).cuda()
+           for k, v in inputs.make_prefill_inputs(inputs.SSDConfig("t", 1, T, H, 64, 128, 1, 64, "bf16"), seed=15).items()}
+    args = [dev[k] for k in ("x", "dt", "A", "B", "C", "D")]
+    lens = [[250] * 12, [T - 11] + [1] * 11, [0, 1400, 1, 700, 0, 3, 64, 65, 128, 500, 100, 39]]
+    assert len({ssd.varlen_plan(v, H, 64, 128, 1, 64)["items"] for v in lens}) == 3
+    cu = torch.zeros(nseq + 1, dtype=torch.int32, device="cuda")
+
+    def boundaries(v):
+        cu.copy_(torch.from_numpy(np.concatenate([[0], np.cumsum(v)]).astype(np.int32)))
+
+    boundaries(lens[0])
+    size = int(ssd.raw().ssd_prefill_varlen_workspace_bytes(ssd.make_shape(nseq, T, H, 64, 128, 1, 64, torch.bfloat16)))
+    ws = torch.empty((size,), dtype=torch.uint8, device="cuda")
+    y, st = torch.empty_like(dev["x"]), torch.empty((nseq, H, 64, 128), device="cuda")
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            ssd.ssd_prefill_varlen(*args, cu, 64, y=y, final_state=st, workspace=ws)
+    torch.cuda.current_stream().wait_stream(side)
+    for i in (0, 1, 2, 1, 0):
+        boundaries(lens[i])
+        y_ref, st_ref = ssd.ssd_prefill_varlen(*args, cu, 64)
+        y.fill_(7.0)
+        st.fill_(7.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, y_ref) and torch.equal(st, st_ref), i
