@@ -38,8 +38,10 @@ typedef enum {
                                  pieces, is at most k long runs no separate pass over those states -- every
                                  segment of the full scan sums the slots before it as it loads them; 0: never.
                                  Default 3.  Reset with ssd_testing_reset_knobs */
-  SSD_KNOB_SCAN_HEADS = 9      /* 2 / 4: head slices per workgroup in both passes of the bf16 MFMA prefill; any other
+  SSD_KNOB_SCAN_HEADS = 9,     /* 2 / 4: head slices per workgroup in both passes of the bf16 MFMA prefill; any other
                                  value: library's choice */
+  SSD_KNOB_CHUNK = 10          /* bf16 prefill of a plain batch by the chunk kernels: 1 wherever they can run, 2 never; 0:
+                                 library's choice */
 } ssd_knob;
 
 /* Sets one knob.  Errors: SSD_ERR_SHAPE for an unknown knob. */
@@ -49,7 +51,7 @@ SSD_API ssd_status ssd_testing_set_knob(int32_t knob, int32_t value);
 SSD_API void ssd_testing_reset_knobs(void);
 
 /* How ssd_prefill would run a shape under the current knobs (host arithmetic only: no GPU call, nothing
- * launched).  plan[0]: kernel family, 0 generic fp32 kernels, 1 bf16 MFMA, 2 fp32 MFMA.  For the bf16
+ * launched), if not on the chunk kernels (ssd_testing_prefill_chunks).  plan[0]: kernel family, 0 generic fp32 kernels, 1 bf16 MFMA, 2 fp32 MFMA.  For the bf16
  * MFMA family (per state slice of 128 columns): plan[1] 64-token blocks per segment, plan[2] segments
  * per sequence, plan[3] pieces per segment in the states-only pass, plan[4] 1 if the full scan sums the
  * chain over segment states itself and no separate pass runs (h0_aliases_final_state != 0: as for a call
@@ -60,6 +62,10 @@ SSD_API void ssd_testing_reset_knobs(void);
  * Errors: SSD_ERR_NULL; the shape errors of ssd_prefill. */
 SSD_API ssd_status ssd_testing_prefill_plan(const ssd_shape *shape, int32_t h0_aliases_final_state,
                                             int32_t plan[8]);
+
+/* Chunks per sequence if ssd_prefill would run a shape on the bf16 chunk kernels (a workgroup per 64 headdim columns and
+ * chunk of 256 tokens) under the current knobs, else 0: it then runs as ssd_testing_prefill_plan says. */
+SSD_API int32_t ssd_testing_prefill_chunks(const ssd_shape *shape, int32_t h0_aliases_final_state);
 
 /* How ssd_prefill_varlen would cut up a packed batch of these boundaries (a HOST array here) under the current knobs, on
  * the bf16 MFMA kernels.  plan[1] 64-token blocks per segment, which the device chooses from the boundaries, plan[2]

@@ -96,7 +96,9 @@ ssd_status prefill_impl(const ssd_shape *shape, const void *x, const float *dt, 
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   if (trace) (void)hipEventRecord(trace->ev[0], stream);
   const hipError_t e =
-      use_mfma(d)
+      use_mfma(d) && ssd::chunk_chosen(d, need, h0, final_state)
+          ? ssd::launch_prefill_chunk(d, x, dt, A, B, C, D, h0, y, final_state, workspace, stream, trace)
+      : use_mfma(d)
           ? ssd::launch_prefill_mfma(d, x, dt, A, B, C, D, h0, y, final_state, workspace, stream, trace)
       : use_split_f32(d)
           ? ssd::launch_prefill_split_f32(d, x, dt, A, B, C, D, h0, y, final_state, workspace, stream, trace)
@@ -154,6 +156,12 @@ ssd_status ssd_testing_prefill_plan(const ssd_shape *shape, int32_t h0_aliases_f
     plan[5] = ssd::mfma_f32_time_segments(d);
   }
   return SSD_OK;
+}
+
+int32_t ssd_testing_prefill_chunks(const ssd_shape *shape, int32_t h0_aliases_final_state) {
+  Dims d;
+  if (shape == nullptr || make_dims(shape, false, &d) != SSD_OK || !use_mfma(d)) return 0;
+  return ssd::chunk_chosen(d, workspace_bytes(d), h0_aliases_final_state != 0) ? ssd::chunk_count(d) : 0;
 }
 
 ssd_status ssd_prefill(const ssd_shape *shape, const void *x, const float *dt, const float *A,
@@ -423,6 +431,7 @@ ssd_status ssd_testing_set_knob(int32_t knob, int32_t value) {
     case SSD_KNOB_FORCE_MFMA_F32: k.force_mfma_f32 = value > 0 ? 1 : 0; return SSD_OK;
     case SSD_KNOB_F32_SEGMENTS: k.f32_segments = value > 0 ? value : 0; return SSD_OK;
     case SSD_KNOB_FOLD_MAX_SLOTS: k.fold_max_slots = value > 0 ? value : 0; return SSD_OK;
+    case SSD_KNOB_CHUNK: k.chunk = value == 1 || value == 2 ? value : 0; return SSD_OK;
     case SSD_KNOB_SCAN_HEADS: k.scan_heads = value == 2 || value == 4 ? value : 0; return SSD_OK;
     default: return SSD_ERR_SHAPE;
   }

@@ -123,6 +123,7 @@ struct Knobs {
   int force_mfma_f32 = 0;  // 1: fp32 io takes the fp32 MFMA kernel whenever the shape is eligible
   int f32_segments = 0;    // > 0: time segments per sequence in the fp32 MFMA kernel
   int scan_heads = 0;      // 2 / 4: head slices per workgroup in the bf16 scan; 0: library's choice
+  int chunk = 0;           // bf16 prefill by chunk kernels: 1 wherever they can run, 2 never; 0: library's choice
   int fold_max_slots = 3;  // most state slots a segment sums by itself instead of a pass over segment states (0: never)
 };
 Knobs &knobs();
@@ -166,6 +167,14 @@ hipError_t launch_prefill_mfma(const Dims &d, const void *x, const float *dt, co
                                const void *B, const void *C, const float *D, const float *h0,
                                void *y, float *final_state, void *workspace, hipStream_t stream,
                                KernelTrace *trace = nullptr);
+
+// Small bf16 prompts, a workgroup per (64-column slice, chunk of 256 tokens); see ssd_prefill_chunk.hip.
+int chunk_count(const Dims &d);
+bool chunk_chosen(const Dims &d, size_t workspace_bytes, bool h0_aliases_final_state);
+bool chunk_chosen(const Dims &d, size_t workspace_bytes, const float *h0, const float *final_state);
+hipError_t launch_prefill_chunk(const Dims &d, const void *x, const float *dt, const float *A, const void *B, const void *C,
+                                const float *D, const float *h0, void *y, float *final_state, void *workspace,
+                                hipStream_t stream, KernelTrace *trace = nullptr);
 
 // fp32 io on fp32 MFMA (one launch, no workspace); see ssd_prefill_mfma_f32.hip.
 bool mfma_f32_supported(const Dims &d, bool whenever_eligible);  // false: only where it is expected to win

@@ -23,7 +23,8 @@ EXPORTS = ["ssd_prefill_workspace_bytes", "ssd_prefill", "ssd_prefill_static", "
            "ssd_conv1d_prefill", "ssd_conv1d_step", "ssd_prefill_dt", "ssd_prefill_varlen_dt",
            "ssd_decode_step_layers_dt", "ssd_decode_steps_layers_dt",
            "ssd_prefill_path", "ssd_status_string", "ssd_version",
-           "ssd_testing_set_knob", "ssd_testing_reset_knobs", "ssd_testing_prefill_plan", "ssd_testing_varlen_plan"]
+           "ssd_testing_set_knob", "ssd_testing_reset_knobs", "ssd_testing_prefill_plan", "ssd_testing_varlen_plan",
+           "ssd_testing_prefill_chunks"]
 
 
 class ssd_shape(ctypes.Structure):
@@ -64,6 +65,8 @@ _lib.ssd_testing_reset_knobs.restype = None
 _lib.ssd_testing_reset_knobs.argtypes = []
 _lib.ssd_testing_prefill_plan.restype = ctypes.c_int
 _lib.ssd_testing_prefill_plan.argtypes = [ctypes.POINTER(ssd_shape), ctypes.c_int32, ctypes.POINTER(ctypes.c_int32)]
+_lib.ssd_testing_prefill_chunks.restype = ctypes.c_int32
+_lib.ssd_testing_prefill_chunks.argtypes = [ctypes.POINTER(ssd_shape), ctypes.c_int32]
 _lib.ssd_testing_varlen_plan.restype = ctypes.c_int
 _lib.ssd_testing_varlen_plan.argtypes = [ctypes.POINTER(ssd_shape), ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32)]
 _lib.ssd_decode_step.restype = ctypes.c_int
@@ -384,7 +387,7 @@ def ssd_conv1d_step(conv_state, u, weight, bias=None, split=None, activation="si
 
 
 KNOBS = {"force_generic": 0, "seg_chunks": 1, "seg_blocks": 2, "seg_parts": 3, "y_stream": 4, "decode_stream": 5,
-         "force_mfma_f32": 6, "f32_segments": 7, "fold_max_slots": 8, "scan_heads": 9}
+         "force_mfma_f32": 6, "f32_segments": 7, "fold_max_slots": 8, "scan_heads": 9, "chunk": 10}
 
 
 def set_knob(name: str, value: int) -> None:
@@ -408,6 +411,12 @@ def prefill_plan(shape, h0_aliases_final_state: bool = False) -> dict:
         raise SSDError(st, "ssd_testing_prefill_plan")
     return dict(path=("generic_f32", "mfma_bf16", "mfma_f32")[out[0]], seg_blocks=out[1], segments=out[2], parts=out[3],
                 fold=bool(out[4]), f32_segments=out[5])
+
+
+def prefill_chunks(shape, h0_aliases_final_state: bool = False) -> int:
+    """``ssd_testing_prefill_chunks`` (include/ssd_testing.h): chunks per sequence on the bf16 chunk kernels, 0 if
+    ``ssd_prefill`` would not run ``shape`` on them."""
+    return int(_lib.ssd_testing_prefill_chunks(ctypes.byref(shape), int(bool(h0_aliases_final_state))))
 
 
 def varlen_plan(lengths, nheads, headdim, dstate, ngroups, chunk, io_dtype=torch.bfloat16) -> dict:

@@ -1,0 +1,108 @@
+"""bf16 prefill on the chunk kernels (a workgroup per 64 headdim columns and chunk of 256 tokens) against the oracle, at
+the edges of their tiles of 32 tokens, their chunks and the numbers of states folded at a time."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ssd_oracle
+from paper_2603_09555_amd import inputs
+from parity import TOL, assert_close
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ssd():
+    from paper_2603_09555_amd import ssd
+    yield ssd
+    ssd.reset_knobs()
+
+
+@pytest.fixture(autouse=True)
+def _library_choices_restored(ssd):
+    ssd.reset_knobs()
+    yield
+    ssd.reset_knobs()
+
+
+# batch, tokens, heads, headdim, dstate, groups, chunk argument; initial state; raw step sizes; steps that decay everything
+CASES = [((1, 1, 1, 64, 128, 1, 64), False, False, False), ((2, 31, 3, 64, 8, 1, 64), True, False, False),
+         ((1, 33, 2, 128, 120, 2, 64), False, True, False), ((1, 255, 5, 64, 128, 1, 256), True, True, True),
+         ((3, 256, 2, 64, 64, 1, 100), True, False, False), ((1, 257, 3, 64, 128, 3, 64), True, True, False),
+         ((2, 300, 4, 64, 72, 1, 64), False, False, True), ((1, 512, 1, 192, 128, 1, 64), True, False, False),
+         ((1, 1025, 2, 64, 128, 1, 64), True, False, False), ((1, 1500, 3, 64, 128, 1, 256), False, True, True),
+         ((1, 2100, 1, 64, 40, 1, 64), True, True, False), ((1, 16384, 1, 64, 128, 1, 64), True, False, False)]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c[0])) + "-%d%d%d" % c[1:])
+def test_chunk_kernels_match_oracle(ssd, case):
+    dims, with_h0, raw, steep = case
+    cfg = inputs.SSDConfig("t", *dims, "bf16")
+    inp = inputs.make_prefill_inputs(cfg, seed=41)
+    rng = np.random.default_rng(3)
+    if steep:   # (decays up to e^-60 between neighbours, and behind them ordinary tokens)
+        inp["dt"] = inp["dt"] * torch.from_numpy(rng.choice([1.0, 40.0], inp["dt"].shape)).float()
+    h0 = 0.1 * inputs.make_state(cfg, seed=41) if with_h0 else None
+    kw, dt = {}, inp["dt"]
+    if raw:
+        bias = torch.from_numpy(rng.normal(-4.0, 0.3, cfg.nheads)).float()
+        inp["dt"] = torch.from_numpy(rng.normal(0.0, 2.0, inp["dt"].shape)).float()
+        kw = dict(dt_bias=bias.cuda(), dt_softplus=True, dt_limit=(1e-3, 0.5))
+        dt = ssd_oracle.dt_transform(inp["dt"], bias, True, (1e-3, 0.5))
+    ssd.set_knob("chunk", 1)
+    sh = ssd.make_shape(*dims, torch.bfloat16)
+    assert ssd.prefill_chunks(sh) == (dims[1] + 255) // 256
+    print("chunk kernels", case, flush=True)
+    dev = {k: v.cuda() for k, v in inp.items()}
+    args = [dev[k] for k in ("x", "dt", "A", "B", "C", "D")]
+    y, st = ssd.ssd_prefill(*args, cfg.chunk, h0=None if h0 is None else h0.cuda(), **kw)
+    torch.cuda.synchronize()
+    y_ref, st_ref = ssd_oracle.prefill(inp["x"], dt, inp["A"], inp["B"], inp["C"], inp["D"], h0=h0)
+    assert_close(y, y_ref, TOL["bf16"], "y")
+    assert_close(st, st_ref, TOL["bf16"], "final state")
+    if h0 is not None:   # the state updated in place: the same bits
+        if ssd.prefill_chunks(sh, True):
+            both = h0.cuda()
+            y2, st2 = ssd.ssd_prefill(*args, cfg.chunk, h0=both, final_state=both, **kw)
+            torch.cuda.synchronize()
+            assert torch.equal(y2, y) and torch.equal(st2, st)
+
+
+def test_where_the_chunk_kernels_are_taken(ssd):
+    """Where the launch is about one round of the chip; knobs of the scan kernels ask for those."""
+    shape = lambda *d: ssd.make_shape(*d, 128, 1, 256, torch.bfloat16)   # noqa: E731
+    assert ssd.prefill_chunks(shape(1, 2048, 24, 64)) == 8
+    assert ssd.prefill_chunks(shape(2, 250, 128, 64)) == 1 and ssd.prefill_chunks(shape(2, 250, 129, 64)) == 0
+    assert ssd.prefill_chunks(shape(1, 512, 106, 64)) == 2 and ssd.prefill_chunks(shape(1, 512, 107, 64)) == 0
+    assert ssd.prefill_chunks(shape(1, 16384, 80, 64)) == 0
+    assert ssd.prefill_chunks(ssd.make_shape(1, 2048, 24, 64, 136, 1, 256, torch.bfloat16)) == 0   # two state slices
+    for knob, value in (("seg_blocks", 2), ("seg_chunks", 1), ("scan_heads", 4), ("y_stream", 0), ("fold_max_slots", 0),
+                        ("force_generic", 1), ("chunk", 2)):
+        ssd.reset_knobs()
+        ssd.set_knob(knob, value)
+        assert ssd.prefill_chunks(shape(1, 2048, 24, 64)) == 0, knob
+
+
+def test_chunk_kernels_replayed_from_a_hip_graph(ssd):
+    """Two launches and a hand-over through the workspace: every replay follows the inputs it finds."""
+    for dims in ((2, 600, 4, 64, 128, 1, 256), (2, 200, 4, 64, 128, 1, 256)):
+        cfg = inputs.SSDConfig("t", *dims, "bf16")
+        a, b = [{k: v.cuda() for k, v in inputs.make_prefill_inputs(cfg, seed=s).items()} for s in (1, 2)]
+        sh = ssd.make_shape(*dims, torch.bfloat16)
+        assert ssd.prefill_chunks(sh) > 0
+        buf = {k: v.clone() for k, v in a.items()}
+        y, st = torch.empty_like(buf["x"]), torch.empty((2, 4, 64, 128), device="cuda")
+        ws = torch.empty((ssd.prefill_workspace_bytes(sh),), dtype=torch.uint8, device="cuda")
+        call = lambda d, **kw: ssd.ssd_prefill(*[d[k] for k in ("x", "dt", "A", "B", "C", "D")], cfg.chunk, **kw)   # noqa: E731
+        want = [[t.clone() for t in call(d)] for d in (a, b)]
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            call(buf, y=y, final_state=st, workspace=ws)
+        for i in range(5):
+            for k in buf:
+                buf[k].copy_((a, b)[i & 1][k])
+            ws.fill_(255)   # (nothing is left over from the replay before)
+            g.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(y, want[i & 1][0]) and torch.equal(st, want[i & 1][1]), (dims, i)
