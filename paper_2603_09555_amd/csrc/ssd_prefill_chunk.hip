@@ -3,7 +3,7 @@
 //
 // With cs_l the inclusive prefix sum of dt*A inside the chunk and S_c the state entering chunk c (Alg. 1; Eq. 3):
 //     chunk_states   L_c = sum_s dt_s exp(cs_end - cs_s) x_s (x) B_s          every chunk's own contribution
-//     chunk_outputs  S_c = sum_k<c exp(decay of the chunks between) L_k       summed as the states are loaded
+//     chunk_outputs  S_c = exp(decay of chunk c-1) S_c-1 + L_c-1             summed from S_0 on as the states are loaded
 //                    y_l = exp(cs_l) C_l . S_c + sum_s<=l (C_l . B_s) dt_s exp(cs_l - cs_s) x_s + D x_l
 // The second is the quadratic form of the chunk on tiles of 32 x 32 tokens, eight rows of tiles for eight waves; waves w
 // and w + 4, which share a SIMD, take rows w and 7 - w, nine tiles in all.  The scores never leave the registers: a tile
@@ -255,10 +255,10 @@ __device__ __forceinline__ void chunk_outputs(const ChunkParams &p, const Item &
   u32x4 xr[4];  // the wave's own rows again, for the skip term
 #pragma unroll
   for (int k = 0; k < 4; ++k) xr[k] = buf_load16(rx, (kTile * tt + (lane >> 3) + 8 * k) * xrow + it.h * (kP * 2) + 16 * (lane & 7));
-  // the states of the chunks before, from the nearest back: one now, the others kAhead at a time; the first chunk starts from h0
-  // (or its copy, where final_state takes h0's place)
+  // the states of the chunks before, oldest first: one now, the others kAhead at a time; the first chunk starts from h0 (or its
+  // copy, where final_state takes h0's place)
   const bool from_h0 = (kSingle || it.c == 0) && p.h0 != nullptr && !(!kSingle && p.keep_h0);
-  const int newest = !kSingle && it.c > 0 ? it.c - 1 : p.h0 == nullptr ? -1 : from_h0 ? 0 : p.chunks, oldest = !kSingle && it.c > 0 ? 0 : newest;
+  const int newest = !kSingle && it.c > 0 ? it.c - 1 : p.h0 == nullptr ? -1 : from_h0 ? 0 : p.chunks, oldest = !kSingle && it.c > 0 ? 0 : max(newest, 0);
   // (piece tid + 256 i of a state: headdim row 32 (i & 1) + r, state columns 32 wave + 8 (i / 2) + 4 kg ..)
   constexpr int kOwn = kSlot / 4 / (kThr / 2);
   const uint32_t vs = static_cast<uint32_t>(tid) * 16;
@@ -266,7 +266,7 @@ __device__ __forceinline__ void chunk_outputs(const ChunkParams &p, const Item &
   auto request = [&](int k, u32x4 raw[kOwn]) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < kOwn; ++i)
-      raw[i] = buf_load16(rs, k >= oldest && newest >= 0 ? static_cast<uint32_t>(k) * (kSlot * 4) + i * (kThr / 2 * 16) + vs : kNowhere);
+      raw[i] = buf_load16(rs, k <= newest ? static_cast<uint32_t>(k) * (kSlot * 4) + i * (kThr / 2 * 16) + vs : kNowhere);
   };
   u32x4 first[kOwn];
   if (folds) {
@@ -278,37 +278,30 @@ __device__ __forceinline__ void chunk_outputs(const ChunkParams &p, const Item &
         first[i] = buf_load16(rh, n0 < p.N ? ((32 * (i & 1) + r) * p.N + n0) * 4u : kNowhere);
       }
     } else {
-      request(newest, first);
+      request(oldest, first);
     }
   }
 
-  // ---- the entering state: lane k holds the weight of chunk k, the decay of the chunks between it and this one ----
-  float between = __shfl_down(chunk_decay, 1, 64);
-  between = lane < 63 ? between : 0.f;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const float down = __shfl_down(between, off, 64);
-    between += lane + off < 64 ? down : 0.f;
-  }
-  const float weight = !kSingle && it.c > 0 ? exp2_fast(between) : 1.f;
-  f32x4 S[kOwn] = {};
-  auto add = [&](int k, const u32x4 raw[kOwn]) __attribute__((always_inline)) {
-    const float wk = k >= oldest ? read_lane(weight, it.c > 0 ? max(k, 0) : 0) : 0.f;
-#pragma unroll
-    for (int i = 0; i < kOwn; ++i) {
-      const f32x4 v = __builtin_bit_cast(f32x4, raw[i]);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) S[i][e] = fmaf(wk, v[e], S[i][e]);
-    }
-  };
+  // ---- the entering state; lane k holds the decay over chunk k ----
+  const float factor = exp2_fast(chunk_decay);
+  f32x4 S[kOwn];
   auto fold = [&]() __attribute__((always_inline)) {
-    add(newest, first);
-    for (int k0 = newest - 1; k0 >= oldest; k0 -= kAhead) {
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) S[i] = __builtin_bit_cast(f32x4, first[i]);
+    for (int k0 = oldest + 1; k0 <= newest; k0 += kAhead) {
       u32x4 raw[kAhead][kOwn];
 #pragma unroll
-      for (int k = 0; k < kAhead; ++k) request(k0 - k, raw[k]);
+      for (int k = 0; k < kAhead; ++k) request(k0 + k, raw[k]);
 #pragma unroll
-      for (int k = 0; k < kAhead; ++k) add(k0 - k, raw[k]);
+      for (int k = 0; k < kAhead; ++k) {
+        const float e = k0 + k <= newest ? read_lane(factor, min(k0 + k, newest)) : 1.f;  // (a state beyond: zero)
+#pragma unroll
+        for (int i = 0; i < kOwn; ++i) {
+          const f32x4 v = __builtin_bit_cast(f32x4, raw[k][i]);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) S[i][q] = fmaf(e, S[i][q], v[q]);
+        }
+      }
     }
   };
   if (!kSingle && it.c == p.chunks) {  // the final state
