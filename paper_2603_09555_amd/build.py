@@ -1,8 +1,9 @@
-"""Compile the HIP sources under ``csrc/`` (in-tree, gfx950 only) into two shared libraries:
+"""Compile the HIP sources under ``csrc/`` (in-tree, gfx950 only) into two shared libraries, and the Python binding:
 
 * ``libssd_hip.so``      the product: every source directly under ``csrc/``;
 * ``libssd_measure.so``  the same objects plus ``csrc/measure/`` (per-kernel timing of a prefill, peak
-  probes): calls that create events and wait, kept out of the product library.
+  probes): calls that create events and wait, kept out of the product library;
+* ``_ssd_binding.so``    the native marshalling of ``ssd.py`` (``csrc/binding/``, host code, against torch's C++ headers).
 
 ``hipcc`` cross-compiles without a GPU.  Every source is compiled to an object once and the objects are
 linked twice.  Packed-fp32 instruction selection is disabled (``-Xclang -target-feature -Xclang
@@ -15,6 +16,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
@@ -23,6 +25,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libssd_hip.so")
 MEASURE_LIB = os.path.join(HERE, "libssd_measure.so")
+BINDING = os.path.join(HERE, "_ssd_binding.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
@@ -39,12 +42,34 @@ def measure_sources():
     return sorted(glob.glob(os.path.join(CSRC, "measure", "*.hip")))
 
 
+def binding_sources():
+    return sorted(glob.glob(os.path.join(CSRC, "binding", "*.cpp")))
+
+
+def build_binding(verbose: bool = False) -> None:
+    import torch
+    home = os.path.dirname(torch.__file__)
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"))))
+    includes = [INCLUDE, os.path.join(home, "include"), os.path.join(home, "include", "torch", "csrc", "api", "include"),
+                os.path.join(rocm, "include"), "/opt/rocm/include", sysconfig.get_path("include")]
+    tmp = BINDING + ".tmp%d" % os.getpid()
+    lib = os.path.join(home, "lib")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1",
+           "-DUSE_ROCM=1", "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)]
+    cmd += [a for i in includes for a in ("-isystem", i)] + binding_sources() + ["-o", tmp, "-L" + lib]
+    cmd += ["-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10_hip", "-lc10", "-Wl,-rpath," + lib]
+    if verbose:
+        print(" ".join(cmd), file=sys.stderr)
+    subprocess.run(cmd, check=True)
+    os.replace(tmp, BINDING)
+
+
 def needs_build() -> bool:
-    if not os.path.exists(LIB) or not os.path.exists(MEASURE_LIB):
+    if not all(os.path.exists(f) for f in (LIB, MEASURE_LIB, BINDING)):
         return True
-    t = min(os.path.getmtime(LIB), os.path.getmtime(MEASURE_LIB))
+    t = min(os.path.getmtime(f) for f in (LIB, MEASURE_LIB, BINDING))
     deps = sources() + measure_sources() + glob.glob(os.path.join(CSRC, "*.hpp")) + \
-        glob.glob(os.path.join(INCLUDE, "*.h"))
+        glob.glob(os.path.join(INCLUDE, "*.h")) + binding_sources()
     return any(os.path.getmtime(f) > t for f in deps)
 
 
@@ -64,7 +89,9 @@ def build(force: bool = True, verbose: bool = False) -> str:
             return obj
 
         with ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as pool:
+            binding = pool.submit(build_binding, verbose)
             objs = list(pool.map(compile_one, sources() + measure_sources()))
+            binding.result()
         n = len(sources())
         for lib, members in ((LIB, objs[:n]), (MEASURE_LIB, objs)):
             tmp = lib + ".tmp%d" % os.getpid()

@@ -96,6 +96,16 @@ _lib.ssd_status_string.restype = ctypes.c_char_p
 _lib.ssd_status_string.argtypes = [ctypes.c_int]
 _lib.ssd_version.restype = ctypes.c_int
 
+try:
+    from . import _ssd_binding as _native
+except ImportError as e:
+    raise ImportError("_ssd_binding.so is missing or does not load: build it with `python -m paper_2603_09555_amd.build`") from e
+_native.init([ctypes.cast(getattr(_lib, n), ctypes.c_void_p).value for n in
+              ("ssd_prefill_workspace_bytes", "ssd_prefill", "ssd_prefill_dt", "ssd_prefill_varlen_workspace_bytes",
+               "ssd_prefill_varlen", "ssd_prefill_varlen_dt", "ssd_decode_step", "ssd_decode_step_layers",
+               "ssd_decode_step_layers_dt", "ssd_decode_steps_layers", "ssd_decode_steps_layers_dt", "ssd_conv1d_prefill",
+               "ssd_conv1d_step")])
+
 
 def raw():
     """The ctypes handle, for callers that want to pass raw pointers (tests of error paths)."""
@@ -127,10 +137,15 @@ def prefill_path(shape: ssd_shape) -> str:
     return _lib.ssd_prefill_path(ctypes.byref(shape)).decode()
 
 
-# What a call costs before its first kernel is host time that a single-layer decode step cannot hide: pointers and the
-# stream go to ctypes as plain integers (the argument types make them pointers) and the current stream is asked for as
-# a handle, without a Stream object around it.  Convolution step + decode step of one layer: 29.2 -> 21.6 us, of which the
-# kernels are 7; a call whose kernels take longer than its host time (the smallest fp32 prefill, 11.8 us) does not change.
+# What a call costs before its first kernel is host time that a single-layer decode step cannot hide.  The ordinary call
+# goes through native code (csrc/binding/ssd_binding.cpp), which answers None where anything is out of the ordinary; the
+# Python below it then does the same in full and raises what is wrong.
+def _done(out, where):
+    if type(out) is int:
+        raise SSDError(out, where)
+    return out
+
+
 def _ptr(t):
     return None if t is None else t.data_ptr()
 
@@ -170,6 +185,9 @@ def ssd_prefill(x, dt, A, B, C, D, chunk, h0=None, y=None, final_state=None, wor
     ``ssd_prefill_dt``: ``dt`` is then the raw value and the kernels apply
     ``clamp(softplus(dt + dt_bias), lo, hi)`` as they read it.
     """
+    out = _native.prefill(x, dt, A, B, C, D, chunk, h0, y, final_state, workspace, dt_bias, dt_softplus, dt_limit)
+    if out is not None:
+        return _done(out, "ssd_prefill")
     Bt, T, H, P = x.shape
     G, N = B.shape[2], B.shape[3]
     shape = make_shape(Bt, T, H, P, N, G, chunk, x.dtype)
@@ -227,6 +245,9 @@ def ssd_prefill_static(x, dt, A, B, C, D, chunk, y, final_state, h0=None):
 
 def ssd_decode_step(state, x, dt, A, B, C, D, y=None):
     """``ssd_decode_step``: updates ``state (Bt,H,P,N)`` in place, returns ``y (Bt,H,P)``."""
+    out = _native.decode_step(state, x, dt, A, B, C, D, y)
+    if out is not None:
+        return _done(out, "ssd_decode_step")
     Bt, H, P, N = state.shape
     G = B.shape[1]
     shape = make_shape(Bt, 1, H, P, N, G, 1, x.dtype)
@@ -247,6 +268,9 @@ def ssd_decode_step_layers(state, x, dt, A, B, C, D, y=None, dt_bias=None, dt_so
     """``ssd_decode_step_layers``: every tensor has a leading layer axis; one launch.  With ``dt_bias
     (Ly,H)``, ``dt_softplus`` or ``dt_limit=(lo, hi)`` the call goes through ``ssd_decode_step_layers_dt``
     and ``dt`` is the raw value."""
+    out = _native.decode_step_layers(state, x, dt, A, B, C, D, y, dt_bias, dt_softplus, dt_limit)
+    if out is not None:
+        return _done(out, "ssd_decode_step_layers")
     Ly, Bt, H, P, N = state.shape
     G = B.shape[2]
     shape = make_shape(Bt, 1, H, P, N, G, 1, x.dtype)
@@ -273,6 +297,9 @@ def ssd_decode_steps_layers(state, x, dt, A, B, C, D, y=None, dt_bias=None, dt_s
     ``B, C (steps,Ly,Bt,G,N)``, ``A, D (Ly,H)``; ``state (Ly,Bt,H,P,N)`` updated in place to the
     state after the last step.  Returns ``y (steps,Ly,Bt,H,P)``.  One launch.  ``dt_bias (Ly,H)``,
     ``dt_softplus``, ``dt_limit``: as for ``ssd_decode_step_layers`` (``ssd_decode_steps_layers_dt``)."""
+    out = _native.decode_steps_layers(state, x, dt, A, B, C, D, y, dt_bias, dt_softplus, dt_limit)
+    if out is not None:
+        return _done(out, "ssd_decode_steps_layers")
     Ly, Bt, H, P, N = state.shape
     S, G = x.shape[0], B.shape[3]
     shape = make_shape(Bt, 1, H, P, N, G, 1, x.dtype)
@@ -300,6 +327,10 @@ def ssd_prefill_varlen(x, dt, A, B, C, D, cu_seqlens, chunk, h0=None, y=None, fi
     ``cu_seqlens (nseq+1)`` int32 on the device, ``h0 (nseq,H,P,N)`` optional.
     Returns ``(y (tokens,H,P), final_state (nseq,H,P,N))``.  ``dt_bias (H)``, ``dt_softplus``, ``dt_limit``: as
     for ``ssd_prefill`` (``ssd_prefill_varlen_dt``)."""
+    out = _native.prefill_varlen(x, dt, A, B, C, D, cu_seqlens, chunk, h0, y, final_state, workspace, dt_bias, dt_softplus,
+                                 dt_limit)
+    if out is not None:
+        return _done(out, "ssd_prefill_varlen")
     T, H, P = x.shape
     G, N = B.shape[1], B.shape[2]
     nseq = cu_seqlens.numel() - 1
@@ -347,6 +378,9 @@ def ssd_conv1d_prefill(u, weight, bias=None, conv_state=None, split=None, activa
     """``ssd_conv1d_prefill``: ``u (Bt,T,C)`` channels-last, ``weight (C,k)`` fp32, ``bias (C)`` fp32 or None,
     ``conv_state (Bt,C,k-1)`` or None.  Returns ``(outputs, new_conv_state)`` where outputs is a list of
     dense tensors ``(Bt,T,split[i])`` (one tensor ``(Bt,T,C)`` without ``split``)."""
+    out = _native.conv1d_prefill(u, weight, bias, conv_state, split, activation)
+    if out is not None:
+        return _done(out, "ssd_conv1d_prefill")
     Bt, T, C = u.shape
     k = weight.shape[1]
     split = _conv_split(C, split)
@@ -369,6 +403,9 @@ def ssd_conv1d_prefill(u, weight, bias=None, conv_state=None, split=None, activa
 def ssd_conv1d_step(conv_state, u, weight, bias=None, split=None, activation="silu"):
     """``ssd_conv1d_step``: ``u (Bt,C)``, ``conv_state (Bt,C,k-1)`` updated in place.  Returns the list of
     outputs ``(Bt,split[i])``."""
+    out = _native.conv1d_step(conv_state, u, weight, bias, split, activation)
+    if out is not None:
+        return _done(out, "ssd_conv1d_step")
     Bt, C = u.shape
     k = weight.shape[1]
     split = _conv_split(C, split)
