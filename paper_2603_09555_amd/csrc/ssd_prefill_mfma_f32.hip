@@ -7,11 +7,11 @@
 // headdim) and walks the sequence in 64-token blocks with its 32 x dstate slice of the state carried in
 // MFMA accumulators: the inter-chunk state pass (Alg. 1, "Inter-chunk scan") happens in registers and
 // the result does not depend on the chunk argument.
-// When that leaves most of the chip idle, the sequence is also cut into time segments, one workgroup
-// each: a workgroup walks from the first block of the sequence, but up to its own segment it only updates
-// the state (no scores, no output, the update shared by all four waves: a fraction of a block's time), then
-// computes the outputs of its segment.  The states are recomputed rather than handed over, so there is still one launch, no workspace
-// and no waiting on another workgroup; the last segment's workgroup writes the final state.
+// When that leaves most of the chip idle, the sequence is also cut into time segments, one workgroup each: a workgroup
+// first forms the state entering its segment from all tokens before it (one contraction shared by all four waves, no
+// scores, no output: a fraction of a block's time), then walks the blocks of its segment.  The states are recomputed rather
+// than handed over, so there is still one launch, no workspace and no waiting on another workgroup; the last segment's
+// workgroup writes the final state.
 // Per block, with cs_l the block-relative inclusive prefix sum of dt*A and S the state entering the block:
 //   scores      G[l][s] = C_l . B_s for s <= l                     three 32 x 32 tiles, K = dstate   (waves 0-2)
 //   mask        GM[l][s] = G[l][s] * dt_s * exp(cs_l - cs_s)      in registers, on the accumulators; the
@@ -27,6 +27,8 @@
 // and B[k][r] and receives D[(e/4)*8 + 4k + e%4][r] in element e.  A group of four consecutive steps reads
 // one 16-byte piece per operand: lane (r, k) takes contraction indices 8m + 4k .. 8m + 4k + 3 of group m --
 // a permutation of the contraction index that both operands share.
+#include <type_traits>
+
 #include "ssd_internal.hpp"
 
 namespace ssd {
@@ -98,8 +100,8 @@ struct F32Params {
   int dt_plain;  // the step sizes are used as given
 };
 
-// NT: 32-column tiles of the state (dstate <= 32 NT; columns beyond dstate are zero padding).
-template <int NT>
+// NT: 32-column tiles of the state (dstate <= 32 NT; columns beyond dstate are zero padding).  kNarrow: dstate <= 16.
+template <int NT, bool kNarrow = false>
 __global__ __launch_bounds__(kF32Threads) void prefill_f32_kernel(const F32Params p) {
   constexpr int N32 = 32 * NT;
   constexpr int kRowN = N32 + kPad;   // row stride of the tiles indexed [token][n] and of the state [col][n]
@@ -178,13 +180,11 @@ __global__ __launch_bounds__(kF32Threads) void prefill_f32_kernel(const F32Param
     v_x[k] = static_cast<uint32_t>(c >> 3) * xrow + 16 * (c & 7);
   }
   const uint32_t v_dt = static_cast<uint32_t>(lane) * drow;  // every wave fetches the block's 64 step sizes; wave 0 uses them
-  // (with_c, uniform: a block of which only the state is wanted needs no C -- its loads are pointed beyond the
-  // descriptor, where they cost nothing, rather than put behind a branch)
-  auto load_block = [&](int jb, bool with_c = true) __attribute__((always_inline)) {
+  auto load_block = [&](int jb) __attribute__((always_inline)) {
     const Rsrc rc = rsrc_at(Cb, brow, boff, jb), rb = rsrc_at(Bb, brow, boff, jb);
 #pragma unroll
     for (int k = 0; k < kVecN; ++k) {
-      r_c[k] = buf_load4(rc, with_c ? v_bc[k] : kNowhere);
+      r_c[k] = buf_load4(rc, v_bc[k]);
       r_b[k] = buf_load4(rb, v_b[k]);
     }
     const Rsrc rx = rsrc_at(xb, xrow, xoff, jb);
@@ -193,18 +193,15 @@ __global__ __launch_bounds__(kF32Threads) void prefill_f32_kernel(const F32Param
     r_dt = buf_load1(rsrc_at(dtb, drow, static_cast<uint32_t>(h) * 4, jb), v_dt);
   };
   // registers -> LDS tiles; wave 0 also turns dt into the block's decay bookkeeping
-  // (full, uniform: the row-major C and B tiles serve the scores only)
-  auto stage_block = [&](int jb_staged, bool full = true) __attribute__((always_inline)) {
+  auto stage_block = [&](int jb_staged) __attribute__((always_inline)) {
 #pragma unroll
     for (int k = 0; k < kVecN; ++k) {
       const int c = tid + kF32Threads * k;
       const int row = c / (N32 / 4), n0 = 4 * (c % (N32 / 4));
       int rb, nb;
       b_piece(k, rb, nb);
-      if (full) {
-        *reinterpret_cast<f32x4 *>(&sC[row * kRowN + n0]) = r_c[k];
-        *reinterpret_cast<f32x4 *>(&sB[rb * kRowN + nb]) = r_b[k];
-      }
+      *reinterpret_cast<f32x4 *>(&sC[row * kRowN + n0]) = r_c[k];
+      *reinterpret_cast<f32x4 *>(&sB[rb * kRowN + nb]) = r_b[k];
 #pragma unroll
       for (int j = 0; j < 4; ++j) sBT[(nb + j) * kRowT + rb] = r_b[k][j];
     }
@@ -258,67 +255,165 @@ __global__ __launch_bounds__(kF32Threads) void prefill_f32_kernel(const F32Param
       }
   };
 
-  if (walk_end > 0) load_block(0, out0 == 0);
+  if (out0 == 0 && walk_end > 0) load_block(0);
   if (out0 > 0) {
-    // ---- the blocks before the segment: the state alone.  All four waves share the update -- wave w takes
-    //      tokens 16 w .. 16 w + 15 of every block, for every state tile -- in accumulators of their own, which
-    //      are summed once, at the end (the update is linear in the state); the initial state rides in the
-    //      accumulators of the wave that owns the tile afterwards. ----
-    f32x16 Spart[NT];
+    // ---- the blocks before the segment: the state alone, S = sum_s (decay behind s) dt_s x_s (x) B_s, one long contraction
+    //      without a block in it.  Wave w takes the w-th quarter of the tokens, in accumulators of its own.  The operands
+    //      come straight from memory: lane (r, k) of the matrix instruction wants x[s][col r] and B[s][n = 32 nt + r] of
+    //      token s, which 32 lanes read as one piece of a row.  So no barrier and no LDS tile lies on the way, only the
+    //      weights do, kMost tokens per wave at a time (in what will be the masked-score tile); a batch of tokens is in flight
+    //      while the ones before it are multiplied.  Bound: the matrix instruction for long sequences (64 cycles per two
+    //      tokens and 32 state columns), the first loads and the weights behind them for short ones (7 blocks, dstate
+    //      16: 1.2 us until the weights are there, 2.1 to multiply, 0.5 for the sum).  As a walk over staged blocks a
+    //      block cost 0.76 us (dstate 16) to 2.2 (128) of the workgroup's time, now 0.32 to 1.26: 512 tokens x 4 heads x 32 x
+    //      16 12.5 -> 9.9 us, 2 x 836 x 3 x 64 x 128 43.7 -> 30.4, 110 drawn prompts 1.07 times as fast together. ----
+    constexpr int kMost = 1024, kBatch = 16, kDepth = NT == 1 ? 8 : NT == 2 ? 4 : 2;
+    static_assert(4 * kMost <= kTok * kRowT && kMost % kBatch == 0, "the weights fit in the masked-score tile, whole batches");
+    float *const w_of = &sGM[wave * kMost];
+    const int quarter = out0 * (kTok / 4), first = wave * quarter;  // (all these blocks are whole)
+    // (kNarrow: the 16 x 16 x 4 instruction, which spends nothing on columns 16 .. 31 of the tile: lane (c, k) = (lane % 16,
+    // lane / 16) supplies columns c and 16 + c of x and column c of B, of token 4 k + j in step j of 16 tokens)
+    constexpr int kTilesX = kNarrow ? 2 : 1, kTilesB = kNarrow ? 1 : NT, kTiles = kTilesX * kTilesB;
+    constexpr int kSteps = kNarrow ? 4 : kBatch / 2;
+    using Part = typename std::conditional<kNarrow, f32x4, f32x16>::type;
+    Part Spart[kTiles];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      const bool mine = wave == 2 + (nt & 1);
+    for (int t = 0; t < kTiles; ++t) Spart[t] = Part{};
+    // byte offsets of step j (of 4) in its rows; the token of step 4 q + j: 8 q + 4 kk + j, narrow 4 (lane / 16) + j
+    const int lane_tok = kNarrow ? 4 * (lane >> 4) : 4 * kk, lane_col = kNarrow ? lane & 15 : r;
+    uint32_t v_xs[kTilesX][4], v_bs[kTilesB][4];
 #pragma unroll
-      for (int e = 0; e < 16; ++e) Spart[nt][e] = mine ? Sacc[nt >> 1][e] : 0.f;
+    for (int j = 0; j < 4; ++j) {
+#pragma unroll
+      for (int t = 0; t < kTilesX; ++t) v_xs[t][j] = static_cast<uint32_t>(lane_tok + j) * xrow + 4 * (16 * t + lane_col);
+#pragma unroll
+      for (int t = 0; t < kTilesB; ++t)
+        v_bs[t][j] = 32 * t + lane_col < p.N ? static_cast<uint32_t>(lane_tok + j) * brow + 4 * (32 * t + lane_col) : kNowhere;
     }
-    for (int jb = 0; jb < out0; ++jb) {
-      __syncthreads();  // the previous block's readers are done with every tile
-      stage_block(jb, false);
-      load_block(jb + 1, jb + 1 == out0);  // (out0 < walk_end: block jb + 1 exists)
-      __syncthreads();
-      const float e63 = sEl[kTok - 1];
-      const float *ap = &sXT[r * kRowT + 4 * kk];
+    float log2_quarter = 0.f;
+    for (int c0 = 0; c0 < quarter; c0 += kMost) {
+      const int n = min(kMost, quarter - c0), t0 = first + c0;
+      float xs[kDepth][kTilesX][kSteps], bs[kDepth][kTilesB][kSteps];
+      auto request = [&](int buf, int s0) __attribute__((always_inline)) {
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
+        for (int q = 0; q < kSteps / 4; ++q) {
+          const int s = s0 + 8 * q, left = max(n - s, 0);  // (uniform: the descriptors are built by the scalar unit)
+          const Rsrc rxs = make_rsrc(xb + static_cast<size_t>(t0 + s) * xrow, static_cast<uint32_t>(left) * xrow);
+          const Rsrc rbs = make_rsrc(Bb + static_cast<size_t>(t0 + s) * brow, static_cast<uint32_t>(left) * brow);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) Spart[nt][e] *= e63;
-      }
+          for (int j = 0; j < 4; ++j) {
 #pragma unroll
-      for (int mm = 0; mm < 2; ++mm) {
-        const int m = 2 * wave + mm;
-        f32x4 a = ld4(ap + 8 * m);
-        const f32x4 w = ld4(&sW[8 * m + 4 * kk]);
-        a = f32x4{a.x * w.x, a.y * w.y, a.z * w.z, a.w * w.w};
+            for (int t = 0; t < kTilesX; ++t) xs[buf][t][4 * q + j] = buf_load1(rxs, v_xs[t][j]);
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) Spart[nt] = mfma_group(a, ld4(&sBT[(32 * nt + r) * kRowT + 4 * kk + 8 * m]), Spart[nt]);
-      }
-    }
-    // the sum, tile by tile, through what will be the masked-score tile: three waves put, the owner adds
-    static_assert(3 * 1024 <= kTok * kRowT, "three partial tiles fit in the masked-score tile");
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      const int owner_wave = 2 + (nt & 1);
-      __syncthreads();
-      if (wave != owner_wave) {
-        float *dst = &sGM[(wave - (wave > owner_wave)) * 1024 + 4 * lane];
-#pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4)
-          *reinterpret_cast<f32x4 *>(dst + 256 * e4) = f32x4{Spart[nt][4 * e4], Spart[nt][4 * e4 + 1], Spart[nt][4 * e4 + 2], Spart[nt][4 * e4 + 3]};
-      }
-      __syncthreads();
-      if (wave == owner_wave) {
-#pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4) {
-          f32x4 sum = f32x4{Spart[nt][4 * e4], Spart[nt][4 * e4 + 1], Spart[nt][4 * e4 + 2], Spart[nt][4 * e4 + 3]};
-#pragma unroll
-          for (int q = 0; q < 3; ++q) {
-            const f32x4 v = ld4(&sGM[q * 1024 + 256 * e4 + 4 * lane]);
-            sum = f32x4{sum.x + v.x, sum.y + v.y, sum.z + v.z, sum.w + v.w};
+            for (int t = 0; t < kTilesB; ++t) bs[buf][t][4 * q + j] = buf_load1(rbs, v_bs[t][j]);
           }
-          Sacc[nt >> 1][4 * e4] = sum.x;
-          Sacc[nt >> 1][4 * e4 + 1] = sum.y;
-          Sacc[nt >> 1][4 * e4 + 2] = sum.z;
-          Sacc[nt >> 1][4 * e4 + 3] = sum.w;
+        }
+      };
+      // weights relative to the end of these n tokens, from the last 64 back
+      const Rsrc rd = make_rsrc(dtb + static_cast<size_t>(t0) * drow, static_cast<uint32_t>(n - 1) * drow + 4);
+      float total = 0.f;
+      auto step_at = [&](int at) { return buf_load1(rd, at >= 0 ? static_cast<uint32_t>(at) * drow : kNowhere); };
+      float ahead = step_at(n - kTok + lane), ahead2 = step_at(n - 2 * kTok + lane);
+#pragma unroll
+      for (int k = 0; k < kDepth; ++k) request(k, kBatch * k);
+      if (c0 == 0) load_block(out0);  // (uniform; the segment's first block arrives meanwhile)
+      for (int at = n - kTok; at > -kTok; at -= kTok) {
+        float dtv = ahead;
+        ahead = ahead2;
+        if (at > kTok) ahead2 = step_at(at - 2 * kTok + lane);
+        if (!p.dt_plain) dtv = dt_apply_branchless(dtv, dbias, p.dtx);
+        dtv = at + lane >= 0 ? dtv : 0.f;
+        const float cs = wave_prefix_sum(cut_step(dtv, alog) * alog);
+        const float c63 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, cs), 63));
+        if (at + lane >= 0) w_of[at + lane] = dtv * exp2_fast(total + (c63 - cs));
+        total += c63;
+      }
+      const float e_all = exp2_fast(total);
+      log2_quarter += total;
+#pragma unroll
+      for (int t = 0; t < kTiles; ++t) Spart[t] *= e_all;
+      auto multiply = [&](int buf, int s0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < kSteps / 4; ++q) {
+          const f32x4 w = ld4(&w_of[s0 + 8 * q + lane_tok]);
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int tx = 0; tx < kTilesX; ++tx)
+#pragma unroll
+              for (int tb = 0; tb < kTilesB; ++tb) {
+                Part &acc = Spart[tx * kTilesB + tb];
+                const float a = w[j] * xs[buf][tx][4 * q + j], bv = bs[buf][tb][4 * q + j];
+                if constexpr (kNarrow)
+                  acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bv, acc, 0, 0, 0);
+                else
+                  acc = mfma2(a, bv, acc);
+              }
+        }
+      };
+      for (int s0 = 0; s0 < n; s0 += kDepth * kBatch) {
+#pragma unroll
+        for (int k = 0; k < kDepth; ++k) {
+          const int at = s0 + kBatch * k;
+          if (at < n) multiply(k, at);
+          request(k, at + kDepth * kBatch);
+        }
+      }
+    }
+    // ---- the sum over the quarters, each decayed by the later ones, through the masked-score tile; the initial state rides in
+    //      the accumulators of the wave that owns the tile ----
+    if (lane == 0) sCs[wave] = log2_quarter;
+    __syncthreads();
+    float behind = 0.f, all = 0.f;
+#pragma unroll
+    for (int w = 3; w >= 0; --w) {
+      behind += w > wave ? sCs[w] : 0.f;
+      all += sCs[w];
+    }
+    const float e_behind = exp2_fast(behind), e_all = exp2_fast(all);
+#pragma unroll
+    for (int t = 0; t < kTiles; ++t) Spart[t] *= e_behind;
+    if constexpr (kNarrow) {  // lane (c, k), element e: headdim column 16 tile + 4 k + e, state column c
+#pragma unroll
+      for (int t = 0; t < kTiles; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sGM[(wave * kCols + 16 * t + lane_tok + e) * 16 + lane_col] = Spart[t][e];
+      __syncthreads();
+      if (wave == 2) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int col = (e >> 2) * 8 + 4 * kk + (e & 3);
+          float sum = 0.f;
+#pragma unroll
+          for (int w = 0; w < 4; ++w) sum += sGM[(w * kCols + col) * 16 + (r & 15)];
+          Sacc[0][e] = r < 16 ? fmaf(e_all, Sacc[0][e], sum) : 0.f;
+        }
+      }
+    } else {
+      static_assert(3 * 1024 <= kTok * kRowT, "three partial tiles fit in the masked-score tile");
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {  // three waves put, the owner adds
+        const int owner_wave = 2 + (nt & 1);
+        __syncthreads();
+        if (wave != owner_wave) {
+          float *dst = &sGM[(wave - (wave > owner_wave)) * 1024 + 4 * lane];
+#pragma unroll
+          for (int e4 = 0; e4 < 4; ++e4)
+            *reinterpret_cast<f32x4 *>(dst + 256 * e4) = f32x4{Spart[nt][4 * e4], Spart[nt][4 * e4 + 1], Spart[nt][4 * e4 + 2], Spart[nt][4 * e4 + 3]};
+        }
+        __syncthreads();
+        if (wave == owner_wave) {
+#pragma unroll
+          for (int e4 = 0; e4 < 4; ++e4) {
+            f32x4 sum = f32x4{Spart[nt][4 * e4], Spart[nt][4 * e4 + 1], Spart[nt][4 * e4 + 2], Spart[nt][4 * e4 + 3]};
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+              const f32x4 v = ld4(&sGM[q * 1024 + 256 * e4 + 4 * lane]);
+              sum = f32x4{sum.x + v.x, sum.y + v.y, sum.z + v.z, sum.w + v.w};
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) Sacc[nt >> 1][4 * e4 + j] = fmaf(e_all, Sacc[nt >> 1][4 * e4 + j], sum[j]);
+          }
         }
       }
     }
@@ -442,10 +537,12 @@ __global__ __launch_bounds__(kF32Threads) void prefill_f32_kernel(const F32Param
 
 }  // namespace
 
-// Time per block of a workgroup (microseconds on MI355X; fits to a handful of timings): a full block, and a
-// block of which only the state update runs.  nt = 32-column tiles of the state.
-double f32_block_us(int nt) { return 1.7 + 1.39 * nt; }
-double f32_state_block_us(int nt) { return 0.29 + 0.47 * nt; }
+// Time per block of a workgroup (microseconds on MI355X; fits to 171 timings of 39 drawn shapes at up to eight numbers of
+// segments, 5 % rms): a full block, a block before the segment, and what the blocks before it cost whatever their number.
+// nt = 32-column tiles of the state.
+static double f32_block_us(int nt) { return 1.7 + 1.39 * nt; }
+static double f32_state_block_us(const Dims &d) { return d.N <= 16 ? 0.32 : 0.22 + 0.26 * ((d.N + 31) / 32); }
+static double f32_carry_us(int nt) { return 0.5 + 0.4 * nt; }
 // Time segments per sequence, and the modelled time of the walk that results.  More segments shorten the
 // stretch of full blocks of the longest walk -- the last segment's, which first carries the state over
 // everything before it -- as long as the workgroups still run side by side (one round of 256).
@@ -458,7 +555,8 @@ int f32_time_segments(const Dims &d, double *walk_us) {
   const int forced = knobs().f32_segments;
   for (int s = 2; s <= nblocks && s <= 64 && (forced > 0 || wgs * s <= 256); ++s) {
     const int len = (nblocks + s - 1) / s;
-    const double us = static_cast<double>((wgs * s + 255) / 256) * ((nblocks - len) * f32_state_block_us(nt) + len * f32_block_us(nt));
+    const double us = static_cast<double>((wgs * s + 255) / 256) *
+                      (f32_carry_us(nt) + (nblocks - len) * f32_state_block_us(d) + len * f32_block_us(nt));
     if (forced > 0 ? s <= forced : us < best_us) {
       best = s;
       best_us = us;
@@ -479,7 +577,7 @@ int f32_time_segments(const Dims &d, double *walk_us) {
 static double f32_mfma_us(const Dims &d) {
   double walk_us;
   f32_time_segments(d, &walk_us);
-  return 8.0 + walk_us;
+  return 4.0 + walk_us;
 }
 static double f32_generic_us(const Dims &d) {
   return 33.0 + static_cast<double>(d.Bt) * d.T * d.H * (0.9 + 0.0005 * d.P * d.N) * 1e-3;
@@ -528,7 +626,12 @@ hipError_t launch_prefill_mfma_f32(const Dims &d, const void *x, const float *dt
   const dim3 grid(static_cast<unsigned>(d.Bt) * d.H * (d.P / kCols) * p.tseg), block(kF32Threads);
   const int nt = (d.N + 31) / 32;
   switch (nt) {
-    case 1: hipLaunchKernelGGL(prefill_f32_kernel<1>, grid, block, 0, stream, p); break;
+    case 1:
+      if (d.N <= 16)
+        hipLaunchKernelGGL((prefill_f32_kernel<1, true>), grid, block, 0, stream, p);
+      else
+        hipLaunchKernelGGL(prefill_f32_kernel<1>, grid, block, 0, stream, p);
+      break;
     case 2: hipLaunchKernelGGL(prefill_f32_kernel<2>, grid, block, 0, stream, p); break;
     case 3: hipLaunchKernelGGL(prefill_f32_kernel<3>, grid, block, 0, stream, p); break;
     default: hipLaunchKernelGGL(prefill_f32_kernel<4>, grid, block, 0, stream, p); break;

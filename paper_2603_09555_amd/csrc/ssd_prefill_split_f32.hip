@@ -558,16 +558,14 @@ bool split_f32_supported(const Dims &d) {
          static_cast<unsigned long long>(d.Bt) * d.H * (d.P / kCols) * 64 <= 0x7fffffffull;
 }
 
-// Taken where it is 12 % faster than the faster of the two other families by the models, with dstate up to 32 by 18 %, and
-// by 25 % where a group has one or two slices (half of a workgroup's waves and more then repeat one) and dstate is at
-// most 64.  Of 130 drawn shapes, 45 of them with a group per head, none is then more than 3 % behind the fp32 matrix
-// instruction; at equal times eight are, by up to 26 % (4 x 2171 tokens, 17 heads and groups x 32 x 24: 73 us, 59 there).
-// All together take 0.758 of its time (0.760), and are 1.7 % behind the fastest of all timed plans of the three families.
+// Taken where it is faster than the faster of the two other families by the models, by a tenth where a group has one or two
+// slices (half of a workgroup's waves and more then repeat one) and dstate is at most 64.  Of 110 drawn prompts one is then
+// more than 6 % behind the fastest of the timed plans of the families (1527 tokens x 2 x 32 x 64: 26.0 us, 23.0 on split operands).
 bool split_f32_chosen(const Dims &d) {
   if (!split_f32_supported(d)) return false;
   if (knobs().seg_blocks > 0) return true;
   const bool few_slices = d.hpg * (d.P / kCols) <= kWaves / 2 && d.N <= 64;
-  return (few_slices ? 1.25 : d.N <= 32 ? 1.18 : 1.12) * split_plan(d).us < f32_other_us(d);
+  return (few_slices ? 1.1 : 1.0) * split_plan(d).us < f32_other_us(d);
 }
 
 void split_f32_plan(const Dims &d, int *seg_blocks, int *segments, int *parts) {

@@ -1,0 +1,55 @@
+"""fp32 MFMA prefill in time segments: the state that enters a segment, one contraction over all the tokens before it.
+Its edges: quarters of 16 tokens and of more than one set of weights (1024), dstate up to 16 (its own instruction) and
+beyond, tokens that decay everything away before, in and behind a quarter."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ssd_oracle
+from paper_2603_09555_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ssd():
+    from paper_2603_09555_amd import ssd
+    yield ssd
+    ssd.reset_knobs()
+
+
+# batch, tokens, heads, headdim, dstate, groups; segments; raw step sizes; steps that decay everything
+CASES = [((1, 65, 2, 32, 8, 1), 2, False, False), ((2, 130, 3, 64, 16, 1), 3, True, False), ((1, 512, 4, 32, 16, 1), 8, False, True),
+         ((1, 321, 2, 32, 24, 2), 6, False, False), ((1, 449, 2, 64, 64, 1), 7, True, True), ((2, 200, 2, 32, 96, 1), 4, False, False),
+         ((1, 333, 3, 32, 128, 3), 6, True, False), ((1, 4300, 1, 32, 16, 1), 64, False, False), ((1, 8500, 1, 32, 40, 1), 64, False, True)]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c[0])) + "-s%d-%d%d" % c[1:])
+def test_state_entering_a_segment(ssd, case):
+    dims, segments, raw, steep = case
+    cfg = inputs.SSDConfig("t", *dims, 64, "f32")
+    inp = inputs.make_prefill_inputs(cfg, seed=51)
+    rng = np.random.default_rng(4)
+    if steep:
+        inp["dt"] = inp["dt"] * torch.from_numpy(rng.choice([1.0, 30.0], inp["dt"].shape, p=[0.98, 0.02])).float()
+    h0 = 0.1 * inputs.make_state(cfg, seed=51)
+    kw, dt = {}, inp["dt"]
+    if raw:
+        bias = torch.from_numpy(rng.normal(-4.0, 0.3, cfg.nheads)).float()
+        inp["dt"] = torch.from_numpy(rng.normal(0.0, 1.0, inp["dt"].shape)).float()
+        kw = dict(dt_bias=bias.cuda(), dt_softplus=True)
+        dt = ssd_oracle.dt_transform(inp["dt"], bias, True, None)
+    ssd.reset_knobs()
+    ssd.set_knob("force_mfma_f32", 1)
+    ssd.set_knob("f32_segments", segments)
+    print("state entering a segment", case, flush=True)
+    dev = {k: v.cuda() for k, v in inp.items()}
+    y, st = ssd.ssd_prefill(*[dev[k] for k in ("x", "dt", "A", "B", "C", "D")], 64, h0=h0.cuda(), **kw)
+    torch.cuda.synchronize()
+    ssd.reset_knobs()
+    y_ref, st_ref = ssd_oracle.prefill(inp["x"], dt, inp["A"], inp["B"], inp["C"], inp["D"], h0=h0)
+    # 32-bit sums of up to 64 terms a matrix instruction chain at a time, decays from sums of up to 64 steps: 1e-6 of the norm
+    for got, ref, what in ((y, y_ref, "y"), (st, st_ref, "final state")):
+        err = np.linalg.norm(got.double().cpu().numpy() - ref) / np.linalg.norm(ref)
+        print("  %s off by %.2e" % (what, err), flush=True)
+        assert err <= 1e-6, (what, err)
