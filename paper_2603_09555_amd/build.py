@@ -33,6 +33,10 @@ HIPCC_FLAGS = [
     "-Wall", "-Wno-unused-function", "-Wno-unknown-warning-option",
 ]
 
+# Per source: matrix instructions on architectural registers.  In a kernel with one wave per SIMD the compiler otherwise
+# keeps accumulators in accumulation registers and moves them, 8 cycles each, wherever the vector unit works on them.
+EXTRA_FLAGS = {"ssd_prefill_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+
 
 def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
@@ -82,7 +86,8 @@ def build(force: bool = True, verbose: bool = False) -> str:
     try:
         def compile_one(src):
             obj = os.path.join(tmpdir, os.path.basename(src) + ".o")
-            cmd = [hipcc] + HIPCC_FLAGS + ["-I", INCLUDE, "-I", CSRC, "-c", src, "-o", obj]
+            cmd = [hipcc] + HIPCC_FLAGS + EXTRA_FLAGS.get(os.path.basename(src), [])
+            cmd += ["-I", INCLUDE, "-I", CSRC, "-c", src, "-o", obj]
             if verbose:
                 print(" ".join(cmd), file=sys.stderr)
             subprocess.run(cmd, check=True)

@@ -415,6 +415,30 @@ __device__ __forceinline__ void buf_store16(Rsrc r, uint32_t voff, u32x4 v) {
   __builtin_amdgcn_raw_buffer_store_b128(v, r, voff, 0, kPolicy);
 }
 
+// Memory straight into LDS: the wave's 64 lanes fetch 16 bytes each, from wherever their offsets say, and the 1024 bytes
+// land in lane order from the LDS address `to` on (uniform, as are the descriptor and soff; lanes beyond the descriptor
+// write zeros).  Nothing passes through registers.  Written as assembly because the compiler, which does not tell the
+// LDS buffers apart, would let every later LDS read wait for it: the caller waits itself (vector memory operations
+// complete in order), before the barrier that hands the buffer over.
+__device__ __forceinline__ uint32_t uniform32(uint32_t v) { return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v))); }
+__device__ __forceinline__ u32x4 raw_rsrc(const void *base, uint32_t bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(base);
+  return u32x4{uniform32(static_cast<uint32_t>(a)), uniform32(static_cast<uint32_t>(a >> 32)) & 0xFFFFu, uniform32(bytes), 0x00020000u};
+}
+__device__ __forceinline__ void load_to_lds(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t to) {
+  asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+               :: "v"(voff), "s"(rsrc), "s"(uniform32(soff)), "s"(uniform32(to)) : "memory");
+}
+
+// Four of them to consecutive places.  The places come from the instructions' offsets, which move the addresses in
+// memory as well: voff[k] is to be 1024 k less than the offset that is meant.  (With m0 written before each of them a request
+// holds its wave for 95 cycles when the four SIMDs of a CU make them, in pairs behind one write for 45.)
+__device__ __forceinline__ void load_to_lds4(u32x4 rsrc, uint32_t v0, uint32_t v1, uint32_t v2, uint32_t v3, uint32_t to) {
+  asm volatile("s_mov_b32 m0, %5\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %4, 0 offen lds\n\tbuffer_load_dwordx4 %1, %4, 0 offen offset:1024 lds\n\t"
+               "buffer_load_dwordx4 %2, %4, 0 offen offset:2048 lds\n\tbuffer_load_dwordx4 %3, %4, 0 offen offset:3072 lds"
+               :: "v"(v0), "v"(v1), "v"(v2), "v"(v3), "s"(rsrc), "s"(uniform32(to)) : "memory");
+}
+
 // A 64-bit value that is the same in every lane, moved to scalar registers.
 __device__ __forceinline__ size_t uniform_size(size_t v) {
   const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v));
@@ -844,6 +868,7 @@ __device__ __forceinline__ void wait_all_loads() { __builtin_amdgcn_s_waitcnt(0x
 // The MFMA writes row m of a 32-row result to lane group kg = (m >> 2) & 1, element 4 (m >> 3) + (m & 3).
 // Giving MFMA row m the headdim column pi(m) = 16 kg + element makes every lane own 16 consecutive
 // columns of its token: 32 contiguous bytes of y per lane instead of four 8-byte pieces.
+__device__ __forceinline__ int swap_row(int m) { return (m & ~12) | (m & 4) << 1 | (m & 8) >> 1; }
 __device__ __forceinline__ int pi_of_row(int m) { return 16 * ((m >> 2) & 1) + 4 * (m >> 3) + (m & 3); }
 
 // One wave per (head, half of headdim): the wave owns a 128 x 32 slice of the state (64
@@ -1013,9 +1038,7 @@ __device__ __forceinline__ void scan_walk(const ScanParams &p, const SeqView &sv
 #pragma unroll
   for (int k = 0; k < kCPieces; ++k) {
     const int c = tid + kThr * k;
-    // C columns are permuted inside each group of 16 so that one 16-byte read yields
-    // n-offsets {4kg..4kg+3, 8+4kg..8+4kg+3}
-    lds_c[k] = (c >> 4) * kCStride + 16 * ((c & 15) >> 1) + 4 * (c & 1);
+    lds_c[k] = (c >> 4) * kCStride + 8 * (c & 15);
   }
   // Xm^T: column 8cg + c of the half goes to row pi^-1(8cg + c) = 16 (cg & 1) + 4 (cg >> 1) + 8 (c >> 2) + (c & 3)
   uint16_t *const xm_dst = myX + (16 * (cg & 1) + 4 * (cg >> 1)) * kXStride + 4 * tg;
@@ -1043,9 +1066,7 @@ __device__ __forceinline__ void scan_walk(const ScanParams &p, const SeqView &sv
     } else if constexpr (!kStatesOnly) {
       const int c = piece - kBtPieces, k = c - kCPieces;
       if (k < 0) {
-        uint16_t *d2 = &sC[buf][lds_c[c]];
-        *reinterpret_cast<u32x2 *>(d2) = mk2(r_c[c].x, r_c[c].y);
-        *reinterpret_cast<u32x2 *>(d2 + 8) = mk2(r_c[c].z, r_c[c].w);
+        *reinterpret_cast<u32x4 *>(&sC[buf][lds_c[c]]) = r_c[c];
       } else {
         *reinterpret_cast<u32x4 *>(&sG[buf][lds_g[k]]) = r_g[k];
       }
@@ -1076,7 +1097,9 @@ __device__ __forceinline__ void scan_walk(const ScanParams &p, const SeqView &sv
     }
   };
 
-  // ---- state slice: Hacc[nt][i] = Ht^T[n = 32nt + (i/4)*8 + 4kg + i%4][headdim column 32 ph + pi_of_row(r)] ----
+  // ---- state slice: Hacc[nt][i] = Ht^T[n = 32nt + (i/8)*16 + 8kg + i%8][headdim column 32 ph + pi_of_row(r)]: the full
+  //      kernel reads the rows of B^T in the order that leaves eight consecutive state columns in a lane (swap_row), which is how
+  //      C's 16-byte pieces hold them.  (The states-only pass reads them as they come: n = 32nt + (i/4)*8 + 4kg + i%4.) ----
   f32x16 Hacc[4];
   u32x4 hraw[16];          // the entering state as loaded (full kernel)
   bool has_state = false;  // uniform over the workgroup
@@ -1131,7 +1154,7 @@ __device__ __forceinline__ void scan_walk(const ScanParams &p, const SeqView &sv
   const uint32_t a_c = r * kCStride + 8 * kg;    // + 32 rows for the second token half, + 16 kk
   const uint32_t a_g0 = r * kGLowStride + 8 * kg;                     // token r, + 16 q (q < 2)
   const uint32_t a_g1 = 32 * kGLowStride + r * kGStride + 8 * kg;     // token 32 + r, + 16 q
-  const uint32_t a_bt = r * kBtStride + 8 * kg;  // + 32 nt rows, + 16 q
+  const uint32_t a_bt = (kStatesOnly ? r : swap_row(r)) * kBtStride + 8 * kg;  // + 32 nt rows, + 16 q
   const uint16_t *const raw_src = myRaw + r * kRawStride + 16 * kg;   // + 32 rows for the second half, + 8 c
   uint16_t *const raw_rw = myRaw + r * kRawStride + 16 * kg;
   // output rows.  Half rows: lane i handles 16 bytes of token i/4 (+16k) of the wave's own half.  Whole
@@ -1306,7 +1329,7 @@ __device__ __forceinline__ void scan_walk(const ScanParams &p, const SeqView &sv
         for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
           for (int i4 = 0; i4 < 4; ++i4) {
-            const f32x4 v = *reinterpret_cast<const f32x4 *>(turn + pi_of_row(r) * kTurnStride + 32 * nt + 8 * i4 + 4 * kg);
+            const f32x4 v = *reinterpret_cast<const f32x4 *>(turn + pi_of_row(r) * kTurnStride + 32 * nt + 16 * (i4 >> 1) + 8 * kg + 4 * (i4 & 1));
             Hacc[2 * half + nt][4 * i4 + 0] = v.x;
             Hacc[2 * half + nt][4 * i4 + 1] = v.y;
             Hacc[2 * half + nt][4 * i4 + 2] = v.z;
@@ -1340,7 +1363,7 @@ __device__ __forceinline__ void scan_walk(const ScanParams &p, const SeqView &sv
             for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
               for (int i4 = 0; i4 < 4; ++i4) {
-                const f32x4 v = *reinterpret_cast<const f32x4 *>(turn + pi_of_row(r) * kTurnStride + 32 * nt + 8 * i4 + 4 * kg);
+                const f32x4 v = *reinterpret_cast<const f32x4 *>(turn + pi_of_row(r) * kTurnStride + 32 * nt + 16 * (i4 >> 1) + 8 * kg + 4 * (i4 & 1));
                 Hacc[2 * half + nt][4 * i4 + 0] += wgt * v.x;
                 Hacc[2 * half + nt][4 * i4 + 1] += wgt * v.y;
                 Hacc[2 * half + nt][4 * i4 + 2] += wgt * v.z;
@@ -1446,8 +1469,7 @@ __device__ __forceinline__ void scan_walk(const ScanParams &p, const SeqView &sv
           go[0][1] = lds16(tG + a_g1);
           go[0][0] = lds16(tG + a_g0);
         }
-        // bf16 copy of a 16-column slice of Ht as an MFMA operand: slice 2nt+u covers n = 32nt + 16u +
-        // {4kg..4kg+3, 8+4kg..8+4kg+3} (the order in which sC stores each group of 16 columns)
+        // bf16 copy of a 16-column slice of Ht as an MFMA operand: slice 2nt+u covers n = 32nt + 16u + 8kg + {0..7}
         f32x16 &hv = Hacc[kk >> 1];
         const int u = kk & 1;
         Operand ho;
@@ -1714,7 +1736,7 @@ __device__ __forceinline__ void scan_walk(const ScanParams &p, const SeqView &sv
 #pragma unroll
         for (int i4 = 0; i4 < 4; ++i4) {
           const f32x16 &t = Hacc[2 * half + nt];
-          *reinterpret_cast<f32x4 *>(turn + pi_of_row(r) * kTurnStride + 32 * nt + 8 * i4 + 4 * kg) =
+          *reinterpret_cast<f32x4 *>(turn + pi_of_row(r) * kTurnStride + 32 * nt + 16 * (i4 >> 1) + 8 * kg + 4 * (i4 & 1)) =
               f32x4{t[4 * i4 + 0], t[4 * i4 + 1], t[4 * i4 + 2], t[4 * i4 + 3]};
         }
 #pragma unroll
@@ -1755,6 +1777,568 @@ __device__ __forceinline__ bool walk_meets_steep_block(const ScanParams &p, cons
   return __builtin_amdgcn_ballot_w64(lowest < 0.f) != 0;
 }
 
+// ---- the full scan with two heads per workgroup -------------------------------------------------------
+// Two waves per head as above; four of these, one to a SIMD, compute, and the other wave of each SIMD feeds them.
+//   - Everything a block needs -- the shared tiles, x, the decay record -- travels straight from memory into LDS
+//     (load_to_lds) at the feeding waves' request: no registers, no LDS writes, no waits but the feeders' own, one per
+//     block.  A wave that makes such a request stands still for 95 cycles, a load into registers 60 (measured with
+//     requests 64 vector instructions apart): with the fourteen requests and four stores of a block among its own instructions a
+//     computing wave took FEEDA cycles a block, without them FEEDB.
+//   - The feeders also scale x and turn it for the matrix instructions (without that FEEDC).
+//   - The tiles and the record of the next block arrive during a block, in the buffer of a pair that it does not use.  A
+//     block of x goes through one of three buffers: it arrives until the middle of the block before its own, when the feeder that
+//     requested it turns it into Xm^T; it serves the skip term of its block and is replaced, in place, by y; and
+//     the feeders store y in whole rows in the block after, before they request x into the same place.
+//   - So a block has one barrier.
+//   - A group of matrix instructions finds its LDS operands two groups ahead of it, and the vector work of a block is
+//     spread so that every group has some.
+// (The matrix instructions work on architectural registers, see the build flags: with the state in accumulation registers
+// a block moved 160 of them, 8 cycles each.)
+// LDS, in bytes: [x 3 x 16384][tiles 2 x 38912: C, B^T, G rows 32..63, G rows 0..31][Xm^T 2 x 16384][records 2 x 1024].
+struct PairLds {
+  static constexpr int kX = 0, kXBuf = 2 * kBlk * kP * 2, kTiles = 3 * kXBuf, kBt = kBlk * kN * 2, kGHigh = 2 * kBt,
+                       kGLow = kGHigh + 32 * kBlk * 2, kTileBuf = kGLow + 32 * 32 * 2, kXm = kTiles + 2 * kTileBuf,
+                       kXmHead = kP * kBlk * 2, kRec = kXm + 4 * kXmHead, kRecBuf = 1024, kBytes = kRec + 2 * kRecBuf;
+};
+static_assert(PairLds::kBytes <= 160 * 1024 && PairLds::kTiles % 256 == 0 && PairLds::kTileBuf % 256 == 0 && PairLds::kXm % 256 == 0,
+              "fits the LDS of a CU; a row of C, two of B^T and G, four of x and of G's short rows cover the 64 banks");
+
+template <typename T>
+using lds_as = __attribute__((address_space(3))) T;
+typedef lds_as<uint8_t> lds_u8;
+
+// Where the 16-byte pieces of a row lie.  Sixteen lanes that read the same piece of sixteen consecutive rows (the
+// operands of the matrix instructions) have to meet sixteen different places of the 256 bytes that the banks hold:
+//   C, 256-byte rows: piece c of row t at place c ^ (t & 15);
+//   B^T, G rows 32..63 and Xm^T, 128-byte rows: c ^ (t / 2 & 7) (Xm^T also ^ 4 in its upper half, for the writes);
+//   G rows 0..31, 64-byte rows of the 32 columns that matter: c ^ (t / 4 & 3);
+//   x, per head two halves of 32 tokens, each two halves ph of 32 columns: of the latter token t's piece c at place 64 (t / 16 & 1) +
+//     16 (t & 3) + 4 ((t / 4 & 3) ^ 2 ph) + (c ^ (t & 3)), which also serves the four tokens per lane of the turn and whole rows of y.
+
+// The feeding waves, 4..7: feeder w serves head w / 2 and, of x and y, tokens 32 (w & 1) .. + 31.
+template <int kYMode>
+__device__ __forceinline__ void pair_feed(const ScanParams &p, const SeqView &sv, lds_u8 *const lds) {
+  using L = PairLds;
+  const uint32_t lds_at = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds));
+  const int tid = threadIdx.x & 255, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int hw = wave >> 1, ph = wave & 1;
+  const int g = sv.col / p.cpg, slot = (sv.col % p.cpg) * 2 + hw;
+  const bool live = slot < p.hpg;
+  const int h = g * p.hpg + min(slot, p.hpg - 1);
+  const bool plain = p.vp.tok0 == nullptr;
+  const size_t tile0 = plain ? (sv.blk0 * p.G + static_cast<size_t>(g) * sv.blk_stride) : (g * sv.blk_stride + sv.blk0);
+  const int hrec = h / p.pdiv;
+  const size_t rec0 = plain ? (sv.blk0 * p.Hrec + static_cast<size_t>(hrec) * sv.blk_stride) : (hrec * sv.blk_stride + sv.blk0);
+  const int jb0 = min(sv.nb, sv.sg * sv.seg_blocks), jb1 = min(sv.nb, jb0 + sv.seg_blocks), jlast = jb1 - 1;
+  const uint32_t xrow = static_cast<uint32_t>(p.H) * (kP * 2), crow = static_cast<uint32_t>(p.G) * (kN * 2);
+  const uint32_t xbytes = sv.len * xrow;
+  const uint32_t cbytes = sv.len > 0 ? sv.len * crow - static_cast<uint32_t>(g) * (kN * 2) : 0;
+  const uint8_t *const xb = p.x + sv.tok0 * xrow;
+  uint8_t *const yb = p.y + sv.tok0 * xrow;
+  const uint8_t *const cb = p.C + (sv.tok0 * p.G + g) * (kN * 2);
+  const uint8_t *const btb = p.Btr + tile0 * (kN * kBlk * 2), *const gb = p.Gd + tile0 * (kBlk * kBlk * 2);
+  const float *const prep_bh = p.prep + rec0 * kRec;
+
+  // ---- requests: per-lane offsets that never change, descriptors that start at the block.  Of x and C a wave fetches four
+  //      times 1024 bytes to consecutive places (see load_to_lds4) from rows that may be nearer to each other than that: their
+  //      descriptors start 3072 bytes earlier, and all that is asked of them lies beyond these ----
+  constexpr uint32_t kEarly = 3072;
+  uint32_t vx[4], vc[4];  // x: 16 tokens of one half of headdim each, the first half's first
+#pragma unroll
+  for (int o = 0; o < 4; ++o) {
+    const int i = lane >> 4, half = o >> 1, t = 32 * ph + 16 * (o & 1) + 4 * ((lane >> 2 & 3) ^ 2 * half) + i;
+    vx[o] = static_cast<uint32_t>(t) * xrow + static_cast<uint32_t>(h) * (kP * 2) + 64 * half + 16 * ((lane & 3) ^ i) + (kEarly - 1024 * o);
+    const int row = 16 * wave + 4 * o + (lane >> 4);
+    vc[o] = static_cast<uint32_t>(row) * crow + 16 * ((lane ^ row) & 15) + (kEarly - 1024 * o);
+  }
+  // B^T: rows 32 wave + 8 k + lane / 8; the places of consecutive k differ by an exchange of the halves of a row
+  uint32_t vb[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) vb[k] = static_cast<uint32_t>(32 * wave + (lane >> 3)) * (kBlk * 2) + 16 * ((lane ^ (lane >> 4) ^ 4 * k) & 7);
+  const uint32_t vt = static_cast<uint32_t>(tid >> 3) * (kBlk * 2) + 16 * ((tid ^ (tid >> 4)) & 7);
+  // The tenth request of a wave: waves 0 and 1 fetch a half of G's short rows each, waves 2 and 3 (both the same) the record
+  // entries that the two heads need next: 32 lanes the input factors of block jb + 2, 32 the output-row factors of jb + 1.
+  const bool fetches_g = wave < 2;
+  const int h_first = g * p.hpg + min((sv.col % p.cpg) * 2, p.hpg - 1), h_second = g * p.hpg + min((sv.col % p.cpg) * 2 + 1, p.hpg - 1);
+  const uint32_t head_step = static_cast<uint32_t>((h_second / p.pdiv - h_first / p.pdiv) * sv.blk_stride) * (kRec * 4);
+  const float *const rec_first = prep_bh - static_cast<ptrdiff_t>(hrec - h_first / p.pdiv) * static_cast<ptrdiff_t>(sv.blk_stride) * kRec;
+  const uint32_t vg = fetches_g ? static_cast<uint32_t>(16 * wave + (lane >> 2)) * (kBlk * 2) + 16 * ((lane ^ (lane >> 4)) & 3)
+                                : ((lane & 16) ? head_step : 0u) + (lane < 32 ? (kRec + kBlk) * 4u : 0u) + 16 * (lane & 15);
+  // this wave's ten requests of block jb's tiles (and records); `no` block: empty descriptors, which fetch nothing
+  auto fetch_tiles = [&](int jb, int buf, bool no) __attribute__((always_inline)) {
+    const uint32_t to = lds_at + L::kTiles + buf * L::kTileBuf;
+    const uint8_t *const gt = gb + static_cast<size_t>(jb) * (kBlk * kBlk * 2);
+    load_to_lds4(raw_rsrc(cb + static_cast<size_t>(jb) * kBlk * crow - kEarly, no ? 0 : cbytes - static_cast<uint32_t>(jb) * kBlk * crow + kEarly),
+                 vc[0], vc[1], vc[2], vc[3], to + wave * 4096);
+    load_to_lds4(raw_rsrc(btb + static_cast<size_t>(jb) * (kN * kBlk * 2), no ? 0 : kN * kBlk * 2), vb[0], vb[1], vb[0], vb[1], to + L::kBt + wave * 4096);
+    load_to_lds(raw_rsrc(gt, no ? 0 : kBlk * kBlk * 2), vt, 32 * kBlk * 2, to + L::kGHigh + wave * 1024);
+    load_to_lds(raw_rsrc(fetches_g ? gt : reinterpret_cast<const uint8_t *>(rec_first + static_cast<size_t>(jb) * kRec),
+                         no ? 0 : fetches_g ? kBlk * kBlk * 2u : head_step + static_cast<uint32_t>(sv.nb - jb) * (kRec * 4)),
+                vg, 0, fetches_g ? to + L::kGLow + wave * 1024 : lds_at + L::kRec + buf * L::kRecBuf);
+  };
+  auto fetch_x = [&](int jb, uint32_t xbuf, bool no) __attribute__((always_inline)) {
+    load_to_lds4(raw_rsrc(xb + static_cast<size_t>(jb) * kBlk * xrow - kEarly, no ? 0 : xbytes - static_cast<uint32_t>(jb) * kBlk * xrow + kEarly),
+                 vx[0], vx[1], vx[2], vx[3], lds_at + L::kX + xbuf + wave * 4096);
+  };
+  auto y_rsrc = [&](int jb, bool no) { return make_rsrc(yb + static_cast<size_t>(jb) * kBlk * xrow, live && !no ? xbytes - static_cast<uint32_t>(jb) * kBlk * xrow : 0u); };
+
+  auto lds16 = [&](uint32_t at) {
+    Operand o;
+    o.q = *(lds_as<u32x4> *)(lds + at);
+    return o;
+  };
+  // whole rows of y: tokens 32ph + 4 (lane / 8) + k, piece lane % 8, of which 0..3 come from the head's first wave
+  const int y_tile = (lane & 7) >> 2;
+  auto row_at = [&](int k) {
+    return L::kX + wave * 4096 + y_tile * 2048 + (lane >> 5) * 1024 + k * 256 + (((lane >> 3) & 3) ^ 2 * y_tile) * 64 + ((lane & 3) ^ k) * 16;
+  };
+  const uint32_t vy = static_cast<uint32_t>(32 * ph + 4 * (lane >> 3)) * xrow + static_cast<uint32_t>(h) * (kP * 2) + 16 * (lane & 7);
+  u32x4 yo[4];
+  auto read_y = [&](uint32_t xbuf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) yo[k] = lds16(row_at(k) + xbuf).q;
+  };
+  auto add_y = [&](Rsrc ry) __attribute__((always_inline)) {  // kYAdd: to what y holds so far
+    u32x4 prev[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) prev[k] = buf_load16(ry, vy + static_cast<uint32_t>(k) * xrow, 0);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+      for (int w = 0; w < 4; ++w)
+        yo[k][w] = pack2(bf_lo(yo[k][w]) + bf_lo(prev[k][w]), bf_hi(yo[k][w]) + bf_hi(prev[k][w]));
+  };
+  auto store_y = [&](Rsrc ry, int k) __attribute__((always_inline)) {
+    buf_store16<kYMode == kYStream ? kStreamStore : 0>(ry, vy + static_cast<uint32_t>(k) * xrow, yo[k]);
+  };
+
+  // the turn: this lane has tokens 32ph + 4tg + i, columns 8cg + c, which go to row pi^-1 = 16 (cg & 1) + 4 (cg / 2 & 1) + 8 (c / 4) +
+  // (c & 3) of their half (cg / 4)
+  const int cg = lane & 7, tg = lane >> 3, half = cg >> 2;
+  uint32_t a_turn[4], a_xmw[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    a_turn[i] = L::kX + wave * 4096 + half * 2048 + (tg >> 2) * 1024 + i * 256 + ((tg & 3) ^ 2 * half) * 64 + ((cg & 3) ^ i) * 16;
+    const int row = 16 * (cg & 1) + 4 * (cg >> 1 & 1) + 8 * (i >> 1) + 2 * (i & 1);  // (of columns 4 (i / 2) + 2 (i & 1) and the next)
+    a_xmw[i] = L::kXm + (2 * hw + half) * (L::kXmHead / 2) + row * (kBlk * 2) + 16 * ((4 * ph + (tg >> 1)) ^ (row >> 1 & 7) ^ (row >> 4) * 4) + 8 * (tg & 1);
+  }
+  // x times the input factors (of the record buffer `rec`) to Xm^T: four tokens per 8-byte write
+  u32x4 xr[4], f;
+  auto read_turn = [&](uint32_t xbuf, uint32_t rec) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) xr[i] = lds16(a_turn[i] + xbuf).q;
+    f = lds16(L::kRec + rec + hw * 256 + ph * 128 + 16 * tg).q;
+  };
+  auto turn = [&](uint32_t xm) __attribute__((always_inline)) {
+    const float f0 = __uint_as_float(f.x), f1 = __uint_as_float(f.y), f2 = __uint_as_float(f.z), f3 = __uint_as_float(f.w);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const uint32_t a0 = xr[0][c >> 1], a1 = xr[1][c >> 1], a2 = xr[2][c >> 1], a3 = xr[3][c >> 1];
+      lds_as<u32x2> *const dst = (lds_as<u32x2> *)(lds + a_xmw[c >> 1] + xm + (c & 1) * (kBlk * 2));
+      if (c & 1)
+        *dst = mk2(pack2(f0 * bf_hi(a0), f1 * bf_hi(a1)), pack2(f2 * bf_hi(a2), f3 * bf_hi(a3)));
+      else
+        *dst = mk2(pack2(f0 * bf_lo(a0), f1 * bf_lo(a1)), pack2(f2 * bf_lo(a2), f3 * bf_lo(a3)));
+    }
+  };
+  // ---- prologue: the first block's tiles, input factors and x, the second block's x ----
+  if (jb0 < jb1) {
+    fetch_x(jb0, 0, false);
+    // (the factors of the first block, which every feeder fetches for itself: the records come a block behind them)
+    const uint32_t vf = ((lane & 16) ? head_step : 0u) + kBlk * 4u + 16 * (lane & 15);
+    load_to_lds(raw_rsrc(rec_first + static_cast<size_t>(jb0) * kRec, head_step + static_cast<uint32_t>(sv.nb - jb0) * (kRec * 4)), vf, 0,
+                lds_at + L::kRec + L::kRecBuf);
+    fetch_tiles(jb0, 0, false);
+    fetch_x(min(jb0 + 1, jlast), L::kXBuf, jb0 == jlast);
+    asm volatile("s_waitcnt vmcnt(14)" ::: "memory");  // (tiles and the second block's x)
+    read_turn(0, L::kRecBuf);
+    turn(0);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  }
+  __syncthreads();
+  uint32_t x_prev = 2 * L::kXBuf, x_cur = 0, x_next = L::kXBuf;  // the buffers of blocks jb - 1 (and then jb + 2), jb, jb + 1
+  for (int jb = jb0; jb < jb1; ++jb) {
+    const int rel = jb - jb0;
+    const uint32_t par = rel & 1;
+    const bool more = jb < jlast, more2 = jb + 1 < jlast;
+    const Rsrc ry = y_rsrc(jb - (rel > 0 ? 1 : 0), rel == 0);
+    read_y(x_prev);
+    fetch_tiles(more ? jb + 1 : jlast, par ^ 1, !more);
+    if constexpr (kYMode == kYAdd) add_y(ry);
+    asm volatile("" : "+v"(yo[0]), "+v"(yo[1]), "+v"(yo[2]), "+v"(yo[3])::"memory");  // (read before x is requested into its place)
+    asm volatile("s_waitcnt vmcnt(14)" ::: "memory");  // x of the next block; younger: the stores before, tiles
+    read_turn(x_next, par * L::kRecBuf);
+    fetch_x(more2 ? jb + 2 : jlast, x_prev, !more2);
+    turn((par ^ 1) * (2 * L::kXmHead));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) store_y(ry, k);
+    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");  // the next block's tiles and record; younger: x, stores
+    __syncthreads();  // ... and its Xm^T are visible, this block's may be overwritten
+    const uint32_t t = x_prev;
+    x_prev = x_cur;
+    x_cur = x_next;
+    x_next = t;
+  }
+  if (jb0 < jb1) {
+    const Rsrc ry = y_rsrc(jlast, false);
+    read_y(x_prev);
+    if constexpr (kYMode == kYAdd) add_y(ry);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) store_y(ry, k);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (no request may outlive the workgroup's LDS)
+}
+
+// The computing waves, 0..3: wave w has half w & 1 of headdim of head w / 2.  Returns false, having done nothing, if the common
+// walk meets a steep block.
+template <bool kMixed>
+__device__ __forceinline__ bool pair_walk(const ScanParams &p, const SeqView &sv, lds_u8 *const lds) {
+  using L = PairLds;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  const int hw = wave >> 1, ph = wave & 1;
+  const int g = sv.col / p.cpg, slot = (sv.col % p.cpg) * 2 + hw;
+  const bool live = slot < p.hpg;
+  const int h = g * p.hpg + min(slot, p.hpg - 1);
+  const bool plain = p.vp.tok0 == nullptr;
+  const int hrec = h / p.pdiv;
+  const size_t rec0 = plain ? (sv.blk0 * p.Hrec + static_cast<size_t>(hrec) * sv.blk_stride) : (hrec * sv.blk_stride + sv.blk0);
+  const size_t slot0 = plain ? (sv.slot0 * p.H + static_cast<size_t>(h) * sv.slot_stride) : (h * sv.slot_stride + sv.slot0);
+  const size_t bh = static_cast<size_t>(sv.b) * p.H + h;
+  const int r = lane & 31, kg = lane >> 5;
+  const int jb0 = min(sv.nb, sv.sg * sv.seg_blocks), jb1 = min(sv.nb, jb0 + sv.seg_blocks), jlast = jb1 - 1;
+  const float *const prep_bh = p.prep + rec0 * kRec;
+
+  // ---- LDS addresses of this lane, in bytes ----
+  auto lds16 = [&](uint32_t at) {
+    Operand o;
+    o.q = *(lds_as<u32x4> *)(lds + at);
+    return o;
+  };
+  const int br = swap_row(r);
+  const uint32_t a_c = L::kTiles + r * (kN * 2) + 16 * (kg ^ (r & 15));                         // ^ 32 kk, + 32 rows
+  const uint32_t a_bt = L::kTiles + L::kBt + br * (kBlk * 2) + 16 * (kg ^ (br >> 1 & 7));       // ^ 32 q, + 32 nt rows
+  const uint32_t a_g1 = L::kTiles + L::kGHigh + r * (kBlk * 2) + 16 * (kg ^ (r >> 1 & 7));      // token 32 + r, ^ 32 q
+  const uint32_t a_g0 = L::kTiles + L::kGLow + r * 64 + 16 * (kg ^ (r >> 2 & 3));               // token r, ^ 32 q (q < 2)
+  const uint32_t a_xm = L::kXm + (2 * hw + ph) * (L::kXmHead / 2) + r * (kBlk * 2) + 16 * (kg ^ (r >> 1 & 7) ^ (r >> 4) * 4);  // ^ 32 q
+  // x and y in output layout: token r (+ 32: 4096 bytes on), columns 16kg + 8c
+  const uint32_t a_out = L::kX + hw * 8192 + ph * 2048 + (r >> 4) * 1024 + (r & 3) * 256 + ((r >> 2 & 3) ^ 2 * ph) * 64;
+  auto out_at = [&](int c) { return a_out + 16 * ((2 * kg + c) ^ (r & 3)); };
+  // Where a wave turns 32 x 64 elements of its state between the accumulators' layout and whole rows: in the second
+  // tile buffer, before its first tiles are requested and after its last ones have been used.
+  constexpr int kTurnStride = 64 + 4;  // floats
+  static_assert(4 * 32 * kTurnStride * sizeof(float) <= L::kTileBuf, "four turning tiles fit in a tile buffer");
+  lds_as<float> *const turn = (lds_as<float> *)(lds + L::kTiles + L::kTileBuf) + wave * (32 * kTurnStride);
+
+  // ---- prologue: everything it needs from memory is requested before any of it is waited for ----
+  auto factor_ptr = [&](int jb) { return prep_bh + static_cast<size_t>(jb) * kRec + 2 * kBlk; };
+  float Dh = p.D == nullptr ? 0.f : p.D[hrec];
+  u32x4 hraw[16];
+  bool has_state = false;  // uniform over the workgroup
+  auto load_state = [&](const float *base, uint32_t row_floats, uint32_t valid) __attribute__((always_inline)) {
+    const Rsrc rs = make_rsrc(base != nullptr ? base : p.prep, base != nullptr ? ((kP - 1) * row_floats + valid) * 4u : 0u);
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const uint32_t row = 32 * ph + 4 * (k & 7) + (lane >> 4), n0 = 64 * (k >> 3) + 4 * (lane & 15);
+      hraw[k] = buf_load16(rs, n0 < valid ? (row * row_floats + n0) * 4u : 0xFFFFFF00u, 0);
+    }
+  };
+  {
+    // (a sequence of one segment, and the first of a folded chain, start from h0 itself; see scan_walk)
+    const float *hbase = nullptr;
+    uint32_t hrow = kN, hvalid = kN;
+    if (sv.S > 1 && !(p.fold && sv.sg == 0)) {
+      hbase = p.Hin + (slot0 + static_cast<size_t>(sv.sg) * p.parts) * (kP * kN);
+    } else if (p.h0 != nullptr) {
+      hbase = p.h0 + bh * kP * p.ns.width + p.ns.off;
+      hrow = static_cast<uint32_t>(p.ns.width);
+      hvalid = static_cast<uint32_t>(p.ns.valid);
+    }
+    has_state = hbase != nullptr;
+    load_state(hbase, hrow, hvalid);
+  }
+  // {middle -> end, log2 of the total decay, start -> middle, middle -> middle of the next block} of 64 blocks, a lane each
+  f32x4 facv = {0.f, 0.f, 0.f, 0.f};
+  if (jb0 < jb1) {
+    facv = *reinterpret_cast<const f32x4 *>(factor_ptr(min(jb0 + lane, jlast)));
+    if constexpr (!kMixed) {  // whether a block of the walk is steep: its record's entry 130 is negative
+      float lowest = facv.z;
+      for (int j = jb0 + 64; j < jb1; j += 64)
+        if (j + lane < jb1) lowest = fminf(lowest, factor_ptr(j + lane)[2]);
+      if (__builtin_amdgcn_ballot_w64(lowest < 0.f) != 0) return false;
+    }
+  }
+
+  // ---- state slice: Hacc[nt][i] = Ht^T[n = 32nt + (i/8)*16 + 8kg + i%8][headdim column 32 ph + pi_of_row(r)]: the rows of
+  //      B^T are read in the order that leaves eight consecutive state columns in a lane (swap_row), which is how
+  //      C's 16-byte pieces hold them ----
+  f32x16 Hacc[4] = {};
+  auto add_state = [&](float wgt, bool first) __attribute__((always_inline)) {
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        *(lds_as<u32x4> *)(turn + (4 * k + (lane >> 4)) * kTurnStride + 4 * (lane & 15)) = hraw[8 * half + k];
+#pragma unroll
+      for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) {
+          const f32x4 v = *(lds_as<f32x4> *)(turn + pi_of_row(r) * kTurnStride + 32 * nt + 16 * (i4 >> 1) + 8 * kg + 4 * (i4 & 1));
+#pragma unroll
+          for (int e = 0; e < 4; ++e) Hacc[2 * half + nt][4 * i4 + e] = first ? v[e] : Hacc[2 * half + nt][4 * i4 + e] + wgt * v[e];
+        }
+    }
+  };
+  if (has_state) {
+    add_state(1.f, true);
+    if (p.fold && sv.sg >= 1) {  // (the earlier pieces' local end states and h0, see scan_walk)
+      float log2_decay = 0.f;
+      for (int k = sv.sg * p.parts - 1; k >= 0; --k) {
+        log2_decay += p.seg_decay[slot0 + k];
+        if (k == 0 && p.h0 == nullptr) break;
+        load_state(k > 0 ? p.Hin + (slot0 + k) * (kP * kN) : p.h0 + bh * kP * p.ns.width + p.ns.off,
+                   k > 0 ? kN : static_cast<uint32_t>(p.ns.width), k > 0 ? kN : static_cast<uint32_t>(p.ns.valid));
+        add_state(fast_exp2(log2_decay), false);
+      }
+    }
+  }
+  float pending = 1.f;  // as in scan_walk: what the accumulators are still owed
+  bool steep_cur = false;
+  auto of_block = [&](float v, int rel) { return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), rel & 63)); };
+  if (jb0 < jb1) {
+    pending = of_block(facv.z, 0);
+    if constexpr (kMixed) {
+      steep_cur = __float_as_int(pending) < 0;
+      if (steep_cur) pending = 1.f;
+    }
+  }
+
+  wait_all_loads();
+  // (pinned as arrived: the waits for them would otherwise stand at their first use in the loop)
+  asm volatile("" : "+v"(Dh), "+v"(facv)::"memory");
+  __syncthreads();
+
+  // One block; par: the parity of its number in the walk (a compile-time constant), which is that of its buffers but x's.
+  uint32_t x_cur = 0;
+  auto body = [&](int par, int jb, auto steep_tag) __attribute__((always_inline)) {
+    constexpr bool kSteep = decltype(steep_tag)::value;
+    static_assert(kMixed || !kSteep, "a steep block is only met in the mixed walk");
+    const int rel = jb - jb0;
+    const uint32_t tile = par * L::kTileBuf, rec = L::kRec + par * L::kRecBuf, xm = par * (2 * L::kXmHead);
+    const bool more = jb < jlast;
+
+    // ---- phase 1: Y^T[row][l] = sum_n Ht[row][n] C[l][n]  +  sum_{s<=l} Xm[s][row] G[l][s] ----
+    Operand co[3][2], go0[2], go1[4], xo[4], bto[2][4], xe[4];
+    auto read_c = [&](int kk) __attribute__((always_inline)) {
+      co[kk % 3][0] = lds16((a_c ^ (32 * kk)) + tile);
+      co[kk % 3][1] = lds16((a_c ^ (32 * kk)) + tile + 32 * kN * 2);
+    };
+    auto read_bt = [&](int q, int nt) __attribute__((always_inline)) { bto[q & 1][nt] = lds16((a_bt ^ (32 * q)) + tile + 32 * nt * kBlk * 2); };
+    read_c(0);
+    read_c(1);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) xo[q] = lds16((a_xm ^ (32 * q)) + xm);
+    float rowf[2] = {*(lds_as<float> *)(lds + rec + 512 + hw * 256 + 4 * r), *(lds_as<float> *)(lds + rec + 512 + hw * 256 + 128 + 4 * r)};
+    float dt_t = 0.f, cs_t = 0.f;  // steep: step size and inclusive prefix sum of dt*A*log2(e) of token `lane`
+    if constexpr (kSteep) {
+      const float alog = of_block(facv.w, rel);
+      dt_t = kg ? rowf[1] : rowf[0];
+      cs_t = cut_step(dt_t, alog) * alog;
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const float up = __shfl_up(cs_t, off, 64);
+        if (lane >= off) cs_t += up;
+      }
+    }
+    f32x16 Y[2] = {};
+    // bf16 copy of a 16-column slice of Ht as a matrix operand, n = 16 kk + 8kg + {0..7}
+    Operand ho[2];
+    auto convert = [&](int kk) __attribute__((always_inline)) {
+      f32x16 &hv = Hacc[kk >> 1];
+      const int u = kk & 1;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        hv[8 * u + 2 * k] *= pending;
+        hv[8 * u + 2 * k + 1] *= pending;
+        ho[kk & 1].u[k] = pack2(hv[8 * u + 2 * k], hv[8 * u + 2 * k + 1]);
+      }
+    };
+    convert(0);
+    __builtin_amdgcn_sched_barrier(0);
+    // (Behind every matrix instruction stands the vector work that is done while it runs: two in a row make the wave wait
+    // 28 cycles for the pipe.)
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) {
+      if (kk < 6) {
+        read_c(kk + 2);
+      } else if (!kSteep) {
+        go1[2 * (kk - 6)] = lds16((a_g1 ^ (64 * (kk - 6))) + tile);
+        go1[2 * (kk - 6) + 1] = lds16((a_g1 ^ (64 * (kk - 6) + 32)) + tile);
+        go0[kk - 6] = lds16((a_g0 ^ (32 * (kk - 6))) + tile);
+      }
+      Y[0] = mfma(ho[kk & 1], co[kk % 3][0], Y[0]);
+      __builtin_amdgcn_sched_barrier(0);
+      if (kk < 7) convert(kk + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      Y[1] = mfma(ho[kk & 1], co[kk % 3][1], Y[1]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // ---- the masked product ----
+    if constexpr (kSteep) {
+      const float csl[2] = {__shfl(cs_t, r, 64), __shfl(cs_t, 32 + r, 64)};
+      const float s0 = fast_exp2(csl[0]), s1 = fast_exp2(csl[1]);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        Y[0][i] *= s0;
+        Y[1][i] *= s1;
+      }
+      const int col = pi_of_row(r);  // this lane's column of the raw rows
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        float cs_s[8], dt_s[8];
+        Operand xs;  // raw x^T[row r][s = 16q + 8kg ..]
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const int src = 16 * q + 8 * kg + j;
+          cs_s[j] = __shfl(cs_t, src, 64);
+          dt_s[j] = __shfl(dt_t, src, 64);
+        }
+        auto raw_at = [&](int t) {
+          return static_cast<uint32_t>(*(lds_as<uint16_t> *)(
+              lds + L::kX + x_cur + hw * 8192 + (t >> 5) * 4096 + ph * 2048 + (t >> 4 & 1) * 1024 + (t & 3) * 256 + ((t >> 2 & 3) ^ 2 * ph) * 64 + ((col >> 3) ^ (t & 3)) * 16 + (col & 7) * 2));
+        };
+#pragma unroll
+        for (int k = 0; k < 4; ++k) xs.u[k] = raw_at(16 * q + 8 * kg + 2 * k) | raw_at(16 * q + 8 * kg + 2 * k + 1) << 16;
+#pragma unroll
+        for (int lt = (q < 2 ? 0 : 1); lt < 2; ++lt) {
+          const Operand gq = lds16(lt ? (a_g1 ^ (32 * q)) + tile : (a_g0 ^ (32 * q)) + tile);
+          Operand gh;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const float w0 = dt_s[2 * k] * fast_exp2(fminf(csl[lt] - cs_s[2 * k], 0.f));
+            const float w1 = dt_s[2 * k + 1] * fast_exp2(fminf(csl[lt] - cs_s[2 * k + 1], 0.f));
+            gh.u[k] = pack2(bf_lo(gq.u[k]) * w0, bf_hi(gq.u[k]) * w1);
+          }
+          Y[lt] = mfma(xs, gh, Y[lt]);
+        }
+      }
+#pragma unroll
+      for (int nt = 0; nt < 4; ++nt) read_bt(0, nt);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) xe[q] = lds16(out_at(q & 1) + x_cur + (q >> 1) * 4096);
+      const float e63 = fast_exp2(of_block(facv.y, rel));  // the state, so far at the start of the block, to its end
+#pragma unroll
+      for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) Hacc[nt][i] *= e63;
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int q = 0; q < (kSteep ? 0 : 4); ++q) {
+      if (q < 2) {
+        read_bt(0, 2 * q);
+        read_bt(0, 2 * q + 1);
+      } else {
+        xe[2 * (q - 2)] = lds16(out_at(0) + x_cur + (q - 2) * 4096);
+        xe[2 * (q - 2) + 1] = lds16(out_at(1) + x_cur + (q - 2) * 4096);
+      }
+      Y[1] = mfma(xo[q], go1[q], Y[1]);
+      if (q < 2) Y[0] = mfma(xo[q], go0[q], Y[0]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // ---- phase 2: H'^T[n][col] = Ht^T[n][col] + sum_s B^T[n][s] Xm[s][col]; alongside, the output
+    //      epilogue of the block (y[l][col] = rowf_l Y + D x; element i of the lane is column
+    //      32ph + 16kg + i), one quarter per group ----
+    if constexpr (kSteep) rowf[0] = rowf[1] = 1.f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (q < 3) {
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) read_bt(q + 1, nt);
+      }
+      const int lt = q >> 1, c = q & 1;
+      u32x4 o;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        Hacc[w] = mfma(bto[q & 1][w], xo[q], Hacc[w]);
+        __builtin_amdgcn_sched_barrier(0);
+        o[w] = pack2(rowf[lt] * Y[lt][8 * c + 2 * w] + Dh * bf_lo(xe[q].u[w]), rowf[lt] * Y[lt][8 * c + 2 * w + 1] + Dh * bf_hi(xe[q].u[w]));
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      // the quarter replaces, in place, the x it was computed from
+      *(lds_as<u32x4> *)(lds + out_at(c) + x_cur + lt * 4096) = o;
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // as in scan_walk: from the middle of this block (steep: from its end) to the middle of the next, to its start
+    // if that one is steep; after the last block only the way to its end is left
+    const float to_next = of_block(facv.w, rel), to_end = of_block(facv.x, rel);
+    if constexpr (kMixed) {
+      const float nf = (rel & 63) < 63 ? of_block(facv.z, rel + 1) : __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(factor_ptr(more ? jb + 1 : jlast)[2])));
+      const bool next_steep = more && __float_as_int(nf) < 0;
+      if constexpr (kSteep)
+        pending = more && !next_steep ? nf : 1.f;
+      else
+        pending = more && !next_steep ? to_next : to_end;
+      steep_cur = next_steep;
+    } else {
+      pending = more ? to_next : to_end;
+    }
+    x_cur = x_cur == 2 * L::kXBuf ? 0 : x_cur + L::kXBuf;
+    __syncthreads();  // the next block's tiles are visible, this block's may be overwritten, its y read
+  };
+  auto step = [&](int par, int jb) __attribute__((always_inline)) {
+    if constexpr (kMixed) {
+      if (steep_cur) {
+        body(par, jb, std::true_type{});
+        return;
+      }
+    }
+    body(par, jb, std::false_type{});
+  };
+  for (int first = jb0; first < jb1; first += 64) {
+    if (first > jb0) {
+      facv = *reinterpret_cast<const f32x4 *>(factor_ptr(min(first + lane, jlast)));
+      asm volatile("" : "+v"(facv));
+    }
+    const int last = min(first + 64, jb1);
+    int jb = first;
+    for (; jb + 1 < last; jb += 2) {
+      step(0, jb);
+      step(1, jb + 1);
+    }
+    if (jb < last) step(0, jb);
+  }
+  // ---- the final state, four consecutive n per 16-byte store ----
+  if (sv.sg == sv.S - 1 && live) {
+    float *const rows = p.final_state + (bh * kP + 32 * ph) * p.ns.width + p.ns.off;
+    const int valid = p.ns.valid;
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+#pragma unroll
+      for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) {
+          const f32x16 &t = Hacc[2 * half + nt];
+          *(lds_as<f32x4> *)(turn + pi_of_row(r) * kTurnStride + 32 * nt + 16 * (i4 >> 1) + 8 * kg + 4 * (i4 & 1)) =
+              f32x4{t[4 * i4 + 0], t[4 * i4 + 1], t[4 * i4 + 2], t[4 * i4 + 3]} * pending;
+        }
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int row = 4 * k + (lane >> 4), n0 = 64 * half + 4 * (lane & 15);
+        if (n0 < valid)
+          *reinterpret_cast<f32x4 *>(rows + static_cast<size_t>(row) * p.ns.width + n0) =
+              *(lds_as<f32x4> *)(turn + row * kTurnStride + 4 * (lane & 15));
+      }
+    }
+  }
+  return true;
+}
+
+__device__ __attribute__((noinline)) void pair_walk_mixed(const ScanParams p, const SeqView sv, lds_u8 *const lds) {
+  (void)pair_walk<true>(p, sv, lds);
+}
+
 template <bool kStatesOnly, int HPW, int kYMode = kYPlain>
 __global__ __launch_bounds__(128 * HPW)
 __attribute__((amdgpu_waves_per_eu(kStatesOnly || HPW == kHeadsPerWg ? 2 : 1, kStatesOnly || HPW == kHeadsPerWg ? 2 : 1)))
@@ -1778,6 +2362,18 @@ void chunk_scan_kernel(const ScanParams p) {
     }
   }
   scan_walk<kStatesOnly, HPW, kYMode, false>(p, sv, lds);
+}
+
+template <int kYMode>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void pair_scan_kernel(const ScanParams p) {
+  __shared__ __align__(1024) uint8_t lds[PairLds::kBytes];
+  SeqView sv;
+  if (!wg_coords(p, true, sv)) return;  // uniform over the workgroup
+  // (the two roles, and the two walks, pass the same barriers, block for block)
+  if (threadIdx.x >= 256)
+    pair_feed<kYMode>(p, sv, (lds_u8 *)lds);
+  else if (!pair_walk<false>(p, sv, (lds_u8 *)lds))
+    pair_walk_mixed(p, sv, (lds_u8 *)lds);
 }
 
 // ---- segment_pass: slot[0] = h0; slot[sg] = exp2(decay[sg-1]) * slot[sg-1] + local[sg-1] --------
@@ -2267,9 +2863,9 @@ hipError_t launch_slice(const Dims &d, const NSlice ns, const int32_t *cu, const
   const dim3 grid(kXcds * p.per_xcd), block(128 * pl.heads);
   if (pl.heads == 2) {
     if (add_to_y)
-      hipLaunchKernelGGL((chunk_scan_kernel<false, 2, kYAdd>), grid, block, 0, stream, p);
+      hipLaunchKernelGGL(pair_scan_kernel<kYAdd>, grid, dim3(512), 0, stream, p);
     else
-      hipLaunchKernelGGL((chunk_scan_kernel<false, 2>), grid, block, 0, stream, p);
+      hipLaunchKernelGGL(pair_scan_kernel<kYPlain>, grid, dim3(512), 0, stream, p);
   } else if (add_to_y) {
     hipLaunchKernelGGL((chunk_scan_kernel<false, kHeadsPerWg, kYAdd>), grid, block, 0, stream, p);
   } else if (stream_y(d, rows)) {
