@@ -140,7 +140,7 @@ ssd_status ssd_testing_prefill_plan(const ssd_shape *shape, int32_t h0_aliases_f
   if (const ssd_status st = make_dims(shape, false, &d); st != SSD_OK) return st;
   for (int i = 0; i < 8; ++i) plan[i] = 0;
   if (use_mfma(d)) {
-    const ssd::SlicePlan pl = ssd::mfma_plan(d, h0_aliases_final_state != 0);
+    const ssd::SlicePlan pl = ssd::mfma_plan(d, h0_aliases_final_state != 0, true);
     plan[0] = 1;
     plan[1] = pl.seg_blocks;
     plan[2] = pl.segments;
@@ -155,6 +155,24 @@ ssd_status ssd_testing_prefill_plan(const ssd_shape *shape, int32_t h0_aliases_f
     plan[0] = 2;
     plan[5] = ssd::mfma_f32_time_segments(d);
   }
+  return SSD_OK;
+}
+
+ssd_status ssd_testing_prefill_pair_plan(const ssd_shape *shape, int32_t h0_aliases_final_state, int32_t plan[8]) {
+  Dims d;
+  if (shape == nullptr || plan == nullptr) return SSD_ERR_NULL;
+  if (const ssd_status st = make_dims(shape, false, &d); st != SSD_OK) return st;
+  for (int i = 0; i < 8; ++i) plan[i] = 0;
+  if (!use_mfma(d)) return SSD_OK;
+  const ssd::SlicePlan pl = ssd::mfma_plan(d, h0_aliases_final_state != 0, false);
+  if (pl.two == 0) return SSD_OK;
+  plan[0] = 1;
+  plan[1] = pl.seg_blocks;
+  plan[2] = pl.segments;
+  plan[3] = pl.parts;
+  plan[4] = pl.fold;
+  plan[6] = pl.heads;
+  plan[7] = pl.state_heads;
   return SSD_OK;
 }
 

@@ -153,11 +153,12 @@ hipError_t launch_prefill_generic(const Dims &d, const void *x, const float *dt,
 struct SlicePlan {
   int seg_blocks, segments, parts, fold;
   int heads, state_heads;  // head slices per workgroup: full scan, states-only pass
+  int two = 0;             // the segments are those chosen for two heads per workgroup (two_head_blocks)
   // packed batch: the device chooses the segment length from the sequences' lengths (seg_blocks is the shortest it may)
   bool from_lengths = false;
   int shortest = 0;  // (of mfma_varlen_plan, where seg_blocks is the choice)
 };
-SlicePlan mfma_plan(const Dims &d, bool h0_aliases_final_state);
+SlicePlan mfma_plan(const Dims &d, bool h0_aliases_final_state, bool four);
 // ... and a packed batch of these boundaries (host array): seg_blocks as the device chooses it, segments of the whole batch.
 SlicePlan mfma_varlen_plan(const Dims &d, const int32_t *cu_host);
 int mfma_f32_time_segments(const Dims &d);

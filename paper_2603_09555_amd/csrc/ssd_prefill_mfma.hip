@@ -1781,10 +1781,12 @@ __device__ __forceinline__ bool walk_meets_steep_block(const ScanParams &p, cons
 // Two waves per head as above; four of these, one to a SIMD, compute, and the other wave of each SIMD feeds them.
 //   - Everything a block needs -- the shared tiles, x, the decay record -- travels straight from memory into LDS
 //     (load_to_lds) at the feeding waves' request: no registers, no LDS writes, no waits but the feeders' own, one per
-//     block.  A wave that makes such a request stands still for 95 cycles, a load into registers 60 (measured with
-//     requests 64 vector instructions apart): with the fourteen requests and four stores of a block among its own instructions a
-//     computing wave took FEEDA cycles a block, without them FEEDB.
-//   - The feeders also scale x and turn it for the matrix instructions (without that FEEDC).
+//     block.  A wave that makes such a request stands still for 95 cycles (measured with four waves of a CU making one
+//     each, 64 vector instructions apart): with the fourteen requests and four stores of a block among its own
+//     instructions a computing wave took 4190 cycles a block of 8 x 4096 tokens x 48 heads, with feeders 3660.
+//   - The feeders also scale x and turn it for the matrix instructions (3610: now they are what a block waits for) and
+//     make their requests in runs of four (see load_to_lds4): 3250.  The same work in waves that load into registers and
+//     write LDS themselves takes 5240 cycles.
 //   - The tiles and the record of the next block arrive during a block, in the buffer of a pair that it does not use.  A
 //     block of x goes through one of three buffers: it arrives until the middle of the block before its own, when the feeder that
 //     requested it turns it into Xm^T; it serves the skip term of its block and is replaced, in place, by y; and
@@ -2532,48 +2534,45 @@ int choose_seg_blocks(const Dims &d, int min_blocks, int max_slots, int max_part
   return best_blocks;
 }
 
-// A launch whose workgroups number at most one per CU when they take two heads each takes two: a wave has its SIMD to
-// itself instead of sharing it, which is worth more than the shared tiles that are then staged twice as often.  On 45
-// drawn shapes (64 to 11600 tokens, 4 to 166 slices) at up to 13 segment lengths each: both passes with two heads against
-// four, grids of up to 64 (counted with two heads) 0.87 of the time, up to 128 0.88, up to 256 0.91 (0.82 to 1.01); up
-// to 400, where the second round begins, 1.15.  (2048 tokens x 24 heads 36.1 -> 32.5 us, 376 x 22 in batches of 4 29.9
-// -> 25.6.  The states-only pass alone gains up to 700 workgroups, 0.98, but loses at 16384 tokens x 80 heads, 35.8 ->
-// 40.0 us.)  y must not need the streaming stores (x of more than 64 MiB).
+// A launch whose workgroups number at most one per CU when they take two heads each takes two: its computing waves have
+// their SIMD's vector unit almost to themselves and are fed by others (see pair_walk), which is worth more than the shared tiles
+// that are then fetched twice as often.  (Of the states-only pass alone the same holds: on 45 drawn shapes grids of up to
+// 256 take 0.82 to 1.01 of the time of four heads; it loses at 16384 tokens x 80 heads, 35.8 -> 40.0 us.)
 bool small_grid(long wgs_of_two) { return wgs_of_two <= kNumCUs; }
 
-// Blocks per segment with two heads per workgroup, or 0 where four are expected to be faster than that (blocks4 a
-// segment).  Microseconds of a whole call, fitted to 105 drawn shapes (64 to 14000 tokens, 4 to 200 slices) at every
-// segment length (575 and 378 timings, 3.4 and 5.3 % rms).  The fit for four heads only serves this comparison, where
-// the grid of four would need more than half of the CUs: on 40 other such shapes the choice is 0.9 % behind the fastest
-// of the timed plans.  3 x 3001 tokens x 20 heads 50.3 -> 46.5 (6 blocks instead of 4), 2048 x 80 49.8 -> 46.5.
-int two_head_blocks(const Dims &d, int min_blocks, int blocks4, int parts4) {
+// Blocks per segment of a plain batch with two heads per workgroup, all in one round, and the pieces its states-only pass
+// cuts a segment into; 0 where the sequences alone are more than a round.  Microseconds of a whole call, fitted to 90
+// drawn shapes (300 to 18400 tokens, 2 to 163 slices, batches of up to 12) at the lengths that give 1 to 24 segments (611 timings,
+// 4.6 % rms): the choice is 0.8 % behind the fastest of the timed lengths and takes 0.80 of the time of four heads
+// with their own choice, 1.04 at worst.  Beyond a round four heads are as fast or faster (968 tokens x 141 heads in
+// batches of 12: 150.9 us, two heads 157.7; 2328 x 139 in batches of 4: 130.5, two heads in two rounds 133.8).
+// 8 x 4096 tokens x 48 heads 174 -> 130 us (one segment instead of two), 2016 x 59 in batches of 6 100 -> 70.
+int two_head_blocks(const Dims &d, int min_blocks, int max_slots, int *parts) {
   const int nblocks = (d.T + kBlk - 1) / kBlk;
   const long groups2 = static_cast<long>(d.Bt) * head_groups(d, 2), groups4 = static_cast<long>(d.Bt) * head_groups(d);
   const double seqs = static_cast<double>(d.Bt) * d.H * (d.P / kP);
-  const int fold_max = knobs().fold_max_slots;
   int best = 0;
   double best_us = 0.0;
   for (int cand = min_blocks > 2 ? min_blocks : nblocks < 2 ? 1 : 2; cand <= nblocks; ++cand) {
-    const int S = (nblocks + cand - 1) / cand, slots = S - 1;
+    const int S = (nblocks + cand - 1) / cand;
     if (!small_grid(groups2 * S)) continue;
+    if (cand > min_blocks && best != 0 && S == (nblocks + cand - 2) / (cand - 1)) continue;  // (as many segments, and longer)
     const double load = static_cast<double>(groups2 * S) / kNumCUs;
-    double us = 12.1 + (1.95 + 0.32 * load) * cand + 3.45 * load;
-    if (slots > 0) us += 3.56 + 0.71 * cand + (slots <= fold_max ? (0.98 + 0.0022 * seqs) * slots : 4.74 + 0.0138 * slots * seqs);
+    double us = 11.0 + (1.11 + 1.04 * load) * cand;
+    int k = 1;
+    if (S > 1) {
+      (void)states_cost(groups4, seqs, S, cand, max_slots, 8, &k);
+      const int slots = (S - 1) * k;
+      us += 3.93 + 0.72 * (cand / k) * static_cast<double>((groups2 * slots + kNumCUs - 1) / kNumCUs);
+      us += slots <= knobs().fold_max_slots ? (0.66 + 0.0119 * seqs) * slots : 3.94 + 0.0184 * slots * seqs;
+    }
     if (best == 0 || us < best_us) {
       best = cand;
       best_us = us;
+      *parts = k;
     }
   }
-  const int S4 = (nblocks + blocks4 - 1) / blocks4, slots = (S4 - 1) * parts4;
-  if (best == 0 || small_grid(groups2 * S4)) return best;
-  auto rounds = [](long wgs) { return static_cast<double>((wgs + kNumCUs - 1) / kNumCUs); };
-  const double r = rounds(groups4 * S4), load = groups4 * S4 / (kNumCUs * r);
-  double us4 = 5.2 + r * (2.62 * blocks4 + 20.5 * load);
-  if (slots > 0) {
-    us4 += 1.28 * rounds(groups4 * slots) * (blocks4 / parts4);
-    us4 += slots <= fold_max ? 0.0109 * slots * seqs : 6.25 + 0.012 * slots * seqs;
-  }
-  return best_us < us4 ? best : 0;
+  return best;
 }
 
 // Workspace.  Plain batch: rows = Bt sequences of NB blocks each.  Variable-length batch: one "row" whose
@@ -2659,40 +2658,40 @@ int list_items(const Dims &d, const Layout &w, int seg_blocks) { return d.Bt + f
 // device-side tables hold them per sequence), pieces per segment of the states-only pass, and whether the
 // full scan sums the chain over state slots itself (ScanParams::fold).
 bool packed_uncut(const Dims &d, const SlicePlan &pl);
-SlicePlan plan_slice(const Dims &d, bool varlen, bool h0_aliases_final_state) {
+// four: the plan that does without two_head_blocks' choice (see ssd_testing_prefill_plan).
+SlicePlan plan_slice(const Dims &d, bool varlen, bool h0_aliases_final_state, bool four = false) {
   const Layout w = make_layout(d, varlen);
   Dims one = d;  // the segment length of a packed batch is chosen as for one sequence of all its tokens
   if (varlen) one.Bt = 1;
   SlicePlan pl;
+  const Knobs &kn = knobs();
+  pl.two = 0;
+  pl.heads = pl.state_heads = kn.scan_heads == 2 ? 2 : kHeadsPerWg;
+  // two heads per workgroup (see small_grid)
+  const bool may_choose = kn.scan_heads == 0 && kn.seg_chunks == 0 && kn.seg_blocks == 0 && kn.seg_parts == 0;
+  const bool may_two = kn.scan_heads == 0 && (varlen ? !stream_y(d, 1) : kn.y_stream <= 0);
+  int two_parts = 1;
+  const int two = !varlen && !four && may_choose && may_two ? two_head_blocks(d, (w.NB + w.S_max - 1) / w.S_max, w.S_max, &two_parts) : 0;
   // shortest segment: a chunk for a packed batch; what the state slots allow for a plain one
-  pl.seg_blocks = choose_seg_blocks(one, varlen ? d.L / kBlk : (w.NB + w.S_max - 1) / w.S_max, w.S_max, varlen ? 1 : 8);
+  pl.seg_blocks = two > 0 ? two : choose_seg_blocks(one, varlen ? d.L / kBlk : (w.NB + w.S_max - 1) / w.S_max, w.S_max, varlen ? 1 : 8);
   if (!varlen && (w.NB + pl.seg_blocks - 1) / pl.seg_blocks > w.S_max) pl.seg_blocks = (w.NB + w.S_max - 1) / w.S_max;
   pl.segments = varlen ? 0 : (w.NB + pl.seg_blocks - 1) / pl.seg_blocks;
   // pieces per segment for the states-only pass (see ScanParams): the split with the least modelled
   // time of that pass plus the longer chain over state slots, among the divisors of the segment length
   pl.parts = 1;
-  if (!varlen && pl.segments > 1) {
+  if (two > 0) {
+    pl.two = 1;
+    pl.parts = two_parts;
+  } else if (!varlen && pl.segments > 1) {
     const long groups = static_cast<long>(d.Bt) * head_groups(d);
     const double seqs = static_cast<double>(d.Bt) * d.H * (d.P / kP);
     (void)states_cost(groups, seqs, pl.segments, pl.seg_blocks, w.S_max, 8, &pl.parts);
     if (const int k = knobs().seg_parts; k >= 1 && pl.seg_blocks % k == 0 && (pl.segments - 1) * k + 1 <= w.S_max) pl.parts = k;
   }
-  // two heads per workgroup (see small_grid): possibly other segments, which are then not cut into pieces
-  const Knobs &kn = knobs();
-  const bool may_choose = kn.scan_heads == 0 && kn.seg_chunks == 0 && kn.seg_blocks == 0 && kn.seg_parts == 0;
-  const bool may_two = kn.scan_heads == 0 && !stream_y(d, varlen ? 1 : d.Bt);
   const int seqs = varlen ? 1 : d.Bt;
   // (the lengths of several sequences are known on the device only; see segment_choice)
   pl.from_lengths = varlen && d.Bt > 1 && d.Bt <= kTableThreads && w.NB <= kTableBlocks && list_items(d, w, pl.seg_blocks) <= kTableBlocks &&
                     kn.seg_chunks == 0 && kn.seg_blocks == 0 && full_items(d, w, pl.seg_blocks) > 0;
-  pl.heads = pl.state_heads = kn.scan_heads == 2 ? 2 : kHeadsPerWg;
-  if (!varlen && may_choose && may_two) {
-    if (const int b = two_head_blocks(d, (w.NB + w.S_max - 1) / w.S_max, pl.seg_blocks, pl.parts); b > 0) {
-      if (b != pl.seg_blocks) pl.parts = 1;
-      pl.seg_blocks = b;
-      pl.segments = (w.NB + b - 1) / b;
-    }
-  }
   if (pl.from_lengths) {
     // (on the same 240 batches two heads never are 2.0 % slower on average, wherever the sequences alone fit 1.1 %: few
     // long ones would be cut too coarsely)
@@ -2930,8 +2929,8 @@ bool mfma_supported(const Dims &d) {
 
 size_t mfma_workspace_bytes(const Dims &d) { return make_layout(with_block_chunk(d), false).total; }
 
-SlicePlan mfma_plan(const Dims &d, bool h0_aliases_final_state) {
-  return plan_slice(with_block_chunk(d), false, h0_aliases_final_state);
+SlicePlan mfma_plan(const Dims &d, bool h0_aliases_final_state, bool four) {
+  return plan_slice(with_block_chunk(d), false, h0_aliases_final_state, four);
 }
 
 SlicePlan mfma_varlen_plan(const Dims &d_in, const int32_t *cu) {

@@ -24,7 +24,7 @@ EXPORTS = ["ssd_prefill_workspace_bytes", "ssd_prefill", "ssd_prefill_static", "
            "ssd_decode_step_layers_dt", "ssd_decode_steps_layers_dt",
            "ssd_prefill_path", "ssd_status_string", "ssd_version",
            "ssd_testing_set_knob", "ssd_testing_reset_knobs", "ssd_testing_prefill_plan", "ssd_testing_varlen_plan",
-           "ssd_testing_prefill_chunks"]
+           "ssd_testing_prefill_chunks", "ssd_testing_prefill_pair_plan"]
 
 
 class ssd_shape(ctypes.Structure):
@@ -65,6 +65,8 @@ _lib.ssd_testing_reset_knobs.restype = None
 _lib.ssd_testing_reset_knobs.argtypes = []
 _lib.ssd_testing_prefill_plan.restype = ctypes.c_int
 _lib.ssd_testing_prefill_plan.argtypes = [ctypes.POINTER(ssd_shape), ctypes.c_int32, ctypes.POINTER(ctypes.c_int32)]
+_lib.ssd_testing_prefill_pair_plan.restype = ctypes.c_int
+_lib.ssd_testing_prefill_pair_plan.argtypes = [ctypes.POINTER(ssd_shape), ctypes.c_int32, ctypes.POINTER(ctypes.c_int32)]
 _lib.ssd_testing_prefill_chunks.restype = ctypes.c_int32
 _lib.ssd_testing_prefill_chunks.argtypes = [ctypes.POINTER(ssd_shape), ctypes.c_int32]
 _lib.ssd_testing_varlen_plan.restype = ctypes.c_int
@@ -448,6 +450,15 @@ def prefill_plan(shape, h0_aliases_final_state: bool = False) -> dict:
         raise SSDError(st, "ssd_testing_prefill_plan")
     return dict(path=("generic_f32", "mfma_bf16", "mfma_f32")[out[0]], seg_blocks=out[1], segments=out[2], parts=out[3],
                 fold=bool(out[4]), f32_segments=out[5])
+
+
+def prefill_pair_plan(shape, h0_aliases_final_state: bool = False):
+    """``ssd_testing_prefill_pair_plan`` (include/ssd_testing.h) as a dict, or None for a shape it has no plan for."""
+    out = (ctypes.c_int32 * 8)()
+    st = _lib.ssd_testing_prefill_pair_plan(ctypes.byref(shape), int(bool(h0_aliases_final_state)), out)
+    if st != SSD_OK:
+        raise SSDError(st, "ssd_testing_prefill_pair_plan")
+    return dict(seg_blocks=out[1], segments=out[2], parts=out[3], fold=bool(out[4]), heads=out[6], state_heads=out[7]) if out[0] else None
 
 
 def prefill_chunks(shape, h0_aliases_final_state: bool = False) -> int:
