@@ -251,8 +251,9 @@ __device__ __forceinline__ int wave_reduce(int v, Op op) {
 // segments of s blocks, `items` of them.  The scan: the busiest CU's load -- a workgroup's start counts as some blocks --
 // and the longest walk; with segments that are not the last of their sequence also the states-only pass, the same way, and
 // the chain.  Fitted to 240 drawn batches (2 to 128 sequences, 380 to 16500 tokens, 4 to 80 heads; ragged, equal, one or a
-// few long among short ones) at every length from the host's shortest on; 8 and 9 % rms, the choice 2.2 % behind the
-// fastest of the timed plans.  Against the length of one sequence of all the tokens: 1.07 in the geometric mean.  A length
+// few long among short ones) at every length from the host's shortest on (9 % rms, the choice 2.2 % behind the fastest of
+// the timed plans), for two heads to 70 others (2 to 64 sequences, 740 to 29700 tokens, 4 to 102 heads) at eight lengths each: 7
+// % rms, with its choice the 35 that four heads had served take 0.85 of that time.  Against the length of one sequence of all the tokens: 1.07 in the geometric mean.  A length
 // guessed on the host cannot serve both a ragged batch and one long prompt among short ones: the guess of four times the
 // mean left 8192 + 63 x 1 tokens x 24 heads uncut, 322 us (now 75; 89 with the length of one sequence).
 __host__ __device__ inline float packed_cost(const SegChoice &c, int s, int blocks, int longest, int nseq, int items) {
@@ -261,8 +262,8 @@ __host__ __device__ inline float packed_cost(const SegChoice &c, int s, int bloc
   const float walk = s < longest ? len : static_cast<float>(longest), grid = n * c.fill < 1.f ? n * c.fill : 1.f;
   float us;
   if (c.heads == 2) {
-    us = 8.1f + (1.96f + 0.13f * grid) * both((blocks + 6.7f * n) * c.fill, walk + 6.7f);
-    if (items > nseq) us += 0.021f * full * c.slices + 0.835f * (len + 4.f) * both(1.f, full * c.fill);
+    us = 15.f + (1.13f + 0.24f * grid) * both((blocks + 3.9f * n) * c.fill, walk + 3.9f);
+    if (items > nseq) us += 0.0123f * full * c.slices + 0.82f * (len + 6.4f) * both(1.f, full * c.fill);
   } else {
     us = 10.4f + (2.36f + 0.23f * grid) * both((blocks + 5.1f * n) * c.fill, walk + 5.1f);
     if (items > nseq) us += 0.025f * full * c.slices + 0.76f * (len + 7.2f) * both(1.f, full * c.fill);
@@ -2669,7 +2670,7 @@ SlicePlan plan_slice(const Dims &d, bool varlen, bool h0_aliases_final_state, bo
   pl.heads = pl.state_heads = kn.scan_heads == 2 ? 2 : kHeadsPerWg;
   // two heads per workgroup (see small_grid)
   const bool may_choose = kn.scan_heads == 0 && kn.seg_chunks == 0 && kn.seg_blocks == 0 && kn.seg_parts == 0;
-  const bool may_two = kn.scan_heads == 0 && (varlen ? !stream_y(d, 1) : kn.y_stream <= 0);
+  const bool may_two = kn.scan_heads == 0 && kn.y_stream <= 0;
   int two_parts = 1;
   const int two = !varlen && !four && may_choose && may_two ? two_head_blocks(d, (w.NB + w.S_max - 1) / w.S_max, w.S_max, &two_parts) : 0;
   // shortest segment: a chunk for a packed batch; what the state slots allow for a plain one
@@ -2693,10 +2694,10 @@ SlicePlan plan_slice(const Dims &d, bool varlen, bool h0_aliases_final_state, bo
   pl.from_lengths = varlen && d.Bt > 1 && d.Bt <= kTableThreads && w.NB <= kTableBlocks && list_items(d, w, pl.seg_blocks) <= kTableBlocks &&
                     kn.seg_chunks == 0 && kn.seg_blocks == 0 && full_items(d, w, pl.seg_blocks) > 0;
   if (pl.from_lengths) {
-    // (on the same 240 batches two heads never are 2.0 % slower on average, wherever the sequences alone fit 1.1 %: few
-    // long ones would be cut too coarsely)
-    const long groups2 = head_groups(d, 2);
-    if (may_two && small_grid(d.Bt * groups2) && small_grid((w.NB - d.Bt) * groups2 / 4)) pl.heads = pl.state_heads = 2;
+    // Two heads per workgroup (see small_grid) where the sequences alone are no more than three rounds of them: 35 of 70
+    // drawn batches that four heads had served up to then take 0.85 of that time (4 sequences, 5040 tokens, 96 heads 80 -> 53
+    // us; 1.01 at worst); 32 sequences in 4.5 rounds 44 us, two heads 52, 64 in 11 rounds 132, two heads 139.
+    if (may_two && static_cast<long>(d.Bt) * head_groups(d, 2) <= 3 * kNumCUs) pl.heads = pl.state_heads = 2;
     if (packed_uncut(d, pl)) {
       pl.from_lengths = false;
       pl.seg_blocks = w.NB - d.Bt;
