@@ -2640,9 +2640,9 @@ bool shape_ok(const Dims &d, unsigned long long tokens, unsigned long long nb) {
 // 128 MiB 122 / 110 (two passes over x) and 109 / 97 (one); 160 MiB 151 / 131; 192 MiB 178 / 171 and 175 / 153;
 // 256 MiB 220 / 211; 320 MiB 278 / 281 (nothing left to protect, nothing lost).  With a dstate above 128 the
 // later state slices read y back to add to it, but they read x twice more: the first slice streams y all the
-// same (dstate 256: 333 -> 307 us).  With two heads per workgroup it pays in up to three segments (128, 192, 254 and 258 MiB
-// in 2, 1, 3 and 3: 106 / 103, 136 / 127, 248 / 243 and 259 / 253 us) and not in more (135 and 160 MiB in 6: 146.0 / 146.0 and
-// 150.6 / 152.2).  The y_stream knob overrides (tests, tuning).
+// same (dstate 256: 333 -> 307 us).  With two heads per workgroup (ordinary / non-temporal): the same inputs again and again,
+// 16384 tokens x 80 heads in six segments 144 / 123, 3 packed sequences of 24001 x 63 201 / 181, 8 x 4096 x 48 in one 129 / 119;
+// inputs that change 148 / 152, 200 / 201 and 131 / 126.  The y_stream knob overrides (tests, tuning).
 constexpr unsigned long long kMemCacheBytes = 256ull << 20;
 bool stream_y(const Dims &d, int rows) {
   if (knobs().y_stream >= 0) return knobs().y_stream != 0;
@@ -2866,7 +2866,7 @@ hipError_t launch_slice(const Dims &d, const NSlice ns, const int32_t *cu, const
   if (pl.heads == 2) {
     if (add_to_y)
       hipLaunchKernelGGL(pair_scan_kernel<kYAdd>, grid, dim3(512), 0, stream, p);
-    else if (stream_y(d, rows) && S >= 1 && S <= 3)  // (see stream_y)
+    else if (stream_y(d, rows))
       hipLaunchKernelGGL(pair_scan_kernel<kYStream>, grid, dim3(512), 0, stream, p);
     else
       hipLaunchKernelGGL(pair_scan_kernel<kYPlain>, grid, dim3(512), 0, stream, p);
