@@ -892,8 +892,8 @@ constexpr bool kRowStores = SSD_ROW_STORES != 0;
 constexpr int kRawStride = 40;                       // raw x rows: 32 columns + 16 bytes, in bf16 elements
 constexpr int kGLowStride = 32 + 8;                  // G rows 0..31 keep only columns 0..31 (the rest is masked)
 constexpr int kGTile = 32 * kGLowStride + 32 * kGStride;  // elements of a compacted G tile
-// HPW = heads per workgroup (two waves each): four, where the full kernel's LDS tiles fill the CU and two waves share a
-// SIMD, or two, one wave per SIMD, for launches that would otherwise leave half of the chip idle (see small_grid).
+// HPW = heads per workgroup (two waves each): four, where two waves share a SIMD; in the states-only pass also two, for
+// launches that would otherwise leave half of the chip idle (see small_grid).  (The full scan with two heads: pair_walk.)
 // kYMode, how y leaves: kYPlain -- ordinary stores; kYStream -- non-temporal stores, so that writing y does not
 // evict x, which the states-only pass has just pulled into the memory-side cache, before this kernel reads it
 // again (chosen per launch, see stream_y()); kYAdd -- added to what y already holds (the later state slices
