@@ -396,12 +396,12 @@ __device__ __forceinline__ void chunk_outputs(const ChunkParams &p, const Item &
         xo[pt][u].q = *reinterpret_cast<const u32x4 *>(sXt + (x_row[u ^ pt] ^ ((j & 1) << 6)) + (j >> 1) * 128 + pt * (32 * kChunk * 2));
     request_b(max(j - 1, 0));
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (kDiagonal) {
+    if constexpr (kDiagonal) {  // (fminf would make an undefined decay, of a head whose A is NaN, one of 2^0)
 #pragma unroll
       for (int i4 = 0; i4 < 4; ++i4)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          v[4 * i4 + i] = 8 * i4 + 4 * kg + i <= r ? v[4 * i4 + i] * (dt_s[i4][i] * exp2_fast(fminf(cs - w[i4][i], 0.f))) : 0.f;
+          v[4 * i4 + i] = 8 * i4 + 4 * kg + i <= r ? v[4 * i4 + i] * (dt_s[i4][i] * exp2_fast(min_or_nan(cs - w[i4][i], 0.f))) : 0.f;
     } else {
       const float e = exp2_fast(tiles_between + cs);
       tiles_between += s_total[j];

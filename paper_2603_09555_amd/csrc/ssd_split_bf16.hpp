@@ -92,8 +92,9 @@ __device__ __forceinline__ void split3_even(const float v[8], Op o[3]) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) o[p].u[k] = t[p][k];
 }
-// The larger of two values, or NaN if one is.
+// The larger, and the smaller, of two values, or NaN if one is.
 __device__ __forceinline__ float max_or_nan(float a, float b) { return __builtin_elementwise_maximum(a, b); }
+__device__ __forceinline__ float min_or_nan(float a, float b) { return __builtin_elementwise_minimum(a, b); }
 // The six products, smallest first.
 constexpr int kPairA[6] = {1, 2, 0, 1, 0, 0}, kPairB[6] = {1, 0, 2, 0, 1, 0};
 __device__ __forceinline__ f32x16 mfma6(const Op a[3], const Op b[3], f32x16 c) {

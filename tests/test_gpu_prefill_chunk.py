@@ -106,3 +106,20 @@ def test_chunk_kernels_replayed_from_a_hip_graph(ssd):
             g.replay()
             torch.cuda.synchronize()
             assert torch.equal(y, want[i & 1][0]) and torch.equal(st, want[i & 1][1]), (dims, i)
+
+
+@pytest.mark.parametrize("tokens", [20, 200, 700])
+def test_an_undefined_decay_shows_in_every_row(ssd, tokens):
+    """A head whose A is NaN has no defined output, from its first token on; its neighbour is untouched."""
+    cfg = inputs.SSDConfig("t", 1, tokens, 2, 64, 128, 1, 256, "bf16")
+    dev = {k: v.cuda() for k, v in inputs.make_prefill_inputs(cfg, seed=43).items()}
+    ssd.set_knob("chunk", 1)
+    assert ssd.prefill_chunks(ssd.make_shape(1, tokens, 2, 64, 128, 1, 256, torch.bfloat16)) > 0
+    print("chunk kernels, A undefined", tokens, flush=True)
+    call = lambda: ssd.ssd_prefill(*[dev[k] for k in ("x", "dt", "A", "B", "C", "D")], cfg.chunk)   # noqa: E731
+    y0, st0 = call()
+    dev["A"][0] = float("nan")
+    y, st = call()
+    torch.cuda.synchronize()
+    assert torch.isnan(y[:, :, 0]).all() and torch.isnan(st[:, 0]).all()
+    assert torch.equal(y[:, :, 1], y0[:, :, 1]) and torch.equal(st[:, 1], st0[:, 1])
