@@ -12,6 +12,11 @@
 // exp(decay of the row's tile up to l) times exp(decay of the tiles between) times exp(decay behind s in its tile), all
 // with exponents that are never positive and are sums of decays, not differences.
 //
+// Over 256 tokens such a weight may be zero where the recurrence, step by step, never multiplies an infinity by zero; and a
+// score of zero times it is undefined for tokens before it, too.  So a wave whose results are not all finite forms them again by
+// the recurrence as it stands (recur_states, recur_rows): what is infinite, of which sign, and what is undefined are then
+// the recurrence's.  Finite inputs never get there.
+//
 // What bounds it: latency.  2048 tokens x 24 heads, 192 + 24 workgroups, 19.9 us (scan kernels 33.8, a launch and a trip of
 // the states through memory more): states 4.6 us from the first workgroup's start (loads 2.0, staging 1.5, product 1.1),
 // outputs 10.5 (300 KB of loads to a CU 2.7, staging and the barrier 1.4, tiles 3.5 in the longest row, states and their
@@ -95,6 +100,29 @@ __device__ __forceinline__ void store_state(const ChunkParams &p, size_t bh, con
   }
 }
 
+// ---- the recurrence as it stands ----
+__device__ __forceinline__ bool all_finite(float seen) { return __builtin_amdgcn_ballot_w64(!(seen < __builtin_inff())) == 0; }
+__device__ __forceinline__ float larger(float seen, float v) { return max_or_nan(seen, fabsf(v)); }
+// v + S, decayed by 2^d: finite values that decay below fp32's range are zero, infinities stay what they are.  (d is
+// -infinity, whose factor is a plain zero, where a single token decays everything away; see chunk_states.)
+__device__ __forceinline__ f32x4 chain(f32x4 S, float d, f32x4 v) {
+  const bool far = d < -126.f && d > -__builtin_inff();
+  const float e = far ? 0x1p-126f : exp2_fast(d), again = far ? 0x1p-126f : 1.f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) S[i] = S[i] * e * again * again + v[i];
+  return S;
+}
+// One token: S[i] = dA S[i] + (dt x) B[i] on the columns that exist.
+__device__ __forceinline__ f32x4 recur(f32x4 S, float dA, float ux, u32x2 B) {
+  const float b[4] = {bf_lo(B.x), bf_hi(B.x), bf_lo(B.y), bf_hi(B.y)};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) S[i] = fmaf(dA, S[i], ux * b[i]);
+  return S;
+}
+__device__ __forceinline__ float x_at(Rsrc rx, uint32_t at) {
+  return __uint_as_float(static_cast<uint32_t>(static_cast<uint16_t>(__builtin_amdgcn_raw_buffer_load_b16(rx, at, 0, 0))) << 16);
+}
+
 // ---- L_c and the chunk's total decay; kSingle: the only chunk's, and with h0 the final state ----
 struct StatesLds {
   __align__(16) uint8_t sBt[kN * kChunk * 2];  // B^T [n][s]
@@ -141,7 +169,9 @@ __device__ __forceinline__ void chunk_states(const ChunkParams &p, const Item &i
 
   dtv = dt_apply_branchless(dtv, bias, p.dtx);
   dtv = kTile * wave + r < it.rows ? dtv : 0.f;
-  const float d = cut_decay(dtv * alog), after = suffix32(d), total = read_lane(after + d, 0);
+  // (-infinity where a token decays everything away: its zero is one of the recurrence, not of the product of many decays)
+  const float d = cut_decay(dtv * alog), after = suffix32(d);
+  const float total = __builtin_amdgcn_ballot_w64(d <= kCutLog2) != 0 ? -__builtin_inff() : read_lane(after + d, 0);
   if (lane == 0) s_total[wave] = total;
 #pragma unroll
   for (int k = 0; k < 2; ++k)
@@ -185,19 +215,44 @@ __device__ __forceinline__ void chunk_states(const ChunkParams &p, const Item &i
   float *const slot = p.slots + bh * p.slots_per * kSlot + tid * 4;
   const float e_all = exp2_fast(all);
   if constexpr (kSingle) __syncthreads();  // the operands have been read
+  f32x4 v[4];
+  float seen = 0.f;
 #pragma unroll
   for (int i4 = 0; i4 < 4; ++i4) {
     const f32x4 h = __builtin_bit_cast(f32x4, vh[i4]);
-    f32x4 v = {acc[4 * i4], acc[4 * i4 + 1], acc[4 * i4 + 2], acc[4 * i4 + 3]};
+    v[i4] = f32x4{acc[4 * i4], acc[4 * i4 + 1], acc[4 * i4 + 2], acc[4 * i4 + 3]};
     if (with_h0) {
       if (!kSingle && p.keep_h0) *reinterpret_cast<f32x4 *>(slot + static_cast<size_t>(p.chunks) * kSlot + i4 * (4 * kThr)) = h;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) v[i] = fmaf(e_all, h[i], v[i]);
+      for (int i = 0; i < 4; ++i) v[i4][i] = fmaf(e_all, h[i], v[i4][i]);
     }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) seen = larger(seen, v[i4][i]);
+  }
+  if (!all_finite(seen)) {
+#pragma unroll
+    for (int i4 = 0; i4 < 4; ++i4) v[i4] = __builtin_bit_cast(f32x4, vh[i4]);  // (zero but for the first chunk's h0)
+    for (int j = 0; j < it.rows; j += kTile) {
+      const float dts = dt_apply_branchless(step_size(p, it, head, j + r), bias, p.dtx);
+      const int n = min(kTile, it.rows - j);
+#pragma clang loop unroll(disable)
+      for (int t = 0; t < n; ++t) {
+        const float dt_t = read_lane(dts, t), ux = dt_t * x_at(rx, (j + t) * xrow + it.h * (kP * 2) + 2 * (32 * pt + r));
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) {
+          const int n0 = 32 * nt + 8 * i4 + 4 * kg;
+          const u32x2 b = buf_load8(rB, n0 < p.N ? (j + t) * brow + (g * p.N + n0) * 2 : kNowhere);
+          v[i4] = n0 < p.N ? recur(v[i4], exp2_fast(dt_t * alog), ux, b) : f32x4{};
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int i4 = 0; i4 < 4; ++i4) {
     if constexpr (kSingle)
-      reinterpret_cast<f32x4 *>(sBt)[state_piece(32 * pt + r, 8 * nt + 2 * i4 + kg)] = v;
+      reinterpret_cast<f32x4 *>(sBt)[state_piece(32 * pt + r, 8 * nt + 2 * i4 + kg)] = v[i4];
     else
-      *reinterpret_cast<f32x4 *>(slot + static_cast<size_t>(it.c) * kSlot + i4 * (4 * kThr)) = v;
+      *reinterpret_cast<f32x4 *>(slot + static_cast<size_t>(it.c) * kSlot + i4 * (4 * kThr)) = v[i4];
   }
   if constexpr (kSingle) {
     __syncthreads();
@@ -216,6 +271,55 @@ struct OutputsLds {
   __align__(16) float s_behind[kChunk], s_cs[kChunk], s_dt[kChunk];
   float s_total[kWaves];
 };
+// y of the chunk's tile tt by one wave, from the state that enters the chunk on; a lane has headdim column `lane` and all
+// state columns.
+template <bool kSingle>
+__device__ __forceinline__ void recur_rows(const ChunkParams &p, const Item &it, int tt, Rsrc rx, Rsrc rB, Rsrc rC, Rsrc rs, Rsrc ry,
+                                           bool from_h0, int oldest, int newest, float chunk_decay) {
+  constexpr int kQuads = kN / 4;
+  const int lane = threadIdx.x & 63, head = it.h / p.pdiv, g = it.h / p.hpg;
+  const uint32_t xrow = static_cast<uint32_t>(p.H) * (kP * 2), brow = static_cast<uint32_t>(p.G) * p.N * 2;
+  const float alog = p.A[head] * kLog2e, bias = p.dtx.bias != nullptr ? p.dtx.bias[head] : 0.f, Dh = p.D[head];
+  f32x4 S[kQuads];
+  const Rsrc rh = make_rsrc(from_h0 ? p.h0 + (static_cast<size_t>(it.b) * p.H + it.h) * kP * p.N : p.dt, from_h0 ? kP * p.N * 4u : 0u);
+#pragma unroll
+  for (int i = 0; i < kQuads; ++i) S[i] = __builtin_bit_cast(f32x4, buf_load16(rh, 4 * i < p.N ? (lane * p.N + 4 * i) * 4u : kNowhere));
+  if (!from_h0) {
+#pragma clang loop unroll(disable)
+    for (int k = oldest; k <= newest; ++k) {
+      const float d = k == oldest ? 0.f : read_lane(chunk_decay, k);
+#pragma unroll
+      for (int i = 0; i < kQuads; ++i) {
+        const uint32_t piece = 64 * (i >> 3) + 32 * (i & 1) + (lane & 31) + 256 * ((i & 6) + (lane >> 5));  // (see chunk_outputs)
+        S[i] = chain(S[i], d, __builtin_bit_cast(f32x4, buf_load16(rs, static_cast<uint32_t>(k) * (kSlot * 4) + 16 * piece)));
+      }
+    }
+  }
+  for (int j = 0; j <= tt; ++j) {
+    const float dts = dt_apply_branchless(step_size(p, it, head, kTile * j + (lane & 31)), bias, p.dtx);
+    const int n = min(kTile, it.rows - kTile * j);
+#pragma clang loop unroll(disable)
+    for (int t = 0; t < n; ++t) {
+      const uint32_t row = kTile * j + t, at = row * xrow + it.h * (kP * 2) + 2 * lane, bc = row * brow + g * p.N * 2;
+      const float dt_t = read_lane(dts, t), dA = exp2_fast(dt_t * alog), xv = x_at(rx, at), ux = dt_t * xv;
+      float part = 0.f;
+      int N = p.N;
+      asm volatile("" : "+s"(N));  // (or the comparisons are made ahead of the loop and kept in scalar registers)
+#pragma unroll
+      for (int i = 0; i < kQuads; i += 2) {
+        if (4 * i < N) {  // (no product with the columns that do not exist: zero times an infinity)
+          const u32x4 b = buf_load16(rB, bc + 8 * i), c = buf_load16(rC, bc + 8 * i);
+          S[i] = recur(S[i], dA, ux, u32x2{b.x, b.y});
+          S[i + 1] = recur(S[i + 1], dA, ux, u32x2{b.z, b.w});
+#pragma unroll
+          for (int q = 0; q < 4; ++q) part = fmaf(bf_hi(c[q]), S[i + q / 2][2 * (q & 1) + 1], fmaf(bf_lo(c[q]), S[i + q / 2][2 * (q & 1)], part));
+        }
+      }
+      if (j == tt) __builtin_amdgcn_raw_buffer_store_b16(static_cast<uint16_t>(pack2(fmaf(Dh, xv, part), 0.f)), ry, at, 0, 0);
+    }
+  }
+}
+
 template <bool kSingle>
 __device__ __forceinline__ void chunk_outputs(const ChunkParams &p, const Item &it, OutputsLds &lds) {
   uint8_t *const sB = lds.sB, *const sXt = lds.sXt, *const sH = lds.sH;
@@ -308,6 +412,23 @@ __device__ __forceinline__ void chunk_outputs(const ChunkParams &p, const Item &
     f32x4 *const rows = reinterpret_cast<f32x4 *>(sB);
     if (folds) {
       fold();
+      float seen = 0.f;
+#pragma unroll
+      for (int i = 0; i < kOwn; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) seen = larger(seen, S[i][q]);
+      if (!all_finite(seen)) {
+        request(oldest, first);
+#pragma unroll
+        for (int i = 0; i < kOwn; ++i) S[i] = __builtin_bit_cast(f32x4, first[i]);
+#pragma clang loop unroll(disable)
+        for (int k = oldest + 1; k <= newest; ++k) {
+          request(k, first);
+          const float d = read_lane(chunk_decay, k);
+#pragma unroll
+          for (int i = 0; i < kOwn; ++i) S[i] = chain(S[i], d, __builtin_bit_cast(f32x4, first[i]));
+        }
+      }
 #pragma unroll
       for (int i = 0; i < kOwn; ++i) rows[state_piece(32 * (i & 1) + r, 8 * wave + (i & ~1) + kg)] = S[i];
     }
@@ -453,6 +574,18 @@ __device__ __forceinline__ void chunk_outputs(const ChunkParams &p, const Item &
       for (int i = 0; i < 16; ++i) Y[pt][i] = fmaf(e_row, Z[pt][i], Y[pt][i]);
   }
 
+  const Rsrc ry = make_rsrc(p.y + tok * xrow, static_cast<uint32_t>(it.rows) * xrow);
+  {
+    float seen = 0.f;
+#pragma unroll
+    for (int pt = 0; pt < 2; ++pt)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) seen = larger(seen, Y[pt][i]);
+    if (!all_finite(kTile * tt + r < it.rows ? seen : 0.f)) {
+      recur_rows<kSingle>(p, it, tt, rx, rB, rC, rs, ry, from_h0, oldest, newest, chunk_decay);
+      return;
+    }
+  }
   // ---- y = Y + D x, rounded once, in the place of the x it takes and out as whole rows ----
 #pragma unroll
   for (int pt = 0; pt < 2; ++pt)
@@ -467,7 +600,6 @@ __device__ __forceinline__ void chunk_outputs(const ChunkParams &p, const Item &
       *reinterpret_cast<u32x4 *>(at) = o;
     }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  const Rsrc ry = make_rsrc(p.y + tok * xrow, static_cast<uint32_t>(it.rows) * xrow);
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     const int row = (lane >> 3) + 8 * k;

@@ -159,6 +159,7 @@ template <int kPolicy = 0>
 __device__ __forceinline__ u32x4 buf_load16(Rsrc r, uint32_t voff) {
   return __builtin_amdgcn_raw_buffer_load_b128(r, voff, 0, kPolicy);
 }
+__device__ __forceinline__ u32x2 buf_load8(Rsrc r, uint32_t voff) { return __builtin_amdgcn_raw_buffer_load_b64(r, voff, 0, 0); }
 template <int kPolicy = 0>
 __device__ __forceinline__ void buf_store16(Rsrc r, uint32_t voff, u32x4 v) {
   __builtin_amdgcn_raw_buffer_store_b128(v, r, voff, 0, kPolicy);

@@ -123,3 +123,39 @@ def test_an_undefined_decay_shows_in_every_row(ssd, tokens):
     torch.cuda.synchronize()
     assert torch.isnan(y[:, :, 0]).all() and torch.isnan(st[:, 0]).all()
     assert torch.equal(y[:, :, 1], y0[:, :, 1]) and torch.equal(st[:, 1], st0[:, 1])
+
+
+def _classes(a):
+    return np.where(np.isnan(a), 3, np.where(np.isposinf(a), 1, np.where(np.isneginf(a), 2, 0)))
+
+
+@pytest.mark.parametrize("where", ["x", "B", "C", "dt", "h0"])
+@pytest.mark.parametrize("same_sign", [False, True])
+@pytest.mark.parametrize("tokens, dstate, decay", [(20, 128, 1.0), (256, 64, 1.0), (255, 8, 6.0), (700, 128, 0.02), (700, 72, 1.0), (1100, 128, 5.0)])
+def test_infinities_are_what_the_recurrence_makes_of_them(ssd, where, same_sign, tokens, dstate, decay):
+    """One infinity among the inputs reaches the outputs that the recurrence lets it reach, of the sign that it has there or
+    undefined, however far the weights between the tokens have decayed (2^-decay a token, 256 of them below fp32's range)."""
+    H, P = 2, 64
+    g = torch.Generator().manual_seed(47)
+    draw = lambda *s: (lambda t: t.abs() + 0.25 if same_sign else t)(torch.randn(*s, generator=g))   # noqa: E731
+    x, B, C = draw(1, tokens, H, P), draw(1, tokens, 1, dstate), draw(1, tokens, 1, dstate)
+    dt = 0.05 * (0.8 + 0.4 * torch.rand(1, tokens, H, generator=g))
+    A, D, h0 = torch.full((H,), -decay / 0.05 * float(np.log(2.0))), draw(H), draw(1, H, P, dstate)
+    for at in (10, tokens // 2):
+        v = [t.clone() for t in (x.bfloat16(), dt, A, B.bfloat16(), C.bfloat16(), D, h0)]
+        {"x": v[0][0, at, 0], "B": v[3][0, at, 0], "C": v[4][0, at, 0], "dt": v[1][0, at], "h0": v[6][0, 0, at % P]}[where][
+            0 if where == "dt" else 3] = float("inf")
+        ssd.set_knob("chunk", 1)
+        alias = where == "h0" and tokens > 256
+        assert ssd.prefill_chunks(ssd.make_shape(1, tokens, H, P, dstate, 1, 64, torch.bfloat16), alias) == (tokens + 255) // 256
+        print("chunk kernels, infinite", where, same_sign, tokens, dstate, decay, at, flush=True)
+        dev = [t.cuda() for t in v]
+        y, st = ssd.ssd_prefill(*dev[:6], 64, h0=dev[6], final_state=dev[6] if alias else None)
+        torch.cuda.synchronize()
+        with np.errstate(all="ignore"):
+            refs = ssd_oracle.prefill(*[t.float() for t in v[:6]], h0=v[6])
+        for got, ref, what in ((y, refs[0], "y"), (st, refs[1], "final state")):
+            got = got.double().cpu().numpy()
+            assert np.array_equal(_classes(got), _classes(ref)), (what, at)
+            ok = np.isfinite(ref)
+            assert np.linalg.norm(got[ok] - ref[ok]) <= 2e-2 * np.linalg.norm(ref[ok]), (what, at)
