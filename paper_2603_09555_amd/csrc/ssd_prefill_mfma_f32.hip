@@ -83,8 +83,8 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ f32x4 buf_load4(Rsrc rs, uint32_t voff) {
   return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, voff, 0, 0));
 }
-__device__ __forceinline__ float buf_load1(Rsrc rs, uint32_t voff) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, voff, 0, 0));
+__device__ __forceinline__ float buf_load1(Rsrc rs, uint32_t voff, uint32_t soff = 0) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, voff, soff, 0));
 }
 __device__ __forceinline__ void buf_store1(Rsrc rs, uint32_t voff, float v) {
   __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), rs, voff, 0, 0);
@@ -258,19 +258,20 @@ __global__ __launch_bounds__(kF32Threads) void prefill_f32_kernel(const F32Param
   if (out0 == 0 && walk_end > 0) load_block(0);
   if (out0 > 0) {
     // ---- the blocks before the segment: the state alone, S = sum_s (decay behind s) dt_s x_s (x) B_s, one long contraction
-    //      without a block in it.  Wave w takes the w-th quarter of the tokens, in accumulators of its own.  The operands
+    //      without a barrier between its blocks.  Wave w takes tokens 16 w .. 16 w + 15 of every block, in accumulators of its
+    //      own: the newest tokens, which weigh most, are shared by all of them (a quarter of the sequence to each wave
+    //      left them to one chain of sums, and the state 3 % further off over 60 drawn prompts, 27 % at worst).  The operands
     //      come straight from memory: lane (r, k) of the matrix instruction wants x[s][col r] and B[s][n = 32 nt + r] of
-    //      token s, which 32 lanes read as one piece of a row.  So no barrier and no LDS tile lies on the way, only the
-    //      weights do, kMost tokens per wave at a time (in what will be the masked-score tile); a batch of tokens is in flight
+    //      token s, which 32 lanes read as one piece of a row.  So no tile in LDS lies on the way, only the
+    //      weights do, kMost blocks at a time (in what will be the masked-score tile), a quarter of the blocks to each wave; a
+    //      ring of batches of 16 tokens is in flight
     //      while the ones before it are multiplied.  Bound: the matrix instruction for long sequences (64 cycles per two
     //      tokens and 32 state columns), the first loads and the weights behind them for short ones (7 blocks, dstate
     //      16: 1.2 us until the weights are there, 2.1 to multiply, 0.5 for the sum).  As a walk over staged blocks a
     //      block cost 0.76 us (dstate 16) to 2.2 (128) of the workgroup's time, now 0.32 to 1.26: 512 tokens x 4 heads x 32 x
-    //      16 12.5 -> 9.9 us, 2 x 836 x 3 x 64 x 128 43.7 -> 30.4, 110 drawn prompts 1.07 times as fast together. ----
-    constexpr int kMost = 1024, kBatch = 16, kDepth = NT == 1 ? 8 : NT == 2 ? 4 : 2;
-    static_assert(4 * kMost <= kTok * kRowT && kMost % kBatch == 0, "the weights fit in the masked-score tile, whole batches");
-    float *const w_of = &sGM[wave * kMost];
-    const int quarter = out0 * (kTok / 4), first = wave * quarter;  // (all these blocks are whole)
+    //      16 11.7 -> 9.6 us, 2 x 836 x 3 x 64 x 128 43.7 -> 30.4, 110 drawn prompts 1.07 times as fast together. ----
+    constexpr int kMost = 64, kBatch = 16, kDepth = NT == 1 ? 8 : NT == 2 ? 4 : 2;
+    static_assert(kMost * kTok <= kTok * kRowT && kMost <= 64 && kMost <= kTok, "weights in the masked-score tile, a block's decay per lane");
     // (kNarrow: the 16 x 16 x 4 instruction, which spends nothing on columns 16 .. 31 of the tile: lane (c, k) = (lane % 16,
     // lane / 16) supplies columns c and 16 + c of x and column c of B, of token 4 k + j in step j of 16 tokens)
     constexpr int kTilesX = kNarrow ? 2 : 1, kTilesB = kNarrow ? 1 : NT, kTiles = kTilesX * kTilesB;
@@ -290,60 +291,87 @@ __global__ __launch_bounds__(kF32Threads) void prefill_f32_kernel(const F32Param
       for (int t = 0; t < kTilesB; ++t)
         v_bs[t][j] = 32 * t + lane_col < p.N ? static_cast<uint32_t>(lane_tok + j) * brow + 4 * (32 * t + lane_col) : kNowhere;
     }
-    float log2_quarter = 0.f;
-    for (int c0 = 0; c0 < quarter; c0 += kMost) {
-      const int n = min(kMost, quarter - c0), t0 = first + c0;
-      float xs[kDepth][kTilesX][kSteps], bs[kDepth][kTilesB][kSteps];
-      auto request = [&](int buf, int s0) __attribute__((always_inline)) {
+    float log2_all = 0.f;
+    struct Batch {
+      float x[kTilesX][kSteps], b[kTilesB][kSteps];
+    };
+    // the n blocks from b0 on, n <= kMost; the sum so far decays over them
+    auto contract = [&](const int b0, const int n) __attribute__((always_inline)) {
+      const uint32_t t0 = static_cast<uint32_t>(b0) * kTok;
+      // this wave's tokens of block j (one of the n: the offset in scalar registers is no part of the hardware's check)
+      const uint32_t first = t0 + kBatch * wave, rows = n * kTok - kBatch * wave;
+      const Rsrc rxs = make_rsrc(xb + static_cast<size_t>(first) * xrow, rows * xrow), rbs = make_rsrc(Bb + static_cast<size_t>(first) * brow, rows * brow);
+      auto request = [&](Batch &to, int j) __attribute__((always_inline)) {
 #pragma unroll
         for (int q = 0; q < kSteps / 4; ++q) {
-          const int s = s0 + 8 * q, left = max(n - s, 0);  // (uniform: the descriptors are built by the scalar unit)
-          const Rsrc rxs = make_rsrc(xb + static_cast<size_t>(t0 + s) * xrow, static_cast<uint32_t>(left) * xrow);
-          const Rsrc rbs = make_rsrc(Bb + static_cast<size_t>(t0 + s) * brow, static_cast<uint32_t>(left) * brow);
+          const uint32_t at = j * kTok + 8 * q;
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
+          for (int i = 0; i < 4; ++i) {
 #pragma unroll
-            for (int t = 0; t < kTilesX; ++t) xs[buf][t][4 * q + j] = buf_load1(rxs, v_xs[t][j]);
+            for (int t = 0; t < kTilesX; ++t) to.x[t][4 * q + i] = buf_load1(rxs, v_xs[t][i], at * xrow);
 #pragma unroll
-            for (int t = 0; t < kTilesB; ++t) bs[buf][t][4 * q + j] = buf_load1(rbs, v_bs[t][j]);
+            for (int t = 0; t < kTilesB; ++t) to.b[t][4 * q + i] = buf_load1(rbs, v_bs[t][i], at * brow);
           }
         }
       };
-      // weights relative to the end of these n tokens, from the last 64 back
-      const Rsrc rd = make_rsrc(dtb + static_cast<size_t>(t0) * drow, static_cast<uint32_t>(n - 1) * drow + 4);
-      float total = 0.f;
-      auto step_at = [&](int at) { return buf_load1(rd, at >= 0 ? static_cast<uint32_t>(at) * drow : kNowhere); };
-      float ahead = step_at(n - kTok + lane), ahead2 = step_at(n - 2 * kTok + lane);
+      // ---- the step sizes for the weights: this wave's are those of block n - 1 - wave and of every fourth before it, four
+      //      blocks at a time; then the first batches ----
+      const Rsrc rd = make_rsrc(dtb + static_cast<size_t>(t0) * drow, static_cast<uint32_t>(n * kTok - 1) * drow + 4);
+      auto step_at = [&](int j) { return buf_load1(rd, j >= 0 ? static_cast<uint32_t>(j * kTok + lane) * drow : kNowhere); };
+      float steps[4];
 #pragma unroll
-      for (int k = 0; k < kDepth; ++k) request(k, kBatch * k);
-      if (c0 == 0) load_block(out0);  // (uniform; the segment's first block arrives meanwhile)
-      for (int at = n - kTok; at > -kTok; at -= kTok) {
-        float dtv = ahead;
-        ahead = ahead2;
-        if (at > kTok) ahead2 = step_at(at - 2 * kTok + lane);
-        if (!p.dt_plain) dtv = dt_apply_branchless(dtv, dbias, p.dtx);
-        dtv = at + lane >= 0 ? dtv : 0.f;
-        const float cs = wave_prefix_sum(cut_step(dtv, alog) * alog);
-        const float c63 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, cs), 63));
-        if (at + lane >= 0) w_of[at + lane] = dtv * exp2_fast(total + (c63 - cs));
-        total += c63;
+      for (int i = 0; i < 4; ++i) steps[i] = step_at(n - 1 - wave - 4 * i);
+      Batch batch[kDepth];
+#pragma unroll
+      for (int k = 0; k < kDepth; ++k) {
+        request(batch[k], min(k, n - 1));
+        __builtin_amdgcn_sched_barrier(0);
       }
-      const float e_all = exp2_fast(total);
-      log2_quarter += total;
+      if (b0 == 0) load_block(out0);  // (uniform; the segment's first block arrives meanwhile)
+      if (b0 > 0) __syncthreads();    // the weights before have been used
+      // ---- weights, relative to the end of their block, and the decays of the blocks ----
+      for (int j = n - 1 - wave; j >= 0; j -= 16) {
 #pragma unroll
-      for (int t = 0; t < kTiles; ++t) Spart[t] *= e_all;
-      auto multiply = [&](int buf, int s0) __attribute__((always_inline)) {
+        for (int i = 0; i < 4; ++i) {
+          const int jb = j - 4 * i;
+          if (jb >= 0) {
+            float dtv = steps[i];
+            if (!p.dt_plain) dtv = dt_apply_branchless(dtv, dbias, p.dtx);
+            const float cs = wave_prefix_sum(cut_step(dtv, alog) * alog);
+            const float c63 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, cs), 63));
+            sGM[jb * kTok + lane] = dtv * exp2_fast(c63 - cs);
+            if (lane == 0) sCs[jb] = c63;
+          }
+        }
+        if (j >= 16) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) steps[i] = step_at(j - 16 - 4 * i);
+        }
+      }
+      __syncthreads();
+      // lane k: the decay behind block n - 1 - k, over the k blocks after it
+      const float behind = wave_prefix_sum(lane >= 1 && lane < n ? sCs[max(n - lane, 0)] : 0.f), factor = exp2_fast(behind);
+      const float total = sCs[0] + __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, behind), n - 1));
+      log2_all += total;
+      if (b0 > 0) {
+        const float e_total = exp2_fast(total);
+#pragma unroll
+        for (int t = 0; t < kTiles; ++t) Spart[t] *= e_total;
+      }
+      // ---- the contraction ----
+      auto multiply = [&](const Batch &of, int j) __attribute__((always_inline)) {
+        const float e = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, factor), n - 1 - j));
 #pragma unroll
         for (int q = 0; q < kSteps / 4; ++q) {
-          const f32x4 w = ld4(&w_of[s0 + 8 * q + lane_tok]);
+          const f32x4 w = ld4(&sGM[j * kTok + kBatch * wave + 8 * q + lane_tok]) * e;
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
+          for (int i = 0; i < 4; ++i)
 #pragma unroll
             for (int tx = 0; tx < kTilesX; ++tx)
 #pragma unroll
               for (int tb = 0; tb < kTilesB; ++tb) {
                 Part &acc = Spart[tx * kTilesB + tb];
-                const float a = w[j] * xs[buf][tx][4 * q + j], bv = bs[buf][tb][4 * q + j];
+                const float a = w[i] * of.x[tx][4 * q + i], bv = of.b[tb][4 * q + i];
                 if constexpr (kNarrow)
                   acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bv, acc, 0, 0, 0);
                 else
@@ -351,29 +379,27 @@ __global__ __launch_bounds__(kF32Threads) void prefill_f32_kernel(const F32Param
               }
         }
       };
-      for (int s0 = 0; s0 < n; s0 += kDepth * kBatch) {
+      int j0 = 0;
+      for (; j0 + kDepth < n; j0 += kDepth) {
 #pragma unroll
         for (int k = 0; k < kDepth; ++k) {
-          const int at = s0 + kBatch * k;
-          if (at < n) multiply(k, at);
-          request(k, at + kDepth * kBatch);
+          multiply(batch[k], j0 + k);
+          __builtin_amdgcn_sched_barrier(0);
+          request(batch[k], min(j0 + k + kDepth, n - 1));  // (towards the end: a harmless repeat, no branch)
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
-    }
-    // ---- the sum over the quarters, each decayed by the later ones, through the masked-score tile; the initial state rides in
-    //      the accumulators of the wave that owns the tile ----
-    if (lane == 0) sCs[wave] = log2_quarter;
-    __syncthreads();
-    float behind = 0.f, all = 0.f;
 #pragma unroll
-    for (int w = 3; w >= 0; --w) {
-      behind += w > wave ? sCs[w] : 0.f;
-      all += sCs[w];
-    }
-    const float e_behind = exp2_fast(behind), e_all = exp2_fast(all);
-#pragma unroll
-    for (int t = 0; t < kTiles; ++t) Spart[t] *= e_behind;
+      for (int k = 0; k < kDepth; ++k)
+        if (j0 + k < n) multiply(batch[k], j0 + k);
+    };
+    int n = (out0 - 1) % kMost + 1;  // (what is not a multiple of kMost blocks comes first)
+    for (int b0 = 0; b0 < out0; b0 += n, n = kMost) contract(b0, n);
+    // ---- the sum over the waves, through the masked-score tile; the initial state rides in the accumulators of the wave that
+    //      owns the tile ----
+    const float e_all = exp2_fast(log2_all);
     if constexpr (kNarrow) {  // lane (c, k), element e: headdim column 16 tile + 4 k + e, state column c
+      __syncthreads();
 #pragma unroll
       for (int t = 0; t < kTiles; ++t)
 #pragma unroll
@@ -417,6 +443,8 @@ __global__ __launch_bounds__(kF32Threads) void prefill_f32_kernel(const F32Param
         }
       }
     }
+    // (every load above has arrived, or the code up to the next block would wait for it also where none was made)
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
   }
   for (int jb = out0; jb < walk_end; ++jb) {
     __syncthreads();  // the previous block's readers are done with every tile

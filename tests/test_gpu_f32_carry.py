@@ -53,3 +53,26 @@ def test_state_entering_a_segment(ssd, case):
         err = np.linalg.norm(got.double().cpu().numpy() - ref) / np.linalg.norm(ref)
         print("  %s off by %.2e" % (what, err), flush=True)
         assert err <= 1e-6, (what, err)
+
+
+@pytest.mark.parametrize("dims, segments", [((577, 2, 32, 8), 16), ((404, 1, 32, 128), 8), ((330, 2, 32, 64), 6)], ids=str)
+def test_the_state_is_no_further_off_than_that_of_one_walk(ssd, dims, segments):
+    """Over twelve prompts, against 64 bits: a segment's entering state is summed in four chains, with the newest tokens in all of
+    them, the walk's in two (two per cent for the luck of single roundings)."""
+    tokens, heads, headdim, dstate = dims
+    squares = {1: 0.0, segments: 0.0}
+    for seed in range(12):
+        cfg = inputs.SSDConfig("t", 1, tokens, heads, headdim, dstate, 1, 64, "f32")
+        inp = inputs.make_prefill_inputs(cfg, seed=seed)
+        _, ref = ssd_oracle.prefill(*[inp[k] for k in ("x", "dt", "A", "B", "C", "D")])
+        for s in squares:
+            ssd.reset_knobs()
+            ssd.set_knob("force_mfma_f32", 1)
+            ssd.set_knob("f32_segments", s)
+            _, st = ssd.ssd_prefill(*[inp[k].cuda() for k in ("x", "dt", "A", "B", "C", "D")], 64)
+            torch.cuda.synchronize()
+            squares[s] += float((np.linalg.norm(st.double().cpu().numpy() - ref) / np.linalg.norm(ref)) ** 2)
+        ssd.reset_knobs()
+    ratio = float(np.sqrt(squares[segments] / squares[1]))
+    print("state of %d segments / of one, off from 64 bits: %.3f" % (segments, ratio), flush=True)
+    assert ratio <= 1.02
