@@ -262,14 +262,15 @@ __global__ __launch_bounds__(kF32Threads) void prefill_f32_kernel(const F32Param
     //      own: the newest tokens, which weigh most, are shared by all of them (a quarter of the sequence to each wave
     //      left them to one chain of sums, and the state 3 % further off over 60 drawn prompts, 27 % at worst).  The operands
     //      come straight from memory: lane (r, k) of the matrix instruction wants x[s][col r] and B[s][n = 32 nt + r] of
-    //      token s, which 32 lanes read as one piece of a row.  So no tile in LDS lies on the way, only the
-    //      weights do, kMost blocks at a time (in what will be the masked-score tile), a quarter of the blocks to each wave; a
-    //      ring of batches of 16 tokens is in flight
-    //      while the ones before it are multiplied.  Bound: the matrix instruction for long sequences (64 cycles per two
-    //      tokens and 32 state columns), the first loads and the weights behind them for short ones (7 blocks, dstate
-    //      16: 1.2 us until the weights are there, 2.1 to multiply, 0.5 for the sum).  As a walk over staged blocks a
-    //      block cost 0.76 us (dstate 16) to 2.2 (128) of the workgroup's time, now 0.32 to 1.26: 512 tokens x 4 heads x 32 x
-    //      16 11.7 -> 9.6 us, 2 x 836 x 3 x 64 x 128 43.7 -> 30.4, 110 drawn prompts 1.07 times as fast together. ----
+    //      token s, which 32 lanes read as one piece of a row.  So no tile in LDS lies on the way, only the weights do, kMost
+    //      blocks at a time (in what will be the masked-score tile), a quarter of the blocks to each wave; a ring of batches of 16
+    //      tokens is in flight while the ones before it are multiplied.  Bound: the matrix instruction for long sequences (64
+    //      cycles per two tokens and 32 state columns), the first loads and the weights behind them for short ones.  Up to
+    //      kDepth blocks, which fit the ring, ask for no more than they have: with requests beyond the last block, which bring
+    //      nothing but take their turn, a block or two before the segment cost 1 to 2 us more than as a walk over staged blocks
+    //      (69 tokens x 11 heads x 64 x 32 9.6 us, 8.0 as a walk, now 7.8).  As a walk a block cost 0.76 us (dstate 16) to 2.2
+    //      (128) of the workgroup's time, now 0.32 to 1.26: 512 tokens x 4 heads x 32 x 16 11.7 -> 9.0 us, 2 x 711 x 10 x 32 x 128
+    //      40.5 -> 29.0, 100 drawn prompts 1.09 times as fast together. ----
     constexpr int kMost = 64, kBatch = 16, kDepth = NT == 1 ? 8 : NT == 2 ? 4 : 2;
     static_assert(kMost * kTok <= kTok * kRowT && kMost <= 64 && kMost <= kTok, "weights in the masked-score tile, a block's decay per lane");
     // (kNarrow: the 16 x 16 x 4 instruction, which spends nothing on columns 16 .. 31 of the tile: lane (c, k) = (lane % 16,
@@ -295,8 +296,9 @@ __global__ __launch_bounds__(kF32Threads) void prefill_f32_kernel(const F32Param
     struct Batch {
       float x[kTilesX][kSteps], b[kTilesB][kSteps];
     };
-    // the n blocks from b0 on, n <= kMost; the sum so far decays over them
-    auto contract = [&](const int b0, const int n) __attribute__((always_inline)) {
+    // the n blocks from b0 on, of which n <= kMost (kFew: <= kDepth, all of them); the sum so far decays over them
+    auto contract = [&](const int b0, const int n, auto few_tag) __attribute__((always_inline)) {
+      constexpr bool kFew = decltype(few_tag)::value;
       const uint32_t t0 = static_cast<uint32_t>(b0) * kTok;
       // this wave's tokens of block j (one of the n: the offset in scalar registers is no part of the hardware's check)
       const uint32_t first = t0 + kBatch * wave, rows = n * kTok - kBatch * wave;
@@ -315,7 +317,7 @@ __global__ __launch_bounds__(kF32Threads) void prefill_f32_kernel(const F32Param
         }
       };
       // ---- the step sizes for the weights: this wave's are those of block n - 1 - wave and of every fourth before it, four
-      //      blocks at a time; then the first batches ----
+      //      blocks at a time; then the first batches.  (kFew: no request is made that has no block, 128 of them take 0.9 us) ----
       const Rsrc rd = make_rsrc(dtb + static_cast<size_t>(t0) * drow, static_cast<uint32_t>(n * kTok - 1) * drow + 4);
       auto step_at = [&](int j) { return buf_load1(rd, j >= 0 ? static_cast<uint32_t>(j * kTok + lane) * drow : kNowhere); };
       float steps[4];
@@ -324,7 +326,7 @@ __global__ __launch_bounds__(kF32Threads) void prefill_f32_kernel(const F32Param
       Batch batch[kDepth];
 #pragma unroll
       for (int k = 0; k < kDepth; ++k) {
-        request(batch[k], min(k, n - 1));
+        if (!kFew || k < n) request(batch[k], min(k, n - 1));
         __builtin_amdgcn_sched_barrier(0);
       }
       if (b0 == 0) load_block(out0);  // (uniform; the segment's first block arrives meanwhile)
@@ -380,21 +382,27 @@ __global__ __launch_bounds__(kF32Threads) void prefill_f32_kernel(const F32Param
         }
       };
       int j0 = 0;
-      for (; j0 + kDepth < n; j0 += kDepth) {
+      if constexpr (!kFew) {
+        for (; j0 + kDepth < n; j0 += kDepth) {
 #pragma unroll
-        for (int k = 0; k < kDepth; ++k) {
-          multiply(batch[k], j0 + k);
-          __builtin_amdgcn_sched_barrier(0);
-          request(batch[k], min(j0 + k + kDepth, n - 1));  // (towards the end: a harmless repeat, no branch)
-          __builtin_amdgcn_sched_barrier(0);
+          for (int k = 0; k < kDepth; ++k) {
+            multiply(batch[k], j0 + k);
+            __builtin_amdgcn_sched_barrier(0);
+            request(batch[k], min(j0 + k + kDepth, n - 1));  // (towards the end: a harmless repeat, no branch)
+            __builtin_amdgcn_sched_barrier(0);
+          }
         }
       }
 #pragma unroll
       for (int k = 0; k < kDepth; ++k)
         if (j0 + k < n) multiply(batch[k], j0 + k);
     };
-    int n = (out0 - 1) % kMost + 1;  // (what is not a multiple of kMost blocks comes first)
-    for (int b0 = 0; b0 < out0; b0 += n, n = kMost) contract(b0, n);
+    if (kDepth > 2 && out0 <= kDepth) {
+      contract(0, out0, std::true_type{});
+    } else {
+      int n = (out0 - 1) % kMost + 1;  // (what is not a multiple of kMost blocks comes first)
+      for (int b0 = 0; b0 < out0; b0 += n, n = kMost) contract(b0, n, std::false_type{});
+    }
     // ---- the sum over the waves, through the masked-score tile; the initial state rides in the accumulators of the wave that
     //      owns the tile ----
     const float e_all = exp2_fast(log2_all);

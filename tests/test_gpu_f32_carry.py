@@ -21,6 +21,7 @@ def ssd():
 # batch, tokens, heads, headdim, dstate, groups; segments; raw step sizes; steps that decay everything
 CASES = [((1, 65, 2, 32, 8, 1), 2, False, False), ((2, 130, 3, 64, 16, 1), 3, True, False), ((1, 512, 4, 32, 16, 1), 8, False, True),
          ((1, 321, 2, 32, 24, 2), 6, False, False), ((1, 449, 2, 64, 64, 1), 7, True, True), ((2, 200, 2, 32, 96, 1), 4, False, False),
+         ((1, 640, 2, 32, 16, 1), 10, False, False), ((1, 640, 2, 32, 32, 1), 10, True, False),   # (eight, nine blocks before a segment)
          ((1, 333, 3, 32, 128, 3), 6, True, False), ((1, 4300, 1, 32, 16, 1), 64, False, False), ((1, 8500, 1, 32, 40, 1), 64, False, True)]
 
 
