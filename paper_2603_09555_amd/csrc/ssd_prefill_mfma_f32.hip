@@ -53,6 +53,8 @@ __device__ __forceinline__ f32x16 mfma_group(const f32x4 a, const f32x4 b, f32x1
   return mfma2(a.w, b.w, c);
 }
 __device__ __forceinline__ float exp2_fast(float v) { return __builtin_amdgcn_exp2f(v); }
+// The larger magnitude, or NaN if one is.
+__device__ __forceinline__ float larger(float seen, float v) { return __builtin_elementwise_maximum(seen, __builtin_fabsf(v)); }
 
 template <int kCtrl, int kRowMask>
 __device__ __forceinline__ float dpp_or_zero(float v) {
@@ -447,6 +449,44 @@ __global__ __launch_bounds__(kF32Threads) void prefill_f32_kernel(const F32Param
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j) Sacc[nt >> 1][4 * e4 + j] = fmaf(e_all, Sacc[nt >> 1][4 * e4 + j], sum[j]);
+          }
+        }
+      }
+    }
+    // An infinity times a weight that underflows is undefined, where the recurrence multiplies it by one decay at a time: an owner
+    // whose state is not all finite applies the recurrence as it stands, token by token.
+    if (wave >= 2) {
+      float seen = 0.f;
+#pragma unroll
+      for (int k = 0; k < kTilesPerWave; ++k)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) seen = larger(seen, Sacc[k][e]);
+      if (__builtin_amdgcn_ballot_w64(!(seen < __builtin_inff())) != 0) {
+        const size_t slice = ((static_cast<size_t>(b) * p.H + h) * p.P + kCols * ps) * p.N;
+        const Rsrc rh = make_rsrc(p.h0 != nullptr ? p.h0 + slice : p.dt, p.h0 != nullptr ? kCols * p.N * 4u : 0u);
+#pragma unroll
+        for (int k = 0; k < kTilesPerWave; ++k) {
+          const int n = 32 * state_tile(k) + r;
+#pragma unroll
+          for (int e = 0; e < 16; ++e) Sacc[k][e] = buf_load1(rh, n < p.N ? (((e >> 2) * 8 + 4 * kk + (e & 3)) * p.N + n) * 4u : kNowhere);
+        }
+        for (int j = 0; j < out0; ++j) {
+          const Rsrc rx = rsrc_at(xb, xrow, xoff, j), rb = rsrc_at(Bb, brow, boff, j);
+          float dts = buf_load1(rsrc_at(dtb, drow, static_cast<uint32_t>(h) * 4, j), v_dt);
+          if (!p.dt_plain) dts = dt_apply_branchless(dts, dbias, p.dtx);
+#pragma clang loop unroll(disable)
+          for (int t = 0; t < kTok; ++t) {
+            const float dt_t = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, dts), t)), dA = exp2_fast(dt_t * alog);
+            f32x4 x4[4];
+#pragma unroll
+            for (int e4 = 0; e4 < 4; ++e4) x4[e4] = buf_load4(rx, t * xrow + 4 * (8 * e4 + 4 * kk)) * dt_t;
+#pragma unroll
+            for (int k = 0; k < kTilesPerWave; ++k) {
+              const int n = 32 * state_tile(k) + r;
+              const float bv = buf_load1(rb, n < p.N ? t * brow + 4 * n : kNowhere);
+#pragma unroll
+              for (int e = 0; e < 16; ++e) Sacc[k][e] = n < p.N ? fmaf(dA, Sacc[k][e], x4[e >> 2][e & 3] * bv) : 0.f;
+            }
           }
         }
       }

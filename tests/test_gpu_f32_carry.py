@@ -77,3 +77,41 @@ def test_the_state_is_no_further_off_than_that_of_one_walk(ssd, dims, segments):
     ratio = float(np.sqrt(squares[segments] / squares[1]))
     print("state of %d segments / of one, off from 64 bits: %.3f" % (segments, ratio), flush=True)
     assert ratio <= 1.02
+
+
+def _classes(a):
+    return np.where(np.isnan(a), 3, np.where(np.isposinf(a), 1, np.where(np.isneginf(a), 2, 0)))
+
+
+@pytest.mark.parametrize("where", ["x", "B", "h0"])
+@pytest.mark.parametrize("same_sign", [False, True])
+@pytest.mark.parametrize("tokens, headdim, dstate, segments", [(330, 32, 16, 6), (700, 32, 8, 11), (700, 64, 64, 3), (900, 32, 128, 2), (4700, 32, 32, 3)])
+def test_infinities_survive_the_way_to_a_segment(ssd, where, same_sign, tokens, headdim, dstate, segments):
+    """An infinity in the state stays one while the decay behind it leaves fp32's range (2^-1 a token), as in the recurrence, and
+    reaches the outputs of later blocks as what it is there."""
+    H = 2
+    g = torch.Generator().manual_seed(53)
+    draw = lambda *s: (lambda t: t.abs() + 0.25 if same_sign else t)(torch.randn(*s, generator=g))   # noqa: E731
+    x, B, C = draw(1, tokens, H, headdim), draw(1, tokens, 1, dstate), draw(1, tokens, 1, dstate)
+    dt = 0.05 * (0.8 + 0.4 * torch.rand(1, tokens, H, generator=g))
+    A, D, h0 = torch.full((H,), -20.0 * float(np.log(2.0))), draw(H), draw(1, H, headdim, dstate)
+    for at in (10, tokens // 4):   # (before the last segment either way)
+        v = [t.clone() for t in (x, dt, A, B, C, D, h0)]
+        {"x": v[0][0, at, 0], "B": v[3][0, at, 0], "h0": v[6][0, 0, at % headdim]}[where][3] = float("-inf")
+        ssd.reset_knobs()
+        ssd.set_knob("force_mfma_f32", 1)
+        ssd.set_knob("f32_segments", segments)
+        print("infinite", where, same_sign, tokens, headdim, dstate, segments, at, flush=True)
+        dev = [t.cuda() for t in v]
+        y, st = ssd.ssd_prefill(*dev[:6], 64, h0=dev[6])
+        torch.cuda.synchronize()
+        ssd.reset_knobs()
+        with np.errstate(all="ignore"):
+            y_ref, st_ref = ssd_oracle.prefill(*v[:6], h0=v[6])
+        y, st = y.double().cpu().numpy(), st.double().cpu().numpy()
+        assert np.array_equal(_classes(st), _classes(st_ref)), at
+        if where != "x" or dstate % 32 == 0:   # (x meets the zeros of padded state columns, and masked scores in its own block)
+            later = slice(0 if where == "h0" else (at // 64 + 1) * 64, None)
+            assert np.array_equal(_classes(y[:, later]), _classes(y_ref[:, later])), at
+        ok = np.isfinite(st_ref)   # (exponents of up to 64 are rounded at 2^-18: 2.6e-6 of a factor)
+        assert np.linalg.norm(st[ok] - st_ref[ok]) <= 1e-5 * np.linalg.norm(st_ref[ok])
