@@ -417,27 +417,29 @@ __device__ __forceinline__ void buf_store16(Rsrc r, uint32_t voff, u32x4 v) {
 }
 
 // Memory straight into LDS: the wave's 64 lanes fetch 16 bytes each, from wherever their offsets say, and the 1024 bytes
-// land in lane order from the LDS address `to` on (uniform, as are the descriptor and soff; lanes beyond the descriptor
-// write zeros).  Nothing passes through registers.  Written as assembly because the compiler, which does not tell the
+// land in lane order from the LDS address `to` on (uniform, as is the descriptor; lanes beyond the descriptor write
+// zeros).  Nothing passes through registers.  Written as assembly because the compiler, which does not tell the
 // LDS buffers apart, would let every later LDS read wait for it: the caller waits itself (vector memory operations
-// complete in order), before the barrier that hands the buffer over.
+// complete in order), before the barrier that hands the buffer over.  The compiler does not look for hazards inside: a vector
+// instruction that writes a scalar register, as the moves to uniform registers and the reload of a spilled one are, is
+// followed by five wait states before a vector memory instruction reads it, the write of m0 by one.
 __device__ __forceinline__ uint32_t uniform32(uint32_t v) { return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v))); }
 __device__ __forceinline__ u32x4 raw_rsrc(const void *base, uint32_t bytes) {
   const uint64_t a = reinterpret_cast<uint64_t>(base);
   return u32x4{uniform32(static_cast<uint32_t>(a)), uniform32(static_cast<uint32_t>(a >> 32)) & 0xFFFFu, uniform32(bytes), 0x00020000u};
 }
-__device__ __forceinline__ void load_to_lds(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t to) {
-  asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
-               :: "v"(voff), "s"(rsrc), "s"(uniform32(soff)), "s"(uniform32(to)) : "memory");
+__device__ __forceinline__ void load_to_lds(u32x4 rsrc, uint32_t voff, uint32_t to) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 4\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
+               :: "v"(voff), "s"(rsrc), "s"(uniform32(to)) : "memory", "m0");
 }
 
 // Four of them to consecutive places.  The places come from the instructions' offsets, which move the addresses in
 // memory as well: voff[k] is to be 1024 k less than the offset that is meant.  (With m0 written before each of them a request
 // holds its wave for 95 cycles when the four SIMDs of a CU make them, in pairs behind one write for 45.)
 __device__ __forceinline__ void load_to_lds4(u32x4 rsrc, uint32_t v0, uint32_t v1, uint32_t v2, uint32_t v3, uint32_t to) {
-  asm volatile("s_mov_b32 m0, %5\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %4, 0 offen lds\n\tbuffer_load_dwordx4 %1, %4, 0 offen offset:1024 lds\n\t"
+  asm volatile("s_mov_b32 m0, %5\n\ts_nop 4\n\tbuffer_load_dwordx4 %0, %4, 0 offen lds\n\tbuffer_load_dwordx4 %1, %4, 0 offen offset:1024 lds\n\t"
                "buffer_load_dwordx4 %2, %4, 0 offen offset:2048 lds\n\tbuffer_load_dwordx4 %3, %4, 0 offen offset:3072 lds"
-               :: "v"(v0), "v"(v1), "v"(v2), "v"(v3), "s"(rsrc), "s"(uniform32(to)) : "memory");
+               :: "v"(v0), "v"(v1), "v"(v2), "v"(v3), "s"(rsrc), "s"(uniform32(to)) : "memory", "m0");
 }
 
 // A 64-bit value that is the same in every lane, moved to scalar registers.
@@ -1859,7 +1861,7 @@ __device__ __forceinline__ void pair_feed(const ScanParams &p, const SeqView &sv
   uint32_t vb[2];
 #pragma unroll
   for (int k = 0; k < 2; ++k) vb[k] = static_cast<uint32_t>(32 * wave + (lane >> 3)) * (kBlk * 2) + 16 * ((lane ^ (lane >> 4) ^ 4 * k) & 7);
-  const uint32_t vt = static_cast<uint32_t>(tid >> 3) * (kBlk * 2) + 16 * ((tid ^ (tid >> 4)) & 7);
+  const uint32_t vt = static_cast<uint32_t>(32 + (tid >> 3)) * (kBlk * 2) + 16 * ((tid ^ (tid >> 4)) & 7);  // G's upper rows
   // The tenth request of a wave: waves 0 and 1 fetch a half of G's short rows each, waves 2 and 3 (both the same) the record
   // entries that the two heads need next: 32 lanes the input factors of block jb + 2, 32 the output-row factors of jb + 1.
   const bool fetches_g = wave < 2;
@@ -1875,10 +1877,10 @@ __device__ __forceinline__ void pair_feed(const ScanParams &p, const SeqView &sv
     load_to_lds4(raw_rsrc(cb + static_cast<size_t>(jb) * kBlk * crow - kEarly, no ? 0 : cbytes - static_cast<uint32_t>(jb) * kBlk * crow + kEarly),
                  vc[0], vc[1], vc[2], vc[3], to + wave * 4096);
     load_to_lds4(raw_rsrc(btb + static_cast<size_t>(jb) * (kN * kBlk * 2), no ? 0 : kN * kBlk * 2), vb[0], vb[1], vb[0], vb[1], to + L::kBt + wave * 4096);
-    load_to_lds(raw_rsrc(gt, no ? 0 : kBlk * kBlk * 2), vt, 32 * kBlk * 2, to + L::kGHigh + wave * 1024);
+    load_to_lds(raw_rsrc(gt, no ? 0 : kBlk * kBlk * 2), vt, to + L::kGHigh + wave * 1024);
     load_to_lds(raw_rsrc(fetches_g ? gt : reinterpret_cast<const uint8_t *>(rec_first + static_cast<size_t>(jb) * kRec),
                          no ? 0 : fetches_g ? kBlk * kBlk * 2u : head_step + static_cast<uint32_t>(sv.nb - jb) * (kRec * 4)),
-                vg, 0, fetches_g ? to + L::kGLow + wave * 1024 : lds_at + L::kRec + buf * L::kRecBuf);
+                vg, fetches_g ? to + L::kGLow + wave * 1024 : lds_at + L::kRec + buf * L::kRecBuf);
   };
   auto fetch_x = [&](int jb, uint32_t xbuf, bool no) __attribute__((always_inline)) {
     load_to_lds4(raw_rsrc(xb + static_cast<size_t>(jb) * kBlk * xrow - kEarly, no ? 0 : xbytes - static_cast<uint32_t>(jb) * kBlk * xrow + kEarly),
@@ -1950,7 +1952,7 @@ __device__ __forceinline__ void pair_feed(const ScanParams &p, const SeqView &sv
     fetch_x(jb0, 0, false);
     // (the factors of the first block, which every feeder fetches for itself: the records come a block behind them)
     const uint32_t vf = ((lane & 16) ? head_step : 0u) + kBlk * 4u + 16 * (lane & 15);
-    load_to_lds(raw_rsrc(rec_first + static_cast<size_t>(jb0) * kRec, head_step + static_cast<uint32_t>(sv.nb - jb0) * (kRec * 4)), vf, 0,
+    load_to_lds(raw_rsrc(rec_first + static_cast<size_t>(jb0) * kRec, head_step + static_cast<uint32_t>(sv.nb - jb0) * (kRec * 4)), vf,
                 lds_at + L::kRec + L::kRecBuf);
     fetch_tiles(jb0, 0, false);
     fetch_x(min(jb0 + 1, jlast), L::kXBuf, jb0 == jlast);
