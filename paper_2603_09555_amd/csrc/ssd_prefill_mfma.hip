@@ -2674,7 +2674,7 @@ SlicePlan plan_slice(const Dims &d, bool varlen, bool h0_aliases_final_state, bo
   pl.heads = pl.state_heads = kn.scan_heads == 2 ? 2 : kHeadsPerWg;
   // two heads per workgroup (see small_grid)
   const bool may_choose = kn.scan_heads == 0 && kn.seg_chunks == 0 && kn.seg_blocks == 0 && kn.seg_parts == 0;
-  const bool may_two = kn.scan_heads == 0 && kn.y_stream <= 0;
+  const bool may_two = kn.scan_heads == 0;
   int two_parts = 1;
   const int two = !varlen && !four && may_choose && may_two ? two_head_blocks(d, (w.NB + w.S_max - 1) / w.S_max, w.S_max, &two_parts) : 0;
   // shortest segment: a chunk for a packed batch; what the state slots allow for a plain one

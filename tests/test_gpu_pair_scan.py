@@ -5,7 +5,9 @@ test_gpu_scan_heads.py compare both with the oracle."""
 import pytest
 import torch
 
+from oracle import ssd_oracle
 from paper_2603_09555_amd import inputs
+from parity import TOL, assert_close
 
 pytestmark = pytest.mark.gpu
 
@@ -54,7 +56,42 @@ def test_rule(ssd):
         assert p["heads"] == 2 and batch * -(-heads // 2) * p["segments"] <= 256
         assert p["segments"] == -(-(-(-tokens // 64)) // p["seg_blocks"]) and p["seg_blocks"] % p["parts"] == 0
         assert not plan(batch, tokens, heads, True)["fold"]
-    for knob, value in (("scan_heads", 4), ("y_stream", 1), ("seg_blocks", 2)):
+    for knob, value in (("scan_heads", 4), ("seg_blocks", 2)):
         ssd.set_knob(knob, value)
         assert plan(8, 4096, 48) is None
         ssd.reset_knobs()
+
+
+# batch, tokens, heads, headdim, dstate, groups; blocks per segment
+@pytest.mark.parametrize("heads", [2, 4])
+@pytest.mark.parametrize("dims, seg", [((2, 333, 3, 64, 128, 1), 6), ((1, 700, 5, 64, 72, 1), 3), ((2, 449, 6, 64, 128, 2), 2), ((1, 200, 1, 128, 256, 1), 4)],
+                         ids=str)
+def test_cache_policy_of_the_y_stores_of_either_kernel(ssd, heads, dims, seg):
+    """Non-temporal and ordinary stores of y by the same kernel: ragged tails, workgroups with a head short, several groups and
+    state slices, plain and packed batches.  Equal bit for bit and as the oracle has it."""
+    cfg = inputs.SSDConfig("t", *dims, 64, "bf16")
+    inp = inputs.make_prefill_inputs(cfg, seed=45)
+    dev = {k: v.cuda() for k, v in inp.items()}
+    Bt, T = dims[:2]
+    flat = lambda t: t.reshape(Bt * T, *t.shape[2:]).contiguous()   # noqa: E731
+    cu = torch.tensor([0, 70] + ([T] if Bt > 1 else []) + [Bt * T], dtype=torch.int32, device="cuda")
+    out = []
+    for policy in (0, 1):
+        ssd.reset_knobs()
+        ssd.set_knob("scan_heads", heads)
+        ssd.set_knob("seg_blocks", seg)
+        ssd.set_knob("y_stream", policy)
+        print("y store policy", policy, heads, dims, seg, flush=True)
+        y, st = ssd.ssd_prefill(*[dev[k] for k in ("x", "dt", "A", "B", "C", "D")], cfg.chunk)
+        yp, stp = ssd.ssd_prefill_varlen(flat(dev["x"]), flat(dev["dt"]), dev["A"], flat(dev["B"]), flat(dev["C"]), dev["D"], cu, cfg.chunk)
+        torch.cuda.synchronize()
+        out.append((y, st, yp, stp))
+    ssd.reset_knobs()
+    assert all(torch.equal(a, b) for a, b in zip(*out))
+    y_ref, st_ref = ssd_oracle.prefill(*[inp[k] for k in ("x", "dt", "A", "B", "C", "D")])
+    assert_close(out[1][0], y_ref, TOL["bf16"], "streamed y")
+    assert_close(out[1][1], st_ref, TOL["bf16"], "final state beside streamed y")
+    c = [flat(inp[k]) if k not in "AD" else inp[k] for k in ("x", "dt", "A", "B", "C", "D")]
+    y_ref, st_ref = ssd_oracle.prefill_varlen(*c, cu.cpu().numpy())
+    assert_close(out[1][2], y_ref, TOL["bf16"], "streamed y, packed batch")
+    assert_close(out[1][3], st_ref, TOL["bf16"], "final states, packed batch")

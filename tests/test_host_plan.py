@@ -63,6 +63,18 @@ def test_knobs_and_aliasing_change_the_plan():
     assert ssd.prefill_plan(c0)["f32_segments"] == 8
 
 
+def test_the_store_policy_of_y_is_no_part_of_the_plan():
+    """How y leaves is chosen per launch; the knob that forces it compares two policies of the kernel that is taken, not two
+    kernels."""
+    big = shape_of(inputs.CONFIGS["c2_780m_b8"])
+    plans = []
+    for policy in (-1, 0, 1):
+        ssd.set_knob("y_stream", policy)
+        plans.append((ssd.prefill_pair_plan(big), ssd.prefill_plan(big), ssd.varlen_plan([300, 2000, 40], 24, 64, 128, 1, 256)))
+    assert plans[0][0]["heads"] == 2 and plans[0][2]["heads"] == 2
+    assert plans[1] == plans[0] and plans[2] == plans[0]
+
+
 GRID = list(itertools.product([1, 2, 3, 8, 16], [1, 64, 1000, 2048, 4096, 16384, 50000], [4, 8, 24, 48, 80, 128],
                               [64, 128], [256, 64]))
 
