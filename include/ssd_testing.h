@@ -51,9 +51,8 @@ SSD_API ssd_status ssd_testing_set_knob(int32_t knob, int32_t value);
 SSD_API void ssd_testing_reset_knobs(void);
 
 /* How ssd_prefill would run a shape under the current knobs (host arithmetic only: no GPU call, nothing
- * launched), if not on the chunk kernels (ssd_testing_prefill_chunks) and not in one round of workgroups of two
- * heads (ssd_testing_prefill_pair_plan).  plan[0]: kernel family, 0 generic fp32 kernels, 1 bf16 MFMA, 2 fp32 MFMA.  For the bf16
- * MFMA family (per state slice of 128 columns): plan[1] 64-token blocks per segment, plan[2] segments
+ * launched), if not on the chunk kernels (ssd_testing_prefill_chunks).  plan[0]: kernel family, 0 generic fp32 kernels,
+ * 1 bf16 MFMA, 2 fp32 MFMA.  For the bf16 MFMA family (per state slice of 128 columns): plan[1] 64-token blocks per segment, plan[2] segments
  * per sequence, plan[3] pieces per segment in the states-only pass, plan[4] 1 if the full scan sums the
  * chain over segment states itself and no separate pass runs (h0_aliases_final_state != 0: as for a call
  * whose h0 and final_state share memory, which rules that out), plan[6] and plan[7] head slices per
@@ -64,8 +63,8 @@ SSD_API void ssd_testing_reset_knobs(void);
 SSD_API ssd_status ssd_testing_prefill_plan(const ssd_shape *shape, int32_t h0_aliases_final_state,
                                             int32_t plan[8]);
 
-/* The same for a shape that the bf16 MFMA kernels run, if not on the chunk kernels, in one round of workgroups of two
- * heads under the current knobs; plan[0] 0 (and all others) for any other. */
+/* The same plan where its segments are chosen for one round of workgroups of two heads; plan[0] 0 (and all others) for
+ * any other shape. */
 SSD_API ssd_status ssd_testing_prefill_pair_plan(const ssd_shape *shape, int32_t h0_aliases_final_state, int32_t plan[8]);
 
 /* Chunks per sequence if ssd_prefill would run a shape on the bf16 chunk kernels (a workgroup per 64 headdim columns and

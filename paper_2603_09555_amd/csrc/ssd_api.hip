@@ -140,7 +140,7 @@ ssd_status ssd_testing_prefill_plan(const ssd_shape *shape, int32_t h0_aliases_f
   if (const ssd_status st = make_dims(shape, false, &d); st != SSD_OK) return st;
   for (int i = 0; i < 8; ++i) plan[i] = 0;
   if (use_mfma(d)) {
-    const ssd::SlicePlan pl = ssd::mfma_plan(d, h0_aliases_final_state != 0, true);
+    const ssd::SlicePlan pl = ssd::mfma_plan(d, h0_aliases_final_state != 0);
     plan[0] = 1;
     plan[1] = pl.seg_blocks;
     plan[2] = pl.segments;
@@ -164,7 +164,7 @@ ssd_status ssd_testing_prefill_pair_plan(const ssd_shape *shape, int32_t h0_alia
   if (const ssd_status st = make_dims(shape, false, &d); st != SSD_OK) return st;
   for (int i = 0; i < 8; ++i) plan[i] = 0;
   if (!use_mfma(d)) return SSD_OK;
-  const ssd::SlicePlan pl = ssd::mfma_plan(d, h0_aliases_final_state != 0, false);
+  const ssd::SlicePlan pl = ssd::mfma_plan(d, h0_aliases_final_state != 0);
   if (pl.two == 0) return SSD_OK;
   plan[0] = 1;
   plan[1] = pl.seg_blocks;

@@ -158,7 +158,7 @@ struct SlicePlan {
   bool from_lengths = false;
   int shortest = 0;  // (of mfma_varlen_plan, where seg_blocks is the choice)
 };
-SlicePlan mfma_plan(const Dims &d, bool h0_aliases_final_state, bool four);
+SlicePlan mfma_plan(const Dims &d, bool h0_aliases_final_state);
 // ... and a packed batch of these boundaries (host array): seg_blocks as the device chooses it, segments of the whole batch.
 SlicePlan mfma_varlen_plan(const Dims &d, const int32_t *cu_host);
 int mfma_f32_time_segments(const Dims &d);

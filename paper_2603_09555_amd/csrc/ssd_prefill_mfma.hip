@@ -2663,8 +2663,7 @@ int list_items(const Dims &d, const Layout &w, int seg_blocks) { return d.Bt + f
 // device-side tables hold them per sequence), pieces per segment of the states-only pass, and whether the
 // full scan sums the chain over state slots itself (ScanParams::fold).
 bool packed_uncut(const Dims &d, const SlicePlan &pl);
-// four: the plan that does without two_head_blocks' choice (see ssd_testing_prefill_plan).
-SlicePlan plan_slice(const Dims &d, bool varlen, bool h0_aliases_final_state, bool four = false) {
+SlicePlan plan_slice(const Dims &d, bool varlen, bool h0_aliases_final_state) {
   const Layout w = make_layout(d, varlen);
   Dims one = d;  // the segment length of a packed batch is chosen as for one sequence of all its tokens
   if (varlen) one.Bt = 1;
@@ -2676,7 +2675,7 @@ SlicePlan plan_slice(const Dims &d, bool varlen, bool h0_aliases_final_state, bo
   const bool may_choose = kn.scan_heads == 0 && kn.seg_chunks == 0 && kn.seg_blocks == 0 && kn.seg_parts == 0;
   const bool may_two = kn.scan_heads == 0;
   int two_parts = 1;
-  const int two = !varlen && !four && may_choose && may_two ? two_head_blocks(d, (w.NB + w.S_max - 1) / w.S_max, w.S_max, &two_parts) : 0;
+  const int two = !varlen && may_choose && may_two ? two_head_blocks(d, (w.NB + w.S_max - 1) / w.S_max, w.S_max, &two_parts) : 0;
   // shortest segment: a chunk for a packed batch; what the state slots allow for a plain one
   pl.seg_blocks = two > 0 ? two : choose_seg_blocks(one, varlen ? d.L / kBlk : (w.NB + w.S_max - 1) / w.S_max, w.S_max, varlen ? 1 : 8);
   if (!varlen && (w.NB + pl.seg_blocks - 1) / pl.seg_blocks > w.S_max) pl.seg_blocks = (w.NB + w.S_max - 1) / w.S_max;
@@ -2936,8 +2935,8 @@ bool mfma_supported(const Dims &d) {
 
 size_t mfma_workspace_bytes(const Dims &d) { return make_layout(with_block_chunk(d), false).total; }
 
-SlicePlan mfma_plan(const Dims &d, bool h0_aliases_final_state, bool four) {
-  return plan_slice(with_block_chunk(d), false, h0_aliases_final_state, four);
+SlicePlan mfma_plan(const Dims &d, bool h0_aliases_final_state) {
+  return plan_slice(with_block_chunk(d), false, h0_aliases_final_state);
 }
 
 SlicePlan mfma_varlen_plan(const Dims &d_in, const int32_t *cu) {

@@ -443,7 +443,7 @@ def reset_knobs() -> None:
 
 def prefill_plan(shape, h0_aliases_final_state: bool = False) -> dict:
     """``ssd_testing_prefill_plan`` (include/ssd_testing.h): how ``ssd_prefill`` would run ``shape`` under the
-    current knobs, as a dict.  Host arithmetic only."""
+    current knobs, as a dict, if not on the chunk kernels (``prefill_chunks``).  Host arithmetic only."""
     out = (ctypes.c_int32 * 8)()
     st = _lib.ssd_testing_prefill_plan(ctypes.byref(shape), int(bool(h0_aliases_final_state)), out)
     if st != SSD_OK:
@@ -453,7 +453,8 @@ def prefill_plan(shape, h0_aliases_final_state: bool = False) -> dict:
 
 
 def prefill_pair_plan(shape, h0_aliases_final_state: bool = False):
-    """``ssd_testing_prefill_pair_plan`` (include/ssd_testing.h) as a dict, or None for a shape it has no plan for."""
+    """``ssd_testing_prefill_pair_plan`` (include/ssd_testing.h): the plan of ``prefill_plan`` with the head slices per
+    workgroup of both passes, where it is chosen for one round of workgroups of two heads; else None."""
     out = (ctypes.c_int32 * 8)()
     st = _lib.ssd_testing_prefill_pair_plan(ctypes.byref(shape), int(bool(h0_aliases_final_state)), out)
     if st != SSD_OK:

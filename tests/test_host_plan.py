@@ -24,28 +24,42 @@ def test_plans_of_the_benchmark_shapes():
     plan = {n: ssd.prefill_plan(shape_of(c)) for n, c in inputs.CONFIGS.items() if not c.decode_steps}
     # config 0: fp32 MFMA kernel, eight time segments of one block (four workgroups would leave the chip idle)
     assert plan["c0_tiny_f32"]["path"] == "mfma_f32" and plan["c0_tiny_f32"]["f32_segments"] == 8
-    # config 1: 32 blocks -> 16 segments of 2; a chain of 15 slots is not folded
-    assert plan["c1_130m"] == dict(path="mfma_bf16", seg_blocks=2, segments=16, parts=1, fold=False, f32_segments=0)
-    # config 2: x (201 MB) does not survive in the memory-side cache -> 36 + 28 blocks; the states pass in two
-    # pieces; a chain of two slots is summed by the full scan itself
-    assert plan["c2_780m_b8"] == dict(path="mfma_bf16", seg_blocks=36, segments=2, parts=2, fold=True, f32_segments=0)
-    # config 3: 256 blocks -> 12 segments of 22 (240 workgroups)
-    assert plan["c3_2p7b_long"] == dict(path="mfma_bf16", seg_blocks=22, segments=12, parts=1, fold=False, f32_segments=0)
+    # config 1: eight chunks of 256 tokens on the chunk kernels
+    chunks = {n: ssd.prefill_chunks(shape_of(c)) for n, c in inputs.CONFIGS.items() if not c.decode_steps}
+    assert chunks["c1_130m"] == 8 and all(v == 0 for n, v in chunks.items() if n != "c1_130m")
+    # config 2: one round of workgroups of two heads (192) holds the batch uncut: x is read once
+    assert plan["c2_780m_b8"] == dict(path="mfma_bf16", seg_blocks=64, segments=1, parts=1, fold=False, f32_segments=0)
+    # config 3: 256 blocks -> 6 segments of 43 (240 workgroups of two heads); a chain of five slots is not folded
+    assert plan["c3_2p7b_long"] == dict(path="mfma_bf16", seg_blocks=43, segments=6, parts=1, fold=False, f32_segments=0)
+    for name in ("c2_780m_b8", "c3_2p7b_long"):
+        pair = ssd.prefill_pair_plan(shape_of(inputs.CONFIGS[name]))
+        assert pair["heads"] == 2 and all(pair[k] == plan[name][k] for k in ("seg_blocks", "segments", "parts", "fold"))
+
+
+def test_batches_beyond_a_round_of_two_heads_keep_four():
+    for batch, tokens in ((12, 4096), (16, 1024)):   # 288 and 384 workgroups of two heads
+        sh = shape_of(inputs.CONFIGS["c2_780m_b8"].with_(batch=batch, seqlen=tokens))
+        assert ssd.prefill_pair_plan(sh) is None
+        assert ssd.prefill_plan(sh) == dict(path="mfma_bf16", seg_blocks=tokens // 64, segments=1, parts=1, fold=False, f32_segments=0)
 
 
 def test_knobs_and_aliasing_change_the_plan():
     sh = shape_of(inputs.CONFIGS["c2_780m_b8"])
-    assert ssd.prefill_plan(sh)["fold"]
+    ssd.set_knob("seg_blocks", 36)
+    ssd.set_knob("seg_parts", 2)
+    assert ssd.prefill_plan(sh)["fold"]                                     # 36 + 28 blocks, a chain of two slots
     assert not ssd.prefill_plan(sh, h0_aliases_final_state=True)["fold"]   # h0 and final_state in one buffer
     ssd.set_knob("fold_max_slots", 0)
     assert not ssd.prefill_plan(sh)["fold"]
     ssd.set_knob("fold_max_slots", 1)
-    p = ssd.prefill_plan(sh)                                                # (the choice of lengths knows the limit)
-    assert p["fold"] == ((p["segments"] - 1) * p["parts"] <= 1)
-    ssd.set_knob("seg_blocks", 36)
-    ssd.set_knob("seg_parts", 2)
     assert not ssd.prefill_plan(sh)["fold"]                                 # a chain of two slots is over the limit
     ssd.reset_knobs()
+    ssd.set_knob("scan_heads", 4)
+    ssd.set_knob("fold_max_slots", 1)
+    p = ssd.prefill_plan(sh)                                                # (the choice of lengths knows the limit)
+    assert p["fold"] == ((p["segments"] - 1) * p["parts"] <= 1)
+    ssd.reset_knobs()
+    ssd.set_knob("seg_blocks", 36)
     ssd.set_knob("seg_parts", 1)
     assert ssd.prefill_plan(sh) == dict(path="mfma_bf16", seg_blocks=36, segments=2, parts=1, fold=True, f32_segments=0)
     ssd.reset_knobs()
@@ -80,12 +94,18 @@ GRID = list(itertools.product([1, 2, 3, 8, 16], [1, 64, 1000, 2048, 4096, 16384,
 
 
 def test_plan_invariants_over_a_grid_of_shapes():
+    """Of the plans that are launched: segments and pieces of the scan kernels, with two heads per workgroup and with four, and the
+    chunks of the small ones."""
     base = inputs.CONFIGS["c3_2p7b_long"]
+    pairs = chunked = 0
     for Bt, T, H, P, L in GRID:
         c = base.with_(batch=Bt, seqlen=T, nheads=H, headdim=P, chunk=L)
         sh = shape_of(c)
         p = ssd.prefill_plan(sh)
         assert p["path"] == "mfma_bf16", (Bt, T, H, P, L)
+        pair = ssd.prefill_pair_plan(sh)
+        pairs += pair is not None
+        assert pair is None or (pair["heads"] == 2 and all(pair[k] == p[k] for k in ("seg_blocks", "segments", "parts", "fold")))
         nblocks = (T + 63) // 64
         assert 1 <= p["seg_blocks"] and p["segments"] == (nblocks + p["seg_blocks"] - 1) // p["seg_blocks"]
         assert p["parts"] >= 1 and p["seg_blocks"] % p["parts"] == 0
@@ -96,6 +116,14 @@ def test_plan_invariants_over_a_grid_of_shapes():
         assert ssd.prefill_workspace_bytes(sh) >= slots * per_slot, (Bt, T, H, P, L, p)
         assert p["fold"] == (p["segments"] >= 2 and (p["segments"] - 1) * p["parts"] <= 3)
         assert not ssd.prefill_plan(sh, True)["fold"]
+        # the chunk kernels: a state and a decay per chunk and 64 headdim columns, with h0 in final_state's place one state more
+        for alias in (False, True):
+            n = ssd.prefill_chunks(sh, alias)
+            chunked += n > 0
+            assert n in (0, (T + 255) // 256)
+            if n > 1 or (n and alias):
+                assert ssd.prefill_workspace_bytes(sh) >= Bt * H * (P // 64) * ((n + alias) * 64 * 128 + n) * 4
+    assert pairs > 300 and chunked > 50
 
 
 def test_f32_time_segments_over_a_grid_of_shapes():
