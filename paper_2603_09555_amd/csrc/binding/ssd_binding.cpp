@@ -1,7 +1,8 @@
 // The marshalling of paper_2603_09555_amd/ssd.py in native code: checks, outputs, pointers and the call of the C ABI for the
-// ordinary case, dense device tensors of the expected types and shapes.  Anything else -- other tensor types, missing
-// arguments, shapes that don't fit -- is answered with None before anything is allocated or enqueued, and ssd.py then goes
-// through the call itself and raises what there is to raise.
+// ordinary case, dense device tensors of the expected types and shapes (outputs that the caller brings: of the expected
+// type and large enough).  Anything else -- other tensor types, missing arguments, shapes that don't fit -- is answered with
+// None before anything is allocated or enqueued, and ssd.py then goes through the call itself and raises what there is to
+// raise.
 //
 // Why: a generation step of one layer is bound by the host.  A convolution and a decode step, kernels of 7 us together, took
 // 21.9 us from Python (checks and ctypes some 5 us a call, an output tensor 1.2 to 1.8 us each, the launch 2.5).
@@ -57,6 +58,8 @@ Arg tensor_or_none(PyObject *o) {
 }
 bool is(const Arg &a, std::initializer_list<int64_t> shape) { return a.t->sizes() == at::IntArrayRef(shape); }
 bool f32(const Arg &a) { return a.t->scalar_type() == at::kFloat; }
+// an fp32 vector of (at least) that many values, whatever its shape
+bool f32_of(const Arg &a, int64_t values) { return f32(a) && a.t->numel() >= values; }
 // SSD_F32, SSD_BF16 or -1
 int io_of(const Arg &a) {
   const auto d = a.t->scalar_type();
@@ -148,7 +151,7 @@ bool output_like(PyObject *given, const Arg &like, at::Tensor &own, Arg &out) {
     return true;
   }
   out = tensor(given);
-  return out.ok;
+  return out.ok && out.t->scalar_type() == like.t->scalar_type() && out.t->numel() >= like.t->numel();
 }
 PyObject *result(PyObject *given, at::Tensor &own) { return given == Py_None ? THPVariable_Wrap(std::move(own)) : new_ref(given); }
 
@@ -162,7 +165,8 @@ PyObject *decode_step(PyObject *, PyObject *const *a, Py_ssize_t nargs) {
   if (!state.ok || !x.ok || !dt.ok || !A.ok || !B.ok || !C.ok || !D.ok || state.t->dim() != 4 || B.t->dim() != 3) return none();
   const int64_t Bt = state.t->size(0), H = state.t->size(1), P = state.t->size(2), N = state.t->size(3), G = B.t->size(1);
   const int io = io_of(x);
-  if (io < 0 || !f32(state) || !is(x, {Bt, H, P}) || !is(dt, {Bt, H}) || !is(B, {Bt, G, N}) || !is(C, {Bt, G, N}) || !fits({Bt, H, P, N, G}))
+  if (io < 0 || !f32(state) || !f32(dt) || io_of(B) != io || io_of(C) != io || !f32_of(A, H) || !f32_of(D, H) ||
+      !is(x, {Bt, H, P}) || !is(dt, {Bt, H}) || !is(B, {Bt, G, N}) || !is(C, {Bt, G, N}) || !fits({Bt, H, P, N, G}))
     return none();
   at::Tensor own;
   Arg y;
@@ -190,7 +194,9 @@ PyObject *decode_layers(PyObject *, PyObject *const *a, Py_ssize_t nargs) {
   const int64_t Ly = state.t->size(0), Bt = state.t->size(1), H = state.t->size(2), P = state.t->size(3), N = state.t->size(4), G = B.t->size(2 + k);
   const int64_t S = kSteps ? x.t->size(0) : 1;
   const int io = io_of(x);
-  if (io < 0 || !f32(state) || !is(A, {Ly, H}) || !is(D, {Ly, H}) || !fits({S, Ly, Bt, H, P, N, G})) return none();
+  if (io < 0 || !f32(state) || !f32(dt) || !f32(A) || !f32(D) || io_of(B) != io || io_of(C) != io || !is(A, {Ly, H}) ||
+      !is(D, {Ly, H}) || !fits({S, Ly, Bt, H, P, N, G}))
+    return none();
   if (kSteps ? !is(x, {S, Ly, Bt, H, P}) || !is(dt, {S, Ly, Bt, H}) || !is(B, {S, Ly, Bt, G, N}) || !is(C, {S, Ly, Bt, G, N})
              : !is(x, {Ly, Bt, H, P}) || !is(dt, {Ly, Bt, H}) || !is(B, {Ly, Bt, G, N}) || !is(C, {Ly, Bt, G, N}))
     return none();
@@ -242,23 +248,21 @@ PyObject *prefill(PyObject *, PyObject *const *a, Py_ssize_t nargs) {
   const DtArgs xf = dt_args(a[11 + k], a[12 + k], a[13 + k], {H});
   if (!xf.ok) return none();
   // (given ones are looked at before anything is allocated)
-  if ((gy != Py_None && !tensor(gy).ok) || (gf != Py_None && !tensor(gf).ok) || (gw != Py_None && !tensor(gw).ok)) return none();
-  const ssd_shape sh = {(int32_t)Bt, (int32_t)T, (int32_t)H, (int32_t)P, (int32_t)N, (int32_t)G, (int32_t)chunk, io};
   at::Tensor own_y, own_f, own_w;
   Arg y, f, w;
-  output_like(gy, x, own_y, y);
+  if (gy != Py_None && !output_like(gy, x, own_y, y)) return none();
+  if (gf != Py_None && (!(f = tensor(gf)).ok || !f32_of(f, Bt * H * P * N))) return none();
+  if (gw != Py_None && !(w = tensor(gw)).ok) return none();
+  const ssd_shape sh = {(int32_t)Bt, (int32_t)T, (int32_t)H, (int32_t)P, (int32_t)N, (int32_t)G, (int32_t)chunk, io};
+  if (gy == Py_None) output_like(gy, x, own_y, y);
   if (gf == Py_None) {
     own_f = at::empty({Bt, H, P, N}, x.t->options().dtype(at::kFloat));
     f.t = &own_f;
-  } else {
-    f = tensor(gf);
   }
   if (gw == Py_None) {
     const size_t need = kPacked ? api.varlen_workspace_bytes(&sh) : api.prefill_workspace_bytes(&sh);
     own_w = at::empty({(int64_t)(need > 256 ? need : 256)}, x.t->options().dtype(at::kByte));
     w.t = &own_w;
-  } else {
-    w = tensor(gw);
   }
   const size_t bytes = w.t->nbytes();
   void *const s = stream();

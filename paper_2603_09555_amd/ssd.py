@@ -158,6 +158,17 @@ def _check_dev(*ts):
             raise ValueError("tensors must be contiguous device tensors")
 
 
+def _check_types(io, ios, f32s):
+    if any(t.dtype != io for t in ios) or any(t is not None and t.dtype != torch.float32 for t in f32s):
+        raise ValueError("x, B and C must share one dtype; dt, A, D and states must be fp32")
+
+
+def _check_output(t, dtype, numel):
+    """An output that the caller brings: of the type that is written, and no smaller than what is."""
+    if t is not None and (t.dtype != dtype or t.numel() < numel):
+        raise ValueError("an output tensor has another dtype than it must have, or is too small")
+
+
 if hasattr(torch._C, "_cuda_getCurrentRawStream") and hasattr(torch._C, "_cuda_getDevice"):
     def _stream_ptr():
         return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
@@ -202,6 +213,8 @@ def ssd_prefill(x, dt, A, B, C, D, chunk, h0=None, y=None, final_state=None, wor
             or C.shape != B.shape or B.shape[:2] != (Bt, T) \
             or (h0 is not None and h0.shape != (Bt, H, P, N)):
         raise ValueError("inconsistent tensor shapes")
+    _check_output(y, x.dtype, x.numel())
+    _check_output(final_state, torch.float32, Bt * H * P * N)
     if y is None:
         y = torch.empty_like(x)
     if final_state is None:
@@ -253,11 +266,13 @@ def ssd_decode_step(state, x, dt, A, B, C, D, y=None):
     Bt, H, P, N = state.shape
     G = B.shape[1]
     shape = make_shape(Bt, 1, H, P, N, G, 1, x.dtype)
+    if state.dtype != torch.float32 or x.shape != (Bt, H, P) or dt.shape != (Bt, H) \
+            or B.shape != (Bt, G, N) or C.shape != (Bt, G, N) or A.numel() < H or D.numel() < H:
+        raise ValueError("inconsistent tensor shapes")
+    _check_types(x.dtype, (B, C), (dt, A, D))
+    _check_output(y, x.dtype, x.numel())
     if y is None:
         y = torch.empty_like(x)
-    if state.dtype != torch.float32 or x.shape != (Bt, H, P) or dt.shape != (Bt, H) \
-            or B.shape != (Bt, G, N) or C.shape != (Bt, G, N):
-        raise ValueError("inconsistent tensor shapes")
     _check_dev(state, x, dt, A, B, C, D, y)
     st = _lib.ssd_decode_step(ctypes.byref(shape), _ptr(state), _ptr(x), _ptr(dt), _ptr(A), _ptr(B),
                               _ptr(C), _ptr(D), _ptr(y), _stream_ptr())
@@ -276,12 +291,14 @@ def ssd_decode_step_layers(state, x, dt, A, B, C, D, y=None, dt_bias=None, dt_so
     Ly, Bt, H, P, N = state.shape
     G = B.shape[2]
     shape = make_shape(Bt, 1, H, P, N, G, 1, x.dtype)
-    if y is None:
-        y = torch.empty_like(x)
     if state.dtype != torch.float32 or x.shape != (Ly, Bt, H, P) or dt.shape != (Ly, Bt, H) \
             or A.shape != (Ly, H) or D.shape != (Ly, H) \
             or B.shape != (Ly, Bt, G, N) or C.shape != (Ly, Bt, G, N):
         raise ValueError("inconsistent tensor shapes")
+    _check_types(x.dtype, (B, C), (dt, A, D))
+    _check_output(y, x.dtype, x.numel())
+    if y is None:
+        y = torch.empty_like(x)
     _check_dev(state, x, dt, A, B, C, D, y)
     xf = _dt_transform(dt_bias, dt_softplus, dt_limit, (Ly, H))
     tail = (_ptr(state), _ptr(x), _ptr(dt), _ptr(A), _ptr(B), _ptr(C), _ptr(D), _ptr(y), _stream_ptr())
@@ -305,12 +322,14 @@ def ssd_decode_steps_layers(state, x, dt, A, B, C, D, y=None, dt_bias=None, dt_s
     Ly, Bt, H, P, N = state.shape
     S, G = x.shape[0], B.shape[3]
     shape = make_shape(Bt, 1, H, P, N, G, 1, x.dtype)
-    if y is None:
-        y = torch.empty_like(x)
     if state.dtype != torch.float32 or x.shape != (S, Ly, Bt, H, P) or dt.shape != (S, Ly, Bt, H) \
             or A.shape != (Ly, H) or D.shape != (Ly, H) \
             or B.shape != (S, Ly, Bt, G, N) or C.shape != (S, Ly, Bt, G, N):
         raise ValueError("inconsistent tensor shapes")
+    _check_types(x.dtype, (B, C), (dt, A, D))
+    _check_output(y, x.dtype, x.numel())
+    if y is None:
+        y = torch.empty_like(x)
     _check_dev(state, x, dt, A, B, C, D, y)
     xf = _dt_transform(dt_bias, dt_softplus, dt_limit, (Ly, H))
     tail = (_ptr(state), _ptr(x), _ptr(dt), _ptr(A), _ptr(B), _ptr(C), _ptr(D), _ptr(y), _stream_ptr())
@@ -339,11 +358,12 @@ def ssd_prefill_varlen(x, dt, A, B, C, D, cu_seqlens, chunk, h0=None, y=None, fi
     if cu_seqlens.dtype != torch.int32 or nseq < 1:
         raise ValueError("cu_seqlens must hold nseq + 1 int32 values")
     shape = make_shape(nseq, T, H, P, N, G, chunk, x.dtype)
-    if B.dtype != x.dtype or C.dtype != x.dtype:
-        raise ValueError("x, B and C must share one dtype")
+    _check_types(x.dtype, (B, C), (dt, A, D, h0))
     if dt.shape != (T, H) or A.shape != (H,) or D.shape != (H,) or B.shape != (T, G, N) \
             or C.shape != (T, G, N) or (h0 is not None and h0.shape != (nseq, H, P, N)):
         raise ValueError("inconsistent tensor shapes")
+    _check_output(y, x.dtype, x.numel())
+    _check_output(final_state, torch.float32, nseq * H * P * N)
     if y is None:
         y = torch.empty_like(x)
     if final_state is None:
@@ -413,7 +433,8 @@ def ssd_conv1d_step(conv_state, u, weight, bias=None, split=None, activation="si
     split = _conv_split(C, split)
     io = _IO_DTYPES.get(u.dtype, -1)
     if weight.dtype != torch.float32 or weight.shape != (C, k) or conv_state.dtype != u.dtype \
-            or conv_state.shape != (Bt, C, k - 1) or (bias is not None and bias.shape != (C,)):
+            or conv_state.shape != (Bt, C, k - 1) or (
+                bias is not None and (bias.dtype != torch.float32 or bias.shape != (C,))):
         raise ValueError("inconsistent tensor shapes or dtypes")
     outs = [u.new_empty((Bt, w)) if w > 0 else None for w in split]
     _check_dev(u, weight, bias, conv_state, *outs)

@@ -1,5 +1,6 @@
 """The native marshalling of ssd.py: where anything is out of the ordinary it answers None and does nothing, so that the
 Python path raises what there is to raise; where it takes a call, the results are those of the Python path, bit for bit."""
+import ctypes
 import types
 
 import pytest
@@ -97,3 +98,87 @@ def test_a_failing_call_raises_its_status():
         ssd.ssd_prefill(z, torch.zeros(1, 4, 3, device="cuda"), torch.zeros(3, device="cuda"), torch.zeros(1, 4, 2, 64, device="cuda"),
                         torch.zeros(1, 4, 2, 64, device="cuda"), torch.zeros(3, device="cuda"), 64)
     assert e.value.status == -2
+
+
+ABI = ("ssd_prefill_workspace_bytes", "ssd_prefill", "ssd_prefill_dt", "ssd_prefill_varlen_workspace_bytes", "ssd_prefill_varlen",
+       "ssd_prefill_varlen_dt", "ssd_decode_step", "ssd_decode_step_layers", "ssd_decode_step_layers_dt", "ssd_decode_steps_layers",
+       "ssd_decode_steps_layers_dt", "ssd_conv1d_prefill", "ssd_conv1d_step")
+
+
+@pytest.fixture
+def recorded(monkeypatch):
+    """The C ABI behind both paths exchanged for functions that note a call and do nothing."""
+    calls = []
+    stub = lambda name: ctypes.CFUNCTYPE(ctypes.c_int64)(lambda: calls.append(name) or 0)   # noqa: E731  (0: SSD_OK, no workspace)
+    stubs = {n: stub(n) for n in ABI}
+    init = lambda fs: ssd._native.init([ctypes.cast(f, ctypes.c_void_p).value for f in fs])   # noqa: E731
+    init(stubs.values())
+    lib = ssd._lib
+    monkeypatch.setattr(ssd, "_lib", types.SimpleNamespace(**{n: (lambda *a, n=n: calls.append(n) or 0) for n in ABI}))
+    yield calls
+    init([getattr(lib, n) for n in ABI])
+
+
+def _broken(name, args, kw):
+    """The call with one tensor changed: another type, the last dimension one short, not dense."""
+    names = list(range(len(args))) + list(kw)
+    for key in names:
+        t = args[key] if isinstance(key, int) else kw[key]
+        if not isinstance(t, torch.Tensor):
+            continue
+        other = {torch.float32: torch.bfloat16, torch.bfloat16: torch.float32, torch.int32: torch.int64}[t.dtype]
+        for what, v in (("type", t.to(other)), ("size", t[..., :-1].contiguous()), ("strides", torch.stack([t, t], -1)[..., 0])):
+            if t.dim() and v.is_contiguous() and what == "strides":
+                continue   # (one value)
+            # (calls of their own: a convolution of another type or of fewer taps, without a state; prompts of a smaller head, without a
+            # state; fewer packed sequences)
+            own = {"ssd_conv1d_prefill": [(0, "type"), (1, "size")] if len(args) == 2 else [],
+                   "ssd_prefill": [] if "h0" in kw else [(0, "size")], "ssd_prefill_varlen": [(0, "size"), (6, "size")]}
+            if (key, what) in own.get(name, []):
+                continue
+            a, k = list(args), dict(kw)
+            if isinstance(key, int):
+                a[key] = v
+            else:
+                k[key] = v
+            yield (key, what), a, k
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("io", [torch.bfloat16, torch.float32], ids=str)
+def test_every_argument_is_checked_before_a_call(io, recorded):
+    """Neither path reaches the C ABI with a tensor of the wrong type, of a size that does not fit, or not dense."""
+    outputs = {"ssd_prefill": ("y", "final_state"), "ssd_prefill_varlen": ("y", "final_state"), "ssd_decode_step": ("y",),
+               "ssd_decode_step_layers": ("y",), "ssd_decode_steps_layers": ("y",)}
+    for name, args, kw in _calls(io):
+        f = getattr(ssd, name)
+        if name in outputs:
+            y, st = torch.empty_like(args[1 if "decode" in name else 0]), torch.empty(2, 2, 64, 16, device="cuda")
+            kw = dict(kw, y=y, **({"final_state": st[:1].contiguous() if name == "ssd_prefill" else st} if "final_state" in outputs[name] else {}))
+        recorded.clear()
+        f(*args, **kw)
+        assert recorded, name
+        for which, a, k in _broken(name, args, kw):
+            recorded.clear()
+            try:
+                f(*a, **k)
+            except ValueError:
+                recorded[:] = [c for c in recorded if not c.endswith("workspace_bytes")]   # (host arithmetic)
+                assert not recorded, (name, which)
+            else:
+                pytest.fail("%s took a wrong argument: %s" % (name, which))
+
+
+@pytest.mark.gpu
+def test_larger_outputs_and_other_views_of_the_head_weights_are_taken(recorded):
+    """What was taken before: an output with room to spare, A and D of a decode step in any shape."""
+    io = torch.bfloat16
+    d = [v for n, v, k in _calls(io) if n == "ssd_decode_step"][0]
+    y = torch.empty(d[1].numel() + 5, dtype=io, device="cuda")
+    for native in (True, False):
+        recorded.clear()
+        with pytest.MonkeyPatch.context() as m:
+            if not native:
+                m.setattr(ssd, "_native", types.SimpleNamespace(decode_step=lambda *a: None))
+            assert ssd.ssd_decode_step(*d[:3], d[3].view(1, -1), *d[4:6], d[6].view(-1, 1), y=y) is y
+        assert recorded == ["ssd_decode_step"]
