@@ -364,9 +364,17 @@ PyMethodDef methods[] = {
     SSD_FAST("conv1d_prefill", conv1d<false>),
     SSD_FAST("conv1d_step", conv1d<true>),
     {nullptr, nullptr, 0, nullptr}};
-PyModuleDef module = {PyModuleDef_HEAD_INIT, "_ssd_binding", "Native marshalling of paper_2603_09555_amd.ssd", -1, methods,
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_ssd_binding", "Native marshalling of paper_2603_09555_amd.ssd, built for torch " SSD_TORCH_VERSION ";", -1, methods,
                       nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__ssd_binding(void) { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__ssd_binding(void) {
+  PyObject *const m = PyModule_Create(&module);
+  // (torch's C++ interface has no stable binary form: ssd.py uses the module with the torch it was built for only)
+  if (m != nullptr && PyModule_AddStringConstant(m, "torch_version", SSD_TORCH_VERSION) != 0) {
+    Py_DECREF(m);
+    return nullptr;
+  }
+  return m;
+}

@@ -2,13 +2,15 @@
 
 Every step of prefill and decode runs in the HIP kernels of ``libssd_hip.so``; this module
 turns torch tensors into device pointers, fills the ``ssd_shape`` struct, passes the current
-HIP stream and raises on a non-zero status.  There is no fallback: if the library has not
-been built (``python -m paper_2603_09555_amd.build``) importing this module fails.
+HIP stream and raises on a non-zero status.  There is no fallback for it: if the library has not
+been built (``python -m paper_2603_09555_amd.build``) importing this module fails.  The native
+marshalling (``csrc/binding/``) saves host time only; without it a warning says so.
 """
 from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 
 import torch
 
@@ -100,13 +102,21 @@ _lib.ssd_version.restype = ctypes.c_int
 
 try:
     from . import _ssd_binding as _native
+    if getattr(_native, "torch_version", None) != torch.__version__:
+        raise ImportError("not built for torch %s" % torch.__version__)
+    _native.init([ctypes.cast(getattr(_lib, n), ctypes.c_void_p).value for n in
+                  ("ssd_prefill_workspace_bytes", "ssd_prefill", "ssd_prefill_dt", "ssd_prefill_varlen_workspace_bytes",
+                   "ssd_prefill_varlen", "ssd_prefill_varlen_dt", "ssd_decode_step", "ssd_decode_step_layers",
+                   "ssd_decode_step_layers_dt", "ssd_decode_steps_layers", "ssd_decode_steps_layers_dt", "ssd_conv1d_prefill",
+                   "ssd_conv1d_step")])
 except ImportError as e:
-    raise ImportError("_ssd_binding.so is missing or does not load: build it with `python -m paper_2603_09555_amd.build`") from e
-_native.init([ctypes.cast(getattr(_lib, n), ctypes.c_void_p).value for n in
-              ("ssd_prefill_workspace_bytes", "ssd_prefill", "ssd_prefill_dt", "ssd_prefill_varlen_workspace_bytes",
-               "ssd_prefill_varlen", "ssd_prefill_varlen_dt", "ssd_decode_step", "ssd_decode_step_layers",
-               "ssd_decode_step_layers_dt", "ssd_decode_steps_layers", "ssd_decode_steps_layers_dt", "ssd_conv1d_prefill",
-               "ssd_conv1d_step")])
+    warnings.warn("_ssd_binding.so is missing or does not fit, calls go through Python (some 5 us more host time each): build it "
+                  "with `python -m paper_2603_09555_amd.build` (%s)" % e, RuntimeWarning)
+
+    class _native:
+        """Leaves every call to the Python below."""
+        prefill = prefill_varlen = decode_step = decode_step_layers = decode_steps_layers = conv1d_prefill = conv1d_step = \
+            staticmethod(lambda *args: None)
 
 
 def raw():

@@ -1,12 +1,15 @@
 """The native marshalling of ssd.py: where anything is out of the ordinary it answers None and does nothing, so that the
 Python path raises what there is to raise; where it takes a call, the results are those of the Python path, bit for bit."""
 import ctypes
+import os
+import subprocess
+import sys
 import types
 
 import pytest
 import torch
 
-from paper_2603_09555_amd import ssd
+from paper_2603_09555_amd import build, ssd
 
 NAMES = ("prefill", "prefill_varlen", "decode_step", "decode_step_layers", "decode_steps_layers", "conv1d_prefill", "conv1d_step")
 ARGS = {"prefill": 14, "prefill_varlen": 15, "decode_step": 8, "decode_step_layers": 11, "decode_steps_layers": 11,
@@ -32,6 +35,36 @@ def test_errors_are_those_of_the_python_path():
         ssd.ssd_conv1d_step(torch.zeros(1, 8, 3), torch.zeros(1, 8), torch.zeros(8, 4), split=(4, 5))
     with pytest.raises(ValueError, match="contiguous device tensors"):
         ssd.ssd_prefill(t, torch.zeros(1, 4, 2), torch.zeros(2), t[:, :, :1], t[:, :, :1], torch.zeros(2), 64)
+
+
+@pytest.mark.parametrize("how", ["missing", "another torch"])
+def test_without_the_native_marshalling_everything_is_left_to_python(how):
+    """It saves host time and is no more required than that: a box that cannot build it uses the library all the same."""
+    plant = {"missing": "None", "another torch": "types.SimpleNamespace(torch_version='1.0')"}[how]
+    code = """if True:
+        import sys, types, warnings
+        sys.modules['paper_2603_09555_amd._ssd_binding'] = %s
+        with warnings.catch_warnings(record=True) as w:
+            warnings.simplefilter('always')
+            from paper_2603_09555_amd import ssd
+        assert any('_ssd_binding' in str(v.message) for v in w), w
+        import torch
+        t = torch.zeros(1, 4, 2, 64)
+        try:
+            ssd.ssd_prefill(t, torch.zeros(1, 4, 2), torch.zeros(2), t, t, torch.zeros(2), 64)
+        except ValueError as e:
+            assert 'contiguous device tensors' in str(e), e
+        else:
+            raise AssertionError('taken')
+        """ % plant
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))), timeout=120)
+
+
+def test_a_binding_of_another_torch_is_built_anew(monkeypatch):
+    monkeypatch.setattr(os.path, "getmtime", lambda path: 0.0)   # (no file is newer than another)
+    assert not build.needs_build()
+    monkeypatch.setattr(build, "torch_version", lambda: "1.0")
+    assert build.needs_build()
 
 
 def _calls(io):
