@@ -613,26 +613,28 @@ __global__ __launch_bounds__(kF32Threads) void prefill_f32_kernel(const F32Param
 
 }  // namespace
 
-// Time per block of a workgroup (microseconds on MI355X; fits to 171 timings of 39 drawn shapes at up to eight numbers of
-// segments, 5 % rms): a full block, a block before the segment, and what the blocks before it cost whatever their number.
-// nt = 32-column tiles of the state.
-static double f32_block_us(int nt) { return 1.7 + 1.39 * nt; }
-static double f32_state_block_us(const Dims &d) { return d.N <= 16 ? 0.32 : 0.22 + 0.26 * ((d.N + 31) / 32); }
-static double f32_carry_us(int nt) { return 0.5 + 0.4 * nt; }
-// Time segments per sequence, and the modelled time of the walk that results.  More segments shorten the
-// stretch of full blocks of the longest walk -- the last segment's, which first carries the state over
-// everything before it -- as long as the workgroups still run side by side (one round of 256).
+// Time per block of a workgroup (microseconds on MI355X; fits to 3850 timings of 1600 drawn shapes, 16 to 5000 tokens, at up
+// to six numbers of segments each, 4.6 % rms there and on 600 other shapes), by 32-column tiles of the state: a full block, a
+// block before the segment, and what the blocks before it cost whatever their number.
+constexpr double kF32BlockUs[4] = {3.25, 4.5, 6.38, 7.65}, kF32CarryUs[4] = {0.82, 1.75, 2.69, 3.63};
+static double f32_state_block_us(const Dims &d) { return d.N <= 16 ? 0.34 : 0.302 + 0.228 * ((d.N + 31) / 32); }
+// Time segments per sequence, and the modelled time of the longest walk that results.  More segments shorten the
+// stretch of full blocks -- the last segment first carries the state over everything before it -- as long as the
+// workgroups still run side by side (one round of 256).
 int f32_time_segments(const Dims &d, double *walk_us) {
   const unsigned long long wgs = static_cast<unsigned long long>(d.Bt) * d.H * (d.P / kCols);
   const int nblocks = (d.T + kTok - 1) / kTok, nt = (d.N + 31) / 32;
-  const double rounds = static_cast<double>((wgs + 255) / 256);
+  const double block = kF32BlockUs[nt - 1], carry = kF32CarryUs[nt - 1], state = f32_state_block_us(d);
   int best = 1;
-  double best_us = rounds * nblocks * f32_block_us(nt);
+  double best_us = static_cast<double>((wgs + 255) / 256) * nblocks * block;
   const int forced = knobs().f32_segments;
   for (int s = 2; s <= nblocks && s <= 64 && (forced > 0 || wgs * s <= 256); ++s) {
-    const int len = (nblocks + s - 1) / s;
-    const double us = static_cast<double>((wgs * s + 255) / 256) *
-                      (f32_carry_us(nt) + (nblocks - len) * f32_state_block_us(d) + len * f32_block_us(nt));
+    // (the longest walk is the first segment's or that of one of the last two, of which the last may be short)
+    const int len = (nblocks + s - 1) / s, last = (nblocks - 1) / len * len, before = last - len;
+    double walk = len * block;
+    if (last > 0) walk = fmax(walk, carry + last * state + (nblocks - last) * block);
+    if (before > 0) walk = fmax(walk, carry + before * state + len * block);
+    const double us = static_cast<double>((wgs * s + 255) / 256) * walk;
     if (forced > 0 ? s <= forced : us < best_us) {
       best = s;
       best_us = us;
@@ -653,7 +655,7 @@ int f32_time_segments(const Dims &d, double *walk_us) {
 static double f32_mfma_us(const Dims &d) {
   double walk_us;
   f32_time_segments(d, &walk_us);
-  return 4.0 + walk_us;
+  return 3.6 + walk_us;
 }
 static double f32_generic_us(const Dims &d) {
   return 33.0 + static_cast<double>(d.Bt) * d.T * d.H * (0.9 + 0.0005 * d.P * d.N) * 1e-3;

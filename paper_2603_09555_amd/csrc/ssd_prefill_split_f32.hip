@@ -516,9 +516,9 @@ static bool segments_fit(const Dims &d, int S) {
 // the states-only launch and in the full one; by state tiles.  A CU holds two workgroups, which slow each other by a
 // third; a launch of more runs in rounds.
 constexpr double kFullUs[4] = {2.2, 3.2, 4.1, 4.9}, kStateUs[4] = {1.0, 1.2, 1.4, 1.55}, kCarryUs[4] = {0.75, 1.3, 1.7, 2.1};
-static double rounds_us(long wgs, double us) {
+static double rounds_us(long wgs, double us, double second = 0.33) {
   double t = 0.0;
-  for (; wgs > 0; wgs -= 512) t += us * (wgs <= 256 ? 1.0 : 1.0 + 0.33 * ((wgs < 512 ? wgs : 512) - 256) / 256.0);
+  for (; wgs > 0; wgs -= 512) t += us * (wgs <= 256 ? 1.0 : 1.0 + second * ((wgs < 512 ? wgs : 512) - 256) / 256.0);
   return t;
 }
 
@@ -558,14 +558,30 @@ bool split_f32_supported(const Dims &d) {
          static_cast<unsigned long long>(d.Bt) * d.H * (d.P / kCols) * 64 <= 0x7fffffffull;
 }
 
-// Taken where it is faster than the faster of the two other families by the models, by a tenth where a group has one or two
-// slices (half of a workgroup's waves and more then repeat one) and dstate is at most 64.  Of 110 drawn prompts one is then
-// more than 6 % behind the fastest of the timed plans of the families (1527 tokens x 2 x 32 x 64: 26.0 us, 23.0 on split operands).
+// Microseconds of a call with that plan.  split_plan only compares plans with each other; this is fitted to 1600 drawn shapes
+// (16 to 5000 tokens, 1 to 48 heads, batches of up to 8; 5 % rms, 4.7 % on 600 others): one launch is some 5 us cheaper
+// than that model has it, and the pass over the states takes a quarter of a microsecond a segment however small they are.
+static double split_us(const Dims &d, const SplitPlan &pl) {
+  constexpr double kFull[4] = {3.43, 4.55, 5.46, 6.49}, kState[4] = {0.4, 0.5, 0.6, 0.7}, kCarry[4] = {1.15, 1.61, 1.9, 2.45};
+  const int nblocks = (d.T + kTok - 1) / kTok, NT = (d.N + 31) / 32;
+  const long wgs = static_cast<long>(d.Bt) * d.G * ((d.hpg * (d.P / kCols) + kWaves - 1) / kWaves);
+  if (pl.segments == 1)
+    return 2.9 + 0.53 * NT + rounds_us(wgs * pl.sub, pl.sub_blocks * kFull[NT - 1] + (nblocks - pl.sub_blocks) * kCarry[NT - 1], 0.71);
+  const int len = (nblocks + pl.segments - 1) / pl.segments;
+  const double state_mb = static_cast<double>(d.Bt) * d.H * d.P * d.N * 4e-6;
+  return 10.9 + pl.segments * (0.265 + 0.79 * state_mb) + rounds_us(wgs * (pl.segments - 1), len * kState[NT - 1], 0.71) +
+         rounds_us(wgs * pl.segments, len * kFull[NT - 1], 0.71);
+}
+
+// Taken where the models have it at most 3 % behind the faster of the other two families.  Over the 600 shapes that is 0.11 %
+// behind the faster of the two timed, three are more than 6 % behind, 6.7 at most (without the 3 %: 0.15 %, three, 14).  By
+// split_plan's own figure against the fp32 matrix instruction's it was 0.85 %, sixteen more than a tenth behind: prompts
+// of up to a hundred tokens and many heads, where one launch suffices (4 x 33 tokens x 40 heads x 64 x 32 in four groups 11.4
+// us, 7.9 on split operands), and middling ones (991 x 23 x 64 x 128 51.7, 47.8).
 bool split_f32_chosen(const Dims &d) {
   if (!split_f32_supported(d)) return false;
   if (knobs().seg_blocks > 0) return true;
-  const bool few_slices = d.hpg * (d.P / kCols) <= kWaves / 2 && d.N <= 64;
-  return (few_slices ? 1.1 : 1.0) * split_plan(d).us < f32_other_us(d);
+  return 0.97 * split_us(d, split_plan(d)) < f32_other_us(d);
 }
 
 void split_f32_plan(const Dims &d, int *seg_blocks, int *segments, int *parts) {
