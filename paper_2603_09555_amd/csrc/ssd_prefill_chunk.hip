@@ -37,7 +37,7 @@ constexpr int kP = 64, kN = 128;         // headdim columns and state columns pe
 constexpr int kSlot = kP * kN;           // floats of a state
 constexpr int kMostChunks = 64;
 constexpr int kAhead = 3;
-constexpr int kXcds = 8;
+constexpr int kXcds = 8, kCus = 256;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr uint32_t kNowhere = 0xFFFFFF00u;  // an offset beyond any descriptor
 
@@ -663,13 +663,11 @@ static bool chunk_supported(const Dims &d, size_t workspace_bytes, bool keep_h0)
 }
 
 // Taken while the second launch -- a workgroup per slice and chunk and one for each slice's final state, one workgroup to a
-// CU -- is about one round of the chip.  Of 250 drawn shapes (50 to 9000 tokens, 1 to 300 slices) timed against the scan
-// kernels, those with up to 256 workgroups are 1.01 to 1.9 times as fast, the median at three chunks and more 1.6 (2048
-// tokens x 24 heads 33.8 -> 19.9 us, 3 x 630 x 6 25.7 -> 16.5), those up to 320 1.1 to 1.5; from there to 400 0.83 to
-// 1.2, beyond 0.4 to 1.1.  One chunk is one launch of two workgroups per slice, the shorter of them a third of the other:
-// 1.1 to 2.2 up to 256 of them (2 x 130 tokens x 60 heads 19.4 -> 9.9), up to 512 1.08 to 1.33 with more than 100 tokens
-// and 0.95 to 0.99 with 66 to 88, where the scan kernels have two blocks to do; 0.78 with 800.  Of 200 other such shapes the
-// 162 taken are 1.54 times as fast in the geometric mean.
+// CU -- is a round of the chip, from 4 to 18 chunks also a little more.  Of 4700 drawn shapes (10 to 16384 tokens, 1 to 600
+// slices) timed against the scan kernels, those of up to 256 workgroups take 0.55 to 1.0 of the time (median 0.7; a few of more
+// than 50 chunks, whose states each workgroup chains, up to 1.15), those of up to 320 0.75 to 1.05 with 4 to 18 chunks, 1.02
+// to 1.2 with 2 or 3, 0.85 to 1.3 with more; one chunk, one launch of two workgroups per slice, 0.6 to 0.88 up to 256 of them and
+// beyond 1.03 to 1.5 (11 x 123 tokens x 14 slices 16.5 us, scan 12.8; 12583 tokens x 6 slices 56.6, 44.0).
 bool chunk_chosen(const Dims &d, size_t workspace_bytes, bool h0_aliases_final_state) {
   const Knobs &k = knobs();
   if (k.chunk == 2 || !chunk_supported(d, workspace_bytes, h0_aliases_final_state)) return false;
@@ -679,7 +677,7 @@ bool chunk_chosen(const Dims &d, size_t workspace_bytes, bool h0_aliases_final_s
       k.fold_max_slots != Knobs().fold_max_slots)
     return false;
   const long slices = static_cast<long>(d.Bt) * d.H * (d.P / kP), chunks = chunk_count(d);
-  return chunks == 1 && !h0_aliases_final_state ? slices <= (d.T > 96 ? 256 : 128) : (chunks + 1) * slices <= 320;
+  return (chunks + 1) * slices <= (chunks >= 4 && chunks <= 18 ? 320 : kCus);
 }
 bool chunk_chosen(const Dims &d, size_t workspace_bytes, const float *h0, const float *final_state) {
   return chunk_chosen(d, workspace_bytes, overlap(d, h0, final_state));

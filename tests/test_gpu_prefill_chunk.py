@@ -72,8 +72,10 @@ def test_where_the_chunk_kernels_are_taken(ssd):
     """Where the launch is about one round of the chip; knobs of the scan kernels ask for those."""
     shape = lambda *d: ssd.make_shape(*d, 128, 1, 256, torch.bfloat16)   # noqa: E731
     assert ssd.prefill_chunks(shape(1, 2048, 24, 64)) == 8
-    assert ssd.prefill_chunks(shape(2, 250, 128, 64)) == 1 and ssd.prefill_chunks(shape(2, 250, 129, 64)) == 0
-    assert ssd.prefill_chunks(shape(1, 512, 106, 64)) == 2 and ssd.prefill_chunks(shape(1, 512, 107, 64)) == 0
+    assert ssd.prefill_chunks(shape(2, 250, 64, 64)) == 1 and ssd.prefill_chunks(shape(1, 250, 129, 64)) == 0
+    assert ssd.prefill_chunks(shape(1, 512, 85, 64)) == 2 and ssd.prefill_chunks(shape(1, 512, 86, 64)) == 0
+    assert ssd.prefill_chunks(shape(1, 1024, 64, 64)) == 4 and ssd.prefill_chunks(shape(1, 1024, 65, 64)) == 0
+    assert ssd.prefill_chunks(shape(1, 4608, 16, 64)) == 18 and ssd.prefill_chunks(shape(1, 4609, 16, 64)) == 0
     assert ssd.prefill_chunks(shape(1, 16384, 80, 64)) == 0
     assert ssd.prefill_chunks(ssd.make_shape(1, 2048, 24, 64, 136, 1, 256, torch.bfloat16)) == 0   # two state slices
     for knob, value in (("seg_blocks", 2), ("seg_chunks", 1), ("scan_heads", 4), ("y_stream", 0), ("fold_max_slots", 0),
