@@ -2663,6 +2663,7 @@ int list_items(const Dims &d, const Layout &w, int seg_blocks) { return d.Bt + f
 // device-side tables hold them per sequence), pieces per segment of the states-only pass, and whether the
 // full scan sums the chain over state slots itself (ScanParams::fold).
 bool packed_uncut(const Dims &d, const SlicePlan &pl);
+bool packed_two(const Dims &d, const SlicePlan &pl);
 SlicePlan plan_slice(const Dims &d, bool varlen, bool h0_aliases_final_state) {
   const Layout w = make_layout(d, varlen);
   Dims one = d;  // the segment length of a packed batch is chosen as for one sequence of all its tokens
@@ -2697,10 +2698,7 @@ SlicePlan plan_slice(const Dims &d, bool varlen, bool h0_aliases_final_state) {
   pl.from_lengths = varlen && d.Bt > 1 && d.Bt <= kTableThreads && w.NB <= kTableBlocks && list_items(d, w, pl.seg_blocks) <= kTableBlocks &&
                     kn.seg_chunks == 0 && kn.seg_blocks == 0 && full_items(d, w, pl.seg_blocks) > 0;
   if (pl.from_lengths) {
-    // Two heads per workgroup (see small_grid) where the sequences alone are no more than three rounds of them: 35 of 70
-    // drawn batches that four heads had served up to then take 0.85 of that time (4 sequences, 5040 tokens, 96 heads 80 -> 53
-    // us; 1.01 at worst); 32 sequences in 4.5 rounds 44 us, two heads 52, 64 in 11 rounds 132, two heads 139.
-    if (may_two && static_cast<long>(d.Bt) * head_groups(d, 2) <= 3 * kNumCUs) pl.heads = pl.state_heads = 2;
+    if (may_two && packed_two(d, pl)) pl.heads = pl.state_heads = 2;
     if (packed_uncut(d, pl)) {
       pl.from_lengths = false;
       pl.seg_blocks = w.NB - d.Bt;
@@ -2739,6 +2737,38 @@ SegChoice segment_choice(const Dims &d, const SlicePlan &pl) {
   c.fill = static_cast<float>(groups) / kNumCUs;
   c.slices = static_cast<float>(d.H) * (d.P / kP);
   return c;
+}
+
+// Whether a packed batch takes two heads per workgroup (see small_grid).  Its lengths are known on the device only: the
+// sequences alone are to be no more than a round of such workgroups, or three if a list entry has at most 32 of them (of
+// larger ones too few fit side by side to even out a ragged batch: 7 sequences, 4821 tokens, 91 heads 102 us, four heads
+// 85); and by the model two heads are to be at most a tenth slower both for equal lengths and for one long prompt among rows of
+// a token (17 sequences, 16113 tokens, of which 14417 in one, 28 heads 113, four 97).  Of 2000 drawn batches -- equal, ragged, one
+// or a few long among short ones -- the 1350 that it takes need 0.82 of the time of four heads, 18 of them more than 3 % more,
+// 8.4 % at worst; of the ragged ones of 64 tokens a sequence and more, one (3.1 %).  4 sequences, 5040 tokens, 96 heads 80 -> 53 us.
+bool packed_two(const Dims &d, const SlicePlan &pl) {
+  const int groups2 = head_groups(d, 2), nblocks = (d.T + kBlk - 1) / kBlk;
+  if (static_cast<long>(d.Bt) * groups2 > (groups2 <= kNumCUs / 8 ? 3 : 1) * kNumCUs) return false;
+  SlicePlan as = pl;
+  as.heads = 2;
+  const SegChoice two = segment_choice(d, as);
+  as.heads = kHeadsPerWg;
+  const SegChoice four = segment_choice(d, as);
+  const int each = ((d.T + d.Bt - 1) / d.Bt + kBlk - 1) / kBlk;  // blocks of a sequence, lengths equal
+  for (int mix = 0; mix < 2; ++mix) {
+    auto fastest = [&](const SegChoice &c) {
+      float best = 0.f;
+      for (int k = 0; k < c.count; ++k) {
+        const int s = c.cand[k];
+        const float us = mix == 0 ? packed_cost(c, s, d.Bt * each, each, d.Bt, d.Bt * ((each + s - 1) / s))
+                                  : packed_cost(c, s, nblocks + d.Bt - 1, nblocks, d.Bt, d.Bt - 1 + (nblocks + s - 1) / s);
+        if (k == 0 || us < best) best = us;
+      }
+      return best;
+    };
+    if (fastest(two) > 1.1f * fastest(four)) return false;
+  }
+  return true;
 }
 
 // Whether a short packed batch is left uncut, whatever its lengths: cutting it, or the chance of it, costs the launches of
