@@ -43,7 +43,8 @@
 //   chunk_scan<true>  ("segment_states") per (batch, 4 or 2 heads, segment): the segment's end state from a
 //                  zero start (only the chunk-state accumulation), so that segments can run in parallel.
 //   segment_pass   sequential pass over segment end states -> state entering each segment.
-//   chunk_scan<false> per (batch, 4 or 2 heads, segment): everything above, from the entering state.
+//   chunk_scan<false> per (batch, 4 heads, segment): everything above, from the entering state; with two heads per
+//                  workgroup it is pair_scan.
 // A segment is a whole number of 64-token blocks; with one segment only the first and the last kernel
 // run, and with few segments segment_pass does not: the last kernel sums the few states itself.
 #include <cmath>
@@ -1757,17 +1758,16 @@ __device__ __forceinline__ void scan_walk(const ScanParams &p, const SeqView &sv
 // the kernel around the call, so what the rare steep form needs (it spills) costs the common walk nothing.
 // (Arguments by value: a reference would make the kernel keep its own copy in private memory, where
 // nothing counts as uniform any more.)
-template <int HPW, int kYMode>
+template <int kYMode>
 __device__ __attribute__((noinline)) void scan_walk_mixed(const ScanParams p, const SeqView sv, const LdsTiles lds) {
-  scan_walk<false, HPW, kYMode, true>(p, sv, lds);
+  scan_walk<false, kHeadsPerWg, kYMode, true>(p, sv, lds);
 }
 
 // Whether the blocks this wave walks in the full scan include a steep one: one lane per block reads the
 // marker of its record.
-template <int HPW>
 __device__ __forceinline__ bool walk_meets_steep_block(const ScanParams &p, const SeqView &sv) {
   const int lane = threadIdx.x & 63;
-  const int slot = (sv.col % p.cpg) * HPW + (static_cast<int>(threadIdx.x) >> 7);
+  const int slot = (sv.col % p.cpg) * kHeadsPerWg + (static_cast<int>(threadIdx.x) >> 7);
   const int h = (sv.col / p.cpg) * p.hpg + min(slot, p.hpg - 1);
   const int hrec = h / p.pdiv;
   const bool plain = p.vp.tok0 == nullptr;
@@ -2345,9 +2345,8 @@ __device__ __attribute__((noinline)) void pair_walk_mixed(const ScanParams p, co
 }
 
 template <bool kStatesOnly, int HPW, int kYMode = kYPlain>
-__global__ __launch_bounds__(128 * HPW)
-__attribute__((amdgpu_waves_per_eu(kStatesOnly || HPW == kHeadsPerWg ? 2 : 1, kStatesOnly || HPW == kHeadsPerWg ? 2 : 1)))
-void chunk_scan_kernel(const ScanParams p) {
+__global__ __launch_bounds__(128 * HPW) __attribute__((amdgpu_waves_per_eu(2, 2))) void chunk_scan_kernel(const ScanParams p) {
+  static_assert(kStatesOnly || HPW == kHeadsPerWg, "the full scan with two heads is pair_scan_kernel");
   using L = ScanLds<kStatesOnly, HPW>;
   __shared__ __align__(16) uint16_t sC[L::kCBufs][L::kCElems];
   __shared__ __align__(16) uint16_t sBt[2][L::kBtElems];
@@ -2361,8 +2360,8 @@ void chunk_scan_kernel(const ScanParams p) {
   if constexpr (!kStatesOnly) {
     // Waves of one workgroup may take different walks: both stage the same shared tiles and meet at the
     // same barriers, block for block.
-    if (walk_meets_steep_block<HPW>(p, sv)) {
-      scan_walk_mixed<HPW, kYMode>(p, sv, lds);
+    if (walk_meets_steep_block(p, sv)) {
+      scan_walk_mixed<kYMode>(p, sv, lds);
       return;
     }
   }
