@@ -2745,9 +2745,16 @@ SegChoice segment_choice(const Dims &d, const SlicePlan &pl) {
 // a token (17 sequences, 16113 tokens, of which 14417 in one, 28 heads 113, four 97).  Of 2000 drawn batches -- equal, ragged, one
 // or a few long among short ones -- the 1350 that it takes need 0.82 of the time of four heads, 18 of them more than 3 % more,
 // 8.4 % at worst; of the ragged ones of 64 tokens a sequence and more, one (3.1 %).  4 sequences, 5040 tokens, 96 heads 80 -> 53 us.
+// Past two rounds and with fifteen blocks a CU the mix matters less, the list's many entries even it out: up to 48 workgroups an
+// entry it is two heads without asking the models.  Of 420 drawn batches of 66 to 128 heads the 67 there need 0.93 of the time
+// of four heads, six of them 4 to 10 % more; the other 353 0.99, a quarter of them more than 3 % more, 22 % at worst.  16
+// ragged sequences, 16384 tokens, 80 heads 169 -> 154 us.
 bool packed_two(const Dims &d, const SlicePlan &pl) {
   const int groups2 = head_groups(d, 2), nblocks = (d.T + kBlk - 1) / kBlk;
-  if (static_cast<long>(d.Bt) * groups2 > (groups2 <= kNumCUs / 8 ? 3 : 1) * kNumCUs) return false;
+  const long first = static_cast<long>(d.Bt) * groups2;  // entries of sequences alone, in workgroups
+  if (first > 3 * kNumCUs) return false;
+  if (first > 2 * kNumCUs && groups2 <= 48 && static_cast<long>(nblocks) * groups2 >= 15 * kNumCUs) return true;
+  if (first > kNumCUs && groups2 > kNumCUs / 8) return false;
   SlicePlan as = pl;
   as.heads = 2;
   const SegChoice two = segment_choice(d, as);

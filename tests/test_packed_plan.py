@@ -62,9 +62,12 @@ def test_plans_stay_within_what_the_host_sized():
 @pytest.mark.parametrize("lengths, heads, groups, two", [([1710] + 6 * [518], 91, 1, False), ([3222, 158] + 6 * [1215], 80, 4, False),
                                                          (16 * [19] + [2691], 65, 1, False), (4 * [1260], 96, 1, True), (5 * [500], 64, 1, True),
                                                          (40 * [250], 16, 1, True), (30 * [300], 24, 1, True), (17 * [105] + [14417], 28, 4, False),
-                                                         (64 * [256], 80, 1, False)], ids=lambda v: str(v)[:20])
+                                                         (64 * [256], 80, 1, False), ([700 + 40 * i for i in range(16)], 80, 1, True),
+                                                         (16 * [1024], 100, 1, False), (16 * [256], 80, 1, False),
+                                                         (12 * [1024], 80, 1, False)], ids=lambda v: str(v)[:20])
 def test_heads_per_workgroup_of_a_packed_batch(lengths, heads, groups, two):
     """Two where they are a round of the chip, or a few of list entries that are small beside it, unless one long prompt would
     be cut too coarsely: entries of an eighth of the chip and more leave a ragged batch uneven (7 sequences, 91 heads: 102
-    us, four heads 85)."""
+    us, four heads 85) unless there are many of them and long ones (16 ragged sequences, 16384 tokens, 80 heads: 154, four
+    heads 169)."""
     assert plan(lengths, heads, groups)["heads"] == (2 if two else 4)
