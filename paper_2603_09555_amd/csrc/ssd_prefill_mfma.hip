@@ -2662,7 +2662,7 @@ int list_items(const Dims &d, const Layout &w, int seg_blocks) { return d.Bt + f
 // device-side tables hold them per sequence), pieces per segment of the states-only pass, and whether the
 // full scan sums the chain over state slots itself (ScanParams::fold).
 bool packed_uncut(const Dims &d, const SlicePlan &pl);
-bool packed_two(const Dims &d, const SlicePlan &pl);
+bool packed_two(const Dims &d);
 SlicePlan plan_slice(const Dims &d, bool varlen, bool h0_aliases_final_state) {
   const Layout w = make_layout(d, varlen);
   Dims one = d;  // the segment length of a packed batch is chosen as for one sequence of all its tokens
@@ -2697,7 +2697,7 @@ SlicePlan plan_slice(const Dims &d, bool varlen, bool h0_aliases_final_state) {
   pl.from_lengths = varlen && d.Bt > 1 && d.Bt <= kTableThreads && w.NB <= kTableBlocks && list_items(d, w, pl.seg_blocks) <= kTableBlocks &&
                     kn.seg_chunks == 0 && kn.seg_blocks == 0 && full_items(d, w, pl.seg_blocks) > 0;
   if (pl.from_lengths) {
-    if (may_two && packed_two(d, pl)) pl.heads = pl.state_heads = 2;
+    if (may_two && packed_two(d)) pl.heads = pl.state_heads = 2;
     if (packed_uncut(d, pl)) {
       pl.from_lengths = false;
       pl.seg_blocks = w.NB - d.Bt;
@@ -2738,43 +2738,23 @@ SegChoice segment_choice(const Dims &d, const SlicePlan &pl) {
   return c;
 }
 
-// Whether a packed batch takes two heads per workgroup (see small_grid).  Its lengths are known on the device only: the
-// sequences alone are to be no more than a round of such workgroups, or three if a list entry has at most 32 of them (of
-// larger ones too few fit side by side to even out a ragged batch: 7 sequences, 4821 tokens, 91 heads 102 us, four heads
-// 85); and by the model two heads are to be at most a tenth slower both for equal lengths and for one long prompt among rows of
-// a token (17 sequences, 16113 tokens, of which 14417 in one, 28 heads 113, four 97).  Of 2000 drawn batches -- equal, ragged, one
-// or a few long among short ones -- the 1350 that it takes need 0.82 of the time of four heads, 18 of them more than 3 % more,
-// 8.4 % at worst; of the ragged ones of 64 tokens a sequence and more, one (3.1 %).  4 sequences, 5040 tokens, 96 heads 80 -> 53 us.
-// Past two rounds and with fifteen blocks a CU the mix matters less, the list's many entries even it out: up to 48 workgroups an
-// entry it is two heads without asking the models.  Of 420 drawn batches of 66 to 128 heads the 67 there need 0.93 of the time
-// of four heads, six of them 4 to 10 % more; the other 353 0.99, a quarter of them more than 3 % more, 22 % at worst.  16
-// ragged sequences, 16384 tokens, 80 heads 169 -> 154 us.
-bool packed_two(const Dims &d, const SlicePlan &pl) {
+// Whether a packed batch takes two heads per workgroup (see small_grid).  Its lengths are known on the device only, so the
+// rule is on what the sequences alone come to: a round of such workgroups or less; up to three if a list entry has at
+// most 32 of them (of larger ones too few fit side by side to even out a ragged batch: 7 sequences, 4821 tokens, 91 heads 102
+// us, four heads 85), or at most 48, more than two rounds and fifteen blocks a CU (16 ragged sequences, 16384 tokens, 80
+// heads 154, four heads 169).  Of 2000 drawn batches -- equal, ragged, one or a few long among short ones -- the 1596 taken
+// need 0.84 of the time of four heads, 41 of them more than 3 % more, 8.6 % at worst; of 420 at 66 to 128 heads and one
+// to three rounds the 67 taken 0.93 (six 4 to 10 % more), the others 0.99 (a quarter more than 3 % more, 22 % at worst).  To
+// ask the models whether one long prompt among rows of a token would lose spares some of these 3 to 10 %, and one of 17 (17
+// sequences, 16113 tokens, of which 14417 in one, 28 heads 113 us, four heads 97), but costs one batch in ten 3 to 50 % (4 x 1676
+// x 88 heads 63, four heads 95).  4 sequences, 5040 tokens, 96 heads 80 -> 53 us.
+bool packed_two(const Dims &d) {
   const int groups2 = head_groups(d, 2), nblocks = (d.T + kBlk - 1) / kBlk;
-  const long first = static_cast<long>(d.Bt) * groups2;  // entries of sequences alone, in workgroups
+  const long first = static_cast<long>(d.Bt) * groups2;  // workgroups of uncut sequences
+  if (first <= kNumCUs) return true;
   if (first > 3 * kNumCUs) return false;
-  if (first > 2 * kNumCUs && groups2 <= 48 && static_cast<long>(nblocks) * groups2 >= 15 * kNumCUs) return true;
-  if (first > kNumCUs && groups2 > kNumCUs / 8) return false;
-  SlicePlan as = pl;
-  as.heads = 2;
-  const SegChoice two = segment_choice(d, as);
-  as.heads = kHeadsPerWg;
-  const SegChoice four = segment_choice(d, as);
-  const int each = ((d.T + d.Bt - 1) / d.Bt + kBlk - 1) / kBlk;  // blocks of a sequence, lengths equal
-  for (int mix = 0; mix < 2; ++mix) {
-    auto fastest = [&](const SegChoice &c) {
-      float best = 0.f;
-      for (int k = 0; k < c.count; ++k) {
-        const int s = c.cand[k];
-        const float us = mix == 0 ? packed_cost(c, s, d.Bt * each, each, d.Bt, d.Bt * ((each + s - 1) / s))
-                                  : packed_cost(c, s, nblocks + d.Bt - 1, nblocks, d.Bt, d.Bt - 1 + (nblocks + s - 1) / s);
-        if (k == 0 || us < best) best = us;
-      }
-      return best;
-    };
-    if (fastest(two) > 1.1f * fastest(four)) return false;
-  }
-  return true;
+  return groups2 <= kNumCUs / 8 ||
+         (first > 2 * kNumCUs && groups2 <= 48 && static_cast<long>(nblocks) * groups2 >= 15 * kNumCUs);
 }
 
 // Whether a short packed batch is left uncut, whatever its lengths: cutting it, or the chance of it, costs the launches of

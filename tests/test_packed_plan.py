@@ -61,13 +61,14 @@ def test_plans_stay_within_what_the_host_sized():
 
 @pytest.mark.parametrize("lengths, heads, groups, two", [([1710] + 6 * [518], 91, 1, False), ([3222, 158] + 6 * [1215], 80, 4, False),
                                                          (16 * [19] + [2691], 65, 1, False), (4 * [1260], 96, 1, True), (5 * [500], 64, 1, True),
-                                                         (40 * [250], 16, 1, True), (30 * [300], 24, 1, True), (17 * [105] + [14417], 28, 4, False),
+                                                         (40 * [250], 16, 1, True), (30 * [300], 24, 1, True), (17 * [105] + [14417], 28, 4, True),
                                                          (64 * [256], 80, 1, False), ([700 + 40 * i for i in range(16)], 80, 1, True),
                                                          (16 * [1024], 100, 1, False), (16 * [256], 80, 1, False),
-                                                         (12 * [1024], 80, 1, False)], ids=lambda v: str(v)[:20])
+                                                         (12 * [1024], 80, 1, False), (4 * [1676], 88, 2, True),
+                                                         ([14161, 9290], 60, 4, True)], ids=lambda v: str(v)[:20])
 def test_heads_per_workgroup_of_a_packed_batch(lengths, heads, groups, two):
-    """Two where they are a round of the chip, or a few of list entries that are small beside it, unless one long prompt would
-    be cut too coarsely: entries of an eighth of the chip and more leave a ragged batch uneven (7 sequences, 91 heads: 102
-    us, four heads 85) unless there are many of them and long ones (16 ragged sequences, 16384 tokens, 80 heads: 154, four
-    heads 169)."""
+    """Two where the sequences are a round of the chip, or a few of list entries that are small beside it: entries of an eighth
+    of the chip and more leave a ragged batch uneven (7 sequences, 91 heads: 102 us, four heads 85) unless there are many of
+    them and long ones (16 ragged sequences, 16384 tokens, 80 heads: 154, four heads 169).  Whatever the lengths: what one
+    long prompt might lose (113 us, four heads 97) is less than what equal ones would (4 x 1676 x 88 heads: 63, four heads 95)."""
     assert plan(lengths, heads, groups)["heads"] == (2 if two else 4)
