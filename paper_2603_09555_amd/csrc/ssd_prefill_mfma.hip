@@ -2546,9 +2546,10 @@ bool small_grid(long wgs_of_two) { return wgs_of_two <= kNumCUs; }
 // cuts a segment into; 0 where the sequences alone are more than a round.  Microseconds of a whole call, fitted to 90
 // drawn shapes (300 to 18400 tokens, 2 to 163 slices, batches of up to 12) at the lengths that give 1 to 24 segments (611 timings,
 // 4.6 % rms): the choice is 0.8 % behind the fastest of the timed lengths and takes 0.80 of the time of four heads
-// with their own choice, 1.04 at worst.  Beyond a round four heads are as fast or faster (968 tokens x 141 heads in
+// with their own choice, 1.04 at worst (of 411 others 0.81; six 2 % slower and more, 5 x 3182 tokens x 40 heads with dstate 256 207
+// us to 185, 3 x 9977 x 45 340 to 322; to ask both models would cost up to 39 % elsewhere).  Beyond a round four heads are as fast or faster (968 tokens x 141 heads in
 // batches of 12: 150.9 us, two heads 157.7; 2328 x 139 in batches of 4: 130.5, two heads in two rounds 133.8).
-// 8 x 4096 tokens x 48 heads 174 -> 130 us (one segment instead of two), 2016 x 59 in batches of 6 100 -> 70.
+// 8 x 4096 tokens x 48 heads 161 -> 130 us (one segment instead of two; 123 with y streamed), 2016 x 59 in batches of 6 100 -> 70.
 int two_head_blocks(const Dims &d, int min_blocks, int max_slots, int *parts) {
   const int nblocks = (d.T + kBlk - 1) / kBlk;
   const long groups2 = static_cast<long>(d.Bt) * head_groups(d, 2), groups4 = static_cast<long>(d.Bt) * head_groups(d);
@@ -2643,7 +2644,8 @@ bool shape_ok(const Dims &d, unsigned long long tokens, unsigned long long nb) {
 // later state slices read y back to add to it, but they read x twice more: the first slice streams y all the
 // same (dstate 256: 333 -> 307 us).  With two heads per workgroup (ordinary / non-temporal): the same inputs again and again,
 // 16384 tokens x 80 heads in six segments 144 / 123, 3 packed sequences of 24001 x 63 201 / 181, 8 x 4096 x 48 in one 129 / 119;
-// inputs that change 148 / 152, 200 / 201 and 131 / 126.  The y_stream knob overrides (tests, tuning).
+// inputs that come cold 145 / 148, 208 / 201 and 127 / 121; x just written by the convolution, as a layer finds it, 146 / 146,
+// 207 / 194 and 137 / 123, the pair 213 / 199, 298 / 264 and 225 / 192.  The y_stream knob overrides (tests, tuning).
 constexpr unsigned long long kMemCacheBytes = 256ull << 20;
 bool stream_y(const Dims &d, int rows) {
   if (knobs().y_stream >= 0) return knobs().y_stream != 0;
