@@ -269,6 +269,7 @@ ssd_status ssd_testing_varlen_plan(const ssd_shape *shape, const int32_t *cu_seq
     plan[2] = pl.segments;
     plan[3] = pl.shortest;
     plan[4] = pl.from_lengths;
+    plan[5] = pl.listed;
     plan[6] = pl.heads;
     plan[7] = pl.state_heads;
   }
@@ -450,6 +451,7 @@ ssd_status ssd_testing_set_knob(int32_t knob, int32_t value) {
     case SSD_KNOB_F32_SEGMENTS: k.f32_segments = value > 0 ? value : 0; return SSD_OK;
     case SSD_KNOB_FOLD_MAX_SLOTS: k.fold_max_slots = value > 0 ? value : 0; return SSD_OK;
     case SSD_KNOB_CHUNK: k.chunk = value == 1 || value == 2 ? value : 0; return SSD_OK;
+    case SSD_KNOB_DEAL: k.deal = value == 1 || value == 2 ? value : 0; return SSD_OK;
     case SSD_KNOB_SCAN_HEADS: k.scan_heads = value == 2 || value == 4 ? value : 0; return SSD_OK;
     default: return SSD_ERR_SHAPE;
   }

@@ -123,6 +123,7 @@ struct Knobs {
   int force_mfma_f32 = 0;  // 1: fp32 io takes the fp32 MFMA kernel whenever the shape is eligible
   int f32_segments = 0;    // > 0: time segments per sequence in the fp32 MFMA kernel
   int scan_heads = 0;      // 2 / 4: head slices per workgroup in the bf16 scan; 0: library's choice
+  int deal = 0;            // packed bf16 batches: 1 items dealt to the scan's workgroups, 2 an entry each; 0: library's choice
   int chunk = 0;           // bf16 prefill by chunk kernels: 1 wherever they can run, 2 never; 0: library's choice
   int fold_max_slots = 3;  // most state slots a segment sums by itself instead of a pass over segment states (0: never)
 };
@@ -153,6 +154,7 @@ hipError_t launch_prefill_generic(const Dims &d, const void *x, const float *dt,
 struct SlicePlan {
   int seg_blocks, segments, parts, fold;
   int heads, state_heads;  // head slices per workgroup: full scan, states-only pass
+  bool listed = false;     // packed batch: the full scan's workgroups walk lists of two-head items (pair_list)
   int two = 0;             // the segments are those chosen for two heads per workgroup (two_head_blocks)
   // packed batch: the device chooses the segment length from the sequences' lengths (seg_blocks is the shortest it may)
   bool from_lengths = false;
@@ -206,6 +208,8 @@ struct SegChoice {
   int cand[kMost];
   int count, heads, max_items;  // head slices per workgroup of the scan; list entries that still run side by side
   float fill, slices;           // share of the chip that one entry's workgroups take; 64-column slices of all heads
+  bool dealt;                   // the scan's workgroups are dealt items (then fill is an entry's share of a round of these)
+  float state_fill;             // the states-only pass's fill
 };
 void launch_varlen_tables(const int32_t *cu, int total, int blk_len, const SegChoice &choice, int item_cap, const VarPlan &vp,
                           hipStream_t stream);

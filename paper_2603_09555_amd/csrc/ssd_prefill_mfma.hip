@@ -257,12 +257,19 @@ __device__ __forceinline__ int wave_reduce(int v, Op op) {
 // % rms, with its choice the 35 that four heads had served take 0.85 of that time.  Against the length of one sequence of all the tokens: 1.07 in the geometric mean.  A length
 // guessed on the host cannot serve both a ragged batch and one long prompt among short ones: the guess of four times the
 // mean left 8192 + 63 x 1 tokens x 24 heads uncut, 322 us (now 75; 89 with the length of one sequence).
+// Dealt items (see Deal), fitted to 400 batches of more than a round of these (draws, equal lengths, one or a few long among short ones), 1150
+// timings at up to eight lengths, 10 % rms.  The deal in rounds is less even than the model has it where a few items are long: of
+// lengths within 5 % of the cheapest the shortest is taken, which is 1.1 % behind the fastest timed in the geometric mean, 19 % at worst.
+constexpr float kDealtMargin = 1.05f;
 __host__ __device__ inline float packed_cost(const SegChoice &c, int s, int blocks, int longest, int nseq, int items) {
   auto both = [](float a, float b) { return sqrtf(a * a + b * b); };
   const float n = static_cast<float>(items), full = static_cast<float>(items - nseq), len = static_cast<float>(s);
   const float walk = s < longest ? len : static_cast<float>(longest), grid = n * c.fill < 1.f ? n * c.fill : 1.f;
   float us;
-  if (c.heads == 2) {
+  if (c.dealt) {
+    us = 21.8f + 1.57f * both((blocks + 3.6f * n) * c.fill, walk);
+    if (items > nseq) us += 0.0376f * full * c.slices + 0.69f * len * both(1.f, full * c.state_fill);
+  } else if (c.heads == 2) {
     us = 15.f + (1.13f + 0.24f * grid) * both((blocks + 3.9f * n) * c.fill, walk + 3.9f);
     if (items > nseq) us += 0.0123f * full * c.slices + 0.82f * (len + 6.4f) * both(1.f, full * c.fill);
   } else {
@@ -336,8 +343,10 @@ __global__ __launch_bounds__(kTableThreads) void varlen_tables_kernel(
     __syncthreads();
     // the cheapest, the shortest of equals: a positive float orders like its bits, whose last five give way to the index
     int best = lane < choice.count ? ((__float_as_int(s_cost[lane]) & ~31) | lane) : 0x7fffffff;
-    best = wave_reduce(best, [](int x, int y) { return min(x, y); });
-    seg_blocks = s_cand[best & 31];
+    best = wave_reduce(best, [](int x, int y) { return min(x, y); }) & 31;
+    if (choice.dealt)  // (the shortest that is about as cheap)
+      best = __builtin_ctzll(__builtin_amdgcn_ballot_w64(lane < choice.count && s_cost[lane] <= kDealtMargin * s_cost[best]));
+    seg_blocks = s_cand[best];
   }
   const int segs = tid < nseq ? max(1, (n + seg_blocks - 1) / seg_blocks) : 0;
   // exclusive sums over the sequences: blocks, segments, state slots
@@ -750,6 +759,7 @@ struct ScanParams {
   const uint8_t *Gd;
   const uint8_t *Btr;
   const float *prep;
+  uint32_t prep_bytes;
   uint8_t *y;
   const float *h0;         // (sequences, H, P, N) initial states, or nullptr = zeros (read by one-segment sequences)
   const float *Hin;        // state entering each segment of a sequence of several: one slot per segment
@@ -771,8 +781,17 @@ struct ScanParams {
   int pdiv, Hrec;          // slices per head (headdim / 64); heads (owners of decay records, A, D)
   NSlice ns;               // columns of h0 / final_state (rows of ns.width floats) this launch works on
   int cols, segs, total, per_xcd;  // workgroup mapping, see wg_coords
+  uint32_t cpg_inv, pdiv_inv, cols_inv, segs_inv;  // for quotient()
   VarPlan vp;              // tok0 == nullptr: plain batch
 };
+
+// n / d of scalars by a multiplication with (2^32 - 1) / d, which falls short by one at most.  The start of every workgroup is
+// a few such divisions, of 20 to 30 dependent instructions otherwise.
+__device__ __forceinline__ int quotient(int n, int d, uint32_t inv) {
+  const int q = static_cast<int>(__umulhi(static_cast<uint32_t>(n), inv));
+  return q + (n - q * d >= d ? 1 : 0);
+}
+inline uint32_t inverse_of(int d) { return 0xFFFFFFFFu / static_cast<uint32_t>(d); }
 
 // Where a workgroup works: head group `col`, segment `sg` of `S` of sequence `b`, whose `nb` blocks
 // start at token `tok0` of the packed token axis (`len` tokens), at workspace tile / record number
@@ -798,9 +817,10 @@ __device__ __forceinline__ bool wg_coords(const ScanParams &p, bool last_too, Se
   const int id = blockIdx.x;
   const int w = (id % kXcds) * p.per_xcd + id / kXcds;
   if (w >= p.total) return false;
-  v.col = w % p.cols;
-  v.sg = (w / p.cols) % p.segs;
-  v.b = w / (p.cols * p.segs);
+  const int item = quotient(w, p.cols, p.cols_inv);
+  v.col = w - item * p.cols;
+  v.b = quotient(item, p.segs, p.segs_inv);
+  v.sg = item - v.b * p.segs;
   v.S = p.S;
   v.nb = p.NB;
   v.seg_blocks = p.seg_blocks;
@@ -835,8 +855,8 @@ __device__ __forceinline__ bool wg_coords_varlen(const ScanParams &p, bool last_
   if (id / kXcds >= per_xcd) return false;
   const int w = (id % kXcds) * per_xcd + id / kXcds;
   if (w >= total) return false;
-  v.col = w % p.cols;
-  int item = w / p.cols;
+  int item = quotient(w, p.cols, p.cols_inv);
+  v.col = w - item * p.cols;
   if (last_too) {
     const int base = n_list / kXcds, rem = n_list % kXcds;  // hands 0..rem-1 hold base + 1 entries
     const int big = rem * (base + 1);
@@ -947,15 +967,15 @@ __device__ __forceinline__ void scan_walk(const ScanParams &p, const SeqView &sv
   // The heads of a workgroup share one B/C group.  A group whose number of (64-column) slices is not a
   // multiple of four leaves slots of its last workgroup without a slice: those waves repeat the group's last
   // slice -- they take part in the shared staging and the barriers like any other -- and write nothing.
-  const int g = col / p.cpg;
-  const int slot = (col % p.cpg) * HPW + hw;
+  const int g = quotient(col, p.cpg, p.cpg_inv);
+  const int slot = (col - g * p.cpg) * HPW + hw;
   const bool live = slot < p.hpg;
   const int h = g * p.hpg + min(slot, p.hpg - 1);
   // workspace numbering: tiles (b, g, block), records (b, h, block), state slots (b, h, segment) for a
   // plain batch; (g, block), (h, block), (h, segment) with batch-wide block / segment numbers otherwise
   const bool plain = p.vp.tok0 == nullptr;
   const size_t tile0 = plain ? (sv.blk0 * p.G + static_cast<size_t>(g) * sv.blk_stride) : (g * sv.blk_stride + sv.blk0);
-  const int hrec = h / p.pdiv;  // the head this slice belongs to
+  const int hrec = quotient(h, p.pdiv, p.pdiv_inv);  // the head this slice belongs to
   const size_t rec0 = plain ? (sv.blk0 * p.Hrec + static_cast<size_t>(hrec) * sv.blk_stride) : (hrec * sv.blk_stride + sv.blk0);
   const size_t slot0 = plain ? (sv.slot0 * p.H + static_cast<size_t>(h) * sv.slot_stride) : (h * sv.slot_stride + sv.slot0);
   const size_t bh = static_cast<size_t>(sv.b) * p.H + h;  // row of final_state
@@ -1820,30 +1840,159 @@ typedef lds_as<uint8_t> lds_u8;
 //   x, per head two halves of 32 tokens, each two halves ph of 32 columns: of the latter token t's piece c at place 64 (t / 16 & 1) +
 //     16 (t & 3) + 4 ((t / 4 & 3) ^ 2 ph) + (c ^ (t & 3)), which also serves the four tokens per lane of the turn and whole rows of y.
 
+// ---- what a workgroup walks: items, an item being two heads of an entry of the segment list ----
+// The walk goes from the last block of an item to the first of the next as it goes from block to block: what the next
+// item's blocks need is requested while this one's are computed.  A workgroup of its own for every entry pays 5 us for its start, and
+// where they are several a CU they end unevenly: 64 ragged sequences, 16384 tokens, 80 heads 173 us with four heads to a
+// workgroup (148 of them the scan, 1280 workgroups), dealt 157 (134).  What is left is the memory: x, y and a final state of 32 KB a
+// sequence and head are 504 MB, 3.8 TB/s; an item's end costs 3400 cycles, a block 3300.
+struct ItemView {
+  uint32_t tok0, len, blk0, slot0, b;  // as in SeqView
+  int sg, S, col, nb, jb0, jb1;
+};
+__device__ __forceinline__ void item_blocks(ItemView &v, int seg_blocks) {
+  v.nb = static_cast<int>((v.len + kBlk - 1) / kBlk);
+  v.jb0 = min(v.nb, v.sg * seg_blocks);
+  v.jb1 = min(v.nb, v.jb0 + seg_blocks);
+}
+
+// The item of a workgroup that has one at most: true if it has one.
+__device__ __forceinline__ bool one_item(const ScanParams &p, int &seg_blocks, ItemView &first) {
+  SeqView v;
+  if (!wg_coords(p, true, v)) return false;
+  seg_blocks = v.seg_blocks;
+  first.tok0 = static_cast<uint32_t>(v.tok0);
+  first.len = v.len;
+  first.blk0 = static_cast<uint32_t>(v.blk0);
+  first.slot0 = static_cast<uint32_t>(v.slot0);
+  first.b = v.b;
+  first.sg = v.sg;
+  first.S = v.S;
+  first.col = v.col;
+  item_blocks(first, seg_blocks);
+  return true;
+}
+
+// A packed batch of more items than workgroups.  The items, entry by entry and so longest first (but for those that are not the
+// last of their sequence, which are first and equal), are dealt in rounds of a workgroup per CU: the first round forth, all later
+// ones back, so that who had the longest item gets the shortest of every later round.  (Simulated over 300 drawn batches:
+// the last workgroup ends 1.10 times as late as an even share of the work, or its longest item, asks for; dealt forth and back in
+// turn 1.13, longest-first to whoever is free, over the whole chip, 1.05, as the hardware does it with every entry bound to
+// an XCD 1.42.  A list made to measure by every workgroup comes to 1.05 too, and costs each 12 us: its 8 KB of code run once,
+// at the rate at which instructions come from the L2.)  A round's places go XCD by XCD, so that an entry's tiles are fetched into few L2s.
+struct Deal {
+  int n_full, n_mine, place, seg_blocks;
+};
+__device__ __forceinline__ Deal deal_of(const ScanParams &p) {
+  Deal d;
+  const int entries = table_at(p.vp.item0, p.vp.nseq), total = entries * p.cols, wgs = gridDim.x;
+  d.seg_blocks = table_at(p.vp.len, p.vp.nseq);
+  d.n_full = entries - p.vp.nseq;
+  const int xcd = blockIdx.x % kXcds, in_xcd = blockIdx.x / kXcds, per_xcd = total < wgs ? (total + kXcds - 1) / kXcds : wgs / kXcds;
+  d.place = xcd * per_xcd + in_xcd;
+  d.n_mine = in_xcd < per_xcd && d.place < total ? 1 : 0;
+  const int back = total - wgs - (wgs - 1 - d.place);  // items from the second round's on
+  if (total > wgs && back > 0) d.n_mine += (back + wgs - 1) / wgs;
+  return d;
+}
+// Its item i: entry and column, and (looked up in two steps, each an item ahead of the next) the entry's sequence, the rest.
+struct ItemPlace {
+  int entry, col, q;
+};
+__device__ __forceinline__ ItemPlace item_place(const ScanParams &p, const Deal &d, int i) {
+  const int wgs = gridDim.x;
+  const int pos = i == 0 ? d.place : i * wgs + wgs - 1 - d.place;
+  ItemPlace at;
+  at.entry = quotient(pos, p.cols, p.cols_inv);
+  at.col = pos - at.entry * p.cols;
+  at.q = table_at(p.vp.item_seq, at.entry);
+  return at;
+}
+__device__ __forceinline__ ItemView item_at(const ScanParams &p, const Deal &d, const ItemPlace &at) {
+  ItemView v;
+  const int first = table_at(p.vp.item0, at.q);
+  v.b = at.q;
+  v.S = table_at(p.vp.item0, at.q + 1) - first;
+  v.sg = at.entry < d.n_full ? at.entry - (first - at.q) : v.S - 1;
+  v.col = at.col;
+  v.len = table_at(p.vp.len, at.q);
+  v.tok0 = table_at(p.vp.tok0, at.q);
+  v.blk0 = table_at(p.vp.blk0, at.q);
+  v.slot0 = table_at(p.vp.slot0, at.q);
+  item_blocks(v, d.seg_blocks);
+  return v;
+}
+// The items in turn.  kList: several, from the deal; otherwise the one.
+template <bool kList>
+struct Items {
+  Deal deal;
+  ItemView ahead;        // item `next`
+  ItemPlace ahead2 = {};  // and where the one after it is
+  int next = 0, n;
+  __device__ __forceinline__ Items(const Deal &d, const ItemView &first) : deal(d), ahead(first), n(1) {}
+  __device__ __forceinline__ Items(const ScanParams &p, const Deal &d, int i) : deal(d), next(i), n(d.n_mine) {
+    ahead = item_at(p, d, item_place(p, d, i));
+    if (i + 1 < n) ahead2 = item_place(p, d, i + 1);
+  }
+  __device__ __forceinline__ ItemView take(const ScanParams &p) {
+    const ItemView v = ahead;
+    ++next;
+    if constexpr (kList) {
+      if (next < n) ahead = item_at(p, deal, ahead2);
+      if (next + 1 < n) ahead2 = item_place(p, deal, next + 1);
+    }
+    return v;
+  }
+};
+
+// The thread's number, as something that is only known here: what is computed from it stays in the role that needs it,
+// instead of being kept in registers through the others (whose spills would wait for all requests under way).
+__device__ __forceinline__ int here(unsigned thread) {
+  int t = static_cast<int>(thread);
+  asm volatile("" : "+v"(t));
+  return t;
+}
+// ... and the lane's in its wave, from nothing that would have to be kept.
+__device__ __forceinline__ int lane_here() {
+  int t;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(t));
+  return t;
+}
+
 // The feeding waves, 4..7: feeder w serves head w / 2 and, of x and y, tokens 32 (w & 1) .. + 31.
-template <int kYMode>
-__device__ __forceinline__ void pair_feed(const ScanParams &p, const SeqView &sv, lds_u8 *const lds) {
+template <int kYMode, bool kList>
+__device__ __forceinline__ void pair_feed(const ScanParams &p, Items<kList> items, lds_u8 *const lds) {
   using L = PairLds;
   const uint32_t lds_at = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds));
-  const int tid = threadIdx.x & 255, lane = tid & 63;
+  const int tid = here(threadIdx.x) & 255, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int hw = wave >> 1, ph = wave & 1;
-  const int g = sv.col / p.cpg, slot = (sv.col % p.cpg) * 2 + hw;
-  const bool live = slot < p.hpg;
-  const int h = g * p.hpg + min(slot, p.hpg - 1);
   const bool plain = p.vp.tok0 == nullptr;
-  const size_t tile0 = plain ? (sv.blk0 * p.G + static_cast<size_t>(g) * sv.blk_stride) : (g * sv.blk_stride + sv.blk0);
-  const int hrec = h / p.pdiv;
-  const size_t rec0 = plain ? (sv.blk0 * p.Hrec + static_cast<size_t>(hrec) * sv.blk_stride) : (hrec * sv.blk_stride + sv.blk0);
-  const int jb0 = min(sv.nb, sv.sg * sv.seg_blocks), jb1 = min(sv.nb, jb0 + sv.seg_blocks), jlast = jb1 - 1;
   const uint32_t xrow = static_cast<uint32_t>(p.H) * (kP * 2), crow = static_cast<uint32_t>(p.G) * (kN * 2);
-  const uint32_t xbytes = sv.len * xrow;
-  const uint32_t cbytes = sv.len > 0 ? sv.len * crow - static_cast<uint32_t>(g) * (kN * 2) : 0;
-  const uint8_t *const xb = p.x + sv.tok0 * xrow;
-  uint8_t *const yb = p.y + sv.tok0 * xrow;
-  const uint8_t *const cb = p.C + (sv.tok0 * p.G + g) * (kN * 2);
-  const uint8_t *const btb = p.Btr + tile0 * (kN * kBlk * 2), *const gb = p.Gd + tile0 * (kBlk * kBlk * 2);
-  const float *const prep_bh = p.prep + rec0 * kRec;
+
+  // ---- what has to be known of a block to request and store what belongs to it ----
+  struct Block {
+    size_t x_at, c_at;       // bytes from the start of x (and y) to its first row, of C
+    uint32_t xb, cb;         // bytes behind these that belong to the sequence; 0: there is no such block
+    uint32_t tile;           // of B^T and G
+    uint32_t rec0, rec1;     // decay records of the two heads
+  };
+  bool live = false;  // y of the item's blocks is stored
+  auto first_block = [&](const ItemView &v, Block &b) __attribute__((always_inline)) {
+    const int g = quotient(v.col, p.cpg, p.cpg_inv), slot = (v.col - g * p.cpg) * 2;
+    live = slot + hw < p.hpg;
+    const int h0 = g * p.hpg + min(slot, p.hpg - 1), h1 = g * p.hpg + min(slot + 1, p.hpg - 1), h = hw ? h1 : h0;
+    const uint32_t tok = v.tok0 + static_cast<uint32_t>(v.jb0) * kBlk, rest = v.len - static_cast<uint32_t>(v.jb0) * kBlk;
+    b.x_at = static_cast<size_t>(tok) * xrow + static_cast<uint32_t>(h) * (kP * 2);
+    b.c_at = (static_cast<size_t>(tok) * p.G + g) * (kN * 2);
+    b.xb = rest * xrow - static_cast<uint32_t>(h) * (kP * 2);
+    b.cb = rest * crow - static_cast<uint32_t>(g) * (kN * 2);
+    const uint32_t stride = plain ? p.NB : p.vp.nb_cap;
+    b.tile = v.blk0 * (plain ? p.G : 1) + g * stride + v.jb0;
+    const uint32_t rec = v.blk0 * (plain ? p.Hrec : 1) + v.jb0;
+    b.rec0 = rec + quotient(h0, p.pdiv, p.pdiv_inv) * stride;
+    b.rec1 = rec + quotient(h1, p.pdiv, p.pdiv_inv) * stride;
+  };
 
   // ---- requests: per-lane offsets that never change, descriptors that start at the block.  Of x and C a wave fetches four
   //      times 1024 bytes to consecutive places (see load_to_lds4) from rows that may be nearer to each other than that: their
@@ -1853,7 +2002,7 @@ __device__ __forceinline__ void pair_feed(const ScanParams &p, const SeqView &sv
 #pragma unroll
   for (int o = 0; o < 4; ++o) {
     const int i = lane >> 4, half = o >> 1, t = 32 * ph + 16 * (o & 1) + 4 * ((lane >> 2 & 3) ^ 2 * half) + i;
-    vx[o] = static_cast<uint32_t>(t) * xrow + static_cast<uint32_t>(h) * (kP * 2) + 64 * half + 16 * ((lane & 3) ^ i) + (kEarly - 1024 * o);
+    vx[o] = static_cast<uint32_t>(t) * xrow + 64 * half + 16 * ((lane & 3) ^ i) + (kEarly - 1024 * o);
     const int row = 16 * wave + 4 * o + (lane >> 4);
     vc[o] = static_cast<uint32_t>(row) * crow + 16 * ((lane ^ row) & 15) + (kEarly - 1024 * o);
   }
@@ -1863,30 +2012,24 @@ __device__ __forceinline__ void pair_feed(const ScanParams &p, const SeqView &sv
   for (int k = 0; k < 2; ++k) vb[k] = static_cast<uint32_t>(32 * wave + (lane >> 3)) * (kBlk * 2) + 16 * ((lane ^ (lane >> 4) ^ 4 * k) & 7);
   const uint32_t vt = static_cast<uint32_t>(32 + (tid >> 3)) * (kBlk * 2) + 16 * ((tid ^ (tid >> 4)) & 7);  // G's upper rows
   // The tenth request of a wave: waves 0 and 1 fetch a half of G's short rows each, waves 2 and 3 (both the same) the record
-  // entries that the two heads need next: 32 lanes the input factors of block jb + 2, 32 the output-row factors of jb + 1.
+  // entries that the two heads need next: 32 lanes the input factors of the block after, 32 the output-row factors.
   const bool fetches_g = wave < 2;
-  const int h_first = g * p.hpg + min((sv.col % p.cpg) * 2, p.hpg - 1), h_second = g * p.hpg + min((sv.col % p.cpg) * 2 + 1, p.hpg - 1);
-  const uint32_t head_step = static_cast<uint32_t>((h_second / p.pdiv - h_first / p.pdiv) * sv.blk_stride) * (kRec * 4);
-  const float *const rec_first = prep_bh - static_cast<ptrdiff_t>(hrec - h_first / p.pdiv) * static_cast<ptrdiff_t>(sv.blk_stride) * kRec;
-  const uint32_t vg = fetches_g ? static_cast<uint32_t>(16 * wave + (lane >> 2)) * (kBlk * 2) + 16 * ((lane ^ (lane >> 4)) & 3)
-                                : ((lane & 16) ? head_step : 0u) + (lane < 32 ? (kRec + kBlk) * 4u : 0u) + 16 * (lane & 15);
-  // this wave's ten requests of block jb's tiles (and records); `no` block: empty descriptors, which fetch nothing
-  auto fetch_tiles = [&](int jb, int buf, bool no) __attribute__((always_inline)) {
+  const uint32_t vg = static_cast<uint32_t>(16 * (wave & 1) + (lane >> 2)) * (kBlk * 2) + 16 * ((lane ^ (lane >> 4)) & 3);
+  // this wave's ten requests of a block's tiles (and records): C from c (cb bytes), B^T and G number `tile`, and the tenth; `no` block:
+  // empty descriptors, which fetch nothing
+  auto fetch_nine = [&](const uint8_t *c, uint32_t cb, const uint8_t *bt, const uint8_t *g, int buf, bool no) __attribute__((always_inline)) {
     const uint32_t to = lds_at + L::kTiles + buf * L::kTileBuf;
-    const uint8_t *const gt = gb + static_cast<size_t>(jb) * (kBlk * kBlk * 2);
-    load_to_lds4(raw_rsrc(cb + static_cast<size_t>(jb) * kBlk * crow - kEarly, no ? 0 : cbytes - static_cast<uint32_t>(jb) * kBlk * crow + kEarly),
-                 vc[0], vc[1], vc[2], vc[3], to + wave * 4096);
-    load_to_lds4(raw_rsrc(btb + static_cast<size_t>(jb) * (kN * kBlk * 2), no ? 0 : kN * kBlk * 2), vb[0], vb[1], vb[0], vb[1], to + L::kBt + wave * 4096);
-    load_to_lds(raw_rsrc(gt, no ? 0 : kBlk * kBlk * 2), vt, to + L::kGHigh + wave * 1024);
-    load_to_lds(raw_rsrc(fetches_g ? gt : reinterpret_cast<const uint8_t *>(rec_first + static_cast<size_t>(jb) * kRec),
-                         no ? 0 : fetches_g ? kBlk * kBlk * 2u : head_step + static_cast<uint32_t>(sv.nb - jb) * (kRec * 4)),
-                vg, fetches_g ? to + L::kGLow + wave * 1024 : lds_at + L::kRec + buf * L::kRecBuf);
+    load_to_lds4(raw_rsrc(c - kEarly, no ? 0 : cb + kEarly), vc[0], vc[1], vc[2], vc[3], to + wave * 4096);
+    load_to_lds4(raw_rsrc(bt, no ? 0 : kN * kBlk * 2), vb[0], vb[1], vb[0], vb[1], to + L::kBt + wave * 4096);
+    load_to_lds(raw_rsrc(g, no ? 0 : kBlk * kBlk * 2), vt, to + L::kGHigh + wave * 1024);
   };
-  auto fetch_x = [&](int jb, uint32_t xbuf, bool no) __attribute__((always_inline)) {
-    load_to_lds4(raw_rsrc(xb + static_cast<size_t>(jb) * kBlk * xrow - kEarly, no ? 0 : xbytes - static_cast<uint32_t>(jb) * kBlk * xrow + kEarly),
-                 vx[0], vx[1], vx[2], vx[3], lds_at + L::kX + xbuf + wave * 4096);
+  auto fetch_tenth = [&](const uint8_t *g, const uint8_t *rec, uint32_t rec_bytes, uint32_t vr, int buf, bool no) __attribute__((always_inline)) {
+    load_to_lds(raw_rsrc(fetches_g ? g : rec, no ? 0 : fetches_g ? kBlk * kBlk * 2u : rec_bytes), vr,
+                fetches_g ? lds_at + L::kTiles + buf * L::kTileBuf + L::kGLow + wave * 1024 : lds_at + L::kRec + buf * L::kRecBuf);
   };
-  auto y_rsrc = [&](int jb, bool no) { return make_rsrc(yb + static_cast<size_t>(jb) * kBlk * xrow, live && !no ? xbytes - static_cast<uint32_t>(jb) * kBlk * xrow : 0u); };
+  auto fetch_x = [&](const uint8_t *x, uint32_t xb, uint32_t xbuf, bool no) __attribute__((always_inline)) {
+    load_to_lds4(raw_rsrc(x - kEarly, no ? 0 : xb + kEarly), vx[0], vx[1], vx[2], vx[3], lds_at + L::kX + xbuf + wave * 4096);
+  };
 
   auto lds16 = [&](uint32_t at) {
     Operand o;
@@ -1898,7 +2041,7 @@ __device__ __forceinline__ void pair_feed(const ScanParams &p, const SeqView &sv
   auto row_at = [&](int k) {
     return L::kX + wave * 4096 + y_tile * 2048 + (lane >> 5) * 1024 + k * 256 + (((lane >> 3) & 3) ^ 2 * y_tile) * 64 + ((lane & 3) ^ k) * 16;
   };
-  const uint32_t vy = static_cast<uint32_t>(32 * ph + 4 * (lane >> 3)) * xrow + static_cast<uint32_t>(h) * (kP * 2) + 16 * (lane & 7);
+  const uint32_t vy = static_cast<uint32_t>(32 * ph + 4 * (lane >> 3)) * xrow + 16 * (lane & 7);
   u32x4 yo[4];
   auto read_y = [&](uint32_t xbuf) __attribute__((always_inline)) {
 #pragma unroll
@@ -1947,35 +2090,23 @@ __device__ __forceinline__ void pair_feed(const ScanParams &p, const SeqView &sv
         *dst = mk2(pack2(f0 * bf_lo(a0), f1 * bf_lo(a1)), pack2(f2 * bf_lo(a2), f3 * bf_lo(a3)));
     }
   };
-  // ---- prologue: the first block's tiles, input factors and x, the second block's x ----
-  if (jb0 < jb1) {
-    fetch_x(jb0, 0, false);
-    // (the factors of the first block, which every feeder fetches for itself: the records come a block behind them)
-    const uint32_t vf = ((lane & 16) ? head_step : 0u) + kBlk * 4u + 16 * (lane & 15);
-    load_to_lds(raw_rsrc(rec_first + static_cast<size_t>(jb0) * kRec, head_step + static_cast<uint32_t>(sv.nb - jb0) * (kRec * 4)), vf,
-                lds_at + L::kRec + L::kRecBuf);
-    fetch_tiles(jb0, 0, false);
-    fetch_x(min(jb0 + 1, jlast), L::kXBuf, jb0 == jlast);
-    asm volatile("s_waitcnt vmcnt(14)" ::: "memory");  // (tiles and the second block's x)
-    read_turn(0, L::kRecBuf);
-    turn(0);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  }
-  __syncthreads();
-  uint32_t x_prev = 2 * L::kXBuf, x_cur = 0, x_next = L::kXBuf;  // the buffers of blocks jb - 1 (and then jb + 2), jb, jb + 1
-  for (int jb = jb0; jb < jb1; ++jb) {
-    const int rel = jb - jb0;
-    const uint32_t par = rel & 1;
-    const bool more = jb < jlast, more2 = jb + 1 < jlast;
-    const Rsrc ry = y_rsrc(jb - (rel > 0 ? 1 : 0), rel == 0);
+  // One block.  y: where that of the block before is stored; tiles: requests the next block's, x: that of the one after.
+  uint32_t x_prev = 2 * L::kXBuf, x_cur = 0, x_next = L::kXBuf;  // the buffers of the block before (and then of the one after the next), of this, of the next
+  auto block = [&](uint32_t par, bool first, auto &&y, auto &&tiles, auto &&x) __attribute__((always_inline)) {
     read_y(x_prev);
-    fetch_tiles(more ? jb + 1 : jlast, par ^ 1, !more);
-    if constexpr (kYMode == kYAdd) add_y(ry);
+    if (first) __syncthreads();  // an item's first block: its tiles and Xm^T are visible, the other tile buffer is free of states
+    __builtin_amdgcn_sched_barrier(0);  // (requests first: the compiler would put all of the block's addresses before them)
+    tiles(par ^ 1);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (kYMode == kYAdd) add_y(y());
     asm volatile("" : "+v"(yo[0]), "+v"(yo[1]), "+v"(yo[2]), "+v"(yo[3])::"memory");  // (read before x is requested into its place)
     asm volatile("s_waitcnt vmcnt(14)" ::: "memory");  // x of the next block; younger: the stores before, tiles
     read_turn(x_next, par * L::kRecBuf);
-    fetch_x(more2 ? jb + 2 : jlast, x_prev, !more2);
+    x(x_prev);
+    __builtin_amdgcn_sched_barrier(0);
     turn((par ^ 1) * (2 * L::kXmHead));
+    __builtin_amdgcn_sched_barrier(0);
+    const Rsrc ry = y();
 #pragma unroll
     for (int k = 0; k < 4; ++k) store_y(ry, k);
     asm volatile("s_waitcnt vmcnt(8)" ::: "memory");  // the next block's tiles and record; younger: x, stores
@@ -1984,36 +2115,130 @@ __device__ __forceinline__ void pair_feed(const ScanParams &p, const SeqView &sv
     x_prev = x_cur;
     x_cur = x_next;
     x_next = t;
-  }
-  if (jb0 < jb1) {
-    const Rsrc ry = y_rsrc(jlast, false);
+  };
+  auto last_y = [&](Rsrc ry) __attribute__((always_inline)) {
     read_y(x_prev);
     if constexpr (kYMode == kYAdd) add_y(ry);
 #pragma unroll
     for (int k = 0; k < 4; ++k) store_y(ry, k);
+  };
+  // ---- prologue: the first block's tiles, input factors and x, the second block's x ----
+  auto start = [&](const uint8_t *first_factors, uint32_t bytes, uint32_t vf, auto &&x0, auto &&tiles0, auto &&x1) __attribute__((always_inline)) {
+    x0(0);
+    // (the factors of the first block, which every feeder fetches for itself: the records come a block behind them)
+    load_to_lds(raw_rsrc(first_factors, bytes), vf + kBlk * 4 + 16 * (lane & 15), lds_at + L::kRec + L::kRecBuf);
+    tiles0(0);
+    x1(L::kXBuf);
+    asm volatile("s_waitcnt vmcnt(14)" ::: "memory");  // (tiles and the second block's x)
+    read_turn(0, L::kRecBuf);
+    turn(0);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  };
+
+  if constexpr (!kList) {
+    const ItemView v = items.take(p);
+    const int jb0 = v.jb0, jlast = v.jb1 - 1;
+    if (jb0 > jlast) return;
+    Block b;
+    first_block(v, b);
+    const uint8_t *const xb = p.x + b.x_at, *const cb = p.C + b.c_at, *const btb = p.Btr + static_cast<size_t>(b.tile) * (kN * kBlk * 2),
+                  *const gb = p.Gd + static_cast<size_t>(b.tile) * (kBlk * kBlk * 2), *const recb = reinterpret_cast<const uint8_t *>(p.prep + static_cast<size_t>(b.rec0) * kRec);
+    uint8_t *const yb = p.y + b.x_at;
+    const uint32_t head_step = (b.rec1 - b.rec0) * (kRec * 4), vh = (lane & 16) ? head_step : 0u;
+    const uint32_t vr = fetches_g ? vg : vh + (lane < 32 ? (kRec + kBlk) * 4u : 0u) + 16 * (lane & 15);
+    auto tiles_of = [&](int rel, int buf, bool no) __attribute__((always_inline)) {
+      const uint8_t *const g = gb + static_cast<size_t>(rel) * (kBlk * kBlk * 2);
+      fetch_nine(cb + static_cast<size_t>(rel) * kBlk * crow, b.cb - static_cast<uint32_t>(rel) * kBlk * crow, btb + static_cast<size_t>(rel) * (kN * kBlk * 2), g, buf, no);
+      fetch_tenth(g, recb + static_cast<size_t>(rel) * (kRec * 4), head_step + static_cast<uint32_t>(v.nb - jb0 - rel) * (kRec * 4), vr, buf, no);
+    };
+    auto x_of = [&](int rel, uint32_t xbuf, bool no) __attribute__((always_inline)) { fetch_x(xb + static_cast<size_t>(rel) * kBlk * xrow, b.xb - static_cast<uint32_t>(rel) * kBlk * xrow, xbuf, no); };
+    auto y_of = [&](int rel, bool no) { return make_rsrc(yb + static_cast<size_t>(rel) * kBlk * xrow, live && !no ? b.xb - static_cast<uint32_t>(rel) * kBlk * xrow : 0u); };
+    const int last = jlast - jb0;
+    start(recb, head_step + static_cast<uint32_t>(v.nb - jb0) * (kRec * 4), vh, [&](uint32_t to) { x_of(0, to, false); }, [&](int buf) { tiles_of(0, buf, false); },
+          [&](uint32_t to) { x_of(min(1, last), to, last == 0); });
+    __syncthreads();
+    for (int rel = 0; rel <= last; ++rel)
+      block(rel & 1, false, [&]() { return y_of(rel - (rel > 0 ? 1 : 0), rel == 0); }, [&](int buf) { tiles_of(rel < last ? rel + 1 : last, buf, rel >= last); },
+            [&](uint32_t to) { x_of(rel + 1 < last ? rel + 2 : last, to, rel + 1 >= last); });
+    last_y(y_of(last, false));
+  } else {
+    // the blocks of the items, one after the other; `after` is where the requests have got to
+    struct Y {
+      size_t at;
+      uint32_t bytes;
+      bool first;
+    };
+    Block next = {}, after = {};  // the block whose tiles are requested next (or now), the one whose x is
+    int jb = 0, jb1 = 0;
+    auto advance = [&]() __attribute__((always_inline)) {  // `after` to the block after it
+      Y y;
+      y.first = ++jb >= jb1;
+      if (y.first) {
+        do {
+          if (items.next >= items.n) {
+            jb = jb1 = 0;
+            after.xb = after.cb = 0;
+            break;
+          }
+          const ItemView v = items.take(p);
+          jb = v.jb0;
+          jb1 = v.jb1;
+          if (jb < jb1) first_block(v, after);
+        } while (jb >= jb1);
+      } else {
+        after.x_at += kBlk * xrow;
+        after.c_at += kBlk * crow;
+        after.xb -= kBlk * xrow;
+        after.cb -= kBlk * crow;
+        ++after.tile;
+        ++after.rec0;
+        ++after.rec1;
+      }
+      y.at = after.x_at;
+      y.bytes = live ? after.xb : 0;
+      return y;
+    };
+    // the requests of `after`'s tiles, which becomes `next`, and of the input factors of the one after it
+    auto tiles_and_advance = [&](int buf, Y &y) __attribute__((always_inline)) {
+      next = after;
+      const uint8_t *const g = p.Gd + static_cast<size_t>(next.tile) * (kBlk * kBlk * 2);
+      fetch_nine(p.C + next.c_at, next.cb, p.Btr + static_cast<size_t>(next.tile) * (kN * kBlk * 2), g, buf, next.cb == 0);
+      __builtin_amdgcn_sched_barrier(0);
+      y = advance();
+      const uint32_t of_next = (lane & 16 ? next.rec1 : next.rec0) * (kRec * 4), of_after = (lane & 16 ? after.rec1 : after.rec0) * (kRec * 4) + kBlk * 4;
+      fetch_tenth(g, reinterpret_cast<const uint8_t *>(p.prep), p.prep_bytes, fetches_g ? vg : (lane < 32 ? of_after : of_next) + 16 * (lane & 15), buf, next.cb == 0);
+    };
+    auto x_of_after = [&](uint32_t to) __attribute__((always_inline)) { fetch_x(p.x + after.x_at, after.xb, to, after.xb == 0); };
+    Y y_before = {0, 0, false}, y_now = advance(), y_next, y_after;
+    if (after.xb == 0) return;
+    start(reinterpret_cast<const uint8_t *>(p.prep), p.prep_bytes, (lane & 16 ? after.rec1 : after.rec0) * (kRec * 4), x_of_after,
+          [&](int buf) { tiles_and_advance(buf, y_next); }, x_of_after);
+    bool more = true;  // (whether there is a block to compute)
+    for (uint32_t par = 0; more; par ^= 1) {
+      block(par, y_now.first, [&]() { return make_rsrc(p.y + y_before.at, y_before.bytes); }, [&](int buf) { tiles_and_advance(buf, y_after); }, x_of_after);
+      more = next.xb != 0;
+      y_before = y_now;
+      y_now = y_next;
+      y_next = y_after;
+    }
+    last_y(make_rsrc(p.y + y_before.at, y_before.bytes));
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (no request may outlive the workgroup's LDS)
 }
 
-// The computing waves, 0..3: wave w has half w & 1 of headdim of head w / 2.  Returns false, having done nothing, if the common
-// walk meets a steep block.
-template <bool kMixed>
-__device__ __forceinline__ bool pair_walk(const ScanParams &p, const SeqView &sv, lds_u8 *const lds) {
+template <bool kList>
+__device__ void pair_walk_mixed(const ScanParams p, const Deal deal, const ItemView first, int item, uint32_t parity, uint32_t x_cur, lds_u8 *const lds);
+
+// The computing waves, 0..3: wave w has half w & 1 of headdim of head w / 2.  kMixed: some of the items' blocks may be steep.
+// kList: there may be several items; otherwise, and without kMixed, it returns false, having done nothing, if a block is steep.
+template <bool kMixed, bool kList>
+__device__ __forceinline__ void pair_walk(const ScanParams &p, Items<kList> items, uint32_t parity, uint32_t x_cur, lds_u8 *const lds) {
   using L = PairLds;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  const int tid = here(threadIdx.x), lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int hw = wave >> 1, ph = wave & 1;
-  const int g = sv.col / p.cpg, slot = (sv.col % p.cpg) * 2 + hw;
-  const bool live = slot < p.hpg;
-  const int h = g * p.hpg + min(slot, p.hpg - 1);
   const bool plain = p.vp.tok0 == nullptr;
-  const int hrec = h / p.pdiv;
-  const size_t rec0 = plain ? (sv.blk0 * p.Hrec + static_cast<size_t>(hrec) * sv.blk_stride) : (hrec * sv.blk_stride + sv.blk0);
-  const size_t slot0 = plain ? (sv.slot0 * p.H + static_cast<size_t>(h) * sv.slot_stride) : (h * sv.slot_stride + sv.slot0);
-  const size_t bh = static_cast<size_t>(sv.b) * p.H + h;
   const int r = lane & 31, kg = lane >> 5;
-  const int jb0 = min(sv.nb, sv.sg * sv.seg_blocks), jb1 = min(sv.nb, jb0 + sv.seg_blocks), jlast = jb1 - 1;
-  const float *const prep_bh = p.prep + rec0 * kRec;
 
   // ---- LDS addresses of this lane, in bytes ----
   auto lds16 = [&](uint32_t at) {
@@ -2030,76 +2255,94 @@ __device__ __forceinline__ bool pair_walk(const ScanParams &p, const SeqView &sv
   // x and y in output layout: token r (+ 32: 4096 bytes on), columns 16kg + 8c
   const uint32_t a_out = L::kX + hw * 8192 + ph * 2048 + (r >> 4) * 1024 + (r & 3) * 256 + ((r >> 2 & 3) ^ 2 * ph) * 64;
   auto out_at = [&](int c) { return a_out + 16 * ((2 * kg + c) ^ (r & 3)); };
-  // Where a wave turns 32 x 64 elements of its state between the accumulators' layout and whole rows: in the second
-  // tile buffer, before its first tiles are requested and after its last ones have been used.
+  // Where a wave turns 32 x 64 elements of its state between the accumulators' layout and whole rows: in the tile buffer
+  // that the item's first block, whose tiles have arrived, does not have, before the feeders request the second block's tiles into it.
   constexpr int kTurnStride = 64 + 4;  // floats
   static_assert(4 * 32 * kTurnStride * sizeof(float) <= L::kTileBuf, "four turning tiles fit in a tile buffer");
-  lds_as<float> *const turn = (lds_as<float> *)(lds + L::kTiles + L::kTileBuf) + wave * (32 * kTurnStride);
 
-  // ---- prologue: everything it needs from memory is requested before any of it is waited for ----
+  // ---- an item: its head, its blocks, where its record and states are ----
+  int jb0 = 0, jb1 = 0, jlast = 0, h = 0, hrec = 0;
+  bool live = false;
+  ItemView v;
+  const float *prep_bh = p.prep;
+  size_t slot0 = 0, bh = 0;
+  auto to_item = [&]() __attribute__((always_inline)) {
+    v = items.take(p);
+    const int g = quotient(v.col, p.cpg, p.cpg_inv), slot = (v.col - g * p.cpg) * 2 + hw;
+    live = slot < p.hpg;
+    h = g * p.hpg + min(slot, p.hpg - 1);
+    hrec = quotient(h, p.pdiv, p.pdiv_inv);
+    const size_t rec0 = plain ? (static_cast<size_t>(v.blk0) * p.Hrec + static_cast<size_t>(hrec) * p.NB) : (static_cast<size_t>(hrec) * p.vp.nb_cap + v.blk0);
+    slot0 = plain ? (static_cast<size_t>(v.slot0) * p.H + static_cast<size_t>(h) * p.slots) : (static_cast<size_t>(h) * p.vp.slot_cap + v.slot0);
+    bh = static_cast<size_t>(v.b) * p.H + h;
+    jb0 = v.jb0;
+    jb1 = v.jb1;
+    jlast = jb1 - 1;
+    prep_bh = p.prep + rec0 * kRec;
+  };
   auto factor_ptr = [&](int jb) { return prep_bh + static_cast<size_t>(jb) * kRec + 2 * kBlk; };
-  float Dh = p.D == nullptr ? 0.f : p.D[hrec];
+  // {middle -> end, log2 of the total decay, start -> middle, middle -> middle of the next block} of 64 blocks, a lane each
+  f32x4 facv = {0.f, 0.f, 0.f, 0.f};
+  float Dv = 0.f;
+  auto request_factors = [&]() __attribute__((always_inline)) {
+    Dv = p.D == nullptr ? 0.f : p.D[hrec];
+    facv = *reinterpret_cast<const f32x4 *>(jb0 < jb1 ? factor_ptr(min(jb0 + lane_here(), jlast)) : p.prep);
+  };
   u32x4 hraw[16];
-  bool has_state = false;  // uniform over the workgroup
   auto load_state = [&](const float *base, uint32_t row_floats, uint32_t valid) __attribute__((always_inline)) {
     const Rsrc rs = make_rsrc(base != nullptr ? base : p.prep, base != nullptr ? ((kP - 1) * row_floats + valid) * 4u : 0u);
+    const int ln = lane_here();  // (what is computed from it is not kept in registers through the walk)
+    const uint32_t n0 = 4 * (ln & 15), at = ((32 * ph + (ln >> 4)) * row_floats + n0) * 4u;
+    const uint32_t beyond[2] = {n0 < valid ? 0u : 0xC0000000u, n0 + 64 < valid ? 0u : 0xC0000000u};  // (no descriptor covers these)
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      const uint32_t row = 32 * ph + 4 * (k & 7) + (lane >> 4), n0 = 64 * (k >> 3) + 4 * (lane & 15);
-      hraw[k] = buf_load16(rs, n0 < valid ? (row * row_floats + n0) * 4u : 0xFFFFFF00u, 0);
+    for (int k = 0; k < 16; ++k) hraw[k] = buf_load16(rs, (at + 16 * (k & 7) * row_floats + 256 * (k >> 3)) | beyond[k >> 3], 0);
+  };
+  // ---- state slice: Hacc[nt][i] = Ht^T[n = 32nt + (i/8)*16 + 8kg + i%8][headdim column 32 ph + pi_of_row(r)]: the rows of
+  //      B^T are read in the order that leaves eight consecutive state columns in a lane (swap_row), which is how
+  //      C's 16-byte pieces hold them ----
+  f32x16 Hacc[4] = {};
+  auto turn_at = [&]() { return (lds_as<float> *)(lds + L::kTiles + (parity ^ 1) * L::kTileBuf) + wave * (32 * kTurnStride); };
+  auto add_state = [&](float wgt, bool first) __attribute__((always_inline)) {
+    lds_as<float> *const turn = turn_at();
+    const int ln = lane_here();
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        *(lds_as<u32x4> *)(turn + (4 * k + (ln >> 4)) * kTurnStride + 4 * (ln & 15)) = hraw[8 * half + k];
+#pragma unroll
+      for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) {
+          const f32x4 v = *(lds_as<f32x4> *)(turn + pi_of_row(ln & 31) * kTurnStride + 32 * nt + 16 * (i4 >> 1) + 8 * (ln >> 5) + 4 * (i4 & 1));
+#pragma unroll
+          for (int e = 0; e < 4; ++e) Hacc[2 * half + nt][4 * i4 + e] = first ? v[e] : Hacc[2 * half + nt][4 * i4 + e] + wgt * v[e];
+        }
     }
   };
-  {
-    // (a sequence of one segment, and the first of a folded chain, start from h0 itself; see scan_walk)
+  // (a sequence of one segment, and the first of a folded chain, start from h0 itself; see scan_walk)
+  bool has_state = false;  // uniform over the workgroup
+  auto request_state = [&]() __attribute__((always_inline)) {
     const float *hbase = nullptr;
     uint32_t hrow = kN, hvalid = kN;
-    if (sv.S > 1 && !(p.fold && sv.sg == 0)) {
-      hbase = p.Hin + (slot0 + static_cast<size_t>(sv.sg) * p.parts) * (kP * kN);
+    if (v.S > 1 && (kList || !(p.fold && v.sg == 0))) {
+      hbase = p.Hin + (slot0 + static_cast<size_t>(v.sg) * p.parts) * (kP * kN);
     } else if (p.h0 != nullptr) {
       hbase = p.h0 + bh * kP * p.ns.width + p.ns.off;
       hrow = static_cast<uint32_t>(p.ns.width);
       hvalid = static_cast<uint32_t>(p.ns.valid);
     }
     has_state = hbase != nullptr;
-    load_state(hbase, hrow, hvalid);
-  }
-  // {middle -> end, log2 of the total decay, start -> middle, middle -> middle of the next block} of 64 blocks, a lane each
-  f32x4 facv = {0.f, 0.f, 0.f, 0.f};
-  if (jb0 < jb1) {
-    facv = *reinterpret_cast<const f32x4 *>(factor_ptr(min(jb0 + lane, jlast)));
-    if constexpr (!kMixed) {  // whether a block of the walk is steep: its record's entry 130 is negative
-      float lowest = facv.z;
-      for (int j = jb0 + 64; j < jb1; j += 64)
-        if (j + lane < jb1) lowest = fminf(lowest, factor_ptr(j + lane)[2]);
-      if (__builtin_amdgcn_ballot_w64(lowest < 0.f) != 0) return false;
-    }
-  }
-
-  // ---- state slice: Hacc[nt][i] = Ht^T[n = 32nt + (i/8)*16 + 8kg + i%8][headdim column 32 ph + pi_of_row(r)]: the rows of
-  //      B^T are read in the order that leaves eight consecutive state columns in a lane (swap_row), which is how
-  //      C's 16-byte pieces hold them ----
-  f32x16 Hacc[4] = {};
-  auto add_state = [&](float wgt, bool first) __attribute__((always_inline)) {
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-#pragma unroll
-      for (int k = 0; k < 8; ++k)
-        *(lds_as<u32x4> *)(turn + (4 * k + (lane >> 4)) * kTurnStride + 4 * (lane & 15)) = hraw[8 * half + k];
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4) {
-          const f32x4 v = *(lds_as<f32x4> *)(turn + pi_of_row(r) * kTurnStride + 32 * nt + 16 * (i4 >> 1) + 8 * kg + 4 * (i4 & 1));
-#pragma unroll
-          for (int e = 0; e < 4; ++e) Hacc[2 * half + nt][4 * i4 + e] = first ? v[e] : Hacc[2 * half + nt][4 * i4 + e] + wgt * v[e];
-        }
-    }
+    if (kList && !has_state) return;
+    load_state(hbase, hrow, hvalid);  // (one item: without a branch, at whose end the compiler would wait)
+    if constexpr (kList) add_state(1.f, true);
   };
-  if (has_state) {
+  auto enter_state = [&]() __attribute__((always_inline)) {
+    if (!has_state) return;
     add_state(1.f, true);
-    if (p.fold && sv.sg >= 1) {  // (the earlier pieces' local end states and h0, see scan_walk)
+    if (p.fold && v.sg >= 1) {  // (the earlier pieces' local end states and h0, see scan_walk)
       float log2_decay = 0.f;
-      for (int k = sv.sg * p.parts - 1; k >= 0; --k) {
+      for (int k = v.sg * p.parts - 1; k >= 0; --k) {
         log2_decay += p.seg_decay[slot0 + k];
         if (k == 0 && p.h0 == nullptr) break;
         load_state(k > 0 ? p.Hin + (slot0 + k) * (kP * kN) : p.h0 + bh * kP * p.ns.width + p.ns.off,
@@ -2107,31 +2350,20 @@ __device__ __forceinline__ bool pair_walk(const ScanParams &p, const SeqView &sv
         add_state(fast_exp2(log2_decay), false);
       }
     }
-  }
+  };
   float pending = 1.f;  // as in scan_walk: what the accumulators are still owed
+  float Dh = 0.f;
+  float fac = 0.f;      // of 64 blocks, a lane each: to the middle of the next, of the last block to its end
   bool steep_cur = false;
-  auto of_block = [&](float v, int rel) { return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), rel & 63)); };
-  if (jb0 < jb1) {
-    pending = of_block(facv.z, 0);
-    if constexpr (kMixed) {
-      steep_cur = __float_as_int(pending) < 0;
-      if (steep_cur) pending = 1.f;
-    }
-  }
-
-  wait_all_loads();
-  // (pinned as arrived: the waits for them would otherwise stand at their first use in the loop)
-  asm volatile("" : "+v"(Dh), "+v"(facv)::"memory");
-  __syncthreads();
+  auto of_block = [&](float f, int rel) { return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(f), rel & 63)); };
 
   // One block; par: the parity of its number in the walk (a compile-time constant), which is that of its buffers but x's.
-  uint32_t x_cur = 0;
   auto body = [&](int par, int jb, auto steep_tag) __attribute__((always_inline)) {
     constexpr bool kSteep = decltype(steep_tag)::value;
     static_assert(kMixed || !kSteep, "a steep block is only met in the mixed walk");
     const int rel = jb - jb0;
     const uint32_t tile = par * L::kTileBuf, rec = L::kRec + par * L::kRecBuf, xm = par * (2 * L::kXmHead);
-    const bool more = jb < jlast;
+    [[maybe_unused]] const bool more = jb < jlast;
 
     // ---- phase 1: Y^T[row][l] = sum_n Ht[row][n] C[l][n]  +  sum_{s<=l} Xm[s][row] G[l][s] ----
     Operand co[3][2], go0[2], go1[4], xo[4], bto[2][4], xe[4];
@@ -2277,8 +2509,8 @@ __device__ __forceinline__ bool pair_walk(const ScanParams &p, const SeqView &sv
     }
     // as in scan_walk: from the middle of this block (steep: from its end) to the middle of the next, to its start
     // if that one is steep; after the last block only the way to its end is left
-    const float to_next = of_block(facv.w, rel), to_end = of_block(facv.x, rel);
     if constexpr (kMixed) {
+      const float to_next = of_block(facv.w, rel), to_end = of_block(facv.x, rel);
       const float nf = (rel & 63) < 63 ? of_block(facv.z, rel + 1) : __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(factor_ptr(more ? jb + 1 : jlast)[2])));
       const bool next_steep = more && __float_as_int(nf) < 0;
       if constexpr (kSteep)
@@ -2287,7 +2519,7 @@ __device__ __forceinline__ bool pair_walk(const ScanParams &p, const SeqView &sv
         pending = more && !next_steep ? to_next : to_end;
       steep_cur = next_steep;
     } else {
-      pending = more ? to_next : to_end;
+      pending = of_block(fac, rel);
     }
     x_cur = x_cur == 2 * L::kXBuf ? 0 : x_cur + L::kXBuf;
     __syncthreads();  // the next block's tiles are visible, this block's may be overwritten, its y read
@@ -2301,23 +2533,14 @@ __device__ __forceinline__ bool pair_walk(const ScanParams &p, const SeqView &sv
     }
     body(par, jb, std::false_type{});
   };
-  for (int first = jb0; first < jb1; first += 64) {
-    if (first > jb0) {
-      facv = *reinterpret_cast<const f32x4 *>(factor_ptr(min(first + lane, jlast)));
-      asm volatile("" : "+v"(facv));
-    }
-    const int last = min(first + 64, jb1);
-    int jb = first;
-    for (; jb + 1 < last; jb += 2) {
-      step(0, jb);
-      step(1, jb + 1);
-    }
-    if (jb < last) step(0, jb);
-  }
   // ---- the final state, four consecutive n per 16-byte store ----
-  if (sv.sg == sv.S - 1 && live) {
-    float *const rows = p.final_state + (bh * kP + 32 * ph) * p.ns.width + p.ns.off;
-    const int valid = p.ns.valid;
+  auto store_state = [&](float *const rows) __attribute__((always_inline)) {
+    lds_as<float> *const turn = turn_at();
+    const int ln = lane_here();
+    // (by descriptor, so that the number of stores, behind which what the next item needs is waited for, is known)
+    const Rsrc rs = make_rsrc(rows, (31u * p.ns.width + p.ns.valid) * 4u);
+    const uint32_t n0 = 4 * (ln & 15), at = ((ln >> 4) * static_cast<uint32_t>(p.ns.width) + n0) * 4u;
+    const uint32_t beyond[2] = {n0 < static_cast<uint32_t>(p.ns.valid) ? 0u : 0xC0000000u, n0 + 64 < static_cast<uint32_t>(p.ns.valid) ? 0u : 0xC0000000u};
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
 #pragma unroll
@@ -2325,23 +2548,92 @@ __device__ __forceinline__ bool pair_walk(const ScanParams &p, const SeqView &sv
 #pragma unroll
         for (int i4 = 0; i4 < 4; ++i4) {
           const f32x16 &t = Hacc[2 * half + nt];
-          *(lds_as<f32x4> *)(turn + pi_of_row(r) * kTurnStride + 32 * nt + 16 * (i4 >> 1) + 8 * kg + 4 * (i4 & 1)) =
+          *(lds_as<f32x4> *)(turn + pi_of_row(ln & 31) * kTurnStride + 32 * nt + 16 * (i4 >> 1) + 8 * (ln >> 5) + 4 * (i4 & 1)) =
               f32x4{t[4 * i4 + 0], t[4 * i4 + 1], t[4 * i4 + 2], t[4 * i4 + 3]} * pending;
         }
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const int row = 4 * k + (lane >> 4), n0 = 64 * half + 4 * (lane & 15);
-        if (n0 < valid)
-          *reinterpret_cast<f32x4 *>(rows + static_cast<size_t>(row) * p.ns.width + n0) =
-              *(lds_as<f32x4> *)(turn + row * kTurnStride + 4 * (lane & 15));
+      for (int k = 0; k < 8; ++k)
+        buf_store16(rs, (at + 16 * k * static_cast<uint32_t>(p.ns.width) + 256 * half) | beyond[half], *(lds_as<u32x4> *)(turn + (4 * k + (ln >> 4)) * kTurnStride + 4 * (ln & 15)));
+    }
+  };
+
+  to_item();
+  if constexpr (!kList) request_state();
+  request_factors();
+  for (;;) {
+    if constexpr (!kMixed) {  // a block of the item is steep (its record's entry 130 is negative): the rest of the walk is mixed
+      float lowest = jb0 < jb1 ? facv.z : 1.f;
+      for (int j = jb0 + 64; j < jb1; j += 64)
+        if (j + lane < jb1) lowest = fminf(lowest, factor_ptr(j + lane)[2]);
+      if (__builtin_amdgcn_ballot_w64(lowest < 0.f) != 0) {
+        pair_walk_mixed<kList>(p, items.deal, v, items.next - 1, parity, x_cur, lds);
+        __builtin_amdgcn_endpgm();  // (so that nothing has to be kept over the call)
       }
     }
+    if constexpr (kList) {
+#pragma unroll
+      for (int nt = 0; nt < 4; ++nt) Hacc[nt] = f32x16{};
+      request_state();
+    } else {
+      enter_state();
+    }
+    Dh = Dv;
+    pending = 1.f;
+    if (jb0 < jb1) {
+      pending = of_block(facv.z, 0);
+      if constexpr (kMixed) {
+        steep_cur = __float_as_int(pending) < 0;
+        if (steep_cur) pending = 1.f;
+      }
+      __syncthreads();  // the first block's tiles are visible; the feeders may request the second's
+    }
+    for (int first = jb0; first < jb1; first += 64) {
+      if (first > jb0) facv = *reinterpret_cast<const f32x4 *>(factor_ptr(min(first + lane_here(), jlast)));
+      const int last = min(first + 64, jb1);
+      if constexpr (!kMixed) {
+        fac = first + lane_here() < jlast ? facv.w : facv.x;
+        asm volatile("" : "+v"(fac));
+      }
+      int jb = first;
+      if (kList && parity != 0) step(1, jb++);  // (otherwise every walk of 64 starts in the first buffer)
+      for (; jb + 1 < last; jb += 2) {
+        step(0, jb);
+        step(1, jb + 1);
+      }
+      parity = 0;
+      if (jb < last) {
+        step(0, jb);
+        parity = 1;
+      }
+    }
+    // ---- its last state, and what the next item needs from memory ----
+    const bool stores = v.sg == v.S - 1 && live;
+    float *const rows = p.final_state + (bh * kP + 32 * ph) * p.ns.width + p.ns.off;
+    const bool more = kList && items.next < items.n;
+    if (more) {
+      to_item();
+      request_factors();
+    }
+    // (the factors' arrival is waited for here, where the stores behind their request can be counted)
+    if (stores) {
+      store_state(rows);
+      asm volatile("" : "+v"(facv), "+v"(Dv)::"memory");
+    } else {
+      asm volatile("" : "+v"(facv), "+v"(Dv)::"memory");
+    }
+    if (!more) return;
   }
-  return true;
 }
 
-__device__ __attribute__((noinline)) void pair_walk_mixed(const ScanParams p, const SeqView sv, lds_u8 *const lds) {
-  (void)pair_walk<true>(p, sv, lds);
+template <bool kList>
+__device__ __attribute__((noinline)) void pair_walk_mixed(const ScanParams p, const Deal deal, const ItemView first, int item, uint32_t parity, uint32_t x_cur,
+                                                          lds_u8 *const lds) {
+  const Deal d = {static_cast<int>(uniform32(deal.n_full)), static_cast<int>(uniform32(deal.n_mine)), static_cast<int>(uniform32(deal.place)),
+                  static_cast<int>(uniform32(deal.seg_blocks))};
+  if constexpr (kList)
+    pair_walk<true, true>(p, Items<true>(p, d, uniform32(item)), uniform32(parity), uniform32(x_cur), lds);
+  else
+    pair_walk<true, false>(p, Items<false>(d, first), 0, 0, lds);
 }
 
 template <bool kStatesOnly, int HPW, int kYMode = kYPlain>
@@ -2368,16 +2660,27 @@ __global__ __launch_bounds__(128 * HPW) __attribute__((amdgpu_waves_per_eu(2, 2)
   scan_walk<kStatesOnly, HPW, kYMode, false>(p, sv, lds);
 }
 
-template <int kYMode>
+// kList: a packed batch, as many workgroups as CUs, each with the items that it is dealt; otherwise an item each.
+// (the two roles, and the two walks, pass the same barriers, block for block; waves of one workgroup may take different walks)
+template <int kYMode, bool kList>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void pair_scan_kernel(const ScanParams p) {
-  __shared__ __align__(1024) uint8_t lds[PairLds::kBytes];
-  SeqView sv;
-  if (!wg_coords(p, true, sv)) return;  // uniform over the workgroup
-  // (the two roles, and the two walks, pass the same barriers, block for block)
-  if (threadIdx.x >= 256)
-    pair_feed<kYMode>(p, sv, (lds_u8 *)lds);
-  else if (!pair_walk<false>(p, sv, (lds_u8 *)lds))
-    pair_walk_mixed(p, sv, (lds_u8 *)lds);
+  __shared__ __align__(1024) uint8_t lds_bytes[PairLds::kBytes];
+  lds_u8 *const lds = (lds_u8 *)lds_bytes;
+  const bool feeds = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x)) >= 256;  // (uniform, and known to be)
+  auto run = [&](const Items<kList> &items) __attribute__((always_inline)) {
+    if (feeds)
+      pair_feed<kYMode, kList>(p, items, lds);
+    else
+      pair_walk<false, kList>(p, items, 0, 0, lds);
+  };
+  if constexpr (kList) {
+    const Deal deal = deal_of(p);
+    if (deal.n_mine > 0) run(Items<true>(p, deal, 0));
+  } else {
+    ItemView first;
+    Deal deal = {0, 1, 0, 0};
+    if (one_item(p, deal.seg_blocks, first)) run(Items<false>(deal, first));
+  }
 }
 
 // ---- segment_pass: slot[0] = h0; slot[sg] = exp2(decay[sg-1]) * slot[sg-1] + local[sg-1] --------
@@ -2663,6 +2966,8 @@ int list_items(const Dims &d, const Layout &w, int seg_blocks) { return d.Bt + f
 // How a call is cut up: blocks per segment, segments per sequence (0 for a packed batch, where the
 // device-side tables hold them per sequence), pieces per segment of the states-only pass, and whether the
 // full scan sums the chain over state slots itself (ScanParams::fold).
+// Whether the two-head scan can be used: it addresses the decay records by 32-bit offsets.
+bool two_possible(const Layout &w) { return w.off_state - w.off_prep < 0xFFFF0000ull; }
 bool packed_uncut(const Dims &d, const SlicePlan &pl);
 bool packed_two(const Dims &d);
 SlicePlan plan_slice(const Dims &d, bool varlen, bool h0_aliases_final_state) {
@@ -2672,10 +2977,11 @@ SlicePlan plan_slice(const Dims &d, bool varlen, bool h0_aliases_final_state) {
   SlicePlan pl;
   const Knobs &kn = knobs();
   pl.two = 0;
-  pl.heads = pl.state_heads = kn.scan_heads == 2 ? 2 : kHeadsPerWg;
+  pl.state_heads = kn.scan_heads == 2 ? 2 : kHeadsPerWg;
+  pl.heads = two_possible(w) ? pl.state_heads : kHeadsPerWg;
   // two heads per workgroup (see small_grid)
   const bool may_choose = kn.scan_heads == 0 && kn.seg_chunks == 0 && kn.seg_blocks == 0 && kn.seg_parts == 0;
-  const bool may_two = kn.scan_heads == 0;
+  const bool may_two = kn.scan_heads == 0 && two_possible(w);
   int two_parts = 1;
   const int two = !varlen && may_choose && may_two ? two_head_blocks(d, (w.NB + w.S_max - 1) / w.S_max, w.S_max, &two_parts) : 0;
   // shortest segment: a chunk for a packed batch; what the state slots allow for a plain one
@@ -2698,6 +3004,10 @@ SlicePlan plan_slice(const Dims &d, bool varlen, bool h0_aliases_final_state) {
   // (the lengths of several sequences are known on the device only; see segment_choice)
   pl.from_lengths = varlen && d.Bt > 1 && d.Bt <= kTableThreads && w.NB <= kTableBlocks && list_items(d, w, pl.seg_blocks) <= kTableBlocks &&
                     kn.seg_chunks == 0 && kn.seg_blocks == 0 && full_items(d, w, pl.seg_blocks) > 0;
+  // Items are dealt where the sequences alone are more than a round of workgroups of two heads (of 120 drawn batches those need 0.87 of
+  // the time of an entry to a workgroup, with two or four heads; 1.06 at worst).  Up to a round dealing has nothing to even out
+  // and its walk costs 1 to 8 %.
+  pl.listed = varlen && two_possible(w) && (kn.deal == 1 || (may_two && kn.deal == 0 && static_cast<long>(d.Bt) * head_groups(d, 2) > kNumCUs));
   if (pl.from_lengths) {
     if (may_two && packed_two(d)) pl.heads = pl.state_heads = 2;
     if (packed_uncut(d, pl)) {
@@ -2733,8 +3043,10 @@ SegChoice segment_choice(const Dims &d, const SlicePlan &pl) {
     c.cand[c.count++] = next > last ? (next < nblocks ? next : nblocks) : last + 1;
   }
   c.heads = pl.heads;
-  const int groups = head_groups(d, pl.heads);
-  c.max_items = pl.heads == 2 ? kNumCUs / groups : 0x7fffffff;
+  c.dealt = pl.listed;
+  const int groups = head_groups(d, pl.listed ? 2 : pl.heads);
+  c.max_items = pl.heads == 2 && !pl.listed ? kNumCUs / groups : 0x7fffffff;
+  c.state_fill = static_cast<float>(head_groups(d, pl.state_heads)) / kNumCUs;
   c.fill = static_cast<float>(groups) / kNumCUs;
   c.slices = static_cast<float>(d.H) * (d.P / kP);
   return c;
@@ -2784,6 +3096,10 @@ void map_to(ScanParams &p, int heads, int segs, int items) {
   p.segs = segs;
   p.total = p.cols * items;
   p.per_xcd = (p.total + kXcds - 1) / kXcds;
+  p.cpg_inv = inverse_of(p.cpg);
+  p.pdiv_inv = inverse_of(p.pdiv);
+  p.cols_inv = inverse_of(p.cols);
+  p.segs_inv = inverse_of(segs > 0 ? segs : 1);
 }
 
 hipError_t launch_slice(const Dims &d, const NSlice ns, const int32_t *cu, const void *x, const float *dt,
@@ -2839,6 +3155,7 @@ hipError_t launch_slice(const Dims &d, const NSlice ns, const int32_t *cu, const
   p.Gd = reinterpret_cast<const uint8_t *>(Gd);
   p.Btr = reinterpret_cast<const uint8_t *>(Btr);
   p.prep = prep;
+  p.prep_bytes = static_cast<uint32_t>(w.off_state - w.off_prep);
   p.y = static_cast<uint8_t *>(y);
   p.h0 = h0;
   p.Hin = seg_state;
@@ -2880,15 +3197,15 @@ hipError_t launch_slice(const Dims &d, const NSlice ns, const int32_t *cu, const
                          dim3(kThreads), 0, stream, seg_state, seg_decay, h0, p.slots, Hs, rows_bh, vp, ns);
     if (!p.fold) trace_mark(trace, stream, "segment_pass");
   }
-  map_to(p, pl.heads, S, varlen ? items : S * d.Bt);
-  const dim3 grid(kXcds * p.per_xcd), block(128 * pl.heads);
-  if (pl.heads == 2) {
-    if (add_to_y)
-      hipLaunchKernelGGL(pair_scan_kernel<kYAdd>, grid, dim3(512), 0, stream, p);
-    else if (stream_y(d, rows))
-      hipLaunchKernelGGL(pair_scan_kernel<kYStream>, grid, dim3(512), 0, stream, p);
-    else
-      hipLaunchKernelGGL(pair_scan_kernel<kYPlain>, grid, dim3(512), 0, stream, p);
+  const int scan_heads = pl.listed ? 2 : pl.heads;
+  map_to(p, scan_heads, S, varlen ? items : S * d.Bt);
+  const bool lists = pl.listed;
+  const dim3 grid(lists ? kNumCUs : kXcds * p.per_xcd), block(128 * scan_heads);
+  if (scan_heads == 2) {
+    auto *const kernel = add_to_y ? (lists ? pair_scan_kernel<kYAdd, true> : pair_scan_kernel<kYAdd, false>)
+                         : stream_y(d, rows) ? (lists ? pair_scan_kernel<kYStream, true> : pair_scan_kernel<kYStream, false>)
+                                             : (lists ? pair_scan_kernel<kYPlain, true> : pair_scan_kernel<kYPlain, false>);
+    hipLaunchKernelGGL(kernel, grid, dim3(512), 0, stream, p);
   } else if (add_to_y) {
     hipLaunchKernelGGL((chunk_scan_kernel<false, kHeadsPerWg, kYAdd>), grid, block, 0, stream, p);
   } else if (stream_y(d, rows)) {
@@ -2962,22 +3279,24 @@ SlicePlan mfma_varlen_plan(const Dims &d_in, const int32_t *cu) {
   SlicePlan pl = plan_slice(d, true, false);
   const SegChoice c = segment_choice(d, pl);
   pl.shortest = pl.seg_blocks;
-  float best = 0.f;
+  float cost[SegChoice::kMost], best = 0.f;
+  int items[SegChoice::kMost];
   for (int k = 0; k < c.count; ++k) {
-    int items = 0, longest = 0, blocks = 0;
+    int longest = 0, blocks = 0;
+    items[k] = 0;
     for (int q = 0; q < d.Bt; ++q) {
       const int n = (cu[q + 1] - cu[q] + kBlk - 1) / kBlk;
-      items += n > c.cand[k] ? (n + c.cand[k] - 1) / c.cand[k] : 1;
+      items[k] += n > c.cand[k] ? (n + c.cand[k] - 1) / c.cand[k] : 1;
       longest = n > longest ? n : longest;
       blocks += n;
     }
-    const float us = c.count > 1 ? packed_cost(c, c.cand[k], blocks, longest, d.Bt, items) : 0.f;
-    if (k == 0 || us < best) {
-      best = us;
-      pl.seg_blocks = c.cand[k];
-      pl.segments = items;
-    }
+    cost[k] = c.count > 1 ? packed_cost(c, c.cand[k], blocks, longest, d.Bt, items[k]) : 0.f;
+    if (k == 0 || cost[k] < best) best = cost[k];
   }
+  int k = 0;
+  while (cost[k] > (c.dealt ? kDealtMargin : 1.f) * best) ++k;
+  pl.seg_blocks = c.cand[k];
+  pl.segments = items[k];
   return pl;
 }
 

@@ -457,7 +457,7 @@ def ssd_conv1d_step(conv_state, u, weight, bias=None, split=None, activation="si
 
 
 KNOBS = {"force_generic": 0, "seg_chunks": 1, "seg_blocks": 2, "seg_parts": 3, "y_stream": 4, "decode_stream": 5,
-         "force_mfma_f32": 6, "f32_segments": 7, "fold_max_slots": 8, "scan_heads": 9, "chunk": 10}
+         "force_mfma_f32": 6, "f32_segments": 7, "fold_max_slots": 8, "scan_heads": 9, "chunk": 10, "deal": 11}
 
 
 def set_knob(name: str, value: int) -> None:
@@ -511,5 +511,5 @@ def varlen_plan(lengths, nheads, headdim, dstate, ngroups, chunk, io_dtype=torch
     st = _lib.ssd_testing_varlen_plan(ctypes.byref(shape), cu, out)
     if st != SSD_OK:
         raise SSDError(st, "ssd_testing_varlen_plan")
-    return dict(mfma=bool(out[0]), seg_blocks=out[1], items=out[2], shortest=out[3], chosen=bool(out[4]), heads=out[6],
+    return dict(mfma=bool(out[0]), seg_blocks=out[1], items=out[2], shortest=out[3], chosen=bool(out[4]), dealt=bool(out[5]), heads=out[6],
                 state_heads=out[7])
