@@ -10,6 +10,14 @@
 
 namespace ssd {
 
+// n / d of scalars by a multiplication with (2^32 - 1) / d, which falls short by one at most.  The start of every workgroup is
+// a few such divisions, of 20 to 30 dependent instructions otherwise.
+__device__ __forceinline__ int quotient(int n, int d, uint32_t inv) {
+  const int q = static_cast<int>(__umulhi(static_cast<uint32_t>(n), inv));
+  return q + (n - q * d >= d ? 1 : 0);
+}
+inline uint32_t inverse_of(int d) { return 0xFFFFFFFFu / static_cast<uint32_t>(d); }
+
 // Optional map from the caller's dt values to the step size (section "Mapping SSD onto JAX
 // primitives" lists softplus and clip among the elementwise neighbours that must fuse with the
 // decay computation): dt = clamp(softplus(raw + bias[h]), lo, hi).  Default: dt is used as given.

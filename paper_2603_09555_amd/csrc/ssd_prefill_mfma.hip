@@ -785,14 +785,6 @@ struct ScanParams {
   VarPlan vp;              // tok0 == nullptr: plain batch
 };
 
-// n / d of scalars by a multiplication with (2^32 - 1) / d, which falls short by one at most.  The start of every workgroup is
-// a few such divisions, of 20 to 30 dependent instructions otherwise.
-__device__ __forceinline__ int quotient(int n, int d, uint32_t inv) {
-  const int q = static_cast<int>(__umulhi(static_cast<uint32_t>(n), inv));
-  return q + (n - q * d >= d ? 1 : 0);
-}
-inline uint32_t inverse_of(int d) { return 0xFFFFFFFFu / static_cast<uint32_t>(d); }
-
 // Where a workgroup works: head group `col`, segment `sg` of `S` of sequence `b`, whose `nb` blocks
 // start at token `tok0` of the packed token axis (`len` tokens), at workspace tile / record number
 // `blk0` (per group / per head: stride `blk_stride`), and whose state slots (one per segment, per

@@ -61,6 +61,7 @@ struct SplitParams {
   float *decay;                    // decay: log2 of every segment's total decay, [batch row][head][segment]
   int T, H, P, N, G, Bt, hpg;
   int nslice, cpg;               // slices per group; workgroups per group
+  uint32_t S_inv, cpg_inv, rows_inv, G_inv, per_head_inv, sub_inv;  // for quotient(); rows: Bt * G, per head: P / 32
   int S;                         // segments per sequence; segment s begins at block segment_begin(s)
   int sub, sub_blocks;           // S = 1: workgroups that share the sequence, output blocks of each
   int slot0;                     // the first segment starts from its slot in y, not from h0 (which final_state aliases)
@@ -68,15 +69,18 @@ struct SplitParams {
   int dt_plain;                    // the step sizes are used as given
 };
 
-__host__ __device__ __forceinline__ int segment_begin(int s, int S, int nblocks) {
-  return static_cast<int>(static_cast<long long>(s) * nblocks / S);
+inline int segment_begin(int s, int S, int nblocks) { return static_cast<int>(static_cast<long long>(s) * nblocks / S); }
+// (A division of 64 bits is some hundred instructions, and the pass over the states had two per segment: 8.3 -> 6.8 us at 2048
+// tokens x 24 heads in 16 segments.  The product is below 2^31, see split_plan.)
+__device__ __forceinline__ int segment_begin(int s, const SplitParams &p, int nblocks) {
+  return quotient(static_cast<uint32_t>(s) * static_cast<uint32_t>(nblocks), p.S, p.S_inv);
 }
 // The state slice of (batch row b, head h, columns p0 ..) that enters segment s: 32 rows (headdim) of NT pieces of 32
 // floats.  In the workspace they lie as in any state; in y, piece (c, nt) is the 32 columns of y's row number c NT + nt
 // of the segment.
 __device__ __forceinline__ float *state_slot(const SplitParams &p, int b, int h, int p0, int s, int nblocks) {
   if (p.slots != nullptr) return p.slots + (((static_cast<size_t>(b) * p.H + h) * p.S + s) * p.P + p0) * p.N;
-  const size_t tok = static_cast<size_t>(b) * p.T + static_cast<size_t>(segment_begin(s, p.S, nblocks)) * kTok;
+  const size_t tok = static_cast<size_t>(b) * p.T + static_cast<size_t>(segment_begin(s, p, nblocks)) * kTok;
   return p.y + (tok * p.H + h) * p.P + p0;
 }
 
@@ -118,12 +122,13 @@ __global__ __launch_bounds__(kThr, 2) void split_f32_kernel(const SplitParams p)
   float *const sG = reinterpret_cast<float *>(smem + L::kBC + L::kX);                     // scores [l][s]
 
   // ---- which slice, segment and blocks ----
-  const int col = blockIdx.x % p.cpg;
-  const int bg = (blockIdx.x / p.cpg) % (p.Bt * p.G), piece = blockIdx.x / p.cpg / (p.Bt * p.G);
-  const int g = bg % p.G, b = bg / p.G;
-  const int seg = kStatesOnly ? piece : piece / p.sub, part = kStatesOnly ? 0 : piece % p.sub;
+  const int wg = blockIdx.x;
+  const int item = quotient(wg, p.cpg, p.cpg_inv), col = wg - item * p.cpg;
+  const int piece = quotient(item, p.Bt * p.G, p.rows_inv), bg = item - piece * (p.Bt * p.G);
+  const int b = quotient(bg, p.G, p.G_inv), g = bg - b * p.G;
+  const int seg = kStatesOnly ? piece : quotient(piece, p.sub, p.sub_inv), part = kStatesOnly ? 0 : piece - seg * p.sub;
   const int nblocks = (p.T + kTok - 1) / kTok;
-  const int j0 = segment_begin(seg, p.S, nblocks), jend = segment_begin(seg + 1, p.S, nblocks);
+  const int j0 = segment_begin(seg, p, nblocks), jend = segment_begin(seg + 1, p, nblocks);
   // the state alone over [j0, j1), everything over [j1, j2)
   const int j1 = kStatesOnly ? jend : min(jend, j0 + part * p.sub_blocks);
   const int j2 = kStatesOnly ? jend : min(jend, j1 + p.sub_blocks);
@@ -133,7 +138,8 @@ __global__ __launch_bounds__(kThr, 2) void split_f32_kernel(const SplitParams p)
   const bool live = slice_raw < p.nslice;  // (a wave without a slice repeats the last one and stores nothing)
   const int slice = live ? slice_raw : p.nslice - 1;
   const int per_head = p.P / kCols;
-  const int h = g * p.hpg + slice / per_head, p0 = kCols * (slice % per_head);
+  const int in_group = quotient(slice, per_head, p.per_head_inv);
+  const int h = g * p.hpg + in_group, p0 = kCols * (slice - in_group * per_head);
   const size_t bh = static_cast<size_t>(b) * p.H + h;
   const float alog = p.A[h] * kLog2e;
   const float Dh = p.D[h];
@@ -529,7 +535,7 @@ static SplitPlan split_plan(const Dims &d) {
   SplitPlan pl = {1, 1, nblocks, 8.0 + 0.5 * NT + rounds_us(wgs, nblocks * kFullUs[NT - 1])};
   if (ks > 0) {
     pl.segments = (nblocks + ks - 1) / ks;
-    while (pl.segments > 1 && !segments_fit(d, pl.segments)) --pl.segments;
+    while (pl.segments > 1 && (!segments_fit(d, pl.segments) || static_cast<long long>(pl.segments) * nblocks > 0x7FFFFFFFll)) --pl.segments;
     pl.sub = kp > 0 && pl.segments == 1 ? kp : 1;
     pl.sub_blocks = (nblocks + pl.sub - 1) / pl.sub;
     return pl;
@@ -638,6 +644,12 @@ hipError_t launch_prefill_split_f32(const Dims &d, const void *x, const float *d
   p.S = pl.segments;
   p.sub = pl.sub;
   p.sub_blocks = pl.sub_blocks;
+  p.S_inv = inverse_of(p.S);
+  p.cpg_inv = inverse_of(p.cpg);
+  p.rows_inv = inverse_of(d.Bt * d.G);
+  p.G_inv = inverse_of(d.G);
+  p.per_head_inv = inverse_of(d.P / kCols);
+  p.sub_inv = inverse_of(p.sub);
   p.dtx = d.dtx;
   p.dt_plain = d.dtx.identity();
   const size_t state_bytes = static_cast<size_t>(d.Bt) * d.H * d.P * d.N * sizeof(float);
@@ -647,6 +659,7 @@ hipError_t launch_prefill_split_f32(const Dims &d, const void *x, const float *d
   if (aliases && p.S == 1) {  // the workgroup that stores the final state must be the one that reads h0
     p.sub = 1;
     p.sub_blocks = (d.T + kTok - 1) / kTok;
+    p.sub_inv = inverse_of(1);
   }
   const unsigned wgs = static_cast<unsigned>(d.Bt) * d.G * p.cpg;
   switch ((d.N + 31) / 32) {
