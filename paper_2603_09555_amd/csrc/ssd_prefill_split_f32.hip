@@ -26,13 +26,17 @@
 // columns.  A segment then has at least as many tokens as a state slice has 128-byte pieces.
 // With one segment only the full launch runs; `sub` workgroups may then share the sequence, each first carrying the
 // state over the blocks of the ones before it (a third of a block's work, no output).
+// Where the states-only launch leaves CUs idle, workgroups of their own split B and C there and form the scores, once for all
+// heads (make_image); the full launch then copies a block's image to LDS.
 // Bound: issue.  A block of four slices takes 5.2 us where one workgroup has the chip, 7.3 with one per CU, 10.3 with two
 // each (dstate 128); the matrix instructions are 1.6 of it (3840 cycles a wave), about 1150 vector instructions a wave
-// (the splits: 700) come between them.  Two waves per slice (half of dstate each, outputs summed through LDS) were 6 %
+// (the splits: 700) come between them.  One wave on a SIMD issues a vector instruction every 5 cycles and they hardly overlap with
+// the matrix instructions (eight of them and one of those: 59 cycles, 32 by itself; 49 with two waves), so that operands
+// read from LDS a step ahead changed nothing.  Of a block's 12900 cycles staging was 2700, the scores 1000; 11100 with images.  Two waves per slice (half of dstate each, outputs summed through LDS) were 6 %
 // faster alone and half as fast for two; matrix and vector instructions interleaved by hand or by scheduling groups 15 %
 // slower and more (spills).
 // Measured against the fp32 matrix instruction kernel (ssd_prefill_mfma_f32.hip), us: 2048 tokens x 24 heads x 64 x 128
-// 108.7 / 52.3 (13 of it the chain and the gaps), 8 such prompts 504 / 191, 3 x 2428 x 20 190 / 90, 2 x 3593 x 11 x 64 x
+// 108.7 / 49.0 (12 of it the chain and the gaps), 8 such prompts 504 / 191, 3 x 2428 x 20 190 / 90, 2 x 3593 x 11 x 64 x
 // 16 70 / 43, 4096 x 4 x 32 x 16 55 / 37; final state against 64 bits 1.4e-7 / 9.5e-8, y
 // 2.6e-8 both.  Of it the checks for values out of range take 1 us of the first, the leading parts rounded instead of cut
 // off 0.7, the mask's sums in two parts 0.3.
@@ -61,9 +65,10 @@ struct SplitParams {
   float *decay;                    // decay: log2 of every segment's total decay, [batch row][head][segment]
   int T, H, P, N, G, Bt, hpg;
   int nslice, cpg;               // slices per group; workgroups per group
-  uint32_t S_inv, cpg_inv, rows_inv, G_inv, per_head_inv, sub_inv;  // for quotient(); rows: Bt * G, per head: P / 32
+  uint32_t S_inv, cpg_inv, rows_inv, G_inv, per_head_inv, sub_inv, nblocks_inv;  // for quotient(); rows: Bt * G, per head: P / 32
   int S;                         // segments per sequence; segment s begins at block segment_begin(s)
   int sub, sub_blocks;           // S = 1: workgroups that share the sequence, output blocks of each
+  uint8_t *images;               // with several segments: [batch row][group][block] as SplitLds::kImage; nullptr: none
   int slot0;                     // the first segment starts from its slot in y, not from h0 (which final_state aliases)
   DtXform dtx;
   int dt_plain;                    // the step sizes are used as given
@@ -89,11 +94,13 @@ struct SplitLds {
   static constexpr int kN = 32 * NT;
   static constexpr int kRow = kN + 8;                       // bf16 elements per row of a part of B or C
   static constexpr int kPart = kTok * kRow;
-  static constexpr int kBC = (kStatesOnly ? 3 : 6) * kPart * 2;  // bytes
-  static constexpr int kX = kWaves * kTok * kXStride * 4;
-  static constexpr int kG = kStatesOnly ? 0 : kTok * kGStride * 4;
+  static constexpr int kB = 3 * kPart * 2, kBC = 2 * kB;    // bytes
+  static constexpr int kG = kTok * kGStride * 4;
+  // The image of a block: the parts of B and C, the scores, and whether a value is out of range (an int behind the scores).
+  static constexpr int kFlag = kBC + kG, kImage = (kFlag + 4 + 4095) / 4096 * 4096, kImagePieces = kImage / (16 * kThr);
+  static constexpr int kX = kWaves * kTok * kXStride * 4, kXAt = kStatesOnly ? kB : kImage;
   static constexpr int kTurn = kWaves * kCols * kTurnStride * 4;
-  static constexpr int kTiles = kBC + kX + kG;
+  static constexpr int kTiles = kXAt + kX > kBC ? kXAt + kX : kBC;  // (the states-only launch also makes the images)
   static constexpr int kBytes = kTiles > kTurn ? kTiles : kTurn;
 };
 
@@ -104,8 +111,90 @@ __device__ __forceinline__ float larger(float seen, f32x4 v) {
 }
 __device__ __forceinline__ bool out_of_range(float seen) { return !(seen < 0x1p30f); }
 
-template <int NT, bool kStatesOnly>
+// Descriptor of the rows of block j that exist, `width` bytes of each.
+__device__ __forceinline__ Rsrc block_rows(const uint8_t *base, uint32_t row, uint32_t width, int j, int T) {
+  const int n = min(kTok, T - j * kTok);
+  return make_rsrc(base + static_cast<size_t>(j) * kTok * row, n > 0 ? (n - 1) * row + width : 0u);
+}
+// Four values of 16-byte piece `item` of a B or C tile, split into its three parts; the columns of a group of 16 in the order
+// 0-3, 8-11, 4-7, 12-15.
+template <int NT>
+__device__ __forceinline__ void put_parts(uint16_t *tile, int item, f32x4 v) {
+  using L = SplitLds<NT, false>;
+  const int c4 = item % (L::kN / 4), dst = (item / (L::kN / 4)) * L::kRow + 16 * (c4 >> 2) + 8 * (c4 & 1) + 4 * ((c4 >> 1) & 1);
+  const float v4[4] = {v.x, v.y, v.z, v.w};
+  uint32_t t[3][2];
+  split3_even<4>(v4, t);
+#pragma unroll
+  for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x2 *>(tile + q * L::kPart + dst) = u32x2{t[q][0], t[q][1]};
+}
+// A quarter of the scores (16 tokens s of `sb`, 16 tokens l of `sc`): lane (tj = lane % 16, lane / 16) gets l = tj, four s.
+template <int NT>
+__device__ __forceinline__ f32x4 scores_quarter(const uint16_t *sb, const uint16_t *sc) {
+  using L = SplitLds<NT, false>;
+  f32x4 acc = {};
+#pragma unroll
+  for (int kk = 0; kk < L::kN / 32; ++kk) {
+    Op bq[3], cq[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      bq[q].q = *reinterpret_cast<const u32x4 *>(sb + q * L::kPart + 32 * kk);
+      cq[q].q = *reinterpret_cast<const u32x4 *>(sc + q * L::kPart + 32 * kk);
+    }
+#pragma unroll
+    for (int t = 0; t < 6; ++t) acc = mfma16(bq[kPairA[t]], cq[kPairB[t]], acc);
+  }
+  return acc;
+}
+
+// The image of block j of batch row and group bg (see SplitLds): what every workgroup of the group would otherwise work out of B
+// and C again, 3900 of the 12900 cycles that a block took (2048 tokens x 24 heads: twelve workgroups a block).  Made by workgroups
+// of the states-only launch, which leaves CUs idle.
+template <int NT>
+__device__ __forceinline__ void make_image(const SplitParams &p, uint8_t *smem, int *s_odd, int bg, int j, int nblocks) {
+  using L = SplitLds<NT, false>;
+  constexpr int N = L::kN, kPieces = kTok * (N / 4) / kThr;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  uint16_t *const sB = reinterpret_cast<uint16_t *>(smem), *const sC = sB + 3 * L::kPart;
+  const uint32_t brow = static_cast<uint32_t>(p.G) * p.N * 4;
+  const size_t first = (static_cast<size_t>(bg / p.G) * p.T * p.G + bg % p.G) * p.N;
+  const Rsrc rB = block_rows(reinterpret_cast<const uint8_t *>(p.B + first), brow, p.N * 4, j, p.T);
+  const Rsrc rC = block_rows(reinterpret_cast<const uint8_t *>(p.C + first), brow, p.N * 4, j, p.T);
+  u32x4 b[kPieces], c[kPieces];
+#pragma unroll
+  for (int k = 0; k < kPieces; ++k) {
+    const int item = tid + kThr * k, n0 = 4 * (item % (N / 4));
+    const uint32_t at = n0 < p.N ? static_cast<uint32_t>(item / (N / 4)) * brow + 4 * n0 : kNowhere;
+    b[k] = buf_load16(rB, at);
+    c[k] = buf_load16(rC, at);
+  }
+  if (tid == 0) *s_odd = 0;
+  float seen = 0.f;
+#pragma unroll
+  for (int k = 0; k < kPieces; ++k) {
+    const f32x4 vb = __builtin_bit_cast(f32x4, b[k]), vc = __builtin_bit_cast(f32x4, c[k]);
+    put_parts<NT>(sB, tid + kThr * k, vb);
+    put_parts<NT>(sC, tid + kThr * k, vc);
+    seen = larger(larger(seen, vb), vc);
+  }
+  __syncthreads();
+  if (__builtin_amdgcn_ballot_w64(out_of_range(seen)) != 0 && lane == 0) *s_odd = 1;
+  uint8_t *const image = p.images + (static_cast<size_t>(bg) * nblocks + j) * L::kImage;
+  for (int at = 16 * tid; at < L::kBC; at += 16 * kThr)
+    *reinterpret_cast<u32x4 *>(image + at) = *reinterpret_cast<const u32x4 *>(smem + at);
+  if (wave < 3) {
+    const int sq = wave >> 1, lq = wave > 0 ? 1 : 0, tj = lane & 15, at = tj * L::kRow + 8 * (lane >> 4);
+    const f32x4 acc = scores_quarter<NT>(sB + 16 * sq * L::kRow + at, sC + 16 * lq * L::kRow + at);
+    *reinterpret_cast<f32x4 *>(image + L::kBC + ((16 * lq + tj) * kGStride + 16 * sq + 4 * (lane >> 4)) * 4) = acc;
+  }
+  __syncthreads();
+  if (tid == 0) *reinterpret_cast<int *>(image + L::kFlag) = *s_odd;
+}
+
+// kImages: the full launch where the states-only launch has left the images of its blocks.
+template <int NT, bool kStatesOnly, bool kImages = false>
 __global__ __launch_bounds__(kThr, 2) void split_f32_kernel(const SplitParams p) {
+  static_assert(!(kStatesOnly && kImages), "the states-only launch makes the images");
   using L = SplitLds<NT, kStatesOnly>;
   constexpr int N = L::kN;                       // dstate padded to whole tiles
   constexpr int kPieces = kTok * (N / 4) / kThr;  // 16-byte pieces of a B or C tile per thread
@@ -118,16 +207,25 @@ __global__ __launch_bounds__(kThr, 2) void split_f32_kernel(const SplitParams p)
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 31, kg = lane >> 5;
-  float *const sX = reinterpret_cast<float *>(smem + L::kBC) + wave * (kTok * kXStride);  // x [token][column], this wave's
-  float *const sG = reinterpret_cast<float *>(smem + L::kBC + L::kX);                     // scores [l][s]
+  float *const sX = reinterpret_cast<float *>(smem + L::kXAt) + wave * (kTok * kXStride);  // x [token][column], this wave's
+  float *const sG = reinterpret_cast<float *>(smem + L::kBC);                              // scores [l][s]
 
   // ---- which slice, segment and blocks ----
-  const int wg = blockIdx.x;
+  const int nblocks = (p.T + kTok - 1) / kTok;
+  int wg = blockIdx.x;
+  if constexpr (kStatesOnly) {
+    const int n_images = p.images != nullptr ? nblocks * p.Bt * p.G : 0;
+    if (wg < n_images) {
+      const int row = quotient(wg, nblocks, p.nblocks_inv);
+      make_image<NT>(p, smem, &s_odd, row, wg - row * nblocks, nblocks);
+      return;
+    }
+    wg -= n_images;
+  }
   const int item = quotient(wg, p.cpg, p.cpg_inv), col = wg - item * p.cpg;
   const int piece = quotient(item, p.Bt * p.G, p.rows_inv), bg = item - piece * (p.Bt * p.G);
   const int b = quotient(bg, p.G, p.G_inv), g = bg - b * p.G;
-  const int seg = kStatesOnly ? piece : quotient(piece, p.sub, p.sub_inv), part = kStatesOnly ? 0 : piece - seg * p.sub;
-  const int nblocks = (p.T + kTok - 1) / kTok;
+  const int seg = kStatesOnly || kImages ? piece : quotient(piece, p.sub, p.sub_inv), part = kStatesOnly || kImages ? 0 : piece - seg * p.sub;
   const int j0 = segment_begin(seg, p, nblocks), jend = segment_begin(seg + 1, p, nblocks);
   // the state alone over [j0, j1), everything over [j1, j2)
   const int j1 = kStatesOnly ? jend : min(jend, j0 + part * p.sub_blocks);
@@ -154,14 +252,11 @@ __global__ __launch_bounds__(kThr, 2) void split_f32_kernel(const SplitParams p)
   const uint8_t *const Bb = reinterpret_cast<const uint8_t *>(p.B) + tok0 * brow + static_cast<size_t>(g) * p.N * 4;
   const uint8_t *const Cb = reinterpret_cast<const uint8_t *>(p.C) + tok0 * brow + static_cast<size_t>(g) * p.N * 4;
   const uint8_t *const db = reinterpret_cast<const uint8_t *>(p.dt) + tok0 * drow + static_cast<size_t>(h) * 4;
-  // descriptor of the rows of block j that exist, `width` bytes of each
-  auto rows_of = [&](const uint8_t *base, uint32_t row, uint32_t width, int j) {
-    const int n = min(kTok, p.T - j * kTok);
-    return make_rsrc(base + static_cast<size_t>(j) * kTok * row, n > 0 ? (n - 1) * row + width : 0u);
-  };
+  auto rows_of = [&](const uint8_t *base, uint32_t row, uint32_t width, int j) { return block_rows(base, row, width, j, p.T); };
 
   // ---- data of a block in flight ----
-  u32x4 r_b[kPieces], r_c[kStatesOnly ? 1 : kPieces], r_x[4];
+  u32x4 r_b[kImages ? 1 : kPieces], r_c[kStatesOnly || kImages ? 1 : kPieces], r_x[4];
+  u32x4 r_img[kImages ? L::kImagePieces : 1];
   float r_dt;
   uint32_t v_bc[kPieces];
 #pragma unroll
@@ -172,14 +267,20 @@ __global__ __launch_bounds__(kThr, 2) void split_f32_kernel(const SplitParams p)
   // (with_c, uniform: a block of which only the state is wanted needs no C; its loads are pointed beyond the
   // descriptor, where they cost nothing, rather than put behind a branch)
   auto load_block = [&](int j, bool with_c) __attribute__((always_inline)) {
-    const Rsrc rB = rows_of(Bb, brow, p.N * 4, j);
+    if constexpr (kImages) {
+      const Rsrc rI = make_rsrc(p.images + (static_cast<size_t>(bg) * nblocks + j) * L::kImage, L::kImage);
 #pragma unroll
-    for (int k = 0; k < kPieces; ++k) r_b[k] = buf_load16(rB, v_bc[k]);
+      for (int k = 0; k < L::kImagePieces; ++k) r_img[k] = buf_load16(rI, 16 * (tid + kThr * k));
+    } else {
+      const Rsrc rB = rows_of(Bb, brow, p.N * 4, j);
+#pragma unroll
+      for (int k = 0; k < kPieces; ++k) r_b[k] = buf_load16(rB, v_bc[k]);
+    }
     const Rsrc rx = rows_of(xb, xrow, 4 * kCols, j);
 #pragma unroll
     for (int k = 0; k < 4; ++k) r_x[k] = buf_load16(rx, static_cast<uint32_t>(8 * k + (lane >> 3)) * xrow + 16 * (lane & 7));
     r_dt = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rows_of(db, drow, 4, j), r * drow, 0, 0));
-    if constexpr (!kStatesOnly) {
+    if constexpr (!kStatesOnly && !kImages) {
       const Rsrc rC = rows_of(Cb, brow, p.N * 4, j);
 #pragma unroll
       for (int k = 0; k < kPieces; ++k) r_c[k] = buf_load16(rC, with_c ? v_bc[k] : kNowhere);
@@ -249,25 +350,20 @@ __global__ __launch_bounds__(kThr, 2) void split_f32_kernel(const SplitParams p)
     __syncthreads();  // the previous block's readers (at first: the turning of the state) are done with LDS
     // ---- registers -> LDS ----
     float seen[3] = {};
+    if constexpr (kImages) {
 #pragma unroll
-    for (int k = 0; k < kPieces; ++k) {
-      const int item = tid + kThr * k, c4 = item % (N / 4);
-      // the columns of a group of 16 in the order 0-3, 8-11, 4-7, 12-15
-      const int dst = (item / (N / 4)) * L::kRow + 16 * (c4 >> 2) + 8 * (c4 & 1) + 4 * ((c4 >> 1) & 1);
-      uint32_t t[3][2];
-      const f32x4 vb = __builtin_bit_cast(f32x4, r_b[k]);
-      const float b4[4] = {vb.x, vb.y, vb.z, vb.w};
-      split3_even<4>(b4, t);
-      seen[0] = larger(seen[0], vb);
+      for (int k = 0; k < L::kImagePieces; ++k) *reinterpret_cast<u32x4 *>(smem + 16 * (tid + kThr * k)) = r_img[k];
+    } else {
 #pragma unroll
-      for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x2 *>(sB + q * L::kPart + dst) = u32x2{t[q][0], t[q][1]};
-      if constexpr (kFull) {
-        const f32x4 vc = __builtin_bit_cast(f32x4, r_c[k]);
-        const float c4v[4] = {vc.x, vc.y, vc.z, vc.w};
-        split3_even<4>(c4v, t);
-        seen[1] = larger(seen[1], vc);
-#pragma unroll
-        for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x2 *>(sC + q * L::kPart + dst) = u32x2{t[q][0], t[q][1]};
+      for (int k = 0; k < kPieces; ++k) {
+        const f32x4 vb = __builtin_bit_cast(f32x4, r_b[k]);
+        put_parts<NT>(sB, tid + kThr * k, vb);
+        seen[0] = larger(seen[0], vb);
+        if constexpr (kFull) {
+          const f32x4 vc = __builtin_bit_cast(f32x4, r_c[k]);
+          put_parts<NT>(sC, tid + kThr * k, vc);
+          seen[1] = larger(seen[1], vc);
+        }
       }
     }
 #pragma unroll
@@ -300,25 +396,14 @@ __global__ __launch_bounds__(kThr, 2) void split_f32_kernel(const SplitParams p)
     if (__builtin_amdgcn_ballot_w64(odd) != 0 && lane == 0) s_odd = 1;
     load_block(min(j + 1, j2 - 1), j + 1 >= j1);  // (after the last block: a harmless repeat, no branch)
     __syncthreads();
-    const int met_odd = s_odd;  // uniform over the workgroup; waited for where the state is about to change
+    const int met_odd = kImages ? s_odd | *reinterpret_cast<const int *>(smem + L::kFlag) : s_odd;  // uniform over the workgroup; waited for where the state is about to change
 
     f32x16 Y = {};
     if constexpr (kFull) {
       // ---- scores: a quarter of the 32 x 32 tile per wave (the fourth wave's, above the diagonal, repeats the third's) ----
-      if (wave < 3) {
-        f32x4 acc = {};
-#pragma unroll
-        for (int kk = 0; kk < N / 32; ++kk) {
-          Op bq[3], cq[3];
-#pragma unroll
-          for (int q = 0; q < 3; ++q) {
-            bq[q].q = *reinterpret_cast<const u32x4 *>(sB + q * L::kPart + a_sb + 32 * kk);
-            cq[q].q = *reinterpret_cast<const u32x4 *>(sC + q * L::kPart + a_sc + 32 * kk);
-          }
-#pragma unroll
-          for (int t = 0; t < 6; ++t) acc = mfma16(bq[kPairA[t]], cq[kPairB[t]], acc);
-        }
-        *reinterpret_cast<f32x4 *>(sG + (16 * lq + tj) * kGStride + 16 * sq + 4 * (lane >> 4)) = acc;
+      if constexpr (!kImages) {
+        if (wave < 3)
+          *reinterpret_cast<f32x4 *>(sG + (16 * lq + tj) * kGStride + 16 * sq + 4 * (lane >> 4)) = scores_quarter<NT>(sB + a_sb, sC + a_sc);
       }
       // ---- Y^T[p][l]: the state's part, then scaled by the decay up to token l = r ----
 #pragma unroll
@@ -334,7 +419,7 @@ __global__ __launch_bounds__(kThr, 2) void split_f32_kernel(const SplitParams p)
       }
 #pragma unroll
       for (int i = 0; i < 16; ++i) Y[i] *= el;
-      __syncthreads();  // the scores are in LDS
+      if constexpr (!kImages) __syncthreads();  // the scores are in LDS
     }
     if (met_odd != 0) return false;
     if constexpr (kStatesOnly) log2_total += total;
@@ -403,7 +488,9 @@ __global__ __launch_bounds__(kThr, 2) void split_f32_kernel(const SplitParams p)
   };
   int j = j0;
   bool in_range = true;
-  for (; j < j1 && in_range; j += in_range) in_range = block(j, std::false_type{});
+  if constexpr (!kImages) {
+    for (; j < j1 && in_range; j += in_range) in_range = block(j, std::false_type{});
+  }
   if constexpr (!kStatesOnly) {
     for (; j < j2 && in_range; j += in_range) in_range = block(j, std::true_type{});
   }
@@ -507,16 +594,20 @@ struct SplitPlan {
   double us;  // modelled time
 };
 
-// Segments whose states fit: the workspace holds (S + 1 values per head and segment fit it), or every segment's rows of
-// y do (see state_slot).
+// Segments whose states fit: the workspace holds them, or every segment's rows of y do (see state_slot).
 static bool slots_in_workspace(const Dims &d, int S) {
   return static_cast<size_t>(d.Bt) * d.H * S * (static_cast<size_t>(d.P) * d.N + 1) * sizeof(float) <= generic_workspace_bytes(d);
 }
-static bool segments_fit(const Dims &d, int S) {
-  const int nblocks = (d.T + kTok - 1) / kTok, rows = kCols * ((d.N + 31) / 32);
-  return slots_in_workspace(d, S) ||
-         (nblocks / S * kTok >= rows && d.T - segment_begin(S - 1, S, nblocks) * kTok >= rows);
+static size_t image_bytes(const Dims &d) {
+  const int nblocks = (d.T + kTok - 1) / kTok;
+  constexpr int kImage[4] = {SplitLds<1, false>::kImage, SplitLds<2, false>::kImage, SplitLds<3, false>::kImage, SplitLds<4, false>::kImage};
+  return static_cast<size_t>(d.Bt) * d.G * nblocks * kImage[(d.N + 31) / 32 - 1];
 }
+static bool slots_in_y(const Dims &d, int S) {
+  const int nblocks = (d.T + kTok - 1) / kTok, rows = kCols * ((d.N + 31) / 32);
+  return nblocks / S * kTok >= rows && d.T - segment_begin(S - 1, S, nblocks) * kTok >= rows;
+}
+static bool segments_fit(const Dims &d, int S) { return slots_in_workspace(d, S) || slots_in_y(d, S); }
 
 // Microseconds on MI355X, fits to timings of 10 shapes: a full block; a block of which only the state is updated, in
 // the states-only launch and in the full one; by state tiles.  A CU holds two workgroups, which slow each other by a
@@ -601,13 +692,17 @@ void split_f32_plan(const Dims &d, int *seg_blocks, int *segments, int *parts) {
 template <int NT>
 static void launch_nt(const SplitParams &p, unsigned wgs, hipStream_t stream, KernelTrace *trace) {
   if (p.S > 1) {
-    hipLaunchKernelGGL((split_f32_kernel<NT, true>), dim3(wgs * (p.S - 1)), dim3(kThr), 0, stream, p);
+    const unsigned images = p.images != nullptr ? static_cast<unsigned>((p.T + kTok - 1) / kTok) * p.Bt * p.G : 0;
+    hipLaunchKernelGGL((split_f32_kernel<NT, true>), dim3(images + wgs * (p.S - 1)), dim3(kThr), 0, stream, p);
     trace_mark(trace, stream, "segment_states");
     hipLaunchKernelGGL(split_pass_kernel, dim3((p.P * p.N + 4 * kPassThr - 1) / (4 * kPassThr), p.Bt * p.H), dim3(kPassThr), 0,
                        stream, p);
     trace_mark(trace, stream, "segment_pass");
   }
-  hipLaunchKernelGGL((split_f32_kernel<NT, false>), dim3(wgs * p.S * p.sub), dim3(kThr), 0, stream, p);
+  if (p.images != nullptr)
+    hipLaunchKernelGGL((split_f32_kernel<NT, false, true>), dim3(wgs * p.S), dim3(kThr), 0, stream, p);
+  else
+    hipLaunchKernelGGL((split_f32_kernel<NT, false>), dim3(wgs * p.S * p.sub), dim3(kThr), 0, stream, p);
   trace_mark(trace, stream, "prefill_f32");
 }
 
@@ -628,9 +723,26 @@ hipError_t launch_prefill_split_f32(const Dims &d, const void *x, const float *d
   // (decays: S values per head, of which the workspace holds at least one per token and head)
   p.decay = static_cast<float *>(workspace);
   p.slots = nullptr;
-  if (pl.segments > 1 && slots_in_workspace(d, pl.segments)) {
-    p.slots = static_cast<float *>(workspace);
-    p.decay = p.slots + static_cast<size_t>(d.Bt) * d.H * pl.segments * d.P * d.N;
+  p.images = nullptr;
+  if (pl.segments > 1) {
+    const size_t row = static_cast<size_t>(d.Bt) * d.H * pl.segments, have = generic_workspace_bytes(d);
+    const size_t images = image_bytes(d), decays = (row * sizeof(float) + 255) / 256 * 256, states = row * d.P * d.N * sizeof(float);
+    uint8_t *const ws = static_cast<uint8_t *>(workspace);
+    // the images have the first claim on the workspace, where the states fit in y instead
+    // Images where the states-only launch has CUs left for them -- at most a workgroup per CU with them -- (2048 tokens x 24 heads
+    // 51.2 -> 49.0 us, 2 x 712 x 27 x 64 x 64 32.6 -> 31.3).  In a fuller launch they delay the states by what the full launch
+    // gains: 40 drawn prompts took 0.96 to 1.07 of the time, 6 x 2184 x 30 138 -> 143 us.
+    const long rows = static_cast<long>(d.Bt) * d.G, nblocks = (d.T + kTok - 1) / kTok;
+    const long wgs = rows * ((d.hpg * (d.P / kCols) + kWaves - 1) / kWaves);
+    const bool idle = wgs * (pl.segments - 1) + rows * nblocks <= 256;
+    const bool images_fit = idle && images + decays <= have && (images + decays + states <= have || slots_in_y(d, pl.segments));
+    if (images_fit) p.images = ws;
+    const size_t before = images_fit ? images : 0;
+    p.decay = reinterpret_cast<float *>(ws + before);
+    if (images_fit ? before + decays + states <= have : slots_in_workspace(d, pl.segments)) {
+      p.slots = reinterpret_cast<float *>(ws + before);
+      p.decay = p.slots + row * d.P * d.N;
+    }
   }
   p.T = d.T;
   p.H = d.H;
@@ -650,6 +762,7 @@ hipError_t launch_prefill_split_f32(const Dims &d, const void *x, const float *d
   p.G_inv = inverse_of(d.G);
   p.per_head_inv = inverse_of(d.P / kCols);
   p.sub_inv = inverse_of(p.sub);
+  p.nblocks_inv = inverse_of((d.T + kTok - 1) / kTok);
   p.dtx = d.dtx;
   p.dt_plain = d.dtx.identity();
   const size_t state_bytes = static_cast<size_t>(d.Bt) * d.H * d.P * d.N * sizeof(float);
