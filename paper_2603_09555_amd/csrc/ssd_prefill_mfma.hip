@@ -1800,8 +1800,10 @@ __device__ __forceinline__ bool walk_meets_steep_block(const ScanParams &p, cons
 //     each, 64 vector instructions apart): with the fourteen requests and four stores of a block among its own
 //     instructions a computing wave took 4190 cycles a block of 8 x 4096 tokens x 48 heads, with feeders 3660.
 //   - The feeders also scale x and turn it for the matrix instructions (3610: now they are what a block waits for) and
-//     make their requests in runs of four (see load_to_lds4): 3250.  The same work in waves that load into registers and
-//     write LDS themselves takes 5240 cycles.
+//     make their requests in runs of four (see load_to_lds4): 3250; ahead of the block's other address arithmetic: 3130, of
+//     which requests take 1430, the turn 1110 and stores 230 of a feeder, and 2490 are a computing wave's.  x loaded into
+//     registers three blocks ahead, with requests between quarters of the turn: 140 us a call instead of 120.  The same work in
+//     waves that load into registers and write LDS themselves takes 5240 cycles.
 //   - The tiles and the record of the next block arrive during a block, in the buffer of a pair that it does not use.  A
 //     block of x goes through one of three buffers: it arrives until the middle of the block before its own, when the feeder that
 //     requested it turns it into Xm^T; it serves the skip term of its block and is replaced, in place, by y; and
