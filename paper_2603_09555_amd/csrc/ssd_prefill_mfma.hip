@@ -752,14 +752,22 @@ __global__ __launch_bounds__(kThreads) void block_prep_kernel(const uint16_t *__
 }
 
 // ---- chunk_scan / segment_states ----------------------------------------------------------------
-struct ScanParams {
+// kPair: with what the two-head scan has besides.  (In the other kernels these members are not there: four heads per workgroup
+// with them, and with multiplications instead of their few divisions, 9 x 2912 tokens x 60 heads in four groups 176.7 us, 172.3
+// without -- the same loop, another start.)
+template <int>
+struct Absent {};
+template <bool kPair>
+struct ScanParamsOf {
+  template <int i>
+  using PairOnly = std::conditional_t<kPair, uint32_t, Absent<i>>;
   const uint8_t *x;
   const uint8_t *C;
   const float *D;
   const uint8_t *Gd;
   const uint8_t *Btr;
   const float *prep;
-  uint32_t prep_bytes;
+  [[no_unique_address]] PairOnly<0> prep_bytes;  // of all decay records
   uint8_t *y;
   const float *h0;         // (sequences, H, P, N) initial states, or nullptr = zeros (read by one-segment sequences)
   const float *Hin;        // state entering each segment of a sequence of several: one slot per segment
@@ -781,9 +789,15 @@ struct ScanParams {
   int pdiv, Hrec;          // slices per head (headdim / 64); heads (owners of decay records, A, D)
   NSlice ns;               // columns of h0 / final_state (rows of ns.width floats) this launch works on
   int cols, segs, total, per_xcd;  // workgroup mapping, see wg_coords
-  uint32_t cpg_inv, pdiv_inv, cols_inv, segs_inv;  // for quotient()
+  [[no_unique_address]] PairOnly<1> cpg_inv;   // for quotient()
+  [[no_unique_address]] PairOnly<2> pdiv_inv;
+  [[no_unique_address]] PairOnly<3> cols_inv;
+  [[no_unique_address]] PairOnly<4> segs_inv;
   VarPlan vp;              // tok0 == nullptr: plain batch
 };
+using ScanParams = ScanParamsOf<false>;
+using PairParams = ScanParamsOf<true>;
+static_assert(sizeof(PairParams) >= sizeof(ScanParams) + 5 * sizeof(uint32_t), "absent members take no room");
 
 // Where a workgroup works: head group `col`, segment `sg` of `S` of sequence `b`, whose `nb` blocks
 // start at token `tok0` of the packed token axis (`len` tokens), at workspace tile / record number
@@ -803,16 +817,24 @@ struct SeqView {
 // group) list, head group fastest.  Ids beyond the list (the grid is rounded up to 8 * per_xcd) idle.
 // `last_too`: whether the last segment of a sequence is in the list (not for the states-only pass).
 constexpr int kXcds = 8;
-__device__ __forceinline__ bool wg_coords_varlen(const ScanParams &p, bool last_too, SeqView &v);
-__device__ __forceinline__ bool wg_coords(const ScanParams &p, bool last_too, SeqView &v) {
+template <bool kPair>
+__device__ __forceinline__ bool wg_coords_varlen(const ScanParamsOf<kPair> &p, bool last_too, SeqView &v);
+template <bool kPair>
+__device__ __forceinline__ bool wg_coords(const ScanParamsOf<kPair> &p, bool last_too, SeqView &v) {
   if (p.vp.tok0 != nullptr) return wg_coords_varlen(p, last_too, v);
   const int id = blockIdx.x;
   const int w = (id % kXcds) * p.per_xcd + id / kXcds;
   if (w >= p.total) return false;
-  const int item = quotient(w, p.cols, p.cols_inv);
-  v.col = w - item * p.cols;
-  v.b = quotient(item, p.segs, p.segs_inv);
-  v.sg = item - v.b * p.segs;
+  if constexpr (kPair) {
+    const int item = quotient(w, p.cols, p.cols_inv);
+    v.col = w - item * p.cols;
+    v.b = quotient(item, p.segs, p.segs_inv);
+    v.sg = item - v.b * p.segs;
+  } else {
+    v.col = w % p.cols;
+    v.sg = (w / p.cols) % p.segs;
+    v.b = w / (p.cols * p.segs);
+  }
   v.S = p.S;
   v.nb = p.NB;
   v.seg_blocks = p.seg_blocks;
@@ -831,7 +853,8 @@ __device__ __forceinline__ bool wg_coords(const ScanParams &p, bool last_too, Se
 __device__ __forceinline__ int table_at(const int32_t *t, int i) {
   return ((const __attribute__((address_space(4))) int32_t *)t)[i];
 }
-__device__ __forceinline__ bool wg_coords_varlen(const ScanParams &p, bool last_too, SeqView &v) {
+template <bool kPair>
+__device__ __forceinline__ bool wg_coords_varlen(const ScanParamsOf<kPair> &p, bool last_too, SeqView &v) {
   const int n_items = table_at(p.vp.item0, p.vp.nseq), seg_blocks = table_at(p.vp.len, p.vp.nseq);
   const int n_full = n_items - p.vp.nseq;
   const int n_list = last_too ? n_items : n_full;
@@ -847,8 +870,14 @@ __device__ __forceinline__ bool wg_coords_varlen(const ScanParams &p, bool last_
   if (id / kXcds >= per_xcd) return false;
   const int w = (id % kXcds) * per_xcd + id / kXcds;
   if (w >= total) return false;
-  int item = quotient(w, p.cols, p.cols_inv);
-  v.col = w - item * p.cols;
+  int item;
+  if constexpr (kPair) {
+    item = quotient(w, p.cols, p.cols_inv);
+    v.col = w - item * p.cols;
+  } else {
+    v.col = w % p.cols;
+    item = w / p.cols;
+  }
   if (last_too) {
     const int base = n_list / kXcds, rem = n_list % kXcds;  // hands 0..rem-1 hold base + 1 entries
     const int big = rem * (base + 1);
@@ -959,15 +988,15 @@ __device__ __forceinline__ void scan_walk(const ScanParams &p, const SeqView &sv
   // The heads of a workgroup share one B/C group.  A group whose number of (64-column) slices is not a
   // multiple of four leaves slots of its last workgroup without a slice: those waves repeat the group's last
   // slice -- they take part in the shared staging and the barriers like any other -- and write nothing.
-  const int g = quotient(col, p.cpg, p.cpg_inv);
-  const int slot = (col - g * p.cpg) * HPW + hw;
+  const int g = col / p.cpg;
+  const int slot = (col % p.cpg) * HPW + hw;
   const bool live = slot < p.hpg;
   const int h = g * p.hpg + min(slot, p.hpg - 1);
   // workspace numbering: tiles (b, g, block), records (b, h, block), state slots (b, h, segment) for a
   // plain batch; (g, block), (h, block), (h, segment) with batch-wide block / segment numbers otherwise
   const bool plain = p.vp.tok0 == nullptr;
   const size_t tile0 = plain ? (sv.blk0 * p.G + static_cast<size_t>(g) * sv.blk_stride) : (g * sv.blk_stride + sv.blk0);
-  const int hrec = quotient(h, p.pdiv, p.pdiv_inv);  // the head this slice belongs to
+  const int hrec = h / p.pdiv;  // the head this slice belongs to
   const size_t rec0 = plain ? (sv.blk0 * p.Hrec + static_cast<size_t>(hrec) * sv.blk_stride) : (hrec * sv.blk_stride + sv.blk0);
   const size_t slot0 = plain ? (sv.slot0 * p.H + static_cast<size_t>(h) * sv.slot_stride) : (h * sv.slot_stride + sv.slot0);
   const size_t bh = static_cast<size_t>(sv.b) * p.H + h;  // row of final_state
@@ -1851,7 +1880,7 @@ __device__ __forceinline__ void item_blocks(ItemView &v, int seg_blocks) {
 }
 
 // The item of a workgroup that has one at most: true if it has one.
-__device__ __forceinline__ bool one_item(const ScanParams &p, int &seg_blocks, ItemView &first) {
+__device__ __forceinline__ bool one_item(const PairParams &p, int &seg_blocks, ItemView &first) {
   SeqView v;
   if (!wg_coords(p, true, v)) return false;
   seg_blocks = v.seg_blocks;
@@ -1877,7 +1906,7 @@ __device__ __forceinline__ bool one_item(const ScanParams &p, int &seg_blocks, I
 struct Deal {
   int n_full, n_mine, place, seg_blocks;
 };
-__device__ __forceinline__ Deal deal_of(const ScanParams &p) {
+__device__ __forceinline__ Deal deal_of(const PairParams &p) {
   Deal d;
   const int entries = table_at(p.vp.item0, p.vp.nseq), total = entries * p.cols, wgs = gridDim.x;
   d.seg_blocks = table_at(p.vp.len, p.vp.nseq);
@@ -1893,7 +1922,7 @@ __device__ __forceinline__ Deal deal_of(const ScanParams &p) {
 struct ItemPlace {
   int entry, col, q;
 };
-__device__ __forceinline__ ItemPlace item_place(const ScanParams &p, const Deal &d, int i) {
+__device__ __forceinline__ ItemPlace item_place(const PairParams &p, const Deal &d, int i) {
   const int wgs = gridDim.x;
   const int pos = i == 0 ? d.place : i * wgs + wgs - 1 - d.place;
   ItemPlace at;
@@ -1902,7 +1931,7 @@ __device__ __forceinline__ ItemPlace item_place(const ScanParams &p, const Deal 
   at.q = table_at(p.vp.item_seq, at.entry);
   return at;
 }
-__device__ __forceinline__ ItemView item_at(const ScanParams &p, const Deal &d, const ItemPlace &at) {
+__device__ __forceinline__ ItemView item_at(const PairParams &p, const Deal &d, const ItemPlace &at) {
   ItemView v;
   const int first = table_at(p.vp.item0, at.q);
   v.b = at.q;
@@ -1924,11 +1953,11 @@ struct Items {
   ItemPlace ahead2 = {};  // and where the one after it is
   int next = 0, n;
   __device__ __forceinline__ Items(const Deal &d, const ItemView &first) : deal(d), ahead(first), n(1) {}
-  __device__ __forceinline__ Items(const ScanParams &p, const Deal &d, int i) : deal(d), next(i), n(d.n_mine) {
+  __device__ __forceinline__ Items(const PairParams &p, const Deal &d, int i) : deal(d), next(i), n(d.n_mine) {
     ahead = item_at(p, d, item_place(p, d, i));
     if (i + 1 < n) ahead2 = item_place(p, d, i + 1);
   }
-  __device__ __forceinline__ ItemView take(const ScanParams &p) {
+  __device__ __forceinline__ ItemView take(const PairParams &p) {
     const ItemView v = ahead;
     ++next;
     if constexpr (kList) {
@@ -1955,7 +1984,7 @@ __device__ __forceinline__ int lane_here() {
 
 // The feeding waves, 4..7: feeder w serves head w / 2 and, of x and y, tokens 32 (w & 1) .. + 31.
 template <int kYMode, bool kList>
-__device__ __forceinline__ void pair_feed(const ScanParams &p, Items<kList> items, lds_u8 *const lds) {
+__device__ __forceinline__ void pair_feed(const PairParams &p, Items<kList> items, lds_u8 *const lds) {
   using L = PairLds;
   const uint32_t lds_at = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds));
   const int tid = here(threadIdx.x) & 255, lane = tid & 63;
@@ -2225,12 +2254,12 @@ __device__ __forceinline__ void pair_feed(const ScanParams &p, Items<kList> item
 }
 
 template <bool kList>
-__device__ void pair_walk_mixed(const ScanParams p, const Deal deal, const ItemView first, int item, uint32_t parity, uint32_t x_cur, lds_u8 *const lds);
+__device__ void pair_walk_mixed(const PairParams p, const Deal deal, const ItemView first, int item, uint32_t parity, uint32_t x_cur, lds_u8 *const lds);
 
 // The computing waves, 0..3: wave w has half w & 1 of headdim of head w / 2.  kMixed: some of the items' blocks may be steep.
 // kList: there may be several items; otherwise, and without kMixed, it returns false, having done nothing, if a block is steep.
 template <bool kMixed, bool kList>
-__device__ __forceinline__ void pair_walk(const ScanParams &p, Items<kList> items, uint32_t parity, uint32_t x_cur, lds_u8 *const lds) {
+__device__ __forceinline__ void pair_walk(const PairParams &p, Items<kList> items, uint32_t parity, uint32_t x_cur, lds_u8 *const lds) {
   using L = PairLds;
   const int tid = here(threadIdx.x), lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -2624,7 +2653,7 @@ __device__ __forceinline__ void pair_walk(const ScanParams &p, Items<kList> item
 }
 
 template <bool kList>
-__device__ __attribute__((noinline)) void pair_walk_mixed(const ScanParams p, const Deal deal, const ItemView first, int item, uint32_t parity, uint32_t x_cur,
+__device__ __attribute__((noinline)) void pair_walk_mixed(const PairParams p, const Deal deal, const ItemView first, int item, uint32_t parity, uint32_t x_cur,
                                                           lds_u8 *const lds) {
   const Deal d = {static_cast<int>(uniform32(deal.n_full)), static_cast<int>(uniform32(deal.n_mine)), static_cast<int>(uniform32(deal.place)),
                   static_cast<int>(uniform32(deal.seg_blocks))};
@@ -2661,7 +2690,7 @@ __global__ __launch_bounds__(128 * HPW) __attribute__((amdgpu_waves_per_eu(2, 2)
 // kList: a packed batch, as many workgroups as CUs, each with the items that it is dealt; otherwise an item each.
 // (the two roles, and the two walks, pass the same barriers, block for block; waves of one workgroup may take different walks)
 template <int kYMode, bool kList>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void pair_scan_kernel(const ScanParams p) {
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void pair_scan_kernel(const PairParams p) {
   __shared__ __align__(1024) uint8_t lds_bytes[PairLds::kBytes];
   lds_u8 *const lds = (lds_u8 *)lds_bytes;
   const bool feeds = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x)) >= 256;  // (uniform, and known to be)
@@ -3088,16 +3117,19 @@ bool packed_uncut(const Dims &d, const SlicePlan &pl) {
 }
 
 // The workgroups of a pass: `heads` head slices each, `segs` segments per sequence, `items` in all.
-void map_to(ScanParams &p, int heads, int segs, int items) {
+template <bool kPair>
+void map_to(ScanParamsOf<kPair> &p, int heads, int segs, int items) {
   p.cpg = (p.hpg + heads - 1) / heads;
   p.cols = p.G * p.cpg;
   p.segs = segs;
   p.total = p.cols * items;
   p.per_xcd = (p.total + kXcds - 1) / kXcds;
-  p.cpg_inv = inverse_of(p.cpg);
-  p.pdiv_inv = inverse_of(p.pdiv);
-  p.cols_inv = inverse_of(p.cols);
-  p.segs_inv = inverse_of(segs > 0 ? segs : 1);
+  if constexpr (kPair) {
+    p.cpg_inv = inverse_of(p.cpg);
+    p.pdiv_inv = inverse_of(p.pdiv);
+    p.cols_inv = inverse_of(p.cols);
+    p.segs_inv = inverse_of(segs > 0 ? segs : 1);
+  }
 }
 
 hipError_t launch_slice(const Dims &d, const NSlice ns, const int32_t *cu, const void *x, const float *dt,
@@ -3145,42 +3177,43 @@ hipError_t launch_slice(const Dims &d, const NSlice ns, const int32_t *cu, const
                      d.T, d.H, d.G, w.NB, n_scores, vp, ns, Cpad, d.dtx);
   trace_mark(trace, stream, "block_prep");
 
-  ScanParams p;
-  p.x = static_cast<const uint8_t *>(x);
-  p.C = Cpad != nullptr ? reinterpret_cast<const uint8_t *>(Cpad) : static_cast<const uint8_t *>(C);
-  p.D = D;
-  p.ns = ns;
-  p.Gd = reinterpret_cast<const uint8_t *>(Gd);
-  p.Btr = reinterpret_cast<const uint8_t *>(Btr);
-  p.prep = prep;
-  p.prep_bytes = static_cast<uint32_t>(w.off_state - w.off_prep);
-  p.y = static_cast<uint8_t *>(y);
-  p.h0 = h0;
-  p.Hin = seg_state;
-  p.final_state = final_state;
-  p.seg_state = seg_state;
-  p.seg_decay = seg_decay;
-  p.T = d.T;
-  const int pdiv = d.P / kP, Hs = d.H * pdiv;
-  p.H = Hs;
-  p.pdiv = pdiv;
-  p.Hrec = d.H;
-  p.G = d.G;
-  p.hpg = d.hpg * pdiv;
-  p.NB = w.NB;
-  p.seg_blocks = seg_blocks;
-  p.S = S;
-  const int parts = pl.parts;
-  p.parts = parts;
-  p.part_blocks = seg_blocks / parts;
-  p.slots = (S - 1) * parts + 1;
-  p.vp = vp;
-  p.fold = pl.fold;
+  const int pdiv = d.P / kP, Hs = d.H * pdiv, parts = pl.parts;
+  auto fill = [&](auto &p) {
+    p.x = static_cast<const uint8_t *>(x);
+    p.C = Cpad != nullptr ? reinterpret_cast<const uint8_t *>(Cpad) : static_cast<const uint8_t *>(C);
+    p.D = D;
+    p.ns = ns;
+    p.Gd = reinterpret_cast<const uint8_t *>(Gd);
+    p.Btr = reinterpret_cast<const uint8_t *>(Btr);
+    p.prep = prep;
+    p.y = static_cast<uint8_t *>(y);
+    p.h0 = h0;
+    p.Hin = seg_state;
+    p.final_state = final_state;
+    p.seg_state = seg_state;
+    p.seg_decay = seg_decay;
+    p.T = d.T;
+    p.H = Hs;
+    p.pdiv = pdiv;
+    p.Hrec = d.H;
+    p.G = d.G;
+    p.hpg = d.hpg * pdiv;
+    p.NB = w.NB;
+    p.seg_blocks = seg_blocks;
+    p.S = S;
+    p.parts = parts;
+    p.part_blocks = seg_blocks / parts;
+    p.slots = (S - 1) * parts + 1;
+    p.vp = vp;
+    p.fold = pl.fold;
+  };
   // no states pass if no sequence can have more than one segment
   const int full_cap = varlen ? full_items(d, w, seg_blocks) : 0;
   if (varlen ? full_cap > 0 : S > 1) {
     // (which sequences of a packed batch have more than one segment is known on the device only: the workgroups of
     // entries that are last segments, or none, leave at once)
+    ScanParams p;
+    fill(p);
     map_to(p, pl.state_heads, (S - 1) * parts, varlen ? full_cap : (S - 1) * parts * d.Bt);
     const dim3 grid(kXcds * p.per_xcd), block(128 * pl.state_heads);
     if (pl.state_heads == 2)
@@ -3195,21 +3228,24 @@ hipError_t launch_slice(const Dims &d, const NSlice ns, const int32_t *cu, const
                          dim3(kThreads), 0, stream, seg_state, seg_decay, h0, p.slots, Hs, rows_bh, vp, ns);
     if (!p.fold) trace_mark(trace, stream, "segment_pass");
   }
-  const int scan_heads = pl.listed ? 2 : pl.heads;
-  map_to(p, scan_heads, S, varlen ? items : S * d.Bt);
-  const bool lists = pl.listed;
-  const dim3 grid(lists ? kNumCUs : kXcds * p.per_xcd), block(128 * scan_heads);
-  if (scan_heads == 2) {
-    auto *const kernel = add_to_y ? (lists ? pair_scan_kernel<kYAdd, true> : pair_scan_kernel<kYAdd, false>)
-                         : stream_y(d, rows) ? (lists ? pair_scan_kernel<kYStream, true> : pair_scan_kernel<kYStream, false>)
-                                             : (lists ? pair_scan_kernel<kYPlain, true> : pair_scan_kernel<kYPlain, false>);
-    hipLaunchKernelGGL(kernel, grid, dim3(512), 0, stream, p);
-  } else if (add_to_y) {
-    hipLaunchKernelGGL((chunk_scan_kernel<false, kHeadsPerWg, kYAdd>), grid, block, 0, stream, p);
-  } else if (stream_y(d, rows)) {
-    hipLaunchKernelGGL((chunk_scan_kernel<false, kHeadsPerWg, kYStream>), grid, block, 0, stream, p);
+  const int scan_items = varlen ? items : S * d.Bt;
+  if (pl.listed || pl.heads == 2) {
+    PairParams p;
+    fill(p);
+    p.prep_bytes = static_cast<uint32_t>(w.off_state - w.off_prep);
+    map_to(p, 2, S, scan_items);
+    auto *const kernel = add_to_y ? (pl.listed ? pair_scan_kernel<kYAdd, true> : pair_scan_kernel<kYAdd, false>)
+                         : stream_y(d, rows) ? (pl.listed ? pair_scan_kernel<kYStream, true> : pair_scan_kernel<kYStream, false>)
+                                             : (pl.listed ? pair_scan_kernel<kYPlain, true> : pair_scan_kernel<kYPlain, false>);
+    hipLaunchKernelGGL(kernel, dim3(pl.listed ? kNumCUs : kXcds * p.per_xcd), dim3(512), 0, stream, p);
   } else {
-    hipLaunchKernelGGL((chunk_scan_kernel<false, kHeadsPerWg>), grid, block, 0, stream, p);
+    ScanParams p;
+    fill(p);
+    map_to(p, kHeadsPerWg, S, scan_items);
+    auto *const kernel = add_to_y              ? chunk_scan_kernel<false, kHeadsPerWg, kYAdd>
+                         : stream_y(d, rows) ? chunk_scan_kernel<false, kHeadsPerWg, kYStream>
+                                             : chunk_scan_kernel<false, kHeadsPerWg, kYPlain>;
+    hipLaunchKernelGGL(kernel, dim3(kXcds * p.per_xcd), dim3(128 * kHeadsPerWg), 0, stream, p);
   }
   trace_mark(trace, stream, "chunk_scan");
   return hipGetLastError();
