@@ -2988,15 +2988,13 @@ bool stream_y(const Dims &d, int rows) {
 int full_items(const Dims &d, const Layout &w, int seg_blocks) { return (w.NB - d.Bt - 1) / seg_blocks; }
 int list_items(const Dims &d, const Layout &w, int seg_blocks) { return d.Bt + full_items(d, w, seg_blocks); }
 
-// d: plain batch (cu == nullptr), or Bt = number of sequences and T = total tokens of a packed batch.
-// One state slice ns (see NSlice): y and final_state columns of that slice are written.
+// Whether items can be dealt: that walk addresses the decay records by 32-bit offsets.
+bool deal_possible(const Layout &w) { return w.off_state - w.off_prep < 0xFFFF0000ull; }
+bool packed_uncut(const Dims &d, const SlicePlan &pl);
+bool packed_two(const Dims &d);
 // How a call is cut up: blocks per segment, segments per sequence (0 for a packed batch, where the
 // device-side tables hold them per sequence), pieces per segment of the states-only pass, and whether the
 // full scan sums the chain over state slots itself (ScanParams::fold).
-// Whether the two-head scan can be used: it addresses the decay records by 32-bit offsets.
-bool two_possible(const Layout &w) { return w.off_state - w.off_prep < 0xFFFF0000ull; }
-bool packed_uncut(const Dims &d, const SlicePlan &pl);
-bool packed_two(const Dims &d);
 SlicePlan plan_slice(const Dims &d, bool varlen, bool h0_aliases_final_state) {
   const Layout w = make_layout(d, varlen);
   Dims one = d;  // the segment length of a packed batch is chosen as for one sequence of all its tokens
@@ -3005,10 +3003,10 @@ SlicePlan plan_slice(const Dims &d, bool varlen, bool h0_aliases_final_state) {
   const Knobs &kn = knobs();
   pl.two = 0;
   pl.state_heads = kn.scan_heads == 2 ? 2 : kHeadsPerWg;
-  pl.heads = two_possible(w) ? pl.state_heads : kHeadsPerWg;
+  pl.heads = pl.state_heads;
   // two heads per workgroup (see small_grid)
   const bool may_choose = kn.scan_heads == 0 && kn.seg_chunks == 0 && kn.seg_blocks == 0 && kn.seg_parts == 0;
-  const bool may_two = kn.scan_heads == 0 && two_possible(w);
+  const bool may_two = kn.scan_heads == 0;
   int two_parts = 1;
   const int two = !varlen && may_choose && may_two ? two_head_blocks(d, (w.NB + w.S_max - 1) / w.S_max, w.S_max, &two_parts) : 0;
   // shortest segment: a chunk for a packed batch; what the state slots allow for a plain one
@@ -3034,7 +3032,7 @@ SlicePlan plan_slice(const Dims &d, bool varlen, bool h0_aliases_final_state) {
   // Items are dealt where the sequences alone are more than a round of workgroups of two heads (of 120 drawn batches those need 0.87 of
   // the time of an entry to a workgroup, with two or four heads; 1.06 at worst).  Up to a round dealing has nothing to even out
   // and its walk costs 1 to 8 %.
-  pl.listed = varlen && two_possible(w) && (kn.deal == 1 || (may_two && kn.deal == 0 && static_cast<long>(d.Bt) * head_groups(d, 2) > kNumCUs));
+  pl.listed = varlen && deal_possible(w) && (kn.deal == 1 || (may_two && kn.deal == 0 && static_cast<long>(d.Bt) * head_groups(d, 2) > kNumCUs));
   if (pl.from_lengths) {
     if (may_two && packed_two(d)) pl.heads = pl.state_heads = 2;
     if (packed_uncut(d, pl)) {
@@ -3132,6 +3130,8 @@ void map_to(ScanParamsOf<kPair> &p, int heads, int segs, int items) {
   }
 }
 
+// d: plain batch (cu == nullptr), or Bt = number of sequences and T = total tokens of a packed batch.
+// One state slice ns (see NSlice): y and final_state columns of that slice are written.
 hipError_t launch_slice(const Dims &d, const NSlice ns, const int32_t *cu, const void *x, const float *dt,
                         const float *A, const void *B, const void *C, const float *D, const float *h0, void *y,
                         bool add_to_y, float *final_state, void *workspace, hipStream_t stream, KernelTrace *trace) {

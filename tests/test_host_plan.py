@@ -77,6 +77,14 @@ def test_knobs_and_aliasing_change_the_plan():
     assert ssd.prefill_plan(c0)["f32_segments"] == 8
 
 
+def test_two_heads_whatever_the_records_take():
+    """Decay records of 4 GiB and more (16 prompts of 1030000 tokens, 32 heads) keep the round of two-head workgroups that any other
+    batch of one round takes: only a walk over several items addresses records by 32-bit offsets."""
+    sh = ssd.make_shape(16, 1030000, 32, 64, 128, 1, 256, torch.bfloat16)
+    assert 16 * 32 * ((1030000 + 63) // 64) * 132 * 4 > 1 << 32
+    assert ssd.prefill_pair_plan(sh) == dict(seg_blocks=16094, segments=1, parts=1, fold=False, heads=2, state_heads=2)
+
+
 def test_the_store_policy_of_y_is_no_part_of_the_plan():
     """How y leaves is chosen per launch; the knob that forces it compares two policies of the kernel that is taken, not two
     kernels."""
