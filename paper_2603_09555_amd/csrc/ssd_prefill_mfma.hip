@@ -199,6 +199,7 @@ __device__ __forceinline__ int owner_of(const int32_t *__restrict__ first, int n
 // ones fill the gaps; and the states-only pass, which needs no last segment, takes a prefix of the
 // list.  Sequence q has item0[q] - q non-last segments before it.
 constexpr int kSortMax = 2048;
+__host__ __device__ inline bool list_sorted(int nseq, int seg_blocks) { return nseq <= kSortMax && seg_blocks < 32768; }
 __global__ __launch_bounds__(256) void varlen_fill_kernel(const int32_t *__restrict__ blk0,
                                                           const int32_t *__restrict__ item0, int nseq,
                                                           int seg_blocks, int32_t *__restrict__ blk_seq,
@@ -216,7 +217,7 @@ __global__ __launch_bounds__(256) void varlen_fill_kernel(const int32_t *__restr
   }
   // (no early return above: the barrier below is reached by every thread)
   __shared__ int16_t last_blocks[kSortMax];  // blocks in the last segment of every sequence (<= seg_blocks)
-  const bool sort = nseq <= kSortMax && seg_blocks < 32768;
+  const bool sort = list_sorted(nseq, seg_blocks);
   const bool ranks_here = static_cast<int>(blockIdx.x) * 256 < n_items && static_cast<int>(blockIdx.x) * 256 + 256 > n_full;
   if (sort && ranks_here)
     for (int k = threadIdx.x; k < nseq; k += 256)
@@ -2991,6 +2992,7 @@ int list_items(const Dims &d, const Layout &w, int seg_blocks) { return d.Bt + f
 // Whether items can be dealt: that walk addresses the decay records by 32-bit offsets.
 bool deal_possible(const Layout &w) { return w.off_state - w.off_prep < 0xFFFF0000ull; }
 bool packed_uncut(const Dims &d, const SlicePlan &pl);
+bool packed_dealt(const Dims &d, int seg_blocks);
 bool packed_two(const Dims &d);
 // How a call is cut up: blocks per segment, segments per sequence (0 for a packed batch, where the
 // device-side tables hold them per sequence), pieces per segment of the states-only pass, and whether the
@@ -3029,10 +3031,7 @@ SlicePlan plan_slice(const Dims &d, bool varlen, bool h0_aliases_final_state) {
   // (the lengths of several sequences are known on the device only; see segment_choice)
   pl.from_lengths = varlen && d.Bt > 1 && d.Bt <= kTableThreads && w.NB <= kTableBlocks && list_items(d, w, pl.seg_blocks) <= kTableBlocks &&
                     kn.seg_chunks == 0 && kn.seg_blocks == 0 && full_items(d, w, pl.seg_blocks) > 0;
-  // Items are dealt where the sequences alone are more than a round of workgroups of two heads (of 120 drawn batches those need 0.87 of
-  // the time of an entry to a workgroup, with two or four heads; 1.06 at worst).  Up to a round dealing has nothing to even out
-  // and its walk costs 1 to 8 %.
-  pl.listed = varlen && deal_possible(w) && (kn.deal == 1 || (may_two && kn.deal == 0 && static_cast<long>(d.Bt) * head_groups(d, 2) > kNumCUs));
+  pl.listed = varlen && deal_possible(w) && (kn.deal == 1 || (may_two && kn.deal == 0 && packed_dealt(d, pl.seg_blocks)));
   if (pl.from_lengths) {
     if (may_two && packed_two(d)) pl.heads = pl.state_heads = 2;
     if (packed_uncut(d, pl)) {
@@ -3075,6 +3074,20 @@ SegChoice segment_choice(const Dims &d, const SlicePlan &pl) {
   c.fill = static_cast<float>(groups) / kNumCUs;
   c.slices = static_cast<float>(d.H) * (d.P / kP);
   return c;
+}
+
+// Whether the scan's workgroups are dealt items (see Deal), by what the sequences alone come to in rounds of two-head
+// workgroups.  Up to a round there is nothing to even out.  Beyond, of 420 drawn batches of up to four rounds (microseconds, an entry to a
+// workgroup over dealt; ragged, equal lengths, one or a few long ones among short): entries of more than 16 workgroups 1.03 to
+// 1.05 for ragged ones up to two rounds and 1.15 to 1.22 beyond 32, more of both after; smaller ones 0.94 to 0.97 up to 1.75
+// rounds (27 ragged sequences, 3923 tokens x 20 heads in four groups, dstate 256: 72.9, dealt 80.0), 1.01 to 1.14 after.  What is lost: equal lengths
+// up to 1.75 rounds 0.92 to 0.98, which four heads to a workgroup serve in one; a few items beside which all others are short
+// 0.85 at worst, because everyone is dealt as many (56 sequences, 5005 tokens, 7 of them 554 long, x 74 heads 92, dealt 103).
+// Only a sorted list is dealt: of one in the caller's order, 2500 sequences x 8 heads with a long one in every 64, the same
+// workgroups got all the long ones (430 us, dealt 639).
+bool packed_dealt(const Dims &d, int seg_blocks) {
+  const int groups2 = head_groups(d, 2);
+  return list_sorted(d.Bt, seg_blocks) && 4l * d.Bt * groups2 > (groups2 > 16 ? 4 : 7) * kNumCUs;
 }
 
 // Whether a packed batch takes two heads per workgroup (see small_grid).  Its lengths are known on the device only, so the

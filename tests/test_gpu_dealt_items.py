@@ -75,7 +75,7 @@ def test_dealt_items_equal_an_entry_each(ssd, name):
     assert_close(out[1][1], st_ref, TOL["bf16"], "final states")
 
 
-@pytest.mark.parametrize("H, n", [(34, 30), (3, 200)])
+@pytest.mark.parametrize("H, n", [(34, 30), (3, 230)])
 def test_the_library_deals_items_beyond_a_round(ssd, H, n):
     """As it runs by itself: the segment length from the device, changing lengths in one workspace, again and again."""
     T, cfg = 3000, inputs.SSDConfig("t", 1, 3000, H, 64, 128, 1, 64, "bf16")

@@ -72,3 +72,34 @@ def test_heads_per_workgroup_of_a_packed_batch(lengths, heads, groups, two):
     them and long ones (16 ragged sequences, 16384 tokens, 80 heads: 154, four heads 169).  Whatever the lengths: what one
     long prompt might lose (113 us, four heads 97) is less than what equal ones would (4 x 1676 x 88 heads: 63, four heads 95)."""
     assert plan(lengths, heads, groups)["heads"] == (2 if two else 4)
+
+
+@pytest.mark.parametrize("nseq, heads, groups, dealt", [
+    (7, 66, 1, False), (8, 66, 1, True),         # entries of 33 workgroups: more than a round of 256
+    (4, 128, 1, False), (5, 128, 1, True),       # exactly a round of 64 each
+    (15, 34, 1, False), (16, 34, 1, True),       # 17 each
+    (27, 20, 4, False), (37, 20, 4, False), (38, 20, 4, True),   # 12 each: more than seven quarters of a round, 448
+    (28, 32, 1, False), (29, 32, 1, True),       # 16 each, exactly 448
+    (448, 2, 1, False), (449, 2, 1, True), (2048, 2, 1, True),
+    (2049, 2, 1, False), (5000, 8, 1, False),    # beyond 2048 sequences the list is in the caller's order
+], ids=lambda v: str(v))
+def test_which_packed_batches_are_dealt_items(nseq, heads, groups, dealt):
+    lengths = [1 + 37 * i % 300 for i in range(nseq)]
+    assert plan(lengths, heads, groups)["dealt"] == dealt
+    ssd.set_knob("deal", 1)
+    assert plan(lengths, heads, groups)["dealt"]
+    ssd.set_knob("deal", 2)
+    assert not plan(lengths, heads, groups)["dealt"]
+    ssd.set_knob("deal", 0)
+    ssd.set_knob("scan_heads", 4)
+    assert not plan(lengths, heads, groups)["dealt"]
+
+
+def test_records_beyond_32_bits_are_not_dealt():
+    """4 GiB of decay records and more, which the dealt walk could not address, whatever the knob says."""
+    ssd.set_knob("deal", 1)
+    assert plan([1] * 2000, 64)["dealt"]
+    big = [1] * 60000   # x 200 heads, a record of 528 bytes each
+    assert not plan(big, 200)["dealt"]
+    ssd.reset_knobs()
+    assert not plan(big, 200)["dealt"]
