@@ -2119,21 +2119,20 @@ __device__ __forceinline__ void pair_feed(const PairParams &p, Items<kList> item
   // (The order is held by fences where there are several items, 64 ragged sequences, 16384 tokens, 80 heads 156.7 -> 156.0 us, 16 of
   // them 122.9 -> 120.4; in the walk of one item they cost a block up to 150 cycles: 7 x 826 tokens x 23 heads 29.5, 28.4 without, 8 x
   // 4096 x 48 120.5, 117.4.)
-  auto fence = []() __attribute__((always_inline)) { if constexpr (kList) __builtin_amdgcn_sched_barrier(0); };
   auto block = [&](uint32_t par, bool first, auto &&y, auto &&tiles, auto &&x) __attribute__((always_inline)) {
     read_y(x_prev);
     if (first) __syncthreads();  // an item's first block: its tiles and Xm^T are visible, the other tile buffer is free of states
-    fence();  // (requests first: the compiler would put all of the block's addresses before them)
+    if constexpr (kList) __builtin_amdgcn_sched_barrier(0);  // (requests first: the compiler would put all of the block's addresses before them)
     tiles(par ^ 1);
-    fence();
+    if constexpr (kList) __builtin_amdgcn_sched_barrier(0);
     if constexpr (kYMode == kYAdd) add_y(y());
     asm volatile("" : "+v"(yo[0]), "+v"(yo[1]), "+v"(yo[2]), "+v"(yo[3])::"memory");  // (read before x is requested into its place)
     asm volatile("s_waitcnt vmcnt(14)" ::: "memory");  // x of the next block; younger: the stores before, tiles
     read_turn(x_next, par * L::kRecBuf);
     x(x_prev);
-    fence();
+    if constexpr (kList) __builtin_amdgcn_sched_barrier(0);
     turn((par ^ 1) * (2 * L::kXmHead));
-    fence();
+    if constexpr (kList) __builtin_amdgcn_sched_barrier(0);
     const Rsrc ry = y();
 #pragma unroll
     for (int k = 0; k < 4; ++k) store_y(ry, k);
