@@ -42,8 +42,8 @@ typedef enum {
                                  value: library's choice */
   SSD_KNOB_CHUNK = 10,         /* bf16 prefill of a plain batch by the chunk kernels: 1 wherever they can run, 2 never; 0:
                                  library's choice */
-  SSD_KNOB_DEAL = 11           /* packed bf16 batches: 1 the full scan's workgroups are dealt items of two heads, however few these are, 2
-                                 they take an entry each; 0: library's choice */
+  SSD_KNOB_DEAL = 11           /* packed bf16 batches: 1 the full scan's workgroups are dealt items of two heads, however few
+                                 these are, unless the decay records take 4 GiB; 2 they take an entry each; 0: library's choice */
 } ssd_knob;
 
 /* Sets one knob.  Errors: SSD_ERR_SHAPE for an unknown knob. */
@@ -75,8 +75,9 @@ SSD_API int32_t ssd_testing_prefill_chunks(const ssd_shape *shape, int32_t h0_al
 
 /* How ssd_prefill_varlen would cut up a packed batch of these boundaries (a HOST array here) under the current knobs, on
  * the bf16 MFMA kernels.  plan[1] 64-token blocks per segment, which the device chooses from the boundaries, plan[2]
- * segments of the whole batch, plan[3] the shortest segment it may choose, plan[4] 1 if there is a choice, plan[5] 1 if the full scan's
- * workgroups are dealt items of two heads (then plan[6] is what an entry of the list would be served with otherwise), plan[6] and plan[7] as above; plan[0] and all others 0 for a call that runs on the generic kernels.
+ * segments of the whole batch, plan[3] the shortest segment it may choose, plan[4] 1 if there is a choice, plan[5] 1 if
+ * the full scan's workgroups are dealt items of two heads, plan[6] and plan[7] as above; plan[0] and all others 0 for a
+ * call that runs on the generic kernels.
  * Errors: SSD_ERR_NULL; the shape errors of ssd_prefill_varlen; SSD_ERR_SHAPE for boundaries it would reject. */
 SSD_API ssd_status ssd_testing_varlen_plan(const ssd_shape *shape, const int32_t *cu_seqlens, int32_t plan[8]);
 

@@ -214,10 +214,10 @@ struct VarPlan {
 struct SegChoice {
   static constexpr int kMost = 32;
   int cand[kMost];
-  int count, heads, max_items;  // head slices per workgroup of the scan; list entries that still run side by side
-  float fill, slices;           // share of the chip that one entry's workgroups take; 64-column slices of all heads
-  bool dealt;                   // the scan's workgroups are dealt items (then fill is an entry's share of a round of these)
-  float state_fill;             // the states-only pass's fill
+  int count, max_items;  // list entries that still run side by side
+  float fill, slices;    // share of the chip that one entry's workgroups take; 64-column slices of all heads
+  bool dealt;            // the scan's workgroups are dealt items (then fill is an entry's share of a round of these)
+  float state_fill;      // the states-only pass's fill
 };
 void launch_varlen_tables(const int32_t *cu, int total, int blk_len, const SegChoice &choice, int item_cap, const VarPlan &vp,
                           hipStream_t stream);

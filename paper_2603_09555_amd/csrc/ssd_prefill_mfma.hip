@@ -252,12 +252,11 @@ __device__ __forceinline__ int wave_reduce(int v, Op op) {
 // Modelled time (us) of a packed batch of `nseq` sequences, `blocks` blocks in all and `longest` in the longest, cut into
 // segments of s blocks, `items` of them.  The scan: the busiest CU's load -- a workgroup's start counts as some blocks --
 // and the longest walk; with segments that are not the last of their sequence also the states-only pass, the same way, and
-// the chain.  Fitted to 240 drawn batches (2 to 128 sequences, 380 to 16500 tokens, 4 to 80 heads; ragged, equal, one or a
-// few long among short ones) at every length from the host's shortest on (9 % rms, the choice 2.2 % behind the fastest of
-// the timed plans), for two heads to 70 others (2 to 64 sequences, 740 to 29700 tokens, 4 to 102 heads) at eight lengths each: 7
-// % rms, with its choice the 35 that four heads had served take 0.85 of that time.  Against the length of one sequence of all the tokens: 1.07 in the geometric mean.  A length
+// the chain.  An entry to a workgroup: fitted to 70 drawn batches (2 to 64 sequences, 740 to 29700 tokens, 4 to 102 heads; ragged,
+// equal, one or a few long among short ones) at eight lengths each, from the host's shortest on, 7 % rms.  (Four heads to a workgroup, which only a
+// test asks for, go by the same.)  A length
 // guessed on the host cannot serve both a ragged batch and one long prompt among short ones: the guess of four times the
-// mean left 8192 + 63 x 1 tokens x 24 heads uncut, 322 us (now 75; 89 with the length of one sequence).
+// mean left 8192 + 63 x 1 tokens x 24 heads uncut, 322 us (now 74; 89 with the length of one sequence).
 // Dealt items (see Deal), fitted to 400 batches of more than a round of these (draws, equal lengths, one or a few long among short ones), 1150
 // timings at up to eight lengths, 10 % rms.  The deal in rounds is less even than the model has it where a few items are long: of
 // lengths within 5 % of the cheapest the shortest is taken, which is 1.1 % behind the fastest timed in the geometric mean, 19 % at worst.
@@ -270,12 +269,9 @@ __host__ __device__ inline float packed_cost(const SegChoice &c, int s, int bloc
   if (c.dealt) {
     us = 21.8f + 1.57f * both((blocks + 3.6f * n) * c.fill, walk);
     if (items > nseq) us += 0.0376f * full * c.slices + 0.69f * len * both(1.f, full * c.state_fill);
-  } else if (c.heads == 2) {
+  } else {
     us = 15.f + (1.13f + 0.24f * grid) * both((blocks + 3.9f * n) * c.fill, walk + 3.9f);
     if (items > nseq) us += 0.0123f * full * c.slices + 0.82f * (len + 6.4f) * both(1.f, full * c.fill);
-  } else {
-    us = 10.4f + (2.36f + 0.23f * grid) * both((blocks + 5.1f * n) * c.fill, walk + 5.1f);
-    if (items > nseq) us += 0.025f * full * c.slices + 0.76f * (len + 7.2f) * both(1.f, full * c.fill);
   }
   return items > c.max_items ? 1.25f * us : us;
 }
@@ -2992,7 +2988,7 @@ int list_items(const Dims &d, const Layout &w, int seg_blocks) { return d.Bt + f
 bool deal_possible(const Layout &w) { return w.off_state - w.off_prep < 0xFFFF0000ull; }
 bool packed_uncut(const Dims &d, const SlicePlan &pl);
 bool packed_dealt(const Dims &d, int seg_blocks);
-bool packed_two(const Dims &d);
+bool dealt_states_two(const Dims &d);
 // How a call is cut up: blocks per segment, segments per sequence (0 for a packed batch, where the
 // device-side tables hold them per sequence), pieces per segment of the states-only pass, and whether the
 // full scan sums the chain over state slots itself (ScanParams::fold).
@@ -3031,8 +3027,11 @@ SlicePlan plan_slice(const Dims &d, bool varlen, bool h0_aliases_final_state) {
   pl.from_lengths = varlen && d.Bt > 1 && d.Bt <= kTableThreads && w.NB <= kTableBlocks && list_items(d, w, pl.seg_blocks) <= kTableBlocks &&
                     kn.seg_chunks == 0 && kn.seg_blocks == 0 && full_items(d, w, pl.seg_blocks) > 0;
   pl.listed = varlen && deal_possible(w) && (kn.deal == 1 || (may_two && kn.deal == 0 && packed_dealt(d, pl.seg_blocks)));
+  if (pl.listed) pl.heads = 2;
   if (pl.from_lengths) {
-    if (may_two && packed_two(d)) pl.heads = pl.state_heads = 2;
+    // (what is not dealt comes to hardly more than a round of workgroups of two heads, see small_grid)
+    if (may_two) pl.heads = 2;
+    if (may_two && (!pl.listed || dealt_states_two(d))) pl.state_heads = 2;
     if (packed_uncut(d, pl)) {
       pl.from_lengths = false;
       pl.seg_blocks = w.NB - d.Bt;
@@ -3065,9 +3064,8 @@ SegChoice segment_choice(const Dims &d, const SlicePlan &pl) {
     const int last = c.cand[c.count - 1], next = static_cast<int>(last * ratio + 0.5);
     c.cand[c.count++] = next > last ? (next < nblocks ? next : nblocks) : last + 1;
   }
-  c.heads = pl.heads;
   c.dealt = pl.listed;
-  const int groups = head_groups(d, pl.listed ? 2 : pl.heads);
+  const int groups = head_groups(d, pl.heads);
   c.max_items = pl.heads == 2 && !pl.listed ? kNumCUs / groups : 0x7fffffff;
   c.state_fill = static_cast<float>(head_groups(d, pl.state_heads)) / kNumCUs;
   c.fill = static_cast<float>(groups) / kNumCUs;
@@ -3089,23 +3087,14 @@ bool packed_dealt(const Dims &d, int seg_blocks) {
   return list_sorted(d.Bt, seg_blocks) && 4l * d.Bt * groups2 > (groups2 > 16 ? 4 : 7) * kNumCUs;
 }
 
-// Whether a packed batch takes two heads per workgroup (see small_grid).  Its lengths are known on the device only, so the
-// rule is on what the sequences alone come to: a round of such workgroups or less; up to three if a list entry has at
-// most 32 of them (of larger ones too few fit side by side to even out a ragged batch: 7 sequences, 4821 tokens, 91 heads 102
-// us, four heads 85), or at most 48, more than two rounds and fifteen blocks a CU (16 ragged sequences, 16384 tokens, 80
-// heads 154, four heads 169).  Of 2000 drawn batches -- equal, ragged, one or a few long among short ones -- the 1596 taken
-// need 0.84 of the time of four heads, 41 of them more than 3 % more, 8.6 % at worst; of 420 at 66 to 128 heads and one
-// to three rounds the 67 taken 0.93 (six 4 to 10 % more), the others 0.99 (a quarter more than 3 % more, 22 % at worst).  To
-// ask the models whether one long prompt among rows of a token would lose spares some of these 3 to 10 %, and one of 17 (17
-// sequences, 16113 tokens, of which 14417 in one, 28 heads 113 us, four heads 97), but costs one batch in ten 3 to 50 % (4 x 1676
-// x 88 heads 63, four heads 95).  4 sequences, 5040 tokens, 96 heads 80 -> 53 us.
-bool packed_two(const Dims &d) {
+// Whether the states-only pass of a dealt batch has two heads per workgroup.  They are faster if its entries -- the segments that
+// are not the last of their sequence, which only the device knows -- come to a round of them (of 160 dealt batches with long
+// sequences among short ones 78 are 1.01 to 1.09 times as fast as with four), and slower beyond (38 of them 0.91 to 0.99).  They are expected to be
+// few up to ten blocks a CU, and up to three rounds of small entries.  By this rule the 160 are 1.014 times as fast as with four
+// heads throughout (1.010 with two throughout, 28 of them slower than with four).
+bool dealt_states_two(const Dims &d) {
   const int groups2 = head_groups(d, 2), nblocks = (d.T + kBlk - 1) / kBlk;
-  const long first = static_cast<long>(d.Bt) * groups2;  // workgroups of uncut sequences
-  if (first <= kNumCUs) return true;
-  if (first > 3 * kNumCUs) return false;
-  return groups2 <= kNumCUs / 8 ||
-         (first > 2 * kNumCUs && groups2 <= 48 && static_cast<long>(nblocks) * groups2 >= 15 * kNumCUs);
+  return static_cast<long>(nblocks) * groups2 < 10 * kNumCUs || (groups2 <= kNumCUs / 8 && static_cast<long>(d.Bt) * groups2 <= 3 * kNumCUs);
 }
 
 // Whether a short packed batch is left uncut, whatever its lengths: cutting it, or the chance of it, costs the launches of
@@ -3241,7 +3230,7 @@ hipError_t launch_slice(const Dims &d, const NSlice ns, const int32_t *cu, const
     if (!p.fold) trace_mark(trace, stream, "segment_pass");
   }
   const int scan_items = varlen ? items : S * d.Bt;
-  if (pl.listed || pl.heads == 2) {
+  if (pl.heads == 2) {
     PairParams p;
     fill(p);
     p.prep_bytes = static_cast<uint32_t>(w.off_state - w.off_prep);

@@ -59,19 +59,29 @@ def test_plans_stay_within_what_the_host_sized():
     assert not p["chosen"] and p["seg_blocks"] == p["shortest"] == 7
 
 
-@pytest.mark.parametrize("lengths, heads, groups, two", [([1710] + 6 * [518], 91, 1, False), ([3222, 158] + 6 * [1215], 80, 4, False),
-                                                         (16 * [19] + [2691], 65, 1, False), (4 * [1260], 96, 1, True), (5 * [500], 64, 1, True),
-                                                         (40 * [250], 16, 1, True), (30 * [300], 24, 1, True), (17 * [105] + [14417], 28, 4, True),
-                                                         (64 * [256], 80, 1, False), ([700 + 40 * i for i in range(16)], 80, 1, True),
-                                                         (16 * [1024], 100, 1, False), (16 * [256], 80, 1, False),
-                                                         (12 * [1024], 80, 1, False), (4 * [1676], 88, 2, True),
-                                                         ([14161, 9290], 60, 4, True)], ids=lambda v: str(v)[:20])
-def test_heads_per_workgroup_of_a_packed_batch(lengths, heads, groups, two):
-    """Two where the sequences are a round of the chip, or a few of list entries that are small beside it: entries of an eighth
-    of the chip and more leave a ragged batch uneven (7 sequences, 91 heads: 102 us, four heads 85) unless there are many of
-    them and long ones (16 ragged sequences, 16384 tokens, 80 heads: 154, four heads 169).  Whatever the lengths: what one
-    long prompt might lose (113 us, four heads 97) is less than what equal ones would (4 x 1676 x 88 heads: 63, four heads 95)."""
-    assert plan(lengths, heads, groups)["heads"] == (2 if two else 4)
+@pytest.mark.parametrize("lengths, heads, groups, dealt", [([1710] + 6 * [518], 91, 1, True), ([3222, 158] + 6 * [1215], 80, 4, True),
+                                                           (16 * [19] + [2691], 65, 1, True), (4 * [1260], 96, 1, False), (5 * [500], 64, 1, False),
+                                                           (40 * [250], 16, 1, False), (30 * [300], 24, 1, False), (17 * [105] + [14417], 28, 4, False),
+                                                           (64 * [256], 80, 1, True), ([700 + 40 * i for i in range(16)], 80, 1, True),
+                                                           (16 * [1024], 100, 1, True), (16 * [256], 80, 1, True), (47 * [256], 32, 1, True), (49 * [700], 32, 1, True),
+                                                           (12 * [1024], 80, 1, True), (4 * [1676], 88, 2, False),
+                                                           ([14161, 9290], 60, 4, False)], ids=lambda v: str(v)[:20])
+def test_kernels_of_a_packed_batch_whose_lengths_choose(lengths, heads, groups, dealt):
+    """Two heads per workgroup, dealt or an entry each, are what is left for a batch of more blocks than a segment has at least.  The
+    states-only pass has two as well, unless the batch is dealt and of ten blocks a CU and more (and of entries of more than 32
+    workgroups, or more than three rounds)."""
+    p = plan(lengths, heads, groups)
+    groups2, blocks = groups * -(-heads // groups // 2), (sum(lengths) + 63) // 64
+    two = not dealt or blocks * groups2 < 2560 or (groups2 <= 32 and len(lengths) * groups2 <= 768)
+    assert (p["heads"], p["state_heads"], p["dealt"]) == (2, 2 if two else 4, dealt)
+
+
+@pytest.mark.parametrize("lengths, heads, heads_per_wg", [(17 * [4], 32, 4), (16 * [4], 32, 2), ([100], 80, 2), (2100 * [3], 1, 4), (250 * [3], 1, 2)],
+                         ids=lambda v: str(v)[:20])
+def test_heads_per_workgroup_without_a_choice_of_lengths(lengths, heads, heads_per_wg):
+    """An entry each, and no length to choose -- too few blocks to cut, one sequence, or more than 1024: two heads up to a round."""
+    p = plan(lengths, heads)
+    assert not p["chosen"] and not p["dealt"] and p["heads"] == heads_per_wg
 
 
 @pytest.mark.parametrize("nseq, heads, groups, dealt", [
@@ -87,7 +97,8 @@ def test_which_packed_batches_are_dealt_items(nseq, heads, groups, dealt):
     lengths = [1 + 37 * i % 300 for i in range(nseq)]
     assert plan(lengths, heads, groups)["dealt"] == dealt
     ssd.set_knob("deal", 1)
-    assert plan(lengths, heads, groups)["dealt"]
+    p = plan(lengths, heads, groups)
+    assert p["dealt"] and p["heads"] == 2
     ssd.set_knob("deal", 2)
     assert not plan(lengths, heads, groups)["dealt"]
     ssd.set_knob("deal", 0)
