@@ -42,8 +42,9 @@ typedef enum {
                                  value: library's choice */
   SSD_KNOB_CHUNK = 10,         /* bf16 prefill of a plain batch by the chunk kernels: 1 wherever they can run, 2 never; 0:
                                  library's choice */
-  SSD_KNOB_DEAL = 11           /* packed bf16 batches: 1 the full scan's workgroups are dealt items of two heads, however few
+  SSD_KNOB_DEAL = 11,          /* packed bf16 batches: 1 the full scan's workgroups are dealt items of two heads, however few
                                  these are, unless the decay records take 4 GiB; 2 they take an entry each; 0: library's choice */
+  SSD_KNOB_SPLIT_IMAGES = 12   /* fp32 io on split operands: 2 no images of blocks; 0: library's choice */
 } ssd_knob;
 
 /* Sets one knob.  Errors: SSD_ERR_SHAPE for an unknown knob. */
@@ -60,7 +61,8 @@ SSD_API void ssd_testing_reset_knobs(void);
  * whose h0 and final_state share memory, which rules that out), plan[6] and plan[7] head slices per
  * workgroup of the full scan and of the states-only pass.  For the fp32 MFMA family: plan[5] time
  * segments per sequence on fp32 MFMA, or 0 on split operands, and then plan[1] 32-token blocks in the longest
- * segment, plan[2] segments, plan[3] workgroups that share one.  The other entries are zero.
+ * segment, plan[2] segments, plan[3] workgroups that share one, plan[6] 1 if images of the blocks are made for all heads,
+ * plan[7] 1 if the states between the launches lie in y.  The other entries are zero.
  * Errors: SSD_ERR_NULL; the shape errors of ssd_prefill. */
 SSD_API ssd_status ssd_testing_prefill_plan(const ssd_shape *shape, int32_t h0_aliases_final_state,
                                             int32_t plan[8]);

@@ -150,7 +150,7 @@ ssd_status ssd_testing_prefill_plan(const ssd_shape *shape, int32_t h0_aliases_f
     plan[7] = pl.state_heads;
   } else if (use_split_f32(d)) {
     plan[0] = 2;
-    ssd::split_f32_plan(d, &plan[1], &plan[2], &plan[3]);
+    ssd::split_f32_plan(d, &plan[1], &plan[2], &plan[3], &plan[6], &plan[7]);
   } else if (use_mfma_f32(d)) {
     plan[0] = 2;
     plan[5] = ssd::mfma_f32_time_segments(d);
@@ -452,6 +452,7 @@ ssd_status ssd_testing_set_knob(int32_t knob, int32_t value) {
     case SSD_KNOB_FOLD_MAX_SLOTS: k.fold_max_slots = value > 0 ? value : 0; return SSD_OK;
     case SSD_KNOB_CHUNK: k.chunk = value == 1 || value == 2 ? value : 0; return SSD_OK;
     case SSD_KNOB_DEAL: k.deal = value == 1 || value == 2 ? value : 0; return SSD_OK;
+    case SSD_KNOB_SPLIT_IMAGES: k.split_images = value == 2 ? 2 : 0; return SSD_OK;
     case SSD_KNOB_SCAN_HEADS: k.scan_heads = value == 2 || value == 4 ? value : 0; return SSD_OK;
     default: return SSD_ERR_SHAPE;
   }

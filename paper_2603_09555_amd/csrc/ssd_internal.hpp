@@ -132,6 +132,7 @@ struct Knobs {
   int f32_segments = 0;    // > 0: time segments per sequence in the fp32 MFMA kernel
   int scan_heads = 0;      // 2 / 4: head slices per workgroup in the bf16 scan; 0: library's choice
   int deal = 0;            // packed bf16 batches: 1 items dealt to the scan's workgroups, 2 an entry each; 0: library's choice
+  int split_images = 0;    // fp32 prefill on split operands: 2 no images of blocks; 0: library's choice
   int chunk = 0;           // bf16 prefill by chunk kernels: 1 wherever they can run, 2 never; 0: library's choice
   int fold_max_slots = 3;  // most state slots a segment sums by itself instead of a pass over segment states (0: never)
 };
@@ -198,7 +199,7 @@ hipError_t launch_prefill_mfma_f32(const Dims &d, const void *x, const float *dt
 bool split_f32_supported(const Dims &d);
 double f32_other_us(const Dims &d);  // modelled time of the faster of the two other families
 bool split_f32_chosen(const Dims &d);
-void split_f32_plan(const Dims &d, int *seg_blocks, int *segments, int *parts);
+void split_f32_plan(const Dims &d, int *seg_blocks, int *segments, int *parts, int *images, int *states_in_y);
 hipError_t launch_prefill_split_f32(const Dims &d, const void *x, const float *dt, const float *A, const void *B,
                                     const void *C, const float *D, const float *h0, void *y, float *final_state,
                                     void *workspace, hipStream_t stream, KernelTrace *trace = nullptr);

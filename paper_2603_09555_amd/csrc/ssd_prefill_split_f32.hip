@@ -681,12 +681,40 @@ bool split_f32_chosen(const Dims &d) {
   return 0.97 * split_us(d, split_plan(d)) < f32_other_us(d);
 }
 
-void split_f32_plan(const Dims &d, int *seg_blocks, int *segments, int *parts) {
+// What several segments leave where for each other: the blocks' images, if they are made, first in the workspace, which then
+// holds the states if it has room for them (else y does, see state_slot), and the decays.
+// Images where the states-only launch has CUs left for them -- at most a workgroup per CU with them -- (2048 tokens x 24 heads
+// 51.2 -> 49.0 us, 2 x 712 x 27 x 64 x 64 32.6 -> 31.3).  In a fuller launch they delay the states by what the full launch
+// gains: 40 drawn prompts took 0.96 to 1.07 of the time, 6 x 2184 x 30 138 -> 143 us.
+struct SplitMemory {
+  bool images, states;  // in the workspace
+  size_t off_states, off_decay;
+};
+static SplitMemory split_memory(const Dims &d, const SplitPlan &pl) {
+  SplitMemory m = {false, false, 0, 0};
+  if (pl.segments == 1) return m;
+  const size_t row = static_cast<size_t>(d.Bt) * d.H * pl.segments, have = generic_workspace_bytes(d);
+  const size_t images = image_bytes(d), decays = (row * sizeof(float) + 255) / 256 * 256, states = row * d.P * d.N * sizeof(float);
+  const long rows = static_cast<long>(d.Bt) * d.G, nblocks = (d.T + kTok - 1) / kTok;
+  const long wgs = rows * ((d.hpg * (d.P / kCols) + kWaves - 1) / kWaves);
+  const bool idle = wgs * (pl.segments - 1) + rows * nblocks <= 256;
+  m.images = knobs().split_images != 2 && idle && images + decays <= have && (images + decays + states <= have || slots_in_y(d, pl.segments));
+  m.off_states = m.images ? images : 0;
+  m.states = m.images ? images + decays + states <= have : slots_in_workspace(d, pl.segments);
+  // (without the states: S decays per head, of which the workspace holds at least one per token and head)
+  m.off_decay = m.off_states + (m.states ? states : 0);
+  return m;
+}
+
+void split_f32_plan(const Dims &d, int *seg_blocks, int *segments, int *parts, int *images, int *states_in_y) {
   const SplitPlan pl = split_plan(d);
+  const SplitMemory m = split_memory(d, pl);
   const int nblocks = (d.T + kTok - 1) / kTok;
   *seg_blocks = (nblocks + pl.segments - 1) / pl.segments;
   *segments = pl.segments;
   *parts = pl.sub;
+  *images = m.images;
+  *states_in_y = pl.segments > 1 && !m.states;
 }
 
 template <int NT>
@@ -720,30 +748,11 @@ hipError_t launch_prefill_split_f32(const Dims &d, const void *x, const float *d
   p.h0 = h0;
   p.y = static_cast<float *>(y);
   p.final_state = final_state;
-  // (decays: S values per head, of which the workspace holds at least one per token and head)
-  p.decay = static_cast<float *>(workspace);
-  p.slots = nullptr;
-  p.images = nullptr;
-  if (pl.segments > 1) {
-    const size_t row = static_cast<size_t>(d.Bt) * d.H * pl.segments, have = generic_workspace_bytes(d);
-    const size_t images = image_bytes(d), decays = (row * sizeof(float) + 255) / 256 * 256, states = row * d.P * d.N * sizeof(float);
-    uint8_t *const ws = static_cast<uint8_t *>(workspace);
-    // the images have the first claim on the workspace, where the states fit in y instead
-    // Images where the states-only launch has CUs left for them -- at most a workgroup per CU with them -- (2048 tokens x 24 heads
-    // 51.2 -> 49.0 us, 2 x 712 x 27 x 64 x 64 32.6 -> 31.3).  In a fuller launch they delay the states by what the full launch
-    // gains: 40 drawn prompts took 0.96 to 1.07 of the time, 6 x 2184 x 30 138 -> 143 us.
-    const long rows = static_cast<long>(d.Bt) * d.G, nblocks = (d.T + kTok - 1) / kTok;
-    const long wgs = rows * ((d.hpg * (d.P / kCols) + kWaves - 1) / kWaves);
-    const bool idle = wgs * (pl.segments - 1) + rows * nblocks <= 256;
-    const bool images_fit = idle && images + decays <= have && (images + decays + states <= have || slots_in_y(d, pl.segments));
-    if (images_fit) p.images = ws;
-    const size_t before = images_fit ? images : 0;
-    p.decay = reinterpret_cast<float *>(ws + before);
-    if (images_fit ? before + decays + states <= have : slots_in_workspace(d, pl.segments)) {
-      p.slots = reinterpret_cast<float *>(ws + before);
-      p.decay = p.slots + row * d.P * d.N;
-    }
-  }
+  const SplitMemory m = split_memory(d, pl);
+  uint8_t *const ws = static_cast<uint8_t *>(workspace);
+  p.images = m.images ? ws : nullptr;
+  p.slots = m.states ? reinterpret_cast<float *>(ws + m.off_states) : nullptr;
+  p.decay = reinterpret_cast<float *>(ws + m.off_decay);
   p.T = d.T;
   p.H = d.H;
   p.P = d.P;

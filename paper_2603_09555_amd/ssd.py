@@ -457,7 +457,7 @@ def ssd_conv1d_step(conv_state, u, weight, bias=None, split=None, activation="si
 
 
 KNOBS = {"force_generic": 0, "seg_chunks": 1, "seg_blocks": 2, "seg_parts": 3, "y_stream": 4, "decode_stream": 5,
-         "force_mfma_f32": 6, "f32_segments": 7, "fold_max_slots": 8, "scan_heads": 9, "chunk": 10, "deal": 11}
+         "force_mfma_f32": 6, "f32_segments": 7, "fold_max_slots": 8, "scan_heads": 9, "chunk": 10, "deal": 11, "split_images": 12}
 
 
 def set_knob(name: str, value: int) -> None:
@@ -491,6 +491,17 @@ def prefill_pair_plan(shape, h0_aliases_final_state: bool = False):
     if st != SSD_OK:
         raise SSDError(st, "ssd_testing_prefill_pair_plan")
     return dict(seg_blocks=out[1], segments=out[2], parts=out[3], fold=bool(out[4]), heads=out[6], state_heads=out[7]) if out[0] else None
+
+
+def split_f32_memory(shape) -> dict:
+    """``ssd_testing_prefill_plan`` for fp32 io on split operands: whether images of the blocks are made for all heads, whether
+    the states between the launches lie in ``y``."""
+    out = (ctypes.c_int32 * 8)()
+    st = _lib.ssd_testing_prefill_plan(ctypes.byref(shape), 0, out)
+    if st != SSD_OK:
+        raise SSDError(st, "ssd_testing_prefill_plan")
+    split = out[0] == 2 and out[5] == 0
+    return dict(images=split and bool(out[6]), states_in_y=split and bool(out[7]))
 
 
 def prefill_chunks(shape, h0_aliases_final_state: bool = False) -> int:

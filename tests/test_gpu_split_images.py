@@ -8,16 +8,16 @@ from parity import TOL, assert_close
 
 pytestmark = pytest.mark.gpu
 
-IMAGE = {1: 20480, 2: 32768, 3: 45056, 4: 57344}  # bytes of a block's image by 32-column tiles of dstate
-
 CASES = [
-    # Bt, T, H, P, N, G, L, h0, blocks per segment
+    # Bt, T, H, P, N, G, L, h0, blocks per segment (0: the library's choice)
     (1, 1000, 24, 64, 128, 1, 64, False, 4),   # states beside the images; a last block of 8 tokens
     (1, 545, 24, 64, 128, 1, 256, True, 6),    # states in y; a last block of one token
     (2, 300, 6, 96, 72, 2, 32, True, 3),       # dstate 72, slices of one head over two workgroups, two groups
     (1, 97, 16, 32, 16, 1, 16, False, 1),      # dstate 16, segments of a block
     (1, 129, 8, 64, 64, 1, 32, True, 2),
+    (1, 1900, 24, 64, 128, 1, 256, True, 0),
 ]
+STATES_IN_Y = {1, 5}  # (of the cases)
 
 
 @pytest.fixture
@@ -42,11 +42,8 @@ def setup(ssd, case):
     shape = ssd.make_shape(*dims, torch.float32)
     plan = ssd.prefill_plan(shape)
     print("images", case, plan, flush=True)
-    Bt, T, H, P, N, G = dims[:6]
-    blocks = (T + 31) // 32
-    slots = Bt * H * plan["segments"] * P * N * 4
-    room = ssd.prefill_workspace_bytes(shape) - Bt * G * blocks * IMAGE[(N + 31) // 32] - 4 * Bt * H * plan["segments"]
-    assert plan["path"] == "mfma_f32" and plan["segments"] > 1 and (room >= slots or (room >= 0 and blocks // plan["segments"] >= (N + 31) // 32))
+    assert plan["path"] == "mfma_f32" and plan["segments"] > 1
+    assert ssd.split_f32_memory(shape) == dict(images=True, states_in_y=CASES.index(case) in STATES_IN_Y)
     inp = inputs.make_prefill_inputs(cfg, seed=13)
     return cfg, inp, inputs.make_state(cfg, seed=13, scale=0.3) if with_h0 else None
 
@@ -60,6 +57,22 @@ def test_images_match_the_oracle(ssd, case):
     assert_close(st, st_ref, TOL["f32"], "final state")
     again = run(ssd, cfg, inp, h0)
     assert torch.equal(y, again[0]) and torch.equal(st, again[1])
+    ssd.set_knob("split_images", 2)
+    assert not ssd.split_f32_memory(ssd.make_shape(*case[:7], torch.float32))["images"]
+    without = run(ssd, cfg, inp, h0)   # (the same operations on the same parts)
+    assert torch.equal(y, without[0]) and torch.equal(st, without[1])
+
+
+@pytest.mark.parametrize("case", [c for c in CASES if c[7]], ids=lambda c: "x".join(map(str, c)))
+def test_images_with_the_state_in_place(ssd, case):
+    """h0 and final_state in one buffer: the first segment then starts from a copy."""
+    cfg, inp, h0 = setup(ssd, case)
+    y, st = run(ssd, cfg, inp, h0)
+    dev = {k: v.cuda() for k, v in inp.items()}
+    state = h0.cuda()
+    y2, st2 = ssd.ssd_prefill(*[dev[k] for k in ("x", "dt", "A", "B", "C", "D")], cfg.chunk, h0=state, final_state=state)
+    torch.cuda.synchronize()
+    assert st2.data_ptr() == state.data_ptr() and torch.equal(y, y2) and torch.equal(st, state)
 
 
 @pytest.mark.parametrize("where", ["B", "C"])

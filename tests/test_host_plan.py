@@ -210,3 +210,22 @@ def test_small_prompts_the_scan_wins_are_left_to_it(dims):
     """One chunk in more than a round of workgroups, a round and a little of two chunks, fifty chunks to chain: the chunk kernels
     take 1.17 to 1.3 times as long."""
     assert ssd.prefill_chunks(ssd.make_shape(*dims, 128, torch.bfloat16)) == 0
+
+
+@pytest.mark.parametrize("dims, seg_blocks, images, states_in_y", [
+    ((1, 2048, 24, 64, 128, 1, 256), 0, True, True),     # 12 x 15 workgroups of the states-only launch + 64 blocks: 244
+    ((1, 2048, 26, 64, 128, 1, 256), 0, False, True),    # 13 x 15 + 64: 259, more than a workgroup per CU
+    ((1, 2048, 8, 64, 128, 1, 256), 1, False, True),
+    ((2, 320, 8, 64, 128, 1, 32), 2, True, False),       # a state per chunk beside the images
+    ((1, 8192, 2, 64, 128, 1, 256), 0, False, True),
+    ((6, 2184, 30, 64, 128, 1, 256), 0, False, False),
+    ((1, 512, 2, 64, 128, 1, 512), 4, False, True),      # idle, but the workspace has no room for 16 images
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_images_where_the_states_only_launch_leaves_cus_idle(dims, seg_blocks, images, states_in_y):
+    ssd.set_knob("seg_blocks", seg_blocks)
+    sh = ssd.make_shape(*dims, torch.float32)
+    Bt, T, H, P, N, G, _ = dims
+    p = ssd.prefill_plan(sh)
+    assert p["path"] == "mfma_f32" and p["f32_segments"] == 0
+    print(dims, p, ssd.split_f32_memory(sh))
+    assert ssd.split_f32_memory(sh) == dict(images=images, states_in_y=states_in_y)
