@@ -256,7 +256,7 @@ __device__ __forceinline__ int wave_reduce(int v, Op op) {
 // equal, one or a few long among short ones) at eight lengths each, from the host's shortest on, 7 % rms.  (Four heads to a workgroup, which only a
 // test asks for, go by the same.)  A length
 // guessed on the host cannot serve both a ragged batch and one long prompt among short ones: the guess of four times the
-// mean left 8192 + 63 x 1 tokens x 24 heads uncut, 322 us (now 74; 89 with the length of one sequence).
+// mean left 8192 + 63 x 1 tokens x 24 heads uncut, 322 us (now 72; 89 with the length of one sequence).
 // Dealt items (see Deal), fitted to 400 batches of more than a round of these (draws, equal lengths, one or a few long among short ones), 1150
 // timings at up to eight lengths, 10 % rms.  The deal in rounds is less even than the model has it where a few items are long: of
 // lengths within 5 % of the cheapest the shortest is taken, which is 1.1 % behind the fastest timed in the geometric mean, 19 % at worst.
@@ -1826,10 +1826,12 @@ __device__ __forceinline__ bool walk_meets_steep_block(const ScanParams &p, cons
 //     each, 64 vector instructions apart): with the fourteen requests and four stores of a block among its own
 //     instructions a computing wave took 4190 cycles a block of 8 x 4096 tokens x 48 heads, with feeders 3660.
 //   - The feeders also scale x and turn it for the matrix instructions (3610: now they are what a block waits for) and
-//     make their requests in runs of four (see load_to_lds4): 3250; ahead of the block's other address arithmetic: 3130, of
-//     which requests take 1430, the turn 1110 and stores 230 of a feeder, and 2490 are a computing wave's.  x loaded into
-//     registers three blocks ahead, with requests between quarters of the turn: 140 us a call instead of 120.  The same work in
-//     waves that load into registers and write LDS themselves takes 5240 cycles.
+//     make their requests in runs of four (see load_to_lds4): 3250.  The same work in waves that load into registers and
+//     write LDS themselves takes 5240.  Addresses counted from the item's first block (by time stamps in the feeders, cold
+//     inputs, cycles on another scale than the ones above): 2700 -> 2590, of which a feeder works 2430 and a computing
+//     wave 2300; 7 x 826 tokens x 23 heads 2750 -> 2680, but 16384 x 80, where 240 workgroups wait for memory, 4080 -> 4190.
+//     x loaded into registers three blocks ahead, with requests between quarters of the turn: 8 x 4096
+//     x 48 140 us a call instead of 120.
 //   - The tiles and the record of the next block arrive during a block, in the buffer of a pair that it does not use.  A
 //     block of x goes through one of three buffers: it arrives until the middle of the block before its own, when the feeder that
 //     requested it turns it into Xm^T; it serves the skip term of its block and is replaced, in place, by y; and
@@ -1864,8 +1866,9 @@ typedef lds_as<uint8_t> lds_u8;
 // The walk goes from the last block of an item to the first of the next as it goes from block to block: what the next
 // item's blocks need is requested while this one's are computed.  A workgroup of its own for every entry pays 5 us for its start, and
 // where they are several a CU they end unevenly: 64 ragged sequences, 16384 tokens, 80 heads 173 us with four heads to a
-// workgroup (148 of them the scan, 1280 workgroups), dealt 157 (134).  What is left is the memory: x, y and a final state of 32 KB a
-// sequence and head are 504 MB, 3.8 TB/s; an item's end costs 3400 cycles, a block 3300.
+// workgroup (152 of them the scan, 1280 workgroups), dealt 155.6 (136, traced).  What is left is the memory: x, y and a final state
+// of 32 KB a sequence and head are 504 MB, 3.7 TB/s; of 5300 cycles a block, ends of items included, a computing wave works
+// 2280 and a feeder 3150, two thirds of them until its requests are taken.
 struct ItemView {
   uint32_t tok0, len, blk0, slot0, b;  // as in SeqView
   int sg, S, col, nb, jb0, jb1;
@@ -2253,7 +2256,7 @@ template <bool kList>
 __device__ void pair_walk_mixed(const PairParams p, const Deal deal, const ItemView first, int item, uint32_t parity, uint32_t x_cur, lds_u8 *const lds);
 
 // The computing waves, 0..3: wave w has half w & 1 of headdim of head w / 2.  kMixed: some of the items' blocks may be steep.
-// kList: there may be several items; otherwise, and without kMixed, it returns false, having done nothing, if a block is steep.
+// Without kMixed, an item with a steep block is left to pair_walk_mixed, with all that come after it.  kList: there may be several items.
 template <bool kMixed, bool kList>
 __device__ __forceinline__ void pair_walk(const PairParams &p, Items<kList> items, uint32_t parity, uint32_t x_cur, lds_u8 *const lds) {
   using L = PairLds;

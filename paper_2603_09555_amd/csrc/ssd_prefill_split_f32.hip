@@ -28,13 +28,14 @@
 // state over the blocks of the ones before it (a third of a block's work, no output).
 // Where the states-only launch leaves CUs idle, workgroups of their own split B and C there and form the scores, once for all
 // heads (make_image); the full launch then copies a block's image to LDS.
-// Bound: issue.  A block of four slices takes 5.2 us where one workgroup has the chip, 7.3 with one per CU, 10.3 with two
-// each (dstate 128); the matrix instructions are 1.6 of it (3840 cycles a wave), about 1150 vector instructions a wave
+// Bound: issue.  A block of four slices without an image takes 5.2 us where one workgroup has the chip, 7.3 with one per CU, 10.3
+// with two each (dstate 128); the matrix instructions are 1.6 of it (3840 cycles a wave), about 1150 vector instructions a wave
 // (the splits: 700) come between them.  One wave on a SIMD issues a vector instruction every 5 cycles and they hardly overlap with
 // the matrix instructions (eight of them and one of those: 59 cycles, 32 by itself; 49 with two waves), so that operands
-// read from LDS a step ahead changed nothing.  Of a block's 12900 cycles staging was 2700, the scores 1000; 11100 with images.  Two waves per slice (half of dstate each, outputs summed through LDS) were 6 %
-// faster alone and half as fast for two; matrix and vector instructions interleaved by hand or by scheduling groups 15 %
-// slower and more (spills).
+// read from LDS a step ahead changed nothing.  Of a block's 12700 cycles (2048 tokens x 24 heads, by time stamps)
+// staging is 3270, the scores 810; with an image 11600, of which copying it is 3040.  Two waves per slice (half of dstate
+// each, outputs summed through LDS) were 6 % faster alone and half as fast for two; matrix and vector instructions
+// interleaved by hand or by scheduling groups 15 % slower and more (spills).
 // Measured against the fp32 matrix instruction kernel (ssd_prefill_mfma_f32.hip), us: 2048 tokens x 24 heads x 64 x 128
 // 108.7 / 49.0 (12 of it the chain and the gaps), 8 such prompts 504 / 191, 3 x 2428 x 20 190 / 90, 2 x 3593 x 11 x 64 x
 // 16 70 / 43, 4096 x 4 x 32 x 16 55 / 37; final state against 64 bits 1.4e-7 / 9.5e-8, y
@@ -75,7 +76,7 @@ struct SplitParams {
 };
 
 inline int segment_begin(int s, int S, int nblocks) { return static_cast<int>(static_cast<long long>(s) * nblocks / S); }
-// (A division of 64 bits is some hundred instructions, and the pass over the states had two per segment: 8.3 -> 6.8 us at 2048
+// (A division of 64 bits is some hundred instructions, and the pass over the states had two per segment: 8.1 -> 6.8 us at 2048
 // tokens x 24 heads in 16 segments.  The product is below 2^31, see split_plan.)
 __device__ __forceinline__ int segment_begin(int s, const SplitParams &p, int nblocks) {
   return quotient(static_cast<uint32_t>(s) * static_cast<uint32_t>(nblocks), p.S, p.S_inv);
@@ -148,8 +149,8 @@ __device__ __forceinline__ f32x4 scores_quarter(const uint16_t *sb, const uint16
 }
 
 // The image of block j of batch row and group bg (see SplitLds): what every workgroup of the group would otherwise work out of B
-// and C again, 3900 of the 12900 cycles that a block took (2048 tokens x 24 heads: twelve workgroups a block).  Made by workgroups
-// of the states-only launch, which leaves CUs idle.
+// and C again (2048 tokens x 24 heads: twelve workgroups a block, 12700 cycles each, 11600 with the image).  Made by workgroups of the
+// states-only launch, which leaves CUs idle.
 template <int NT>
 __device__ __forceinline__ void make_image(const SplitParams &p, uint8_t *smem, int *s_odd, int bg, int j, int nblocks) {
   using L = SplitLds<NT, false>;

@@ -21,7 +21,7 @@ def plan(lengths, heads, groups=1, chunk=256):
                                                   ([8192] + 63 * [1], 80, 18), ([1] * 63 + [8192], 24, 12),
                                                   ([3000, 3000] + 60 * [1], 24, 8)], ids=lambda v: str(v)[:20])
 def test_a_long_prompt_among_short_rows_is_cut(lengths, heads, most):
-    """Uncut, a few workgroups walk the whole prompt while the chip idles (8192 + 63 x 1 tokens: 322 us against 75)."""
+    """Uncut, a few workgroups walk the whole prompt while the chip idles (8192 + 63 x 1 tokens: 322 us against 72)."""
     p = plan(lengths, heads)
     assert p["chosen"] and p["shortest"] <= p["seg_blocks"] <= most
 
