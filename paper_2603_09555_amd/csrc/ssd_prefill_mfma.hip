@@ -3032,7 +3032,7 @@ SlicePlan plan_slice(const Dims &d, bool varlen, bool h0_aliases_final_state) {
   pl.listed = varlen && deal_possible(w) && (kn.deal == 1 || (may_two && kn.deal == 0 && packed_dealt(d, pl.seg_blocks)));
   if (pl.listed) pl.heads = 2;
   if (pl.from_lengths) {
-    // (what is not dealt comes to hardly more than a round of workgroups of two heads, see small_grid)
+    // (what is not dealt comes to 1.75 rounds of workgroups of two heads at most, but for records of 4 GiB; see packed_dealt)
     if (may_two) pl.heads = 2;
     if (may_two && (!pl.listed || dealt_states_two(d))) pl.state_heads = 2;
     if (packed_uncut(d, pl)) {
